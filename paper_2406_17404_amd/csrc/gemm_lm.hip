@@ -1,0 +1,75 @@
+// LM head with the greedy argmax in the projection's epilogue.
+#include "gemm_ring.h"
+
+namespace trj {
+
+// acc layout of v_mfma_f32_32x32x16: lane l, register v -> tile row 8*(v/4) + 4*(l/32) +
+// v%4, tile column l%32.  Rows are output features, columns are token rows.
+
+// ---- epilogue: greedy argmax without logits (Eq. 1's arg max taken where the logits are
+// born).  Every wavefront reduces the 32 vocabulary rows of its tile for each of its 32
+// token columns and writes one candidate (value, index) per (token, row tile); a second,
+// small kernel picks the winner among a token's candidates.  Lowest index wins ties, NaN
+// never wins (a candidate that saw nothing keeps index INT32_MAX).
+struct ArgmaxCand {
+  float v;
+  int32_t i;
+};
+struct EpiArgmax {
+  static constexpr bool kScaled = true;
+  RowScale rs;
+  ArgmaxCand* cand;  // [T][n_tiles]
+  int T, n_tiles;
+  __device__ void operator()(const f32x16& acc, int tile, int ttile, int lane, int) const {
+    float bv = -INFINITY;
+    int bi = INT32_MAX;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {  // ascending row index within the lane
+      const int row = tile * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+      if (acc[v] > bv || (acc[v] == bv && row < bi)) { bv = acc[v]; bi = row; }
+    }
+    const float ov = __shfl_xor(bv, 32);
+    const int oi = __shfl_xor(bi, 32);
+    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    const int t = ttile * 32 + (lane & 31);
+    if (lane < 32 && t < T) cand[(size_t)t * n_tiles + tile] = ArgmaxCand{bv, bi};
+  }
+};
+
+// LM head with the argmax taken in the epilogue: argmax_out[t] = lowest index of the row
+// maximum of x W^T; cand: T * n_out / 32 candidates of scratch
+__global__ __launch_bounds__(256) void argmax_cand_kernel(const ArgmaxCand* __restrict__ cand,
+                                                          int n_tiles, int32_t* __restrict__ out) {
+  const ArgmaxCand* row = cand + (size_t)blockIdx.x * n_tiles;
+  float bv = -INFINITY;
+  int bi = INT32_MAX;
+  for (int j = threadIdx.x; j < n_tiles; j += 256) {
+    const ArgmaxCand c = row[j];
+    if (c.v > bv || (c.v == bv && c.i < bi)) { bv = c.v; bi = c.i; }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const float ov = __shfl_xor(bv, o);
+    const int oi = __shfl_xor(bi, o);
+    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+  }
+  __shared__ float sv[4];
+  __shared__ int si[4];
+  if ((threadIdx.x & 63) == 0) { sv[threadIdx.x >> 6] = bv; si[threadIdx.x >> 6] = bi; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w)
+      if (sv[w] > bv || (sv[w] == bv && si[w] < bi)) { bv = sv[w]; bi = si[w]; }
+    out[blockIdx.x] = bi == INT32_MAX ? 0 : bi;
+  }
+}
+size_t gemm_lm_argmax_scratch_bytes(int T, int n_out) { return (size_t)T * (n_out / 32) * sizeof(ArgmaxCand); }
+int launch_gemm_lm_argmax(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out,
+                          const RowScale& rs, void* cand, int32_t* argmax_out, hipStream_t st) {
+  EpiArgmax e{rs, static_cast<ArgmaxCand*>(cand), T, n_out / 32};
+  int rc = launch_gemm(xp, w, tp, n_in, n_out, 1, e, st);
+  if (rc != TRJ_OK) return rc;
+  argmax_cand_kernel<<<T, 256, 0, st>>>(static_cast<const ArgmaxCand*>(cand), n_out / 32, argmax_out);
+  return check_launch();
+}
+
+}  // namespace trj
