@@ -17,7 +17,9 @@ struct EpiQKV {
   uint16_t* k_layer;
   uint16_t* v_layer;
   int T, n_heads, n_kv_heads, dh, s_pool;
-  __device__ void operator()(const f32x16& acc, int tile, int ttile, int lane, int) const {
+  int tile0;  // row tile of W that the launch starts at (all of them: 0; K and V only: behind q)
+  __device__ void operator()(const f32x16& acc, int launch_tile, int ttile, int lane, int) const {
+    const int tile = tile0 + launch_tile;
     int t = ttile * 32 + (lane & 31);
     if (t >= T) return;
     int slot = row_slot[t];
@@ -68,8 +70,10 @@ int launch_gemm_qkv(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_
                     int n_kv_heads, int dh, int s_pool, const RowScale& rs, const float2* cs,
                     const int32_t* cs_row, const int32_t* row_slot, uint16_t* q, uint16_t* k_layer,
                     uint16_t* v_layer, hipStream_t st) {
-  EpiQKV e{rs, cs, cs_row, row_slot, q, k_layer, v_layer, T, n_heads, n_kv_heads, dh, s_pool};
-  return launch_gemm(xp, w, tp, n_in, (n_heads + 2 * n_kv_heads) * dh, 1, e, st);
+  // without q only the K and V rows of W are read: its row tiles are stored one after the other
+  const int skip = q ? 0 : n_heads * dh;
+  EpiQKV e{rs, cs, cs_row, row_slot, q, k_layer, v_layer, T, n_heads, n_kv_heads, dh, s_pool, skip / 32};
+  return launch_gemm(xp, w + (size_t)skip * n_in, tp, n_in, (n_heads + 2 * n_kv_heads) * dh - skip, 1, e, st);
 }
 
 }  // namespace trj

@@ -138,6 +138,7 @@ int launch_gemm_lm_argmax(const uint16_t* xp, const uint16_t* w, int T, int tp, 
                           const RowScale& rs, void* cand, int32_t* argmax_out, hipStream_t st);
 int launch_gemm_gate_up(const uint16_t* xp, const uint16_t* w, int tp, int n_in, int d_ffn,
                         const RowScale& rs, uint16_t* act, hipStream_t st);
+// q may be null: then only K and V are computed and written (the last layer of a prompt pass)
 int launch_gemm_qkv(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_heads,
                     int n_kv_heads, int dh, int s_pool, const RowScale& rs, const float2* cs,
                     const int32_t* cs_row, const int32_t* row_slot, uint16_t* q, uint16_t* k_layer,
