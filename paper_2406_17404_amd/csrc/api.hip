@@ -451,13 +451,23 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
   carve_tree(c, dtype, B, T, n_heads, head_dim, max_seq_slots, &w);
   if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t st = (hipStream_t)stream;
-  TRJ_TRY(launch_tree_prep(parent, node_off, kv_off, prefix_len, B, T, s_pool, max_seq_slots, w.depth,
-                           w.anc, w.status, w.row_slot, w.row_pos, w.row_seq,
-                           // bf16: rows of malformed sequences read as zeros
-                           dtype == TRJ_BF16 ? out : nullptr, (size_t)T * n_heads * head_dim * 2, st));
-  if (dtype == TRJ_BF16) {
-    TRJ_TRY(launch_attn_items(node_off, prefix_len, kv_off, w.status, B, w.attn_rows, w.attn_qg,
-                              w.attn_bpwg, w.attn_ns, w.items, st));
+  const bool bf16 = dtype == TRJ_BF16;
+  if (B <= PREP_MAX_SEQS) {
+    const StepPrep p{parent, node_off, kv_off, prefix_len, B, T, s_pool, max_seq_slots, w.depth, w.anc, w.status,
+                     w.row_slot, w.row_pos, w.row_seq, nullptr, head_dim, 0.f, w.items, w.attn_rows, w.attn_qg,
+                     w.attn_bpwg, w.attn_ns,
+                     // bf16: rows of malformed sequences read as zeros
+                     bf16 ? (uint16_t*)out : nullptr, n_heads * head_dim, 0};
+    TRJ_TRY(launch_step_prep(p, EmbedRow{}, st));
+  } else {
+    TRJ_TRY(launch_tree_prep(parent, node_off, kv_off, prefix_len, B, T, s_pool, max_seq_slots, w.depth,
+                             w.anc, w.status, w.row_slot, w.row_pos, w.row_seq,
+                             bf16 ? out : nullptr, (size_t)T * n_heads * head_dim * 2, st));
+    if (bf16)
+      TRJ_TRY(launch_attn_items(node_off, prefix_len, kv_off, w.status, B, w.attn_rows, w.attn_qg,
+                                w.attn_bpwg, w.attn_ns, w.items, st));
+  }
+  if (bf16) {
     return launch_tree_attn_bf16((const uint16_t*)q, (const uint16_t*)k_layer,
                                  (const uint16_t*)v_layer, w.anc, node_off, kv_off, prefix_len,
                                  w.status, w.items, B, T, n_heads, n_kv_heads, head_dim, s_pool, max_seq_slots, scale,
@@ -624,16 +634,36 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
   // found through each row's position
   const float2* cs = w.cs;
   const int32_t* cs_row = nullptr;
+  const bool one_prep = B <= PREP_MAX_SEQS;
+  const int tp = padded_rows(T);
+  EmbedRow embed{};
+  if (one_prep) {
+    embed = EmbedRow{weights->embed, tok, T, d, V, w.x, nullptr, 0, nullptr, nullptr, 0, 0};
+    if (bf16) {
+      embed.g = weights->h_layers[0].g_attn;
+      embed.tp = tp;
+      embed.hp = w.hp;
+      embed.ssq = w.ssq;
+      embed.parts = reduce_norm_parts(d);
+      embed.part_threads = reduce_norm_threads(d);
+    }
+  }
   if (tmpl) {
     // what depends on the tree alone comes from the template; one launch does the rest
     TRJ_TRY(launch_template_step_prep(*tmpl, node_off, kv_off, prefix_len, B, T, dh, max_pos, s_pool,
                                       max_seq_slots, status_dev, w.t.row_slot, w.t.row_pos,
                                       w.t.row_seq, w.t.attn_rows, w.t.attn_qg, w.t.attn_bpwg,
-                                      w.t.attn_ns, bf16 ? w.t.items : nullptr, zero, zero_bytes, st));
+                                      w.t.attn_ns, bf16 ? w.t.items : nullptr, zero, zero_bytes, embed, st));
     w.t.depth = tmpl->depth;
     w.t.anc = tmpl->anc;
     cs = tmpl->cs;
     cs_row = w.t.row_pos;
+  } else if (one_prep) {
+    const StepPrep p{parent, node_off, kv_off, prefix_len, B, T, s_pool, max_seq_slots, w.t.depth, w.t.anc,
+                     status_dev, w.t.row_slot, w.t.row_pos, w.t.row_seq, w.cs, dh, m.rope_theta, w.t.items,
+                     w.t.attn_rows, w.t.attn_qg, w.t.attn_bpwg, w.t.attn_ns, bf16 ? w.op : nullptr, hd,
+                     bf16 ? tp : 0};
+    TRJ_TRY(launch_step_prep(p, embed, st));
   } else {
     TRJ_TRY(launch_tree_prep(parent, node_off, kv_off, prefix_len, B, T, s_pool, max_seq_slots,
                              w.t.depth, w.t.anc, status_dev, w.t.row_slot, w.t.row_pos, w.t.row_seq,
@@ -645,12 +675,11 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
   }
 
   if (m.dtype == TRJ_BF16) {
-    const int tp = padded_rows(T);
     const int sk_o = gemm_bf16_split_k(d, tp, hd), sk_d = gemm_bf16_split_k(d, tp, F);
     // the norm's division is done by the projection that consumes hp (RowScale)
     const RowScale rs{w.ssq, reduce_norm_parts(d), tp, 1.0f / (float)d, m.rms_eps};
     const RowScale none{nullptr, 0, tp, 0.f, 0.f};
-    { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_embed_norm((const uint16_t*)weights->embed, tok, T, d, V, w.x,
+    if (!one_prep) { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_embed_norm((const uint16_t*)weights->embed, tok, T, d, V, w.x,
                               weights->h_layers[0].g_attn, tp, w.hp, w.ssq, st)); }
     for (int l = 0; l < m.n_layers; ++l) {
       const trj_layer_weights& lw = weights->h_layers[l];
@@ -679,7 +708,7 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
       TRJ_TRY(launch_gemm_store_f32(w.hp, (const uint16_t*)weights->w_lm, T, tp, d, V, 1, rs, lg, st));
     }
   } else {
-    TRJ_TRY(launch_embed(weights->embed, tok, T, d, V, m.dtype, w.x, st));
+    if (!one_prep) TRJ_TRY(launch_embed(weights->embed, tok, T, d, V, m.dtype, w.x, st));
     for (int l = 0; l < m.n_layers; ++l) {
       const trj_layer_weights& lw = weights->h_layers[l];
       float* kl = (float*)k_pool + (size_t)l * kv_layer_stride;

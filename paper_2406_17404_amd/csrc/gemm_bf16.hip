@@ -193,7 +193,7 @@ int reduce_norm_parts(int d) {
   return p > RS_MAX_PARTS ? RS_MAX_PARTS : p;
 }
 // threads per workgroup (8 columns each): the part's share of the row, in whole wavefronts
-static int reduce_norm_threads(int d) {
+int reduce_norm_threads(int d) {
   const int ngran = d >> 3, parts = reduce_norm_parts(d);
   return ((ngran + parts - 1) / parts + WAVE - 1) / WAVE * WAVE;
 }

@@ -47,6 +47,40 @@ int launch_tree_prep(const int32_t* parent, const int32_t* node_off, const int32
                      const int32_t* prefix_len, int B, int T, int s_pool, int max_seq_slots,
                      int32_t* depth, uint64_t* anc, int32_t* status_dev, int32_t* row_slot, int32_t* row_pos,
                      int32_t* row_seq, void* zero, size_t zero_bytes, hipStream_t st);
+// One launch for all of a call's bookkeeping (see step_prep_kernel), for up to PREP_MAX_SEQS
+// sequences; kv_off and prefix_len are not null.  Optional parts: cs (rotary table [T][dh/2]),
+// items (attention work list), zero (bf16 attention output whose rows without a valid sequence
+// read as zeros: plain rows of zero_cols, or tiled with zero_tp rows, padding rows included),
+// the embedding (EmbedRow::x).
+constexpr int PREP_MAX_SEQS = 64, PREP_THREADS = 1024, PREP_CHUNK = 16;
+struct StepPrep {
+  const int32_t *parent, *node_off, *kv_off, *prefix_len;
+  int B, T, s_pool, max_seq_slots;
+  int32_t* depth;
+  uint64_t* anc;
+  int32_t *status, *row_slot, *row_pos, *row_seq;
+  float2* cs;
+  int dh;
+  float theta;
+  int32_t* items;
+  int rows_per_item, qg_max, blocks_per_item, nsplit_max;
+  uint16_t* zero;
+  int zero_cols, zero_tp;
+};
+// x[t] = E[tok[t]] for T rows; with hp (bf16 mode) the first projection's input for tp rows
+// too, see launch_reduce_norm.  x null: nothing.
+struct EmbedRow {
+  const void* embed;
+  const int32_t* tok;
+  int T, d, vocab;
+  float* x;
+  const float* g;
+  int tp;
+  uint16_t* hp;
+  float* ssq;
+  int parts, part_threads;
+};
+int launch_step_prep(const StepPrep& a, const EmbedRow& e, hipStream_t st);
 // List of the (sequence, key split, query group) triples that exist, for the bf16 attention
 // launch: n records of 8 words {sequence, group, first row, rows, prefix length,
 // kv_off / 32, split, 1 if the sequence has more than one group}, sequences ordered by length (prefix + tree), longest first, when
@@ -78,7 +112,7 @@ int launch_template_step_prep(const TemplateView& v, const int32_t* node_off, co
                               int max_seq_slots, int32_t* status_dev, int32_t* row_slot,
                               int32_t* row_pos, int32_t* row_seq, int rows_per_item, int qg_max,
                               int blocks_per_item, int nsplit_max, int32_t* items, void* zero,
-                              size_t zero_bytes, hipStream_t st);
+                              size_t zero_bytes, const EmbedRow& e, hipStream_t st);
 int launch_argmax(const float* logits, int T, int V, int32_t* out, hipStream_t st);
 int launch_accept(const int32_t* argmax, const int32_t* tok, const int32_t* parent,
                   const int32_t* node_off, const int32_t* status_in, int B, int T,
@@ -127,7 +161,8 @@ struct RowScale {
   int parts, tp;
   float inv_d, eps;
 };
-int reduce_norm_parts(int d);
+int reduce_norm_parts(int d);    // column parts of a row
+int reduce_norm_threads(int d);  // threads per part, 8 columns each, in whole wavefronts
 int gemm_bf16_split_k(int n_out, int tp, int n_in);
 int gemm_bf16_clamp_split(int n_out, int tp, int n_in, int split_k);
 void gemm_bf16_describe_plan(int tp, int n_in, int n_out, int split_k, int32_t out[6]);
@@ -143,7 +178,7 @@ int launch_gemm_qkv(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_
                     int n_kv_heads, int dh, int s_pool, const RowScale& rs, const float2* cs,
                     const int32_t* cs_row, const int32_t* row_slot, uint16_t* q, uint16_t* k_layer,
                     uint16_t* v_layer, hipStream_t st);
-// x[t] = E[tok[t]] (fp32), or x[t] += the split-k partial sums; hp = bf16(x * g) tiled and the
+// x[t] = E[tok[t]] (more than PREP_MAX_SEQS sequences), or x[t] += the split-k partial sums; hp = bf16(x * g) tiled and the
 // rows' partial sums of squares for the consumer's RowScale, one launch
 int launch_embed_norm(const uint16_t* embed, const int32_t* tok, int T, int d, int vocab, float* x,
                       const float* g, int tp, uint16_t* hp, float* ssq, hipStream_t st);

@@ -3,6 +3,7 @@
 // converters.  All results here are exact (no floating point decides anything except
 // the comparisons inside argmax).
 #include "common.h"
+#include "embed_row.h"
 #include "kernels.h"
 
 namespace trj {
@@ -187,6 +188,202 @@ int launch_tree_prep(const int32_t* parent, const int32_t* node_off, const int32
   return check_launch();
 }
 
+// ------------------------------------------------------------------ step prologue
+// Everything a call needs before its first projection or attention launch, in ONE launch for
+// up to PREP_MAX_SEQS sequences: the pieces depend on each other only through a sequence's
+// tree, which is small enough (at most 128 parents) to be worked out again by every workgroup
+// that needs it.  A launch of its own for each piece costs 2-5 us of dispatch and drain for
+// next to no work: clear, tree checks, rotary table, work list and embedding together 19 us of
+// a step, in one launch 7 us (5 rows; attention alone 8.5 -> 4.5 us).  Roles by workgroup id:
+//   B * chunks   sequence s, rows 16c..: tree checks, depth and ancestor bits by pointer
+//                doubling (7 rounds at most, where walking the parents of a 128-node chain
+//                took 14 us); chunk 0 writes the tree's rows, every chunk the rotary table of
+//                its rows (double precision sine and cosine, the longest part, hence chunks)
+//   1            validity of all sequences, the attention work list, rows that no valid
+//                sequence covers
+//   tp - T       padding rows of the attention output
+//   tp           embedding and first norm input of one row (bf16), or the embedding (fp32)
+// Above PREP_MAX_SEQS the launches stay separate: the one workgroup that sees all sequences
+// would take longer than they do.
+__device__ inline void zero_row(const StepPrep& a, int t, int first, int stride) {
+  if (!a.zero) return;
+  if (a.zero_tp > 0) {
+    const u32x4 z = {0, 0, 0, 0};
+    for (int g = first; g < (a.zero_cols >> 3); g += stride)
+      *reinterpret_cast<u32x4*>(a.zero + a_off(t, g * 8, a.zero_tp)) = z;
+  } else {
+    uint32_t* p = reinterpret_cast<uint32_t*>(a.zero + (size_t)t * a.zero_cols);
+    for (int g = first; g < (a.zero_cols >> 1); g += stride) p[g] = 0;
+  }
+}
+__device__ inline bool slots_ok(int ko, int L, int n, int s_pool, int max_seq_slots) {
+  return !(ko < 0 || (ko & (TRJ_KV_BLOCK - 1)) || L < 0 || (long)ko + L + n > (long)s_pool ||
+           (long)L + n > (long)max_seq_slots);
+}
+
+__device__ inline void prep_sequence(const StepPrep& a, int s, int chunk) {
+  __shared__ int32_t jump[TRJ_N_MAX], dep[TRJ_N_MAX];
+  __shared__ uint64_t lo[TRJ_N_MAX], hi[TRJ_N_MAX];
+  __shared__ int32_t bad;
+  const int i = threadIdx.x, r0 = a.node_off[s], r1 = a.node_off[s + 1];
+  const bool range_ok = r0 >= 0 && r1 <= a.T && r1 > r0 && (r1 - r0) <= TRJ_N_MAX;
+  if (!range_ok) {  // its rows are not its own to write: the workgroup that sees all rows does
+    if (chunk == 0 && i == 0) a.status[s] = 1;
+    return;
+  }
+  const int n = r1 - r0, row0 = chunk * PREP_CHUNK;
+  if (row0 >= n) return;
+  const int L = a.prefix_len[s], ko = a.kv_off[s];
+  if (i == 0) bad = !slots_ok(ko, L, n, a.s_pool, a.max_seq_slots);
+  __syncthreads();
+  if (i < n) {
+    const int p = a.parent[r0 + i];
+    if (i == 0 ? p != -1 : (p < 0 || p >= i)) atomicOr(&bad, 1);
+    jump[i] = p;  // nearest ancestor whose bit is not in the row yet, -1: none
+    dep[i] = i > 0;
+    lo[i] = i < 64 ? 1ull << i : 0;
+    hi[i] = i < 64 ? 0 : 1ull << (i - 64);
+  }
+  __syncthreads();
+  const int is_bad = bad;
+  while (!is_bad) {  // parents precede their children, so every jump ends at the root
+    int j = i < n ? jump[i] : -1, jj = -1, dj = 0;
+    uint64_t l = 0, h = 0;
+    if (j >= 0) { jj = jump[j]; dj = dep[j]; l = lo[j]; h = hi[j]; }
+    if (!__syncthreads_or(j >= 0)) break;
+    if (j >= 0) { jump[i] = jj; dep[i] += dj; lo[i] |= l; hi[i] |= h; }
+    __syncthreads();
+  }
+  if (chunk == 0) {
+    if (i == 0) a.status[s] = is_bad;
+    if (i < n) {
+      const int t = r0 + i;
+      a.depth[t] = is_bad ? 0 : dep[i];
+      a.anc[2 * (size_t)t] = is_bad ? 0 : lo[i];
+      a.anc[2 * (size_t)t + 1] = is_bad ? 0 : hi[i];
+      a.row_slot[t] = is_bad ? -1 : ko + L + i;
+      a.row_pos[t] = is_bad ? 0 : L + dep[i];
+      a.row_seq[t] = is_bad ? -1 : s;
+    }
+    if (is_bad)
+      for (int t = r0; t < r1; ++t) zero_row(a, t, i, PREP_THREADS);
+  }
+  if (!a.cs) return;
+  const int half = a.dh >> 1, rows = min(PREP_CHUNK, n - row0);
+  for (int idx = i; idx < rows * half; idx += PREP_THREADS) {
+    const int r = row0 + idx / half, j = idx % half;
+    const double ang = (double)(is_bad ? 0 : L + dep[r]) * pow((double)a.theta, -2.0 * j / a.dh);
+    a.cs[(size_t)(r0 + r) * half + j] = make_float2((float)cos(ang), (float)sin(ang));
+  }
+}
+
+// The attention work list for up to PREP_MAX_SEQS sequences: the records of attn_items_body,
+// one thread per record instead of one per sequence.  ok[s]: LDS or global.
+__device__ inline void few_items_body(const int32_t* node_off, const int32_t* prefix_len, const int32_t* kv_off,
+                                      const int32_t* bad, int B, int rows_per_item, int qg_max,
+                                      int blocks_per_item, int nsplit_max, int32_t* items) {
+  __shared__ int32_t len[PREP_MAX_SEQS], order[PREP_MAX_SEQS], groups[PREP_MAX_SEQS], end[PREP_MAX_SEQS];
+  const int tid = threadIdx.x;
+  int n = 0, l = -1;
+  if (tid < PREP_MAX_SEQS) {
+    if (tid < B && bad[tid] == 0) {
+      n = node_off[tid + 1] - node_off[tid];
+      l = prefix_len[tid] + n;
+    }
+    len[tid] = l;
+    order[tid] = tid;  // places past the last sequence: nothing
+    groups[tid] = end[tid] = 0;
+  }
+  __syncthreads();
+  if (tid < B) {
+    int place = 0;
+    for (int j = 0; j < B; ++j) place += len[j] > l || (len[j] == l && j < tid);
+    const int ng = min((n + rows_per_item - 1) / rows_per_item, qg_max);
+    const int nsp = min((((l + 31) >> 5) + blocks_per_item - 1) / blocks_per_item, nsplit_max);
+    order[place] = tid;
+    groups[place] = ng;
+    end[place] = l < 0 ? 0 : ng * nsp;
+  }
+  __syncthreads();
+  if (tid < WAVE) {  // inclusive sum over the places by one wavefront
+    int v = tid < PREP_MAX_SEQS ? end[tid] : 0;
+    for (int d = 1; d < PREP_MAX_SEQS; d <<= 1) {
+      const int u = __shfl_up(v, d);
+      if (tid >= d) v += u;
+    }
+    if (tid < PREP_MAX_SEQS) end[tid] = v;
+  }
+  __syncthreads();
+  const int total = end[PREP_MAX_SEQS - 1];
+  for (int r = tid; r < total; r += blockDim.x) {
+    int p = 0;
+    while (end[p] <= r) ++p;
+    const int s = order[p], ng = groups[p], j = r - (p ? end[p - 1] : 0);
+    const int rows = node_off[s + 1] - node_off[s];
+    int32_t* rec = items + (size_t)r * 8;
+    rec[0] = s;
+    rec[1] = j % ng;  // the query groups of a split next to each other
+    rec[2] = node_off[s];
+    rec[3] = rows;
+    rec[4] = len[s] - rows;
+    rec[5] = kv_off[s] >> 5;
+    rec[6] = j / ng;
+    rec[7] = ng > 1;  // another query group of the sequence reads the same blocks
+  }
+  if (tid == 0) items[(size_t)B * qg_max * nsplit_max * 8] = total;
+}
+
+__device__ inline void prep_all_sequences(const StepPrep& a) {
+  __shared__ int32_t first[PREP_MAX_SEQS], last[PREP_MAX_SEQS], bad[PREP_MAX_SEQS];
+  const int tid = threadIdx.x;
+  if (tid < a.B) {
+    const int r0 = a.node_off[tid], r1 = a.node_off[tid + 1];
+    const bool ok = r0 >= 0 && r1 <= a.T && r1 > r0 && (r1 - r0) <= TRJ_N_MAX;
+    first[tid] = r0;
+    last[tid] = ok ? r1 : r0;  // an impossible range covers nothing
+    bad[tid] = !ok || !slots_ok(a.kv_off[tid], a.prefix_len[tid], r1 - r0, a.s_pool, a.max_seq_slots);
+  }
+  __syncthreads();
+  for (int t = tid; t < a.T; t += PREP_THREADS) {
+    const int p = a.parent[t];
+    bool covered = false;
+    for (int s = 0; s < a.B; ++s) {
+      const int i = t - first[s];
+      if (i < 0 || t >= last[s]) continue;
+      covered = true;
+      if (i == 0 ? p != -1 : (p < 0 || p >= i)) atomicOr(&bad[s], 1);
+    }
+    if (covered) continue;
+    a.depth[t] = 0;
+    a.anc[2 * (size_t)t] = a.anc[2 * (size_t)t + 1] = 0;
+    a.row_slot[t] = -1;
+    a.row_pos[t] = 0;
+    a.row_seq[t] = -1;
+    zero_row(a, t, 0, 1);
+  }
+  __syncthreads();
+  if (a.items)
+    few_items_body(a.node_off, a.prefix_len, a.kv_off, bad, a.B, a.rows_per_item, a.qg_max, a.blocks_per_item,
+                   a.nsplit_max, a.items);
+}
+
+__global__ __launch_bounds__(PREP_THREADS) void step_prep_kernel(StepPrep a, EmbedRow e, int chunks, int pad_rows) {
+  int b = blockIdx.x;
+  if (b < a.B * chunks) { prep_sequence(a, b / chunks, b % chunks); return; }
+  b -= a.B * chunks;
+  if (b == 0) { prep_all_sequences(a); return; }
+  b -= 1;
+  if (b < pad_rows) { zero_row(a, a.T + b, threadIdx.x, PREP_THREADS); return; }
+  embed_row(e, b - pad_rows);
+}
+
+int launch_step_prep(const StepPrep& a, const EmbedRow& e, hipStream_t st) {
+  const int chunks = a.cs ? ((a.T < TRJ_N_MAX ? a.T : TRJ_N_MAX) + PREP_CHUNK - 1) / PREP_CHUNK : 1;
+  const int pad_rows = a.zero && a.zero_tp > 0 ? a.zero_tp - a.T : 0;
+  step_prep_kernel<<<a.B * chunks + 1 + pad_rows + embed_blocks(e), PREP_THREADS, 0, st>>>(a, e, chunks, pad_rows);
+  return check_launch();
+}
+
 // ------------------------------------------------------------------ static tree template
 // The paper verifies with ONE fixed sparse tree in every step (appendix "Templates for
 // Token Tree"), so everything that depends on the tree alone is computed once into a
@@ -232,11 +429,14 @@ __global__ __launch_bounds__(1024) void tmpl_step_prep_kernel(
     int max_seq_slots, int32_t* __restrict__ status_dev, int32_t* __restrict__ row_slot,
     int32_t* __restrict__ row_pos, int32_t* __restrict__ row_seq, int rows_per_item, int qg_max,
     int blocks_per_item, int nsplit_max, int32_t* __restrict__ items, uint32_t* __restrict__ zero,
-    size_t zero_words) {
+    size_t zero_words, int zero_wgs, EmbedRow e) {
   const int tid = threadIdx.x;
-  if (blockIdx.x > 0) {  // the other workgroups clear the step's padding
-    for (size_t i = (size_t)(blockIdx.x - 1) * 1024 + tid; i < zero_words;
-         i += (size_t)(gridDim.x - 1) * 1024)
+  if (blockIdx.x > zero_wgs) {  // embedding and first norm input, one row each
+    embed_row(e, blockIdx.x - 1 - zero_wgs);
+    return;
+  }
+  if (blockIdx.x > 0) {  // these clear the step's padding
+    for (size_t i = (size_t)(blockIdx.x - 1) * 1024 + tid; i < zero_words; i += (size_t)zero_wgs * 1024)
       zero[i] = 0;
     return;
   }
@@ -271,8 +471,12 @@ __global__ __launch_bounds__(1024) void tmpl_step_prep_kernel(
   }
   if (items) {
     __syncthreads();
-    attn_items_body(node_off, prefix_len, kv_off, status_dev, B, rows_per_item, qg_max,
-                    blocks_per_item, nsplit_max, items, key, cnt, scan);
+    if (B <= PREP_MAX_SEQS)
+      few_items_body(node_off, prefix_len, kv_off, status_dev, B, rows_per_item, qg_max, blocks_per_item,
+                     nsplit_max, items);
+    else
+      attn_items_body(node_off, prefix_len, kv_off, status_dev, B, rows_per_item, qg_max,
+                      blocks_per_item, nsplit_max, items, key, cnt, scan);
   }
 }
 
@@ -281,14 +485,14 @@ int launch_template_step_prep(const TemplateView& v, const int32_t* node_off, co
                               int max_seq_slots, int32_t* status_dev, int32_t* row_slot,
                               int32_t* row_pos, int32_t* row_seq, int rows_per_item, int qg_max,
                               int blocks_per_item, int nsplit_max, int32_t* items, void* zero,
-                              size_t zero_bytes, hipStream_t st) {
+                              size_t zero_bytes, const EmbedRow& e, hipStream_t st) {
   const size_t zw = zero ? zero_bytes / 4 : 0;
   size_t zwgs = (zw + 16 * 1024 - 1) / (16 * 1024);  // 16 words per thread and pass
   if (zwgs > 512) zwgs = 512;
-  tmpl_step_prep_kernel<<<(unsigned)(1 + zwgs), 1024, 0, st>>>(
+  tmpl_step_prep_kernel<<<(unsigned)(1 + zwgs + embed_blocks(e)), 1024, 0, st>>>(
       v, node_off, kv_off, prefix_len, B, T, dh, max_pos, s_pool, max_seq_slots, status_dev, row_slot,
       row_pos, row_seq, rows_per_item, qg_max, blocks_per_item, nsplit_max, items,
-      static_cast<uint32_t*>(zero), zw);
+      static_cast<uint32_t*>(zero), zw, (int)zwgs, e);
   return check_launch();
 }
 
