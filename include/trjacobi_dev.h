@@ -53,7 +53,8 @@ int32_t trj_set_tunable(const char* name, int32_t value);
  * milliseconds to h_ms, their number to h_count, and destroys the events.  Classes:
  * 1 QKV projection, 2 tree attention, 3 attention merge, 4 output projection, 5 split-k
  * sum + residual + RMSNorm, 6 gate/up projection, 7 down projection, 8 LM head, 9 argmax,
- * 10 accept, 11 KV compaction. */
+ * 10 accept with the KV compaction of the step; 9 in bf16 only where the workspace has no
+ * room for the LM head's argmax candidates, 11 none any more. */
 int32_t trj_profile_begin(int32_t kernel_class, int32_t capacity);
 /* The same with a span: the start event goes before a launch of `first_class`, the stop
  * event after the next launch of `last_class` (which the entry point issues later in the

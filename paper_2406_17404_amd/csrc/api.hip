@@ -105,16 +105,16 @@ static void carve_tree(Carver& c, int dtype, int B, int T, int H, int dh, int ma
 }
 
 static void carve_step(Carver& c, const trj_model_desc& m, int B, int T, int max_seq_slots,
-                       bool need_logits, StepWs* w) {
+                       bool head_scratch, StepWs* w) {
   const int d = m.d_model, hd = m.n_heads * m.head_dim, F = m.d_ffn;
   const int kvd = (m.n_kv_heads ? m.n_kv_heads : m.n_heads) * m.head_dim;
   carve_tree(c, m.dtype, B, T, m.n_heads, m.head_dim, max_seq_slots, &w->t);
   w->cs = c.take<float2>((size_t)T * (m.head_dim / 2));
   w->x = c.take<float>((size_t)T * d);
-  // without a logits buffer from the caller the fp32 mode keeps them here; the bf16 mode
-  // takes the argmax in the LM head's epilogue and needs only its candidates
-  w->logits = need_logits && m.dtype != TRJ_BF16 ? c.take<float>((size_t)T * m.vocab) : nullptr;
-  w->cand = need_logits && m.dtype == TRJ_BF16
+  // the head's own scratch: the fp32 mode's logits (if the caller keeps none), the bf16 mode's
+  // argmax candidates from the LM head's epilogue
+  w->logits = head_scratch && m.dtype != TRJ_BF16 ? c.take<float>((size_t)T * m.vocab) : nullptr;
+  w->cand = head_scratch && m.dtype == TRJ_BF16
                 ? c.take<char>(gemm_lm_argmax_scratch_bytes(T, m.vocab)) : nullptr;
   if (m.dtype == TRJ_BF16) {
     const int tp = padded_rows(T);
@@ -526,8 +526,8 @@ int32_t accept_path(const float* logits, const int32_t* tok, const int32_t* pare
   if ((long)T > (long)B * TRJ_N_MAX) return TRJ_ERR_TREE_TOO_LARGE;
   hipStream_t st = (hipStream_t)stream;
   if (logits) TRJ_TRY(launch_argmax(logits, T, V, argmax_out, st));
-  return launch_accept(argmax_out, tok, parent, node_off, nullptr, B, T, accept_len, best_node,
-                       path, bonus_tok, status_dev, st);
+  return launch_accept(argmax_out, tok, parent, node_off, B, T, accept_len, best_node, path, bonus_tok, status_dev,
+                       st);
 }
 
 int32_t kv_compact(void* k_pool, void* v_pool, size_t kv_layer_stride, const int32_t* path,
@@ -566,9 +566,8 @@ int32_t trj_linear(const void* x, const void* w_packed, int32_t T, int32_t n_in,
   float* part = c.take<float>((size_t)sk * T * n_out);
   if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   TRJ_TRY(launch_tile_activation((const uint16_t*)x, T, n_in, tp, xp, st));
-  const RowScale none{nullptr, 0, tp, 0.f, 0.f};
-  if (sk == 1) return launch_gemm_store_f32(xp, (const uint16_t*)w_packed, T, tp, n_in, n_out, 1, none, y, st);
-  TRJ_TRY(launch_gemm_store_f32(xp, (const uint16_t*)w_packed, T, tp, n_in, n_out, sk, none, part, st));
+  if (sk == 1) return launch_gemm_store_f32(xp, (const uint16_t*)w_packed, T, tp, n_in, n_out, 1, y, st);
+  TRJ_TRY(launch_gemm_store_f32(xp, (const uint16_t*)w_packed, T, tp, n_in, n_out, sk, part, st));
   return launch_sum_splits(part, sk, (size_t)T * n_out, y, st);
 }
 
@@ -621,13 +620,17 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
   TuneScope tune_scope;
   Carver c(workspace);
   StepWs w;
-  carve_step(c, m, B, T, max_seq_slots, with_head && logits == nullptr, &w);
+  const bool bf16 = m.dtype == TRJ_BF16;
+  carve_step(c, m, B, T, max_seq_slots, with_head && (bf16 || !logits), &w);
+  if (c.off > ws_bytes && bf16 && logits) {  // no room for the candidates: argmax of the written logits
+    c = Carver(workspace);
+    carve_step(c, m, B, T, max_seq_slots, false, &w);
+  }
   if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   float* lg = logits ? logits : w.logits;
   const float scale = 1.0f / sqrtf((float)dh);
 
   // bf16: the attention output's padding rows and rows of malformed sequences stay zero all step
-  const bool bf16 = m.dtype == TRJ_BF16;
   void* zero = bf16 ? w.op : nullptr;
   const size_t zero_bytes = bf16 ? (size_t)padded_rows(T) * hd * 2 : 0;
   // rotary table: one row per tree row, or (with a prepared template) one row per position,
@@ -678,7 +681,6 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
     const int sk_o = gemm_bf16_split_k(d, tp, hd), sk_d = gemm_bf16_split_k(d, tp, F);
     // the norm's division is done by the projection that consumes hp (RowScale)
     const RowScale rs{w.ssq, reduce_norm_parts(d), tp, 1.0f / (float)d, m.rms_eps};
-    const RowScale none{nullptr, 0, tp, 0.f, 0.f};
     if (!one_prep) { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_embed_norm((const uint16_t*)weights->embed, tok, T, d, V, w.x,
                               weights->h_layers[0].g_attn, tp, w.hp, w.ssq, st)); }
     for (int l = 0; l < m.n_layers; ++l) {
@@ -694,19 +696,15 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
       TRJ_TRY(launch_tree_attn_bf16(w.q, kl, vl, w.t.anc, node_off, kv_off, prefix_len, status_dev,
                                     w.t.items, B, T, H, Hkv, dh, s_pool, max_seq_slots, scale, w.t.attn, 1, tp,
                                     w.op, st));
-      { ProfScope ps_(KC_GEMM_O, st); TRJ_TRY(launch_gemm_store_f32(w.op, (const uint16_t*)lw.wo, T, tp, hd, d, sk_o, none, w.partial, st)); }
+      { ProfScope ps_(KC_GEMM_O, st); TRJ_TRY(launch_gemm_store_f32(w.op, (const uint16_t*)lw.wo, T, tp, hd, d, sk_o, w.partial, st)); }
       { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_o, w.x, lw.g_ffn, T, d, tp, w.hp, w.ssq, st)); }
       { ProfScope ps_(KC_GEMM_GATE_UP, st); TRJ_TRY(launch_gemm_gate_up(w.hp, (const uint16_t*)lw.w_gate_up, tp, d, F, rs, w.act, st)); }
-      { ProfScope ps_(KC_GEMM_DOWN, st); TRJ_TRY(launch_gemm_store_f32(w.act, (const uint16_t*)lw.w_down, T, tp, F, d, sk_d, none, w.partial, st)); }
+      { ProfScope ps_(KC_GEMM_DOWN, st); TRJ_TRY(launch_gemm_store_f32(w.act, (const uint16_t*)lw.w_down, T, tp, F, d, sk_d, w.partial, st)); }
       const float* g_next = l + 1 < m.n_layers ? weights->h_layers[l + 1].g_attn : weights->g_final;
       { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_d, w.x, g_next, T, d, tp, w.hp, w.ssq, st)); }
     }
-    if (!logits) {  // predictions only: argmax in the LM head's epilogue, no logits in memory
-      { ProfScope ps_(KC_GEMM_LM, st); TRJ_TRY(launch_gemm_lm_argmax(w.hp, (const uint16_t*)weights->w_lm, T, tp, d, V, rs, w.cand, argmax_out, st)); }
-    } else {
-      ProfScope ps_(KC_GEMM_LM, st);
-      TRJ_TRY(launch_gemm_store_f32(w.hp, (const uint16_t*)weights->w_lm, T, tp, d, V, 1, rs, lg, st));
-    }
+    ProfScope ps_(KC_GEMM_LM, st);
+    TRJ_TRY(launch_gemm_lm(w.hp, (const uint16_t*)weights->w_lm, T, tp, d, V, rs, logits, w.cand, argmax_out, st));
   } else {
     if (!one_prep) TRJ_TRY(launch_embed(weights->embed, tok, T, d, V, m.dtype, w.x, st));
     for (int l = 0; l < m.n_layers; ++l) {
@@ -728,12 +726,11 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
     TRJ_TRY(launch_rmsnorm_f32(w.x, weights->g_final, T, d, m.rms_eps, w.h, st));
     TRJ_TRY(launch_gemm_f32(w.h, (const float*)weights->w_lm, T, d, V, 0, lg, st));
   }
-  if (lg) { ProfScope ps_(KC_ARGMAX, st); TRJ_TRY(launch_argmax(lg, T, V, argmax_out, st)); }
-  { ProfScope ps_(KC_ACCEPT, st); TRJ_TRY(launch_accept(argmax_out, tok, parent, node_off, status_dev, B, T, accept_len, best_node,
-                        path, bonus_tok, status_dev, st)); }
-  ProfScope ps_(KC_KV_COMPACT, st);
-  return launch_kv_compact(k_pool, v_pool, kv_layer_stride, path, accept_len, kv_off, prefix_len, B,
-                           m.n_layers, Hkv, dh, s_pool, m.dtype, new_len, st);
+  if (!w.cand) { ProfScope ps_(KC_ARGMAX, st); TRJ_TRY(launch_argmax(lg, T, V, argmax_out, st)); }
+  ProfScope ps_(KC_ACCEPT, st);
+  return launch_accept_compact(k_pool, v_pool, kv_layer_stride, argmax_out, tok, parent, node_off, kv_off, prefix_len,
+                               status_dev, B, T, m.n_layers, Hkv, dh, s_pool, m.dtype, accept_len, best_node, path,
+                               bonus_tok, new_len, st);
 }
 
 // workspace bytes of one step_impl call (pure arithmetic)

@@ -1,4 +1,4 @@
-// The projections that store fp32 (split-k partial sums, logits), the launch plan of all
+// The projections that store fp32 split-k partial sums, the launch plan of all
 // projections, and the split-k sum with what follows it.  The kernel is in gemm_ring.h; the
 // projections with a fused epilogue are in gemm_qkv.hip, gemm_gate_up.hip and gemm_lm.hip.
 #include "gemm_ring.h"
@@ -9,10 +9,8 @@ namespace trj {
 // v%4, tile column l%32.  Rows are output features, columns are token rows.
 
 // ---- epilogue: fp32 store, y[split][t][n_out]; 4 consecutive features per store
-template <bool SCALED>
 struct EpiStoreF32T {
-  static constexpr bool kScaled = SCALED;  // are the accumulators divided by the rows' norms first?
-  RowScale rs;
+  static constexpr bool kScaled = false;  // the accumulators are what the caller wants
   float* y;
   int ld, T;
   size_t split_stride;
@@ -170,12 +168,8 @@ int gemm_bf16_split_k(int n_out, int tp, int n_in) {
 }
 
 int launch_gemm_store_f32(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in,
-                          int n_out, int split_k, const RowScale& rs, float* y, hipStream_t st) {
-  if (rs.ssq) {
-    EpiStoreF32T<true> e{rs, y, n_out, T, (size_t)T * n_out};
-    return launch_gemm(xp, w, tp, n_in, n_out, split_k, e, st);
-  }
-  EpiStoreF32T<false> e{rs, y, n_out, T, (size_t)T * n_out};
+                          int n_out, int split_k, float* y, hipStream_t st) {
+  EpiStoreF32T e{y, n_out, T, (size_t)T * n_out};
   return launch_gemm(xp, w, tp, n_in, n_out, split_k, e, st);
 }
 

@@ -114,10 +114,15 @@ int launch_template_step_prep(const TemplateView& v, const int32_t* node_off, co
                               int blocks_per_item, int nsplit_max, int32_t* items, void* zero,
                               size_t zero_bytes, const EmbedRow& e, hipStream_t st);
 int launch_argmax(const float* logits, int T, int V, int32_t* out, hipStream_t st);
-int launch_accept(const int32_t* argmax, const int32_t* tok, const int32_t* parent,
-                  const int32_t* node_off, const int32_t* status_in, int B, int T,
-                  int32_t* accept_len, int32_t* best_node, int32_t* path, int32_t* bonus_tok,
+int launch_accept(const int32_t* argmax, const int32_t* tok, const int32_t* parent, const int32_t* node_off, int B,
+                  int T, int32_t* accept_len, int32_t* best_node, int32_t* path, int32_t* bonus_tok,
                   int32_t* status_dev, hipStream_t st);
+// both of a step; status_dev as the prologue wrote it
+int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const int32_t* argmax, const int32_t* tok,
+                          const int32_t* parent, const int32_t* node_off, const int32_t* kv_off,
+                          const int32_t* prefix_len, const int32_t* status_dev, int B, int T, int n_layers,
+                          int n_heads, int dh, int s_pool, int dtype, int32_t* accept_len, int32_t* best_node,
+                          int32_t* path, int32_t* bonus_tok, int32_t* new_len, hipStream_t st);
 int launch_kv_compact(void* k_pool, void* v_pool, size_t layer_stride, const int32_t* path,
                       const int32_t* accept_len, const int32_t* kv_off, const int32_t* prefix_len,
                       int B, int n_layers, int n_heads, int dh, int s_pool, int dtype,
@@ -167,10 +172,12 @@ int gemm_bf16_split_k(int n_out, int tp, int n_in);
 int gemm_bf16_clamp_split(int n_out, int tp, int n_in, int split_k);
 void gemm_bf16_describe_plan(int tp, int n_in, int n_out, int split_k, int32_t out[6]);
 int launch_gemm_store_f32(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in,
-                          int n_out, int split_k, const RowScale& rs, float* y, hipStream_t st);
+                          int n_out, int split_k, float* y, hipStream_t st);
 size_t gemm_lm_argmax_scratch_bytes(int T, int n_out);
-int launch_gemm_lm_argmax(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out,
-                          const RowScale& rs, void* cand, int32_t* argmax_out, hipStream_t st);
+// fp32 logits (null: none) and the greedy argmax of every row, from candidates of the epilogue
+// (cand null: the logits alone)
+int launch_gemm_lm(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out, const RowScale& rs,
+                   float* logits, void* cand, int32_t* argmax_out, hipStream_t st);
 int launch_gemm_gate_up(const uint16_t* xp, const uint16_t* w, int tp, int n_in, int d_ffn,
                         const RowScale& rs, uint16_t* act, hipStream_t st);
 // q may be null: then only K and V are computed and written (the last layer of a prompt pass)

@@ -499,8 +499,9 @@ int launch_template_step_prep(const TemplateView& v, const int32_t* node_off, co
 // ------------------------------------------------------------------ greedy argmax
 // One workgroup per row; lowest index wins ties; NaN never compares greater.
 // One workgroup per row; every thread keeps ARGMAX_UNROLL 16-byte loads in flight (the row
-// is read once, so the kernel is a latency chain unless the loads are batched).
-constexpr int ARGMAX_THREADS = 1024, ARGMAX_UNROLL = 4;
+// is read once, so the kernel is a latency chain unless the loads are batched: a row of 32000
+// is one batch of eight, 64 such rows 7.2 -> 6.5 us).
+constexpr int ARGMAX_THREADS = 1024, ARGMAX_UNROLL = 8;
 __device__ inline void amax_merge(float& bv, int& bi, float v, int i) {
   if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
 }
@@ -540,9 +541,11 @@ __global__ __launch_bounds__(ARGMAX_THREADS) void argmax_kernel(const float* __r
   __shared__ int si[ARGMAX_THREADS / WAVE];
   if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; }
   __syncthreads();
-  if (tid == 0) {
-    for (int w = 1; w < ARGMAX_THREADS / WAVE; ++w) amax_merge(bv, bi, sv[w], si[w]);
-    out[blockIdx.x] = bi == INT32_MAX ? 0 : bi;
+  if (tid < ARGMAX_THREADS / WAVE) {
+    bv = sv[tid];
+    bi = si[tid];
+    for (int o = ARGMAX_THREADS / WAVE / 2; o > 0; o >>= 1) amax_merge(bv, bi, __shfl_xor(bv, o), __shfl_xor(bi, o));
+    if (tid == 0) out[blockIdx.x] = bi == INT32_MAX ? 0 : bi;
   }
 }
 
@@ -552,80 +555,129 @@ int launch_argmax(const float* logits, int T, int V, int32_t* out, hipStream_t s
 }
 
 // ------------------------------------------------------------------ accept
-// One workgroup of TRJ_N_MAX threads per sequence.  ok[i] is evaluated by walking from
-// i to the root; best = max over ok nodes of (depth, -index).  status_in (optional)
-// marks sequences an earlier kernel already found malformed.
-__global__ __launch_bounds__(TRJ_N_MAX) void accept_kernel(
-    const int32_t* __restrict__ argmax, const int32_t* __restrict__ tok,
-    const int32_t* __restrict__ parent, const int32_t* __restrict__ node_off, int T,
-    const int32_t* status_in, int32_t* __restrict__ accept_len,
-    int32_t* __restrict__ best_node, int32_t* __restrict__ path, int32_t* __restrict__ bonus_tok,
-    int32_t* status_dev) {  // status_in may alias status_dev
-  __shared__ int32_t par[TRJ_N_MAX], tk[TRJ_N_MAX], am[TRJ_N_MAX];
-  __shared__ int32_t bad, best_key;
-  const int s = blockIdx.x, i = threadIdx.x;
-  int r0 = node_off[s], r1 = node_off[s + 1];
-  bool range_ok = r0 >= 0 && r1 <= T && r1 > r0 && (r1 - r0) <= TRJ_N_MAX;
-  int n = range_ok ? r1 - r0 : 0;
-  if (i == 0) {
-    bad = (range_ok && !(status_in && status_in[s] != 0)) ? 0 : 1;
-    best_key = -1;
+// ONE wavefront finds a sequence's longest accepted path, two nodes per lane (node = lane and
+// lane + 64): node i is accepted when its token is the prediction at its parent and the parent
+// is accepted (the root always is); best = max over accepted nodes of (depth, -index).  Depth
+// and acceptance come by pointer doubling on registers passed between lanes, at most 7 rounds
+// and no barrier (64 rows: walking the parents in LDS 3.1 us a launch, doubling in LDS with
+// barriers 4.3, this 3.0; a 128-node chain takes 127 steps to walk).
+struct Accepted {
+  int depth, best, bonus;  // depth of the best node, -1 for a malformed sequence; uniform
+  int path[2];             // nodes lane and lane + 64 of the path, root first; -1 behind its end
+};
+__device__ inline int from_node(const int (&v)[2], int node) {  // v of `node`, any lane's choice
+  const int a = __shfl(v[0], node & 63), b = __shfl(v[1], node & 63);
+  return node < 64 ? a : b;
+}
+__device__ inline Accepted accept_sequence(const int32_t* __restrict__ argmax, const int32_t* __restrict__ tok,
+                                           const int32_t* __restrict__ parent, const int32_t* __restrict__ node_off,
+                                           int T, bool known_bad, int s) {
+  const int lane = threadIdx.x & 63;
+  const int r0 = node_off[s], r1 = node_off[s + 1];
+  const bool range_ok = r0 >= 0 && r1 <= T && r1 > r0 && (r1 - r0) <= TRJ_N_MAX;
+  const int n = range_ok ? r1 - r0 : 0;
+  Accepted r{-1, -1, -1, {-1, -1}};
+  int par[2], tk[2], am[2];
+  bool bad = !range_ok || known_bad;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int i = lane + 64 * h;
+    par[h] = -1;
+    tk[h] = am[h] = 0;
+    if (i >= n) continue;
+    par[h] = parent[r0 + i];
+    tk[h] = tok[r0 + i];
+    am[h] = argmax[r0 + i];
+    bad = bad || (i == 0 ? par[h] != -1 : (par[h] < 0 || par[h] >= i));
   }
-  __syncthreads();
-  if (i < n) {
-    int p = parent[r0 + i];
-    par[i] = p;
-    tk[i] = tok[r0 + i];
-    am[i] = argmax[r0 + i];
-    if (i == 0 ? p != -1 : (p < 0 || p >= i)) atomicOr(&bad, 1);
+  if (__ballot(bad)) return r;
+  // one word per node: nearest ancestor not yet accounted for (255: none), distance to it,
+  // and whether the nodes up to it (itself included, that one not) carry the right tokens
+  int w[2];
+  {
+    int g[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) g[h] = from_node(am, max(par[h], 0));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) w[h] = par[h] < 0 ? 255 | 1 << 16 : par[h] | 1 << 8 | (tk[h] == g[h]) << 16;
   }
-  __syncthreads();
-  int32_t* my_path = path + (size_t)s * TRJ_N_MAX;
-  my_path[i] = -1;
-  if (bad) {
-    if (i == 0) {
-      status_dev[s] = 1;
-      accept_len[s] = -1;
-      best_node[s] = -1;
-      bonus_tok[s] = -1;
-    }
-    return;
+  while (__ballot((w[0] & 255) != 255 || (w[1] & 255) != 255)) {
+    int u[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) u[h] = from_node(w, w[h] & 127);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if ((w[h] & 255) != 255)
+        w[h] = (u[h] & 255) | ((w[h] & 0xff00) + (u[h] & 0xff00)) | (w[h] & u[h] & 0x10000);
   }
-  if (i < n) {
-    bool ok = true;
-    int d = 0;
-    for (int j = i; j > 0; j = par[j]) {
-      ok = ok && (tk[j] == am[par[j]]);
-      ++d;
-    }
-    if (ok) atomicMax(&best_key, (d << 8) | (255 - i));
+  int key = -1;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int i = lane + 64 * h;
+    if (i < n && (w[h] & 0x10000)) key = max(key, (w[h] & 0xff00) | (255 - i));
   }
-  __syncthreads();  // also orders the -1 fill above before the path writes below
-  if (i == 0) {
-    int key = best_key;  // the root is always ok, so key >= 255
-    int b = 255 - (key & 255), d = key >> 8;
-    status_dev[s] = 0;
-    accept_len[s] = d;
-    best_node[s] = b;
-    bonus_tok[s] = am[b];
-    for (int j = b, k = d; j >= 0; j = par[j], --k) my_path[k] = j;
+  for (int o = 32; o > 0; o >>= 1) key = max(key, __shfl_xor(key, o));
+  r.depth = key >> 8;  // the root is always accepted
+  r.best = 255 - (key & 255);
+  r.bonus = from_node(am, r.best);
+  for (int j = r.best, k = r.depth; j >= 0; j = from_node(par, j), --k) {
+    if (lane == k) r.path[0] = j;
+    if (lane + 64 == k) r.path[1] = j;
+  }
+  return r;
+}
+__device__ inline void accept_store(const Accepted& r, int s, int32_t* accept_len, int32_t* best_node, int32_t* path,
+                                    int32_t* bonus_tok) {
+  const int lane = threadIdx.x & 63;
+  path[(size_t)s * TRJ_N_MAX + lane] = r.path[0];
+  path[(size_t)s * TRJ_N_MAX + 64 + lane] = r.path[1];
+  if (lane == 0) {
+    accept_len[s] = r.depth;
+    best_node[s] = r.best;
+    bonus_tok[s] = r.bonus;
   }
 }
 
-int launch_accept(const int32_t* argmax, const int32_t* tok, const int32_t* parent,
-                  const int32_t* node_off, const int32_t* status_in, int B, int T,
-                  int32_t* accept_len, int32_t* best_node, int32_t* path, int32_t* bonus_tok,
+__global__ __launch_bounds__(WAVE) void accept_kernel(
+    const int32_t* __restrict__ argmax, const int32_t* __restrict__ tok,
+    const int32_t* __restrict__ parent, const int32_t* __restrict__ node_off, int T,
+    int32_t* __restrict__ accept_len, int32_t* __restrict__ best_node, int32_t* __restrict__ path,
+    int32_t* __restrict__ bonus_tok, int32_t* __restrict__ status_dev) {
+  const int s = blockIdx.x;
+  const Accepted r = accept_sequence(argmax, tok, parent, node_off, T, false, s);
+  accept_store(r, s, accept_len, best_node, path, bonus_tok);
+  if (threadIdx.x == 0) status_dev[s] = r.depth < 0;
+}
+
+int launch_accept(const int32_t* argmax, const int32_t* tok, const int32_t* parent, const int32_t* node_off, int B,
+                  int T, int32_t* accept_len, int32_t* best_node, int32_t* path, int32_t* bonus_tok,
                   int32_t* status_dev, hipStream_t st) {
-  accept_kernel<<<B, TRJ_N_MAX, 0, st>>>(argmax, tok, parent, node_off, T, status_in, accept_len,
-                                         best_node, path, bonus_tok, status_dev);
+  accept_kernel<<<B, WAVE, 0, st>>>(argmax, tok, parent, node_off, T, accept_len, best_node, path, bonus_tok,
+                                    status_dev);
   return check_launch();
 }
 
 // ------------------------------------------------------------------ KV compaction
-// One workgroup per (sequence, layer*head) plane, one thread per head_dim column.
-// Row j of the accepted path moves from slot base+path[j] to base+j.  path is
-// increasing with path[j] >= j, so copying in increasing j with a barrier between rows
-// never overwrites a row that is still to be read.
+// One workgroup per (sequence, layer*head) plane; a thread owns head_dim columns.  Row j of
+// the accepted path moves from slot base+path[j] to base+j.  path is increasing with
+// path[j] >= j, so copying in increasing j never overwrites a row that is still to be read,
+// and a thread reads and writes its own columns only: no barrier.  (Bound by the scattered
+// reach over 2 x 1024 planes, not by the rows: eight rows requested together, or K rows as
+// 16-byte pieces, took 7.3-7.8 us for a path of 6 in 32 x 32 planes, row by row 6.2.)
+template <typename E>
+__device__ __forceinline__ void compact_plane(E* __restrict__ kp, E* __restrict__ vp, const int32_t* pth, int a,
+                                              int base, int dh, int s_pool) {
+  for (int j = 0; j <= a && j < TRJ_N_MAX; ++j) {
+    const int src = pth[j];
+    if (src <= j || src >= TRJ_N_MAX || base + src >= s_pool) continue;  // uniform over the workgroup
+    for (int c = threadIdx.x; c < dh; c += blockDim.x) {
+      const E kk = kp[k_off(base + src, c, dh)];
+      const E vv = vp[v_off(base + src, c, dh)];
+      kp[k_off(base + j, c, dh)] = kk;
+      vp[v_off(base + j, c, dh)] = vv;
+    }
+  }
+}
 template <typename E>
 __global__ void kv_compact_kernel(E* __restrict__ k_pool, E* __restrict__ v_pool,
                                   size_t layer_stride, const int32_t* __restrict__ path,
@@ -634,27 +686,12 @@ __global__ void kv_compact_kernel(E* __restrict__ k_pool, E* __restrict__ v_pool
                                   const int32_t* __restrict__ prefix_len, int n_heads, int dh,
                                   int s_pool, int32_t* __restrict__ new_len) {
   const int s = blockIdx.x, plane = blockIdx.y;
-  const int layer = plane / n_heads, head = plane % n_heads;
   const int a = accept_len[s];
-  const int L = prefix_len[s];
+  const int L = prefix_len[s], ko = kv_off[s];
   if (plane == 0 && threadIdx.x == 0) new_len[s] = a < 0 ? L : L + a + 1;
-  if (a < 0 || L < 0 || kv_off[s] < 0) return;
-  const int base = kv_off[s] + L;
-  E* kp = k_pool + layer * layer_stride + (size_t)head * s_pool * dh;
-  E* vp = v_pool + layer * layer_stride + (size_t)head * s_pool * dh;
-  const int32_t* pth = path + (size_t)s * TRJ_N_MAX;
-  for (int j = 0; j <= a && j < TRJ_N_MAX; ++j) {
-    int src = pth[j];
-    if (src > j && src < TRJ_N_MAX && base + src < s_pool) {  // uniform over the workgroup
-      for (int c = threadIdx.x; c < dh; c += blockDim.x) {
-        E kk = kp[k_off(base + src, c, dh)];
-        E vv = vp[v_off(base + src, c, dh)];
-        kp[k_off(base + j, c, dh)] = kk;
-        vp[v_off(base + j, c, dh)] = vv;
-      }
-    }
-    __syncthreads();
-  }
+  if (a < 0 || L < 0 || ko < 0) return;
+  const size_t off = (plane / n_heads) * layer_stride + (size_t)(plane % n_heads) * s_pool * dh;
+  compact_plane(k_pool + off, v_pool + off, path + (size_t)s * TRJ_N_MAX, a, ko + L, dh, s_pool);
 }
 
 int launch_kv_compact(void* k_pool, void* v_pool, size_t layer_stride, const int32_t* path,
@@ -671,6 +708,55 @@ int launch_kv_compact(void* k_pool, void* v_pool, size_t layer_stride, const int
     kv_compact_kernel<uint32_t><<<grid, threads, 0, st>>>((uint32_t*)k_pool, (uint32_t*)v_pool,
                                                           layer_stride, path, accept_len, kv_off,
                                                           prefix_len, n_heads, dh, s_pool, new_len);
+  return check_launch();
+}
+
+// Acceptance and compaction of a step in one launch: every plane's workgroup works the path
+// out for itself (three 512-byte reads and a few rounds in LDS) instead of waiting for a launch
+// that does only this; plane 0 writes it out.  Tail of a step 9.4 -> 5.0 us.
+template <typename E>
+__global__ __launch_bounds__(TRJ_N_MAX) void accept_compact_kernel(
+    E* __restrict__ k_pool, E* __restrict__ v_pool, size_t layer_stride, const int32_t* __restrict__ argmax,
+    const int32_t* __restrict__ tok, const int32_t* __restrict__ parent, const int32_t* __restrict__ node_off,
+    const int32_t* __restrict__ kv_off, const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ status_dev,
+    int T, int n_heads, int dh, int s_pool, int32_t* __restrict__ accept_len, int32_t* __restrict__ best_node,
+    int32_t* __restrict__ path, int32_t* __restrict__ bonus_tok, int32_t* __restrict__ new_len) {
+  __shared__ int32_t pth[TRJ_N_MAX];
+  __shared__ int32_t depth;
+  const int s = blockIdx.x, plane = blockIdx.y;
+  const int L = prefix_len[s], ko = kv_off[s];
+  if (threadIdx.x < WAVE) {
+    // the prologue's verdict on tree and slots stands and is not written again (every plane reads it)
+    const Accepted r = accept_sequence(argmax, tok, parent, node_off, T, status_dev[s] != 0, s);
+    if (plane == 0) {
+      accept_store(r, s, accept_len, best_node, path, bonus_tok);
+      if (threadIdx.x == 0) new_len[s] = r.depth < 0 ? L : L + r.depth + 1;
+    }
+    pth[threadIdx.x] = r.path[0];
+    pth[threadIdx.x + WAVE] = r.path[1];
+    if (threadIdx.x == 0) depth = r.depth;
+  }
+  __syncthreads();
+  const int d = depth;
+  if (d < 0) return;  // the prologue checked kv_off and prefix_len of every sequence left
+  const size_t off = (plane / n_heads) * layer_stride + (size_t)(plane % n_heads) * s_pool * dh;
+  compact_plane(k_pool + off, v_pool + off, pth, d, ko + L, dh, s_pool);
+}
+
+int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const int32_t* argmax, const int32_t* tok,
+                          const int32_t* parent, const int32_t* node_off, const int32_t* kv_off,
+                          const int32_t* prefix_len, const int32_t* status_dev, int B, int T, int n_layers,
+                          int n_heads, int dh, int s_pool, int dtype, int32_t* accept_len, int32_t* best_node,
+                          int32_t* path, int32_t* bonus_tok, int32_t* new_len, hipStream_t st) {
+  dim3 grid(B, n_layers * n_heads);
+  if (dtype == TRJ_BF16)
+    accept_compact_kernel<uint16_t><<<grid, TRJ_N_MAX, 0, st>>>(
+        (uint16_t*)k_pool, (uint16_t*)v_pool, layer_stride, argmax, tok, parent, node_off, kv_off, prefix_len,
+        status_dev, T, n_heads, dh, s_pool, accept_len, best_node, path, bonus_tok, new_len);
+  else
+    accept_compact_kernel<uint32_t><<<grid, TRJ_N_MAX, 0, st>>>(
+        (uint32_t*)k_pool, (uint32_t*)v_pool, layer_stride, argmax, tok, parent, node_off, kv_off, prefix_len,
+        status_dev, T, n_heads, dh, s_pool, accept_len, best_node, path, bonus_tok, new_len);
   return check_launch();
 }
 
