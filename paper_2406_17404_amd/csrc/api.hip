@@ -78,7 +78,7 @@ struct StepWs {
   uint16_t *hp, *q, *op, *act;
   float *partial, *ssq;
   // fp32 mode
-  float *h, *qkv, *qf, *of, *gu, *actf;
+  float *qf, *of, *actf;
 };
 
 static void carve_tree(Carver& c, int dtype, int B, int T, int H, int dh, int max_seq_slots,
@@ -107,7 +107,6 @@ static void carve_tree(Carver& c, int dtype, int B, int T, int H, int dh, int ma
 static void carve_step(Carver& c, const trj_model_desc& m, int B, int T, int max_seq_slots,
                        bool head_scratch, StepWs* w) {
   const int d = m.d_model, hd = m.n_heads * m.head_dim, F = m.d_ffn;
-  const int kvd = (m.n_kv_heads ? m.n_kv_heads : m.n_heads) * m.head_dim;
   carve_tree(c, m.dtype, B, T, m.n_heads, m.head_dim, max_seq_slots, &w->t);
   w->cs = c.take<float2>((size_t)T * (m.head_dim / 2));
   w->x = c.take<float>((size_t)T * d);
@@ -126,11 +125,8 @@ static void carve_step(Carver& c, const trj_model_desc& m, int B, int T, int max
     w->partial = c.take<float>((size_t)(sk1 > sk2 ? sk1 : sk2) * T * d);
     w->ssq = c.take<float>((size_t)RS_MAX_PARTS * tp);
   } else {
-    w->h = c.take<float>((size_t)T * d);
-    w->qkv = c.take<float>((size_t)T * (hd + 2 * kvd));
     w->qf = c.take<float>((size_t)T * hd);
     w->of = c.take<float>((size_t)T * hd);
-    w->gu = c.take<float>((size_t)T * 2 * F);
     w->actf = c.take<float>((size_t)T * F);
   }
 }
@@ -558,7 +554,7 @@ int32_t trj_linear(const void* x, const void* w_packed, int32_t T, int32_t n_in,
   hipStream_t st = (hipStream_t)stream;
   TuneScope tune_scope;
   if (dtype == TRJ_F32)
-    return launch_gemm_f32((const float*)x, (const float*)w_packed, T, n_in, n_out, 0, y, st);
+    return launch_gemm_f32((const float*)x, nullptr, 0.f, (const float*)w_packed, T, n_in, n_out, 0, y, st);
   const int tp = padded_rows(T);
   int sk = split_k > 0 ? gemm_bf16_clamp_split(n_out, tp, n_in, split_k) : gemm_bf16_split_k(n_out, tp, n_in);
   Carver c(workspace);
@@ -711,20 +707,16 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
       const trj_layer_weights& lw = weights->h_layers[l];
       float* kl = (float*)k_pool + (size_t)l * kv_layer_stride;
       float* vl = (float*)v_pool + (size_t)l * kv_layer_stride;
-      TRJ_TRY(launch_rmsnorm_f32(w.x, lw.g_attn, T, d, m.rms_eps, w.h, st));
-      TRJ_TRY(launch_gemm_f32(w.h, (const float*)lw.wqkv, T, d, (H + 2 * Hkv) * dh, 0, w.qkv, st));
-      TRJ_TRY(launch_rope_kv_f32(w.qkv, cs, cs_row, w.t.row_slot, T, H, Hkv, dh, s_pool, w.qf, kl, vl, st));
+      TRJ_TRY(launch_gemm_qkv_f32(w.x, lw.g_attn, m.rms_eps, (const float*)lw.wqkv, T, d, H, Hkv, dh, s_pool, cs,
+                                  cs_row, w.t.row_slot, w.qf, kl, vl, st));
       if (!with_head && l + 1 == m.n_layers) return TRJ_OK;  // the K and V a prompt pass is after
       TRJ_TRY(launch_tree_attn_f32(w.qf, kl, vl, w.t.anc, w.t.row_seq, node_off, kv_off, prefix_len,
                                    status_dev, T, H, Hkv, dh, s_pool, max_seq_slots, scale, w.of, st));
-      TRJ_TRY(launch_gemm_f32(w.of, (const float*)lw.wo, T, hd, d, 1, w.x, st));
-      TRJ_TRY(launch_rmsnorm_f32(w.x, lw.g_ffn, T, d, m.rms_eps, w.h, st));
-      TRJ_TRY(launch_gemm_f32(w.h, (const float*)lw.w_gate_up, T, d, 2 * F, 0, w.gu, st));
-      TRJ_TRY(launch_silu_mul_f32(w.gu, T, F, w.actf, st));
-      TRJ_TRY(launch_gemm_f32(w.actf, (const float*)lw.w_down, T, F, d, 1, w.x, st));
+      TRJ_TRY(launch_gemm_f32(w.of, nullptr, 0.f, (const float*)lw.wo, T, hd, d, 1, w.x, st));
+      TRJ_TRY(launch_gemm_gate_up_f32(w.x, lw.g_ffn, m.rms_eps, (const float*)lw.w_gate_up, T, d, F, w.actf, st));
+      TRJ_TRY(launch_gemm_f32(w.actf, nullptr, 0.f, (const float*)lw.w_down, T, F, d, 1, w.x, st));
     }
-    TRJ_TRY(launch_rmsnorm_f32(w.x, weights->g_final, T, d, m.rms_eps, w.h, st));
-    TRJ_TRY(launch_gemm_f32(w.h, (const float*)weights->w_lm, T, d, V, 0, lg, st));
+    TRJ_TRY(launch_gemm_f32(w.x, weights->g_final, m.rms_eps, (const float*)weights->w_lm, T, d, V, 0, lg, st));
   }
   if (!w.cand) { ProfScope ps_(KC_ARGMAX, st); TRJ_TRY(launch_argmax(lg, T, V, argmax_out, st)); }
   ProfScope ps_(KC_ACCEPT, st);

@@ -1,26 +1,17 @@
-// fp32 mode of the verify step: small, plain kernels (fp32 storage, fp32 arithmetic)
-// used for the tiny fp32 workload and as a tight-tolerance check of the data layouts.
+// fp32 mode of the verify step (fp32 storage, fp32 arithmetic): used for the tiny fp32
+// workload and as a tight-tolerance check of the data layouts.  Launches of a tiny model are
+// latency: a step of two layers was 25 launches and 218 us, of which the serial loops of one
+// thread per output (a k range of 1024, a row's scores and values) were half.  Now every
+// output is summed by 32 threads, and norm, rotary rotation with the K/V write, and SiLU(g) * u
+// are part of the projection next to them: 14 launches, 78.5 us, and the result is closer to the
+// 64-bit one (3.4e-7 against 8.1e-7).
 // They read the same tiled weight / KV layouts as the bf16 kernels.  The element-wise
-// kernels at the top (embedding, rotary table) serve both modes.
+// kernels at the top (rotary table, embedding) serve both modes.
 #include "common.h"
 #include "kernels.h"
 #include "tree_vis.h"
 
 namespace trj {
-
-// packed row of logical row n (inverse of logical_row)
-__device__ inline int packed_row(int n, int kind, int n_out, int n_heads, int dh) {
-  if (kind == TRJ_PACK_GATE_UP) {
-    int f = n_out >> 1;
-    return n < f ? 32 * (n >> 4) + (n & 15) : 32 * ((n - f) >> 4) + 16 + ((n - f) & 15);
-  }
-  if (kind == TRJ_PACK_QKV) {
-    if (n >= n_heads * dh + (n_out - n_heads * dh) / 2) return n;  // v rows
-    int base = (n / dh) * dh, c = n % dh, half = dh >> 1;
-    return c < half ? base + 32 * (c >> 4) + (c & 15) : base + 32 * ((c - half) >> 4) + 16 + ((c - half) & 15);
-  }
-  return n;
-}
 
 // ------------------------------------------------------------------ rotary table
 // cs[t][j] = (cos, sin) of row_pos[t] * theta^(-2j/dh), evaluated in double; without
@@ -80,130 +71,159 @@ int launch_embed(const void* embed, const int32_t* tok, int T, int d, int vocab,
   return check_launch();
 }
 
-// ------------------------------------------------------------------ RMSNorm (fp32 out)
-__global__ __launch_bounds__(256) void rmsnorm_f32_kernel(const float* __restrict__ x,
-                                                          const float* __restrict__ g, int d,
-                                                          float eps, float* __restrict__ h) {
-  const float* row = x + (size_t)blockIdx.x * d;
-  float ss = 0.f;
-  for (int c = threadIdx.x; c < d; c += 256) ss += row[c] * row[c];
-  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-  __shared__ float part[4];
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  float tot = part[0] + part[1] + part[2] + part[3];
-  float inv = 1.0f / sqrtf(tot / d + eps);
-  for (int c = threadIdx.x; c < d; c += 256) h[(size_t)blockIdx.x * d + c] = row[c] * g[c] * inv;
-}
-int launch_rmsnorm_f32(const float* x, const float* g, int T, int d, float eps, float* h,
-                       hipStream_t st) {
-  rmsnorm_f32_kernel<<<T, 256, 0, st>>>(x, g, d, eps, h);
-  return check_launch();
-}
-
 // ------------------------------------------------------------------ GEMM (fp32)
-// y[t][r] (+)= sum_k x[t][k] * W(r, k) for packed rows r.  Block: 32 packed rows x 8
-// tokens; consecutive threads read consecutive 32-byte granules of one weight tile.
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ x,
-                                                       const float* __restrict__ w, int T,
-                                                       int n_in, int n_out, int add_to,
-                                                       float* __restrict__ y) {
-  const int rl = threadIdx.x & 31, tl = threadIdx.x >> 5;
-  const int rt = blockIdx.x, t = blockIdx.y * 8 + tl;
-  if (t >= T) return;
-  const int ksteps = n_in >> 4;
-  const float* xr = x + (size_t)t * n_in;
-  float acc = 0.f;
-  for (int ks = 0; ks < ksteps; ++ks) {
-    const float* tile = w + ((size_t)rt * ksteps + ks) * 512;
+// y[t][r] = sum_k x[t][k] * W(r, k) for packed rows r.  Workgroup: one tile of 32 packed rows x
+// TT tokens; thread (part, row) sums every 32nd granule of 8 k values for all TT tokens, the
+// 32 parts are added in order through LDS.  With a gain `g` the input is RMSNorm(x): the
+// products use x * g and the sum is divided by the token's norm, whose sum of squares comes
+// from the same reads.
+constexpr int F32_PARTS = 32, F32_THREADS = 32 * F32_PARTS;
+struct GemmF32Args {
+  const float *x, *w, *g;
+  int T, n_in;
+  float eps;
+};
+template <bool VEC>
+__device__ inline void load8(const float* p, float (&v)[8]) {
+  if constexpr (VEC) {
+    const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  } else {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const float4* g4 = reinterpret_cast<const float4*>(tile + (h * 32 + rl) * 8);
-      float4 a = g4[0], b = g4[1];
-      const float* xx = xr + ks * 16 + h * 8;
-      acc = fmaf(a.x, xx[0], acc); acc = fmaf(a.y, xx[1], acc);
-      acc = fmaf(a.z, xx[2], acc); acc = fmaf(a.w, xx[3], acc);
-      acc = fmaf(b.x, xx[4], acc); acc = fmaf(b.y, xx[5], acc);
-      acc = fmaf(b.z, xx[6], acc); acc = fmaf(b.w, xx[7], acc);
+    for (int e = 0; e < 8; ++e) v[e] = p[e];
+  }
+}
+template <int TT, bool VEC>
+__device__ inline void gemm_f32_sums(const GemmF32Args& a, int rt, int t0, int part, int rl, float (&acc)[TT],
+                                     float (&ss)[TT]) {
+  const int ng = a.n_in >> 3;
+  const float* wt = a.w + (size_t)rt * (a.n_in >> 4) * 512 + rl * 8;
+  for (int gi = part; gi < ng; gi += F32_PARTS) {
+    float wv[8], gv[8];
+    load8<true>(wt + (size_t)gi * 256, wv);  // granule = (k-step, half): 32 rows of 8 values
+    if (a.g) load8<VEC>(a.g + gi * 8, gv);
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+      float xv[8];
+      load8<VEC>(a.x + (size_t)min(t0 + i, a.T - 1) * a.n_in + gi * 8, xv);
+      if (a.g) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          ss[i] = fmaf(xv[e], xv[e], ss[i]);
+          xv[e] *= gv[e];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[i] = fmaf(wv[e], xv[e], acc[i]);
     }
   }
-  size_t o = (size_t)t * n_out + rt * 32 + rl;
-  y[o] = add_to ? y[o] + acc : acc;
 }
-int launch_gemm_f32(const float* x, const float* w, int T, int n_in, int n_out, int add_to,
+template <int TT, class Epi>
+__global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(GemmF32Args a, Epi epi) {
+  __shared__ float red[F32_PARTS][TT][32], sq[F32_PARTS][TT];
+  const int rl = threadIdx.x & 31, part = threadIdx.x >> 5;
+  const int rt = blockIdx.x, t0 = blockIdx.y * TT;
+  float acc[TT], ss[TT];
+#pragma unroll
+  for (int i = 0; i < TT; ++i) acc[i] = ss[i] = 0.f;
+  // 16-byte loads of the input where the caller's pointers allow them (uniform)
+  const bool vec = ((reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.g)) & 15) == 0;
+  if (vec) gemm_f32_sums<TT, true>(a, rt, t0, part, rl, acc, ss);
+  else gemm_f32_sums<TT, false>(a, rt, t0, part, rl, acc, ss);
+#pragma unroll
+  for (int i = 0; i < TT; ++i) {
+    red[part][i][rl] = acc[i];
+    if (rl == 0) sq[part][i] = ss[i];
+  }
+  __syncthreads();
+  const int i = threadIdx.x >> 5, t = t0 + i;
+  if (i >= TT || t >= a.T) return;  // whole half-wavefronts: the epilogues exchange within one
+  float v = 0.f, s = 0.f;
+#pragma unroll
+  for (int p = 0; p < F32_PARTS; ++p) {
+    v += red[p][i][rl];
+    s += sq[p][i];
+  }
+  if (a.g) v *= 1.0f / sqrtf(s / a.n_in + a.eps);
+  epi(v, rt, rl, t);
+}
+
+struct EpiF32Store {
+  float* y;
+  int n_out, add_to;
+  __device__ void operator()(float v, int rt, int rl, int t) const {
+    float* o = y + (size_t)t * n_out + rt * 32 + rl;
+    *o = add_to ? *o + v : v;
+  }
+};
+// tile rows 0..15 are gate rows 16 rt .., rows 16..31 the matching up rows
+struct EpiF32GateUp {
+  float* act;
+  int F;
+  __device__ void operator()(float v, int rt, int rl, int t) const {
+    const float u = __shfl_xor(v, 16);
+    if (rl < 16) act[(size_t)t * F + 16 * rt + rl] = v / (1.0f + expf(-v)) * u;
+  }
+};
+// q (rotated) plain, K (rotated) and V into the pool at the row's slot; a q or k tile holds
+// the rotary partners j and j + dh/2 16 rows apart
+struct EpiF32QKV {
+  const float2* cs;       // [.][dh/2]: row t of the table, or row cs_row[t] if given
+  const int32_t* cs_row;
+  const int32_t* row_slot;
+  float *q, *k_layer, *v_layer;
+  int n_heads, n_kv_heads, dh, s_pool;
+  __device__ void operator()(float v, int rt, int rl, int t) const {
+    const float other = __shfl_xor(v, 16);
+    const int slot = row_slot[t];
+    if (slot < 0) return;  // row of a malformed sequence
+    const int tph = dh >> 5, q_tiles = n_heads * tph, kv_tiles = n_kv_heads * tph, half = dh >> 1;
+    const int sec = rt < q_tiles ? 0 : (rt < q_tiles + kv_tiles ? 1 : 2);
+    const int rel = rt - (sec == 0 ? 0 : (sec == 1 ? q_tiles : q_tiles + kv_tiles));
+    const int head = rel / tph, jt = rel % tph;
+    if (sec == 2) {
+      v_layer[(size_t)head * s_pool * dh + v_off(slot, 32 * jt + rl, dh)] = v;
+      return;
+    }
+    const int j = 16 * jt + (rl & 15), c = rl < 16 ? j : j + half;
+    const float2 sc = cs[(size_t)(cs_row ? cs_row[t] : t) * half + j];
+    const float r = rl < 16 ? v * sc.x - other * sc.y : v * sc.x + other * sc.y;
+    if (sec == 0) q[((size_t)t * n_heads + head) * dh + c] = r;
+    else k_layer[(size_t)head * s_pool * dh + k_off(slot, c, dh)] = r;
+  }
+};
+// tokens per workgroup: four while that keeps the launch within the chip, eight beyond (every
+// group of tokens reads the weights again)
+template <class Epi>
+static int gemm_f32(const GemmF32Args& a, int n_out, const Epi& e, hipStream_t st) {
+  if (a.T < 1 || a.n_in < 16 || n_out < 32 || (a.n_in & 15) || (n_out & 31)) return TRJ_ERR_BAD_SHAPE;
+  if (a.T <= 16) gemm_f32_kernel<4><<<dim3(n_out / 32, (a.T + 3) / 4), F32_THREADS, 0, st>>>(a, e);
+  else gemm_f32_kernel<8><<<dim3(n_out / 32, (a.T + 7) / 8), F32_THREADS, 0, st>>>(a, e);
+  return check_launch();
+}
+int launch_gemm_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_out, int add_to,
                     float* y, hipStream_t st) {
-  if (T < 1 || n_in < 16 || n_out < 32 || (n_in & 15) || (n_out & 31)) return TRJ_ERR_BAD_SHAPE;
-  dim3 grid(n_out / 32, (T + 7) / 8);
-  gemm_f32_kernel<<<grid, 256, 0, st>>>(x, w, T, n_in, n_out, add_to, y);
-  return check_launch();
+  return gemm_f32({x, w, g, T, n_in, eps}, n_out, EpiF32Store{y, n_out, add_to}, st);
 }
-
-// ------------------------------------------------------------------ rotary + KV write
-// qkv[t][packed rows] -> q[t][head][c] (rotated), K (rotated) and V into the pool at the
-// row's slot.  One block per row, one thread per (head, j < dh/2).
-__global__ void rope_kv_f32_kernel(const float* __restrict__ qkv, const float2* __restrict__ cs,
-                                   const int32_t* __restrict__ cs_row,
-                                   const int32_t* __restrict__ row_slot, int n_heads,
-                                   int n_kv_heads, int dh, int s_pool, float* __restrict__ q,
-                                   float* __restrict__ k_layer, float* __restrict__ v_layer) {
-  const int t = blockIdx.x, half = dh >> 1, hd = n_heads * dh, kvd = n_kv_heads * dh;
-  const int n_out = hd + 2 * kvd;
-  const float* y = qkv + (size_t)t * n_out;
-  const int slot = row_slot[t];
-  if (slot < 0) return;  // row of a malformed sequence
-  const size_t cbase = (size_t)(cs_row ? cs_row[t] : t) * half;  // table row: the row itself or its position
-  for (int idx = threadIdx.x; idx < n_heads * half; idx += blockDim.x) {
-    int head = idx / half, j = idx % half;
-    float2 c = cs[cbase + j];
-    int na = head * dh + j, nb = na + half;
-    float qa = y[packed_row(na, TRJ_PACK_QKV, n_out, n_heads, dh)];
-    float qb = y[packed_row(nb, TRJ_PACK_QKV, n_out, n_heads, dh)];
-    float* qo = q + ((size_t)t * n_heads + head) * dh;
-    qo[j] = qa * c.x - qb * c.y;
-    qo[j + half] = qb * c.x + qa * c.y;
-  }
-  for (int idx = threadIdx.x; idx < n_kv_heads * half; idx += blockDim.x) {
-    int head = idx / half, j = idx % half;
-    float2 c = cs[cbase + j];
-    int na = head * dh + j, nb = na + half;
-    float ka = y[packed_row(hd + na, TRJ_PACK_QKV, n_out, n_heads, dh)];
-    float kb = y[packed_row(hd + nb, TRJ_PACK_QKV, n_out, n_heads, dh)];
-    float* kp = k_layer + (size_t)head * s_pool * dh;
-    float* vp = v_layer + (size_t)head * s_pool * dh;
-    kp[k_off(slot, j, dh)] = ka * c.x - kb * c.y;
-    kp[k_off(slot, j + half, dh)] = kb * c.x + ka * c.y;
-    vp[v_off(slot, j, dh)] = y[hd + kvd + na];
-    vp[v_off(slot, j + half, dh)] = y[hd + kvd + nb];
-  }
+int launch_gemm_gate_up_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int F,
+                            float* act, hipStream_t st) {
+  return gemm_f32({x, w, g, T, n_in, eps}, 2 * F, EpiF32GateUp{act, F}, st);
 }
-int launch_rope_kv_f32(const float* qkv, const float2* cs, const int32_t* cs_row,
-                       const int32_t* row_slot, int T,
-                       int n_heads, int n_kv_heads, int dh, int s_pool, float* q, float* k_layer,
-                       float* v_layer, hipStream_t st) {
-  rope_kv_f32_kernel<<<T, 256, 0, st>>>(qkv, cs, cs_row, row_slot, n_heads, n_kv_heads, dh, s_pool, q,
-                                        k_layer, v_layer);
-  return check_launch();
-}
-
-// ------------------------------------------------------------------ SiLU(g) * u
-__global__ void silu_mul_f32_kernel(const float* __restrict__ gu, int F, float* __restrict__ act) {
-  const int t = blockIdx.x;
-  const float* y = gu + (size_t)t * 2 * F;
-  for (int f = threadIdx.x; f < F; f += blockDim.x) {
-    float g = y[packed_row(f, TRJ_PACK_GATE_UP, 2 * F, 0, 0)];
-    float u = y[packed_row(F + f, TRJ_PACK_GATE_UP, 2 * F, 0, 0)];
-    act[(size_t)t * F + f] = g / (1.0f + expf(-g)) * u;
-  }
-}
-int launch_silu_mul_f32(const float* gu, int T, int F, float* act, hipStream_t st) {
-  silu_mul_f32_kernel<<<T, 256, 0, st>>>(gu, F, act);
-  return check_launch();
+int launch_gemm_qkv_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_heads,
+                        int n_kv_heads, int dh, int s_pool, const float2* cs, const int32_t* cs_row,
+                        const int32_t* row_slot, float* q, float* k_layer, float* v_layer, hipStream_t st) {
+  return gemm_f32({x, w, g, T, n_in, eps}, (n_heads + 2 * n_kv_heads) * dh,
+                  EpiF32QKV{cs, cs_row, row_slot, q, k_layer, v_layer, n_heads, n_kv_heads, dh, s_pool}, st);
 }
 
 // ------------------------------------------------------------------ tree attention (fp32)
-// One wavefront per (row, head).  Scores of all visible slots are kept in LDS
-// (max_slots floats), so the sequence length is limited by the LDS size.
-__global__ __launch_bounds__(64) void tree_attn_f32_kernel(
+// One workgroup per (row, head).  Scores of all visible slots are kept in LDS (max_slots
+// floats), so the sequence length is limited by the LDS size.  A thread owns a key for the
+// scores (its row in pieces of 8 values) and, for the values, a column and every FA_PARTS-th
+// group of 4 keys, which are contiguous in a V plane; the parts are added in order through LDS.
+constexpr int FA_THREADS = 512;
+__global__ __launch_bounds__(FA_THREADS) void tree_attn_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k_layer,
     const float* __restrict__ v_layer, const uint64_t* __restrict__ anc,
     const int32_t* __restrict__ row_seq, const int32_t* __restrict__ node_off,
@@ -212,63 +232,104 @@ __global__ __launch_bounds__(64) void tree_attn_f32_kernel(
     int max_slots, float scale, float* __restrict__ out) {
   extern __shared__ float lds[];
   float* qs = lds;            // dh
-  float* sc = lds + dh;       // max_slots
-  const int t = blockIdx.x, head = blockIdx.y, lane = threadIdx.x;
+  float* sc = lds + dh;       // max_slots, then (values' parts) at least FA_THREADS
+  __shared__ float wred[FA_THREADS / WAVE];
+  const int t = blockIdx.x, head = blockIdx.y, tid = threadIdx.x;
   float* o = out + ((size_t)t * n_heads + head) * dh;
   const int s = row_seq[t];
   const int L = s < 0 ? 0 : prefix_len[s], i = s < 0 ? 0 : t - node_off[s];
   const int base = s < 0 ? 0 : kv_off[s];
   const int nk = L + i + 1;  // ancestors have smaller indices than i
-  if (s < 0 || status_dev[s] != 0 || nk > max_slots) {
-    for (int c = lane; c < dh; c += 64) o[c] = 0.f;
+  if (s < 0 || status_dev[s] != 0 || nk > max_slots) {  // uniform
+    for (int c = tid; c < dh; c += FA_THREADS) o[c] = 0.f;
     return;
   }
   const float* kp = k_layer + (size_t)(head / group) * s_pool * dh;  // the group's K/V head
   const float* vp = v_layer + (size_t)(head / group) * s_pool * dh;
   const float* qr = q + ((size_t)t * n_heads + head) * dh;
-  for (int c = lane; c < dh; c += 64) qs[c] = qr[c];
+  for (int c = tid; c < dh; c += FA_THREADS) qs[c] = qr[c];
   __syncthreads();
   const uint64_t a0 = anc[2 * (size_t)t], a1 = anc[2 * (size_t)t + 1];
   float mx = -INFINITY;
-  for (int kk = lane; kk < nk; kk += 64) {
-    const bool vis = tree_key_visible(kk, L, a0, a1);
+  for (int kk = tid; kk < nk; kk += FA_THREADS) {
     float sv = -INFINITY;
-    if (vis) {
-      float acc = 0.f;
-      for (int c = 0; c < dh; ++c) acc = fmaf(qs[c], kp[k_off(base + kk, c, dh)], acc);
-      sv = acc * scale;
+    if (tree_key_visible(kk, L, a0, a1)) {
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int c = 0; c < dh; c += 32) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float* kg = kp + k_off(base + kk, c + 8 * g, dh);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[g] = fmaf(qs[c + 8 * g + e], kg[e], acc[g]);
+        }
+      }
+      sv = ((acc[0] + acc[1]) + (acc[2] + acc[3])) * scale;
     }
     sc[kk] = sv;
     mx = fmaxf(mx, sv);
   }
-  for (int o2 = 32; o2 > 0; o2 >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o2));
+  auto block_reduce = [&](float v, auto op) {  // the same value in every thread, fixed order
+    for (int o2 = 32; o2 > 0; o2 >>= 1) v = op(v, __shfl_xor(v, o2));
+    if ((tid & 63) == 0) wred[tid >> 6] = v;
+    __syncthreads();
+    v = wred[0];
+    for (int w = 1; w < FA_THREADS / WAVE; ++w) v = op(v, wred[w]);
+    __syncthreads();
+    return v;
+  };
+  mx = block_reduce(mx, [](float a, float b) { return fmaxf(a, b); });
   float sum = 0.f;
-  for (int kk = lane; kk < nk; kk += 64) {
-    float p = sc[kk] == -INFINITY ? 0.f : expf(sc[kk] - mx);
+  for (int kk = tid; kk < nk; kk += FA_THREADS) {
+    const float p = sc[kk] == -INFINITY ? 0.f : expf(sc[kk] - mx);
     sc[kk] = p;
     sum += p;
   }
-  for (int o2 = 32; o2 > 0; o2 >>= 1) sum += __shfl_xor(sum, o2);
-  __syncthreads();
+  sum = block_reduce(sum, [](float a, float b) { return a + b; });
   const float inv = 1.0f / sum;
-  for (int c = lane; c < dh; c += 64) {
+  // values: columns [c0, c0 + cols) by `parts` threads each
+  const int cols = dh < FA_THREADS ? dh : FA_THREADS, parts = FA_THREADS / cols;
+  float* red = sc + ((nk + 3) & ~3);  // parts x cols
+  const int col = tid % cols, part = tid / cols;
+  for (int c0 = 0; c0 < dh; c0 += cols) {
+    const int c = c0 + col;
     float acc = 0.f;
-    for (int kk = 0; kk < nk; ++kk) {
-      float p = sc[kk];
-      if (p != 0.f) acc = fmaf(p, vp[v_off(base + kk, c, dh)], acc);
+    if (part < parts && c < dh)
+      for (int k4 = 4 * part; k4 < nk; k4 += 4 * parts) {  // kv_off is a multiple of 32: groups of 4 stay together
+        const float* vg = vp + v_off(base + k4, c, dh);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float p = k4 + e < nk ? sc[k4 + e] : 0.f;
+          if (p != 0.f) acc = fmaf(p, vg[e], acc);  // slots nobody sees may hold anything
+        }
+      }
+    if (part < parts) red[part * cols + col] = acc;
+    __syncthreads();
+    if (part == 0 && c < dh) {
+      for (int p = 1; p < parts; ++p) acc += red[p * cols + col];
+      o[c] = acc * inv;
     }
-    o[c] = acc * inv;
+    __syncthreads();
   }
+}
+// LDS of the attention: query, scores (with the padding to groups of 4), the values' parts
+static size_t attn_f32_lds(int dh, int max_slots) {
+  return (size_t)(dh + max_slots + 4 + FA_THREADS) * sizeof(float);
 }
 int launch_tree_attn_f32(const float* q, const float* k_layer, const float* v_layer,
                          const uint64_t* anc, const int32_t* row_seq, const int32_t* node_off,
                          const int32_t* kv_off, const int32_t* prefix_len,
                          const int32_t* status_dev, int T, int n_heads, int n_kv_heads, int dh,
                          int s_pool, int max_slots, float scale, float* out, hipStream_t st) {
-  size_t lds = (size_t)(dh + max_slots) * sizeof(float);
-  if (lds > 64 * 1024) return TRJ_ERR_BAD_SHAPE;
+  if ((size_t)(dh + max_slots) * sizeof(float) > 64 * 1024) return TRJ_ERR_BAD_SHAPE;
+  const size_t lds = attn_f32_lds(dh, max_slots);
+  static bool big_lds_allowed = false;  // one-time: a little more than 64 KiB at the limit
+  if (!big_lds_allowed) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(tree_attn_f32_kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+    big_lds_allowed = true;
+  }
   dim3 grid(T, n_heads);
-  tree_attn_f32_kernel<<<grid, 64, lds, st>>>(q, k_layer, v_layer, anc, row_seq, node_off,
+  tree_attn_f32_kernel<<<grid, FA_THREADS, lds, st>>>(q, k_layer, v_layer, anc, row_seq, node_off,
                                               kv_off, prefix_len, status_dev, n_heads,
                                               n_heads / n_kv_heads, dh, s_pool, max_slots, scale,
                                               out);

@@ -138,15 +138,14 @@ int launch_rope_table(const int32_t* row_pos, int T, int dh, float theta, float2
                       hipStream_t st);
 int launch_embed(const void* embed, const int32_t* tok, int T, int d, int vocab, int dtype,
                  float* x, hipStream_t st);
-int launch_rmsnorm_f32(const float* x, const float* g, int T, int d, float eps, float* h,
-                       hipStream_t st);
-int launch_gemm_f32(const float* x, const float* w, int T, int n_in, int n_out, int add_to,
+// g: RMSNorm's gain, applied to x with its division (null: x as it is); add_to: y += instead of y =
+int launch_gemm_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_out, int add_to,
                     float* y, hipStream_t st);
-int launch_rope_kv_f32(const float* qkv, const float2* cs, const int32_t* cs_row,
-                       const int32_t* row_slot, int T,
-                       int n_heads, int n_kv_heads, int dh, int s_pool, float* q, float* k_layer,
-                       float* v_layer, hipStream_t st);
-int launch_silu_mul_f32(const float* gu, int T, int F, float* act, hipStream_t st);
+int launch_gemm_gate_up_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int F,
+                            float* act, hipStream_t st);
+int launch_gemm_qkv_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_heads,
+                        int n_kv_heads, int dh, int s_pool, const float2* cs, const int32_t* cs_row,
+                        const int32_t* row_slot, float* q, float* k_layer, float* v_layer, hipStream_t st);
 int launch_tree_attn_f32(const float* q, const float* k_layer, const float* v_layer,
                          const uint64_t* anc, const int32_t* row_seq, const int32_t* node_off,
                          const int32_t* kv_off, const int32_t* prefix_len,
