@@ -81,7 +81,7 @@ struct StepWs {
   float *qf, *of, *actf;
 };
 
-static void carve_tree(Carver& c, int dtype, int B, int T, int H, int dh, int max_seq_slots,
+static void carve_tree(Carver& c, int dtype, int B, int T, int H, int Hkv, int dh, int max_seq_slots,
                        TreeWs* w) {
   w->depth = c.take<int32_t>(T);
   w->row_slot = c.take<int32_t>(T);
@@ -93,21 +93,20 @@ static void carve_tree(Carver& c, int dtype, int B, int T, int H, int dh, int ma
   w->items = nullptr;
   w->attn_rows = w->attn_qg = w->attn_bpwg = w->attn_ns = 0;
   if (dtype == TRJ_BF16) {
-    int ntw, qg, bpwg, ns;
-    attn_bf16_plan(B, T, H, max_seq_slots, &ntw, &qg, &bpwg, &ns);
-    w->attn = c.take<float>(attn_bf16_ws_floats(B, qg * ntw, H, dh, ns));
-    w->items = c.take<int32_t>(ATTN_ITEM_WORDS(B, qg, ns));
-    w->attn_rows = 32 * ntw;
-    w->attn_qg = qg;
-    w->attn_bpwg = bpwg;
-    w->attn_ns = ns;
+    const AttnPlan p = attn_bf16_plan(B, T, H, H != Hkv, max_seq_slots);
+    w->attn = c.take<float>(attn_bf16_ws_floats(B, T, H, dh, max_seq_slots));
+    w->items = c.take<int32_t>(attn_bf16_item_words(B, T, H, max_seq_slots));
+    w->attn_rows = 32 * p.ntw;
+    w->attn_qg = p.qg_max;
+    w->attn_bpwg = p.bpwg;
+    w->attn_ns = p.nsplit_max;
   }
 }
 
 static void carve_step(Carver& c, const trj_model_desc& m, int B, int T, int max_seq_slots,
                        bool head_scratch, StepWs* w) {
   const int d = m.d_model, hd = m.n_heads * m.head_dim, F = m.d_ffn;
-  carve_tree(c, m.dtype, B, T, m.n_heads, m.head_dim, max_seq_slots, &w->t);
+  carve_tree(c, m.dtype, B, T, m.n_heads, m.n_kv_heads ? m.n_kv_heads : m.n_heads, m.head_dim, max_seq_slots, &w->t);
   w->cs = c.take<float2>((size_t)T * (m.head_dim / 2));
   w->x = c.take<float>((size_t)T * d);
   // the head's own scratch: the fp32 mode's logits (if the caller keeps none), the bf16 mode's
@@ -437,14 +436,14 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
   if (static_ws) {  // sizes first: nothing is touched when the call does not fit the array
     Carver need(nullptr);
     TreeWs wn;
-    carve_tree(need, dtype, B, T, n_heads, head_dim, max_seq_slots, &wn);
+    carve_tree(need, dtype, B, T, n_heads, n_kv_heads, head_dim, max_seq_slots, &wn);
     if (need.off > (size_t)TRJ_STATIC_SCRATCH_BYTES) return TRJ_ERR_WORKSPACE_TOO_SMALL;
     TRJ_TRY(static_scratch(&workspace));
     ws_bytes = TRJ_STATIC_SCRATCH_BYTES;
   }
   Carver c(workspace);
   TreeWs w;
-  carve_tree(c, dtype, B, T, n_heads, head_dim, max_seq_slots, &w);
+  carve_tree(c, dtype, B, T, n_heads, n_kv_heads, head_dim, max_seq_slots, &w);
   if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = dtype == TRJ_BF16;
@@ -484,7 +483,7 @@ int32_t tree_attention_workspace_bytes(int32_t B, int32_t T, int32_t n_heads, in
   TuneScope tune_scope;
   Carver c(nullptr);
   TreeWs w;
-  carve_tree(c, dtype, B, T, n_heads, head_dim, max_seq_slots, &w);
+  carve_tree(c, dtype, B, T, n_heads, n_heads, head_dim, max_seq_slots, &w);  // the same for any K/V heads
   *h_bytes = align_up(c.off, 256);
   return TRJ_OK;
 }

@@ -1,10 +1,9 @@
 // Tree-masked attention, bf16 storage, fp32 softmax and accumulation.
 //
-// The work is streaming the sequence's K/V once.  A workgroup of 8 wavefronts owns a
-// contiguous range of 32-slot blocks of one (sequence, head) and one group of 32 or 64
-// query rows (tree nodes); wavefront (kstream, qtile) walks every KS-th block of the range
-// for one tile of 32 queries.  K and V blocks are tiled in memory so that each lane's
-// 16-byte load is directly an MFMA A operand (1 KiB coalesced per wavefront load, no LDS):
+// The work is streaming the sequence's K/V once.  A workgroup owns a contiguous range of
+// 32-slot blocks of one (sequence, head) and one group of query rows (tree nodes), in tiles of
+// 32; wavefront (key stream, tile) walks every KS-th block of the range for one tile.  K and V
+// blocks are tiled in memory so that each lane's 16 bytes are directly an MFMA A operand:
 //   S^T[keys, queries] = K[keys, dh] * Q^T          (v_mfma_f32_32x32x16_bf16)
 //   O^T[dh, queries]  += V^T[dh, keys] * P^T[keys, queries]
 // With keys as the MFMA row dimension each lane holds one query column, so the online
@@ -12,9 +11,18 @@
 // are, after conversion to bf16, exactly the B operand of the second product (the V
 // tiling stores keys in the order in which S^T leaves them in the registers).
 // The ancestor bit rows mask only the blocks that overlap the tree's own slots.
-// The next block's K is requested while the current block's P*V runs and its V while
-// the next S^T runs, so no second set of registers is needed.
-// The wavefronts of a workgroup merge their (m, l, O) through LDS in a fixed tree.  If
+//
+// What bounds it: on long sequences the rate at which K/V arrive, i.e. how much is in flight
+// and that no byte is asked for twice; on short ones (up to about 1000 slots) some 9 us of
+// launch, first loads, merge and stores.  A key stream's wavefronts share a ring of D blocks in
+// LDS that the loads fill without passing through registers; each wavefront fetches its part
+// of every half block, K of block i+D as soon as K of block i has been read by all of them.
+// (Register prefetch, the form before, held one block per wavefront, and the two tiles of a
+// stream each loaded it: 64 rows on 8192 slots of 32 heads with cold caches 57 -> 31 us, 128
+// rows, where two such workgroups read it, 60 -> 39; 16 packed sequences 118 -> 106; 16 rows
+// on 512 slots 8.6 -> 7.9.)  Loads of blocks that no other workgroup reads carry the
+// streaming hint.
+// The wavefronts of a workgroup merge their (m, l, O) through LDS in a fixed order.  If
 // the workgroup covers the whole sequence it writes the normalised rows; otherwise it
 // writes an un-normalised partial and a second, small kernel merges the partials of a
 // row in split order.  (Merging inside the same launch by "last workgroup to arrive"
@@ -29,7 +37,6 @@
 namespace trj {
 
 constexpr float NEG_BIG = -1e30f;
-constexpr int ATTN_WAVES = 8;
 
 struct AttnArgs {
   const uint16_t* q;
@@ -145,12 +152,28 @@ __device__ inline void attn_store_row(const AttnArgs& a, int t, int head, int c,
   *reinterpret_cast<u32x2*>(dst) = v;
 }
 
-template <int DH, int NTW, bool XCHG>
-__global__ __launch_bounds__(ATTN_WAVES * 64) void tree_attn_bf16_kernel(AttnArgs a) {
-  constexpr int KS = ATTN_WAVES / NTW, KSTEPS = DH / 16, MTV = DH / 32;
-  constexpr int OW = MTV * 16 * 64;  // floats of one wavefront's O tile
-  extern __shared__ __align__(16) float red[];  // NTW * MTV * (KS-1) parts of 1024 floats
-  __shared__ float sm_m[ATTN_WAVES][32], sm_l[ATTN_WAVES][32];
+// All but the newest N of this wavefront's loads have landed and its LDS reads are in
+// registers; with two wavefronts per key stream the workgroup then meets, so that both halves
+// of what the stream shares have landed and what both have read may be overwritten.
+template <int N, bool MEET>
+__device__ __forceinline__ void attn_wait() {
+  if constexpr (MEET) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+  else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+
+// NTW query tiles x KS key streams of wavefronts; a stream's ring holds D blocks.  ALIGNED: all
+// operands start at multiples of 16 bytes (else they are copied through registers).
+template <int DH, int NTW, int KS, int D, bool ALIGNED>
+__global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArgs a) {
+  constexpr int KSTEPS = DH / 16, MTV = DH / 32, RING = 2 * D;
+  constexpr int OW = MTV * 16 * 64;     // floats of one wavefront's O tile
+  constexpr int HALF = KSTEPS;          // 1-KiB pieces of a block's K, and of its V
+  constexpr int HP = HALF / NTW;        // of these, requested by one wavefront
+  constexpr int SLOT = HALF * 1024;     // bytes of a ring slot
+  constexpr bool MEET = NTW > 1;
+  static_assert(D == 2 || D == 3, "the tail below");
+  extern __shared__ __align__(16) uint8_t smem[];  // rings: KS x RING slots; then the parts handed over
+  __shared__ float sm_m[KS * NTW][32], sm_l[KS * NTW][32];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -176,24 +199,56 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void tree_attn_bf16_kernel(AttnArg
   if (sp >= nsplit || qg * 32 * NTW >= n) return;  // uniform as well
   const int b0 = sp * a.bpwg, b1 = min(nb, b0 + a.bpwg);
   const int n32 = lane & 31, hh = lane >> 5;
+  // no other workgroup reads these blocks (one query group, one query head per K/V head): the
+  // loads carry the streaming hint; with a second reader through L2 it costs a second trip to HBM
+  const bool stream = a.group == 1 && rec[7] == 0;
 
-  // this wavefront's 32 queries: B operands of the first product, kept in registers
-  const int qi = (qg * NTW + nt) * 32 + n32;
-  const bool valid = qi < n;
-  const int qrow = valid ? r0 + qi : -1;
-  // rows past the tree's end read the last row instead (never stored, always finite):
-  // every load of the prologue is unconditional, so that the query, the ancestor bits and
-  // the first K/V block are all in flight together
-  const int qc = min(qi, n - 1);
-  bf16x8 qreg[KSTEPS];
-  {
-    const uint16_t* qp = a.q + ((size_t)(r0 + qc) * a.n_heads + head) * DH + hh * 8;
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem;
+  const uint32_t ring = __builtin_amdgcn_readfirstlane(lds0 + ks * RING * SLOT);
+  uint8_t* ring_w = smem + (size_t)ks * RING * SLOT + lane * 16;
+  const u32x4* ring_r = reinterpret_cast<const u32x4*>(ring_w);
+  const size_t plane = (size_t)(head / a.group) * a.s_pool * DH;  // the group's K/V head
+  // this stream's blocks: b0 + ks, b0 + ks + KS, ..
+  const int nblk = b0 + ks < b1 ? (b1 - b0 - ks + KS - 1) / KS : 0, rounds = (b1 - b0 + KS - 1) / KS;
+  const size_t first = (size_t)(blk_base + b0 + ks) * SLOT + nt * HP * 1024;
+  const uint8_t* kp = reinterpret_cast<const uint8_t*>(a.k_layer + plane) + first;
+  const uint8_t* vp = reinterpret_cast<const uint8_t*>(a.v_layer + plane) + first;
+  auto request = [&](const uint8_t*& p, int sl) {  // this wavefront's pieces of the next K (or V) into slot sl
+    const uint32_t dst = ring + sl * SLOT + nt * HP * 1024;
 #pragma unroll
-    for (int k = 0; k < KSTEPS; ++k)
-      qreg[k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * k));
+    for (int k = 0; k < HP; ++k) {
+      if constexpr (!ALIGNED) copy_to_lds(p + k * 1024, lane * 16, ring_w + sl * SLOT + (nt * HP + k) * 1024);
+      else if (stream) load_to_lds<true>(p + k * 1024, lane * 16, dst + k * 1024);
+      else load_to_lds<false>(p + k * 1024, lane * 16, dst + k * 1024);
+    }
+    p += (size_t)KS * SLOT;
+  };
+
+  // The queries (as operands of the first product) and their ancestor bits come through LDS
+  // too: registers that the compiler had loaded itself it would wait for together with the
+  // whole ring.  The streams share them, each fetching its part of every tile.  Rows past the
+  // tree's end read the last row instead (never stored, always finite) and see no tree node.
+  const int qi = (qg * NTW + nt) * 32 + n32, qc = min(qi, n - 1);
+  constexpr int QAT = KS * RING * SLOT, ANC_AT = QAT + NTW * SLOT, QP = KSTEPS / KS;
+  {
+    auto fetch = [&](const void* base, uint32_t voff, int at) {
+      if constexpr (ALIGNED) load_to_lds<false>(base, voff, __builtin_amdgcn_readfirstlane(lds0 + at));
+      else copy_to_lds(base, voff, smem + at + lane * 16);
+    };
+    const uint16_t* qh = a.q + ((size_t)r0 * a.n_heads + head) * DH;
+#pragma unroll
+    for (int j = 0; j < QP; ++j) {
+      const int k = ks * QP + j;
+      fetch(qh, (uint32_t)(qc * a.n_heads * DH + hh * 8 + 16 * k) * 2, QAT + nt * SLOT + k * 1024);
+    }
+    if (ks == 0) fetch(a.anc + 2 * (size_t)r0, (uint32_t)qc * 16, ANC_AT + nt * 1024);
   }
-  uint64_t anc0 = a.anc[2 * (size_t)(r0 + qc)];
-  uint64_t anc1 = a.anc[2 * (size_t)(r0 + qc) + 1];
+#pragma unroll
+  for (int i = 0; i < D; ++i)
+    if (i < nblk) {
+      request(kp, 2 * i);
+      request(vp, 2 * i + 1);
+    }
 
   f32x16 o[MTV];
 #pragma unroll
@@ -201,125 +256,93 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void tree_attn_bf16_kernel(AttnArg
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[mt][v] = 0.f;
   float m = NEG_BIG, l = 0.f;
-
-  const size_t plane = (size_t)(head / a.group) * a.s_pool * DH;  // the group's K/V head
-  const u32x4* kp = reinterpret_cast<const u32x4*>(a.k_layer + plane) + lane;
-  const u32x4* vp = reinterpret_cast<const u32x4*>(a.v_layer + plane) + lane;
-  u32x4 kreg[KSTEPS], vreg[2 * MTV];  // 1-KiB pieces of a block; V piece mt * 2 + kg
-  if (!valid) anc0 = anc1 = 0;        // a row that does not exist sees no tree node
-
-  // The walk over the blocks, compiled once per (HALF, STREAM).
-  // NTW == 2: the two wavefronts of a key stream need the same K/V block (one per query
-  // tile).  Each loads HALF of its pieces from memory and hands them to the other through
-  // LDS (two buffers, one LDS barrier per block; every wavefront makes the same number of
-  // trips, one that has run out of blocks reloads its last one and skips the arithmetic),
-  // so every byte is asked for once.  (Handing K over before the first product and V
-  // before the second, with a barrier each, measured slower at every length.)
-  // STREAM: no other workgroup reads these blocks (one query group, one query head per K/V
-  // head), so the loads carry the streaming hint; with a second reader shortly after
-  // (through L2, or the other wavefront of the pair before the exchange existed) the hint
-  // costs a second trip to HBM.
-  auto run = [&](auto half_c, auto stream_c) {
-    constexpr int HALF = decltype(half_c)::value;
-    constexpr bool STREAM = decltype(stream_c)::value;
-    constexpr bool PAIR = NTW == 2 && XCHG;
-    constexpr int KN = PAIR ? KSTEPS / 2 : KSTEPS, K0 = PAIR ? HALF * KN : 0;
-    constexpr int VN = PAIR ? MTV : 2 * MTV, V0 = PAIR ? HALF * VN : 0;
-    auto ldg = [&](const u32x4* p) -> u32x4 {
-      if constexpr (STREAM) return __builtin_nontemporal_load(p);
-      else return *p;
-    };
-    auto load_k = [&](int blk) {
-      const u32x4* kb = kp + (size_t)(blk_base + blk) * KSTEPS * 64;
+  u32x4 kreg[KSTEPS], vreg[2 * MTV];
+  auto read = [&](u32x4 (&r)[KSTEPS], int sl) {
 #pragma unroll
-      for (int k = 0; k < KN; ++k) kreg[K0 + k] = ldg(kb + (K0 + k) * 64);
-    };
-    auto load_v = [&](int blk) {
-      const u32x4* vb = vp + (size_t)(blk_base + blk) * MTV * 2 * 64;
-#pragma unroll
-      for (int i = 0; i < VN; ++i) vreg[V0 + i] = ldg(vb + (V0 + i) * 64);
-    };
-    u32x4* xch = reinterpret_cast<u32x4*>(red);  // [2 buffers][KS][2 halves][KN + VN][64]
-    const int iters = (b1 - b0 + KS - 1) / KS;   // the same for every wavefront
-    int b = b0 + ks;
-    if (PAIR || b < b1) {
-      load_k(min(b, b1 - 1));
-      load_v(min(b, b1 - 1));
-    }
-    for (int it = 0; it < iters; ++it, b += KS) {
-      const bool live = b < b1;  // the same for both wavefronts of a stream
-      if constexpr (PAIR) {
-        constexpr int KO = (HALF ^ 1) * KN, VO = (HALF ^ 1) * VN;
-        u32x4* mine = xch + (size_t)((((it & 1) * KS + ks) * 2 + HALF) * (KN + VN)) * 64 + lane;
-        const u32x4* theirs =
-            xch + (size_t)((((it & 1) * KS + ks) * 2 + (HALF ^ 1)) * (KN + VN)) * 64 + lane;
-#pragma unroll
-        for (int k = 0; k < KN; ++k) mine[k * 64] = kreg[K0 + k];
-#pragma unroll
-        for (int i = 0; i < VN; ++i) mine[(KN + i) * 64] = vreg[V0 + i];
-        lds_barrier();
-#pragma unroll
-        for (int k = 0; k < KN; ++k) kreg[KO + k] = theirs[k * 64];
-#pragma unroll
-        for (int i = 0; i < VN; ++i) vreg[VO + i] = theirs[(KN + i) * 64];
-      }
-      const bool more = PAIR ? it + 1 < iters : b + KS < b1;
-      const int bn = min(b + KS, b1 - 1);
-      const int key0 = b * 32;
-      f32x16 sacc;
-      if (live) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
-#pragma unroll
-        for (int k = 0; k < KSTEPS; ++k)
-          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[k]),
-                                                         qreg[k], sacc, 0, 0, 0);
-      }
-      if (more) load_k(bn);  // uniform branch; in flight during the softmax and P*V
-      if (live) {
-        if (key0 + 32 > total) {
-          // slots past the sequence's last row may hold anything (NaN bit patterns too):
-          // clear them in the V operand, their probabilities are exactly zero
-#pragma unroll
-          for (int kg = 0; kg < 2; ++kg)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              int key = key0 + 16 * kg + 4 * hh + 8 * (e >> 2) + (e & 3);
-              if (key >= total) {
-                uint32_t keep = (e & 1) ? 0x0000ffffu : 0xffff0000u;
-#pragma unroll
-                for (int mt = 0; mt < MTV; ++mt) vreg[mt * 2 + kg][e >> 1] &= keep;
-              }
-            }
-        }
-        float alpha;
-        u32x4 pk[2];
-        if (key0 + 32 > L)
-          softmax_tile_tree(sacc, key0, hh, L, anc0, anc1, a.scale_log2e, m, l, alpha, pk);
-        else
-          softmax_tile_prefix(sacc, a.scale_log2e, m, l, alpha, pk);
-        rescale_o<MTV>(o, alpha);
-#pragma unroll
-        for (int mt = 0; mt < MTV; ++mt)
-#pragma unroll
-          for (int kg = 0; kg < 2; ++kg)
-            o[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, vreg[mt * 2 + kg]), __builtin_bit_cast(bf16x8, pk[kg]),
-                o[mt], 0, 0, 0);
-      }
-      if (more) load_v(bn);  // in flight during the next S^T and softmax
-    }
+    for (int k = 0; k < KSTEPS; ++k) r[k] = ring_r[(sl * HALF + k) * 64];
   };
-  {
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    // uniform over the workgroup; two wavefronts that load the same block rule it out too
-    const bool stream = (NTW == 1 || XCHG) && a.group == 1 && rec[7] == 0;
-    if (NTW == 2 && XCHG && nt == 1) {
-      if (stream) run(I1{}, std::true_type{}); else run(I1{}, std::false_type{});
-    } else {
-      if (stream) run(I0{}, std::true_type{}); else run(I0{}, std::false_type{});
+  // queries, bits and K of the first block: behind it its V and the blocks already requested
+  if (nblk >= D) attn_wait<(2 * D - 1) * HP, true>();
+  else if (D > 2 && nblk == 2) attn_wait<3 * HP, true>();
+  else if (nblk == 1) attn_wait<HP, true>();
+  else attn_wait<0, true>();
+  bf16x8 qreg[KSTEPS];
+#pragma unroll
+  for (int k = 0; k < KSTEPS; ++k)
+    qreg[k] = __builtin_bit_cast(bf16x8, reinterpret_cast<const u32x4*>(smem + QAT + nt * SLOT)[k * 64 + lane]);
+  const u32x4 bits = reinterpret_cast<const u32x4*>(smem + ANC_AT + nt * 1024)[lane];
+  const uint64_t anc0 = qi < n ? (uint64_t)bits[1] << 32 | bits[0] : 0;
+  const uint64_t anc1 = qi < n ? (uint64_t)bits[3] << 32 | bits[2] : 0;
+  // Block i of this stream: its K is in kreg; its V and the next blocks are on the way (slots
+  // 2(i%D)+1, ..).  AHEAD: blocks behind it, D when there are at least as many; then block i+D
+  // is requested into the slots that get free.  V is read under S^T and softmax, the next K
+  // under P*V; at every wait 2(D-1) half blocks of the stream stay in flight.  A wavefront
+  // without a row only requests and meets.
+  const bool live = (qg * NTW + nt) * 32 < n;
+  int cur = 0;  // slot of this block's K
+  auto block = [&](int i, auto ahead_c) {
+    constexpr int AHEAD = decltype(ahead_c)::value;
+    const int key0 = (b0 + ks + i * KS) * 32, next = cur + 2 == RING ? 0 : cur + 2;
+    f32x16 sacc;
+    if (live) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
+#pragma unroll
+      for (int k = 0; k < KSTEPS; ++k)
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[k]), qreg[k], sacc, 0, 0, 0);
     }
+    attn_wait<(AHEAD < D ? 2 * AHEAD : 2 * (D - 1)) * HP, MEET>();
+    if constexpr (AHEAD == D) request(kp, cur);
+    float alpha;
+    u32x4 pk[2];
+    if (live) {
+      read(vreg, cur + 1);
+      if (key0 + 32 > L)  // uniform
+        softmax_tile_tree(sacc, key0, hh, L, anc0, anc1, a.scale_log2e, m, l, alpha, pk);
+      else
+        softmax_tile_prefix(sacc, a.scale_log2e, m, l, alpha, pk);
+    }
+    attn_wait<(AHEAD == 0 ? 0 : (AHEAD < D ? 2 * AHEAD - 1 : 2 * (D - 1))) * HP, MEET>();
+    if constexpr (AHEAD == D) request(vp, cur + 1);
+    cur = next;
+    if (!live) return;
+    if constexpr (AHEAD > 0) read(kreg, next);
+    if (key0 + 32 > total) {
+      // slots past the sequence's last row may hold anything (NaN bit patterns too):
+      // clear them in the V operand, their probabilities are exactly zero
+#pragma unroll
+      for (int kg = 0; kg < 2; ++kg)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          int key = key0 + 16 * kg + 4 * hh + 8 * (e >> 2) + (e & 3);
+          if (key >= total) {
+            uint32_t keep = (e & 1) ? 0x0000ffffu : 0xffff0000u;
+#pragma unroll
+            for (int mt = 0; mt < MTV; ++mt) vreg[mt * 2 + kg][e >> 1] &= keep;
+          }
+        }
+    }
+    rescale_o<MTV>(o, alpha);
+#pragma unroll
+    for (int kg = 0; kg < 2; ++kg)
+#pragma unroll
+      for (int mt = 0; mt < MTV; ++mt)
+        o[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vreg[mt * 2 + kg]),
+                                                        __builtin_bit_cast(bf16x8, pk[kg]), o[mt], 0, 0, 0);
+  };
+  if (nblk > 0) {
+    read(kreg, 0);
+    int i = 0;
+    for (; i + D < nblk; ++i) block(i, std::integral_constant<int, D>{});
+    if constexpr (D > 2) {
+      if (nblk - 1 - i >= 2) block(i++, std::integral_constant<int, 2>{});
+    }
+    if (nblk - 1 - i >= 1) block(i++, std::integral_constant<int, 1>{});
+    block(i, std::integral_constant<int, 0>{});
+  }
+  if (MEET && nblk < rounds) {  // a stream with a block less than the others meets them as often
+    attn_wait<0, MEET>();
+    attn_wait<0, MEET>();
   }
 
   // ---- merge the KS key streams of every query tile (fixed order, deterministic)
@@ -328,7 +351,8 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void tree_attn_bf16_kernel(AttnArg
     sm_m[wv][n32] = m;
     sm_l[wv][n32] = lt;
   }
-  __syncthreads();
+  __syncthreads();  // the rings are free too
+  float* red_all = reinterpret_cast<float*>(smem);
   float mg = NEG_BIG;
 #pragma unroll
   for (int k = 0; k < KS; ++k) mg = fmaxf(mg, sm_m[nt + NTW * k][n32]);
@@ -351,7 +375,7 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void tree_attn_bf16_kernel(AttnArg
   for (int mt = 0; mt < MTV; ++mt) {
     const int owner = mt % KS;
     if (ks != owner) {
-      float* dst = red + (((nt * MTV + mt) * (KS - 1)) + (ks < owner ? ks : ks - 1)) * PART + lane;
+      float* dst = red_all + (((nt * MTV + mt) * (KS - 1)) + (ks < owner ? ks : ks - 1)) * PART + lane;
 #pragma unroll
       for (int v = 0; v < 16; ++v) dst[v * 64] = o[mt][v];
     }
@@ -367,19 +391,19 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void tree_attn_bf16_kernel(AttnArg
 #pragma unroll
   for (int mt = 0; mt < MTV; ++mt) {
     if (ks != mt % KS) continue;
-    const float* src = red + ((nt * MTV + mt) * (KS - 1)) * PART + lane;
+    const float* src = red_all + ((nt * MTV + mt) * (KS - 1)) * PART + lane;
 #pragma unroll
     for (int k = 0; k < KS - 1; ++k)
 #pragma unroll
       for (int v = 0; v < 16; ++v) o[mt][v] += src[(k * 16 + v) * 64];
     if (nsplit == 1) {
       // the workgroup saw every key: write the normalised rows
-      if (qrow >= 0) {
+      if (qi < n) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           u32x2 v = {pack2bf(o[mt][4 * g] * inv, o[mt][4 * g + 1] * inv),
                      pack2bf(o[mt][4 * g + 2] * inv, o[mt][4 * g + 3] * inv)};
-          attn_store_row<DH>(a, qrow, head, 32 * mt + 8 * g + 4 * hh, v);
+          attn_store_row<DH>(a, r0 + qi, head, 32 * mt + 8 * g + 4 * hh, v);
         }
       }
     } else {
@@ -466,36 +490,61 @@ int launch_zero_bytes(void* p, size_t bytes, hipStream_t st) {
 }
 
 // Launch shape: query tiles per workgroup, query groups, blocks per workgroup, splits.
-void attn_bf16_plan(int B, int T, int n_heads, int max_seq_slots, int* ntw, int* qg_max, int* bpwg,
-                    int* nsplit_max) {
-  int nmax = T < TRJ_N_MAX ? T : TRJ_N_MAX;
-  *ntw = nmax <= 32 ? 1 : 2;
-  *qg_max = (nmax + 32 * *ntw - 1) / (32 * *ntw);
-  const int ks = ATTN_WAVES / *ntw;
+AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_slots) {
+  AttnPlan p;
+  const int nmax = T < TRJ_N_MAX ? T : TRJ_N_MAX;
   int nb = (max_seq_slots + 31) / 32;
   if (nb < 1) nb = 1;
+  // Query tiles per workgroup: one or two with four key streams, and four with two streams for
+  // trees of more than 64 rows (on average) on long sequences, whose K/V is then read once; as
+  // two groups of two tiles both groups wait for HBM (32 heads, 128 rows on 4096 slots 39.5
+  // against 29.7 us, on 1536 24.4 against 21.0, on 1024 the shorter walks win: 18.9 against
+  // 20.4).  Query heads that share K/V find it in L2 either way (27.8 against 29.2 on 4096).
+  // A sequence with more rows than a workgroup takes has several groups.
+  p.ntw = nmax <= 32 ? 1 : (!shared_kv && T > 64 * B && nb >= 44 ? 4 : 2);
+  p.qg_max = (nmax + 32 * p.ntw - 1) / (32 * p.ntw);
   // the host does not know the trees' sizes (they are device data): the number of work
   // items lies between max(B, T / rows per item) and B * qg_max; the lower figure sizes
   // the split (too few workgroups cost more than too many), the upper one the launch
-  const int rows = 32 * *ntw;
+  const int rows = 32 * p.ntw;
   const int items_est = B > (T + rows - 1) / rows ? B : (T + rows - 1) / rows;
-  long cols = (long)items_est * n_heads;
-  int b = (int)((nb * cols + tune().attn_target_wgs - 1) / tune().attn_target_wgs);
-  // shortest walk worth a workgroup, in blocks per wavefront: one for trees of up to 64 nodes
-  // (measured at 64 nodes on 1024 slots: 13.7 against 14.1 us; at 16 on 8192: 30 against
-  // 32 us), two with two query groups, whose extra workgroups otherwise crowd the launch
-  // (128 nodes on 8192 slots: 47.5 against 49 us)
-  const int min_bpw = tune().attn_min_bpw > 0 ? tune().attn_min_bpw : (nmax > 64 ? 2 : 1);
-  if (b < min_bpw * ks) b = min_bpw * ks;
+  const long cols = (long)items_est * n_heads, target = tune().attn_target_wgs;
+  int b;
+  if (p.ntw == 4) {  // whole rounds of workgroups at most: a split is four tiles' partials
+    const long split = cols < target ? target / cols : 1;
+    b = (int)((nb + split - 1) / split);
+  } else {
+    b = (int)((nb * cols + target - 1) / target);
+  }
+  // shortest walk worth a workgroup, in blocks: one per key stream for 33..64 rows, two else
+  // (64 rows on 1024 slots: 13.7 against 14.1 us; 128 rows on 1024 18.9 against 21.4)
+  const int min_b = tune().attn_min_bpw > 0 ? tune().attn_min_bpw * (p.ntw == 4 ? 2 : 4)
+                                            : (p.ntw == 4 || (p.ntw == 2 && nmax <= 64) ? 4 : 8);
+  if (b < min_b) b = min_b;
   if (b > nb) b = nb;
-  *bpwg = b;
-  *nsplit_max = (nb + b - 1) / b;
+  p.bpwg = b;
+  p.nsplit_max = (nb + b - 1) / b;
+  return p;
 }
 
-size_t attn_bf16_ws_floats(int B, int tiles_per_seq, int n_heads, int dh, int nsplit_max) {
-  // partials: none needed when every sequence fits one workgroup
-  return nsplit_max > 1 ? (size_t)B * tiles_per_seq * n_heads * nsplit_max * (dh / 32 * 1024 + 64)
-                        : 64;
+// scratch for either answer to "do query heads share K/V": the workspace queries do not know
+size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots) {
+  size_t most = 64;  // no partials needed when every sequence fits one workgroup
+  for (bool shared : {false, true}) {
+    const AttnPlan p = attn_bf16_plan(B, T, n_heads, shared, max_seq_slots);
+    const size_t n = p.nsplit_max > 1 ? (size_t)B * p.qg_max * p.ntw * n_heads * p.nsplit_max * (dh / 32 * 1024 + 64) : 0;
+    most = n > most ? n : most;
+  }
+  return most;
+}
+size_t attn_bf16_item_words(int B, int T, int n_heads, int max_seq_slots) {
+  size_t most = 0;
+  for (bool shared : {false, true}) {
+    const AttnPlan p = attn_bf16_plan(B, T, n_heads, shared, max_seq_slots);
+    const size_t n = (size_t)B * p.qg_max * p.nsplit_max * 8 + 8;
+    most = n > most ? n : most;
+  }
+  return most;
 }
 
 int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint16_t* v_layer,
@@ -505,8 +554,8 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
                           int n_heads, int n_kv_heads, int dh, int s_pool, int max_seq_slots,
                           float scale, float* ws, int tiled, int tp, uint16_t* out, hipStream_t st) {
   if (dh != 64 && dh != 128) return TRJ_ERR_BAD_SHAPE;
-  int ntw, qg_max, bpwg, nsplit_max;
-  attn_bf16_plan(B, T, n_heads, max_seq_slots, &ntw, &qg_max, &bpwg, &nsplit_max);
+  const AttnPlan p = attn_bf16_plan(B, T, n_heads, n_heads != n_kv_heads, max_seq_slots);
+  const int ntw = p.ntw, qg_max = p.qg_max, bpwg = p.bpwg, nsplit_max = p.nsplit_max;
   const int tiles_per_seq = qg_max * ntw;
   size_t parts = nsplit_max > 1 ? (size_t)B * tiles_per_seq * n_heads * nsplit_max : 0;
   float* po = ws;
@@ -517,40 +566,35 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
              items + (size_t)B * qg_max * nsplit_max * 8, scale * 1.4426950408889634f, po, pm, pl, tiles_per_seq, out, tiled, tp};
   const int group = n_heads / n_kv_heads;
   dim3 grid((B * qg_max * n_kv_heads * nsplit_max + 7) / 8 * 8 * group);
-  const int ks = ATTN_WAVES / ntw;
-  size_t lds = (size_t)ntw * (dh / 32) * (ks - 1) * 16 * 64 * sizeof(float);  // parts handed over
-  // With two query tiles per workgroup the wavefront pairs either both load every block, or
-  // split the loads and exchange halves through LDS.  The exchange costs a barrier per block
-  // and pays once a wavefront walks enough blocks (measured: 2 blocks per wavefront 13.2
-  // against 12 us, 8: 33.9 against 31.9, 20: 119 against 137, 32: 89 against 98).
-  // It is the streaming hint that pays for it, and the hint needs blocks that nobody else
-  // reads: one query head per K/V head, and trees of at most 64 nodes (known here only on
-  // average; a sequence with more runs the exchange without the hint, 3-6 % slower than
-  // the plain pair).
-  const bool xchg = ntw == 2 && bpwg >= tune().attn_xchg_min_blocks && n_heads == n_kv_heads &&
-                    T <= 64 * B;
-  if (xchg) {  // 2 buffers x streams x halves x pieces
-    size_t xch = (size_t)2 * ks * 2 * (dh / 32 + dh / 32) * 1024;
-    if (xch > lds) lds = xch;
-  }
   {
     ProfScope ps_(KC_ATTN, st);
-#define TRJ_ATTN(D, Q, X)                                                                     \
-  do {                                                                                        \
-    static bool big_lds_allowed = false; /* one-time, per instantiation */                    \
-    if (!big_lds_allowed) {                                                                   \
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(tree_attn_bf16_kernel<D, Q, X>), \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);      \
-      big_lds_allowed = true;                                                                 \
-    }                                                                                         \
-    tree_attn_bf16_kernel<D, Q, X><<<grid, ATTN_WAVES * 64, lds, st>>>(a);                    \
+    const bool aligned = (((uintptr_t)q | (uintptr_t)k_layer | (uintptr_t)v_layer | (uintptr_t)anc) & 15) == 0;
+#define TRJ_ATTN_A(DH, Q, KS, D, AL)                                                            \
+  do {                                                                                          \
+    constexpr size_t rings = (size_t)(KS * 2 * D + Q) * DH * 64 + Q * 1024;                     \
+    constexpr size_t handed = (size_t)Q * DH * (KS - 1) * 128;                                  \
+    constexpr size_t lds = rings > handed ? rings : handed;                                     \
+    auto kern = tree_attn_bf16_kernel<DH, Q, KS, D, AL>;                                        \
+    static bool big_lds_allowed = false; /* one-time, per instantiation */                      \
+    if (!big_lds_allowed) {                                                                     \
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                            \
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);          \
+      big_lds_allowed = true;                                                                   \
+    }                                                                                           \
+    kern<<<grid, KS * Q * 64, lds, st>>>(a);                                                    \
+  } while (0)
+#define TRJ_ATTN(DH, Q, KS, D)                                                                  \
+  do {                                                                                          \
+    if (aligned) TRJ_ATTN_A(DH, Q, KS, D, true);                                                \
+    else TRJ_ATTN_A(DH, Q, KS, D, false);                                                       \
   } while (0)
     if (dh == 128) {
-      if (ntw == 1) TRJ_ATTN(128, 1, false); else if (xchg) TRJ_ATTN(128, 2, true); else TRJ_ATTN(128, 2, false);
+      if (ntw == 1) TRJ_ATTN(128, 1, 4, 2); else if (ntw == 2) TRJ_ATTN(128, 2, 4, 2); else TRJ_ATTN(128, 4, 2, 3);
     } else {
-      if (ntw == 1) TRJ_ATTN(64, 1, false); else if (xchg) TRJ_ATTN(64, 2, true); else TRJ_ATTN(64, 2, false);
+      if (ntw == 1) TRJ_ATTN(64, 1, 4, 2); else if (ntw == 2) TRJ_ATTN(64, 2, 4, 2); else TRJ_ATTN(64, 4, 2, 3);
     }
 #undef TRJ_ATTN
+#undef TRJ_ATTN_A
   }
   int rc = check_launch();
   if (rc || nsplit_max == 1) return rc;

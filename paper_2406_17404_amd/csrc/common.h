@@ -87,6 +87,25 @@ __device__ inline void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// 1 KiB from global memory (uniform base, 16 bytes per lane at `voff`) to LDS at byte `lds`
+// (uniform; lane l's 16 bytes land at lds + 16 l).  Has no destination register; completion
+// is counted by vmcnt, in order with the wavefront's other loads.  (m0 is written here and
+// read by the next instruction; nothing the compiler emits in these kernels uses it.)
+// Both addresses must be multiples of 16; copy_to_lds is the form for those that are not, at
+// the price of registers and a wait.
+template <bool NT>
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "s"(lds)
+                 : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
+                 : "memory");
+}
+__device__ __forceinline__ void copy_to_lds(const void* base, uint32_t voff, void* lane_dst) {
+  *static_cast<u32x4*>(lane_dst) = *reinterpret_cast<const u32x4*>(static_cast<const uint8_t*>(base) + voff);
+}
+
 // ---- error bookkeeping (defined in api.hip)
 void note_hip_error(hipError_t e);
 inline int check_launch() {

@@ -72,19 +72,6 @@ __device__ inline f32x16 scaled(const f32x16& acc, float f) {
   return r;
 }
 
-// 1 KiB from global memory (uniform base, 16 bytes per lane at `voff`) to LDS at byte `lds`
-// (uniform; lane l's 16 bytes land at lds + 16 l).  Has no destination register; completion
-// is counted by vmcnt, in order with the wavefront's other loads.  (m0 is written here and
-// read by the next instruction; nothing the compiler emits in these kernels uses it.)
-template <bool NT>
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
-  if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "s"(lds)
-                 : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
-                 : "memory");
-}
 // all but the newest N loads of this wavefront have landed and its LDS reads are done; then
 // the workgroup meets.  (Loads the compiler issues by itself only make the wait stricter.)
 template <int N>
@@ -106,7 +93,9 @@ __device__ __forceinline__ void wait_and_meet() {
 // repeated step gets in), in the last phase and in front of the MFMA only: a mask right
 // behind the LDS read makes the wavefront wait for the read there (22016 x 4096 at 128 rows
 // 56.0 against 48.6 us).
-template <int RT, int CT, int KW, int WT, int MT, int PH, int NB, bool NT, class Epi>
+//
+// ALIGNED: xp and w start at multiples of 16 bytes (else they are copied through registers).
+template <int RT, int CT, int KW, int WT, int MT, int PH, int NB, bool NT, bool ALIGNED, class Epi>
 __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs a, Epi epi) {
   constexpr int NW = RT * CT * KW, WR = RT * WT, XC = CT * MT, WS = PH / KW;
   constexpr int XP = PH * XC, P = XP + PH * WR, PL = (P + NW - 1) / NW, REM = P % NW;
@@ -121,7 +110,7 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
   const int rt = wv % RT, ct = (wv / RT) % CT, kw = wv / (RT * CT);
   const int ksteps = a.n_in >> 4, nph = (ksteps + PH - 1) / PH;
   const int ph0 = blockIdx.y * a.phases_per_split;
-  const int n = min(nph, ph0 + a.phases_per_split) - ph0;  // phases of this workgroup, >= 1
+  const int n = min(nph, ph0 + a.phases_per_split) - ph0;  // phases of this workgroup, >= 1 if ALIGNED
   const int ttiles = a.tp >> 5, ntiles = a.n_out >> 5, tblocks = (ttiles + XC - 1) / XC;
   // Workgroup ids go round-robin over the 8 dies (XCDs), each with its own L2.  With several
   // token blocks the workgroups that stream the SAME weight rows get ids that land on one die,
@@ -164,6 +153,10 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
     for (int j = 0; j < PL; ++j) {
       const int p = j * NW + wv;
       if (REM != 0 && j == PL - 1 && p >= P) break;
+      if constexpr (!ALIGNED) {  // waited for at once and counted by nobody: the waits below only get stricter
+        copy_to_lds(p < XP ? xs : ws, voff[j], smem + (ibuf - lds0) + j * NW * 1024 + lane * 16);
+        continue;
+      }
       if ((j + 1) * NW <= XP || (j * NW < XP && p < XP)) load_to_lds<false>(xs, voff[j], ibuf + j * NW * 1024);
       else load_to_lds<NT>(ws, voff[j], ibuf + j * NW * 1024);
     }
@@ -247,23 +240,25 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
   constexpr std::integral_constant<int, 2> k2{};
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
-  for (int p = 0; p < NB && p < n; ++p) request();
-  if (n >= NB) wait_younger(std::integral_constant<int, NB - 1>{});
-  else if (NB > 3 && n == 3) wait_younger(k2);
-  else if (NB > 2 && n == 2) wait_younger(k1);
-  else wait_younger(k0);
-  read(0, 0);
-  int ph = 0;
-  for (; ph + NB < n; ++ph) phase(std::integral_constant<int, NB - 2>{}, yes, no);
-  // the last phases have nothing left to request and ever fewer phases behind them
-  if constexpr (NB > 3) {
-    if (n - 1 - ph > 2) { phase(k2, no, no); ++ph; }
+  if (ALIGNED || n > 0) {
+    for (int p = 0; p < NB && p < n; ++p) request();
+    if (n >= NB) wait_younger(std::integral_constant<int, NB - 1>{});
+    else if (NB > 3 && n == 3) wait_younger(k2);
+    else if (NB > 2 && n == 2) wait_younger(k1);
+    else wait_younger(k0);
+    read(0, 0);
+    int ph = 0;
+    for (; ph + NB < n; ++ph) phase(std::integral_constant<int, NB - 2>{}, yes, no);
+    // the last phases have nothing left to request and ever fewer phases behind them
+    if constexpr (NB > 3) {
+      if (n - 1 - ph > 2) { phase(k2, no, no); ++ph; }
+    }
+    if constexpr (NB > 2) {
+      if (n - 1 - ph > 1) { phase(k1, no, no); ++ph; }
+    }
+    if (n - 1 - ph > 0) phase(k0, no, no);
+    phase(k0, no, yes);
   }
-  if constexpr (NB > 2) {
-    if (n - 1 - ph > 1) { phase(k1, no, no); ++ph; }
-  }
-  if (n - 1 - ph > 0) phase(k0, no, no);
-  phase(k0, no, yes);
   // only now: the compiler, which does not count the ring's loads, waits for all of them here
   if constexpr (Epi::kScaled) {
 #pragma unroll
@@ -325,18 +320,19 @@ constexpr int gemm_phase(GemmShape s) {
   return s == GS_2x4 || s == GS_1x4 || s == GS_3x2 || s == GS_MANY_2 ? 8 : (s == GS_16 || s >= GS_MANY_4x4 ? 2 : 4);
 }
 
-template <int RT, int CT, int KW, int WT, int MT, int PH, int NB, bool NT, class Epi>
+template <int RT, int CT, int KW, int WT, int MT, int PH, int NB, bool NT, bool ALIGNED = true, class Epi>
 static void launch_ring_t(const uint16_t* xp, const uint16_t* w, int tp, int n_in, int n_out, int split_k,
                           const Epi& epi, hipStream_t st) {
   constexpr int WR = RT * WT, XC = CT * MT;
   const int nph = ((n_in >> 4) + PH - 1) / PH, pps = (nph + split_k - 1) / split_k;
   const int rgs = (n_out / 32 + WR - 1) / WR, tblocks = (tp / 32 + XC - 1) / XC;
   GemmArgs a{xp, w, n_in, n_out, tp, pps};
-  dim3 grid(tblocks == 1 ? rgs : (rgs + 7) / 8 * 8 * tblocks, (nph + pps - 1) / pps);
+  // (the unaligned form stands in for a shape with more phases: its last splits may be empty)
+  dim3 grid(tblocks == 1 ? rgs : (rgs + 7) / 8 * 8 * tblocks, ALIGNED ? (nph + pps - 1) / pps : split_k);
   constexpr size_t lds_x = (size_t)NB * PH * (XC + WR) * 1024, lds_r = (size_t)(KW - 1) * CT * WR * MT * 4096;
   constexpr size_t lds = lds_x > lds_r ? lds_x : lds_r;
   static_assert(lds <= 160 * 1024, "LDS");
-  auto kern = gemm_ring_kernel<RT, CT, KW, WT, MT, PH, NB, NT, Epi>;
+  auto kern = gemm_ring_kernel<RT, CT, KW, WT, MT, PH, NB, NT, ALIGNED, Epi>;
   static bool big_lds_allowed = false;  // one-time, per instantiation
   if (!big_lds_allowed) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -367,6 +363,10 @@ static int launch_gemm(const uint16_t* xp, const uint16_t* w, int tp, int n_in, 
                        const Epi& epi, hipStream_t st) {
   if (tp < 32 || (tp & 31) || (n_in & 15) || (n_out & 31)) return TRJ_ERR_BAD_SHAPE;
   const GemmPlan g = plan_gemm(tp, n_in, n_out, split_k);
+  if ((((uintptr_t)xp | (uintptr_t)w) & 15) != 0) {  // one shape for callers' odd pointers
+    launch_ring_t<2, 1, 2, 1, 1, gemm_phase(GS_2x2), 2, false, false>(xp, w, tp, n_in, n_out, g.split_k, epi, st);
+    return check_launch();
+  }
   switch (g.shape) {
     case GS_MANY_2:
       launch_ring_t<2, 1, 4, 1, 4, gemm_phase(GS_MANY_2), 3, false>(xp, w, tp, n_in, n_out, g.split_k, epi, st);

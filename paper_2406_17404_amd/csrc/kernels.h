@@ -12,8 +12,8 @@ struct Tunables {
   int gemm_big_t = 256;        // padded token rows from which wavefronts own two row tiles (0: never)
   int attn_target_wgs = 256;   // attention workgroups per launch aimed at (one per CU)
   int gemm_big_wt = 0;         // row tiles per wavefront of the many-rows kernel (2, 4; 0 = choose)
-  int attn_xchg_min_blocks = 48;  // blocks per workgroup from which wavefront pairs split their loads
-  int attn_min_bpw = 0;        // 32-slot blocks per wavefront, at least (0: 1 for trees of up to 64 nodes, else 2)
+  int attn_xchg_min_blocks = 48;  // no effect any more: the wavefronts of a key stream always share their loads
+  int attn_min_bpw = 0;        // 32-slot blocks per key stream, at least (0: chosen from the tree size)
 };
 // trj_set_tunable writes the process-wide set; every entry point copies it once on entry
 // (TuneScope) and every launch plan of that call, on that thread, reads the copy, so the
@@ -86,7 +86,6 @@ int launch_step_prep(const StepPrep& a, const EmbedRow& e, hipStream_t st);
 // kv_off / 32, split, 1 if the sequence has more than one group}, sequences ordered by length (prefix + tree), longest first, when
 // B <= 1024 (else in index order); word 8 * B * qg_max * nsplit_max holds n.  Sequences
 // whose status is not 0 are left out.  Must follow launch_tree_prep on the stream.
-#define ATTN_ITEM_WORDS(B, qg_max, nsplit_max) ((size_t)(B) * (qg_max) * (nsplit_max) * 8 + 8)
 int launch_attn_items(const int32_t* node_off, const int32_t* prefix_len, const int32_t* kv_off,
                       const int32_t* status_dev, int B, int rows_per_item, int qg_max,
                       int blocks_per_item, int nsplit_max, int32_t* items, hipStream_t st);
@@ -194,9 +193,13 @@ int launch_sum_splits(const float* partial, int n_split, size_t n, float* y, hip
 int launch_tile_activation(const uint16_t* x, int T, int n, int tp, uint16_t* xp, hipStream_t st);
 
 // attn_bf16.hip
-void attn_bf16_plan(int B, int T, int n_heads, int max_seq_slots, int* ntw, int* qg_max, int* bpwg,
-                    int* nsplit_max);
-size_t attn_bf16_ws_floats(int B, int tiles_per_seq, int n_heads, int dh, int nsplit_max);
+struct AttnPlan {
+  int ntw, qg_max;       // query tiles of 32 rows per workgroup, groups of them per sequence at most
+  int bpwg, nsplit_max;  // 32-slot blocks per workgroup, key splits per sequence at most
+};
+AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_slots);
+size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots);
+size_t attn_bf16_item_words(int B, int T, int n_heads, int max_seq_slots);
 int launch_zero_bytes(void* p, size_t bytes, hipStream_t st);
 int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint16_t* v_layer,
                           const uint64_t* anc, const int32_t* node_off,

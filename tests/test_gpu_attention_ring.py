@@ -1,0 +1,87 @@
+"""The bf16 attention's ring of K/V blocks at its edges: key streams with no, one and a few
+blocks (fewer and more than the ring holds), four query tiles per workgroup with idle and
+ragged ones, batches that mix tree sizes, and operands that do not start at a multiple of 16
+bytes (which the loads straight to LDS cannot take), for the projections too."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import layouts
+from gpu_util import DEV, Batch, rel_err, to_dev
+from oracle import tr_oracle as O
+from paper_2406_17404_amd import binding as b
+from paper_2406_17404_amd import inputs as I
+from test_gpu_attention import TOL, case, run_attention
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,dh,L,n", [
+    (2, 128, 1400, 65), (1, 64, 1407, 128), (2, 128, 1536, 97), (1, 128, 2047, 69),   # four tiles
+    (2, 128, 1000, 33), (1, 64, 700, 64), (2, 128, 600, 17)])                         # two, one
+def test_streams_with_few_and_many_blocks(H, dh, L, n):
+    c = case(3 * L + n, H, dh, L, n, "bf16")
+    want = O.tree_attention(*c)
+    try:
+        for wgs, blocks in ((1, 0), (8, 1), (24, 1), (64, 1), (4096, 1), (4096, 3)):
+            b.trj_set_tunable("attn_target_wgs", wgs)
+            b.trj_set_tunable("attn_min_bpw", blocks)
+            got = run_attention("bf16", H, dh, [c])[0]
+            assert np.isfinite(got).all(), (wgs, blocks)
+            assert rel_err(got, want) <= TOL["bf16"], (wgs, blocks)
+    finally:
+        b.trj_set_tunable("attn_target_wgs", 256)
+        b.trj_set_tunable("attn_min_bpw", 0)
+
+
+def test_batch_of_large_and_small_trees_takes_four_tiles():
+    sizes, lens = [128, 128, 33, 97, 1, 96], [1500, 3, 1411, 0, 900, 64]
+    cases = [case(70 + s, 2, 128, L, n, "bf16") for s, (n, L) in enumerate(zip(sizes, lens))]
+    assert sum(sizes) > 64 * len(sizes)
+    for g, c in zip(run_attention("bf16", 2, 128, cases, align=32), cases):
+        assert rel_err(g, O.tree_attention(*c)) <= TOL["bf16"]
+
+
+def shifted(a, dtype, by):
+    """The array on the device, starting `by` elements behind an allocation's start."""
+    buf = torch.zeros(a.size + by, dtype=dtype, device=DEV)
+    buf[by:].copy_(torch.from_numpy(np.ascontiguousarray(a, np.float32).reshape(-1)).to(dtype))
+    return buf[by:]
+
+
+@pytest.mark.parametrize("which", ["q", "k", "v", "workspace"])
+@pytest.mark.parametrize("L,n", [(100, 20), (300, 50), (1450, 80)])
+def test_attention_operands_at_any_alignment(which, L, n):
+    H, dh = 2, 128
+    c = case(9 + L, H, dh, L, n, "bf16")
+    batch = Batch([c[3]], [L])
+    kp, vp = np.zeros((H, batch.s_pool * dh), np.float32), np.zeros((H, batch.s_pool * dh), np.float32)
+    layouts.kv_to_pool(c[1].astype(np.float32), c[2].astype(np.float32), batch.s_pool, int(batch.kv_off_h[0]), kp, vp)
+    q, k, v = (shifted(a, torch.bfloat16, int(which == w)) for a, w in ((c[0], "q"), (kp, "k"), (vp, "v")))
+    need = b.tree_attention_workspace_bytes(1, n, H, dh, batch.max_seq_slots, b.BF16)
+    ws = torch.empty(need + 8, dtype=torch.uint8, device=DEV)[8 * (which == "workspace"):]
+    out = torch.full((n, H, dh), float("nan"), dtype=torch.bfloat16, device=DEV)
+    b.tree_attention(q, k, v, batch.parent, batch.node_off, batch.kv_off, batch.prefix, 1, n, H, dh, batch.s_pool,
+                     batch.max_seq_slots, b.BF16, 1.0 / math.sqrt(dh), ws, out, n_kv_heads=H)
+    torch.cuda.synchronize()
+    assert rel_err(out.float().cpu().numpy(), O.tree_attention(*c)) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("which", ["w", "workspace"])
+@pytest.mark.parametrize("T,n_in,n_out", [(20, 272, 96), (64, 1040, 4096), (300, 528, 4096)])
+def test_projection_operands_at_any_alignment(which, T, n_in, n_out):
+    rng = np.random.default_rng(T)
+    x = I.bf16_round(rng.standard_normal((T, n_in)).astype(np.float32))
+    w = I.bf16_round((rng.standard_normal((n_out, n_in)) * 0.05).astype(np.float32))
+    wd = to_dev(w, torch.bfloat16)
+    packed = torch.empty(n_out * n_in + 1, dtype=torch.bfloat16, device=DEV)[int(which == "w"):][:n_out * n_in]
+    b.trj_pack_weight(packed, wd, n_out, n_in, b.BF16, b.PACK_PLAIN)
+    y = torch.full((T, n_out), float("nan"), dtype=torch.float32, device=DEV)
+    size = 2 * 128 * ((T + 127) // 128) * n_in + 32 * T * n_out + 1024
+    ws = torch.empty(size + 8, dtype=torch.uint8, device=DEV)[8 * (which == "workspace"):]
+    b.trj_linear(to_dev(x, torch.bfloat16), packed, T, n_in, n_out, b.BF16, 0, ws, y)
+    torch.cuda.synchronize()
+    # bf16 products are exact in fp32: only the order of at most 1040 additions differs
+    assert rel_err(y.cpu().numpy(), x.astype(np.float64) @ w.astype(np.float64).T) <= 1e-5
