@@ -446,8 +446,9 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
   carve_tree(c, dtype, B, T, n_heads, n_kv_heads, head_dim, max_seq_slots, &w);
   if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t st = (hipStream_t)stream;
-  const bool bf16 = dtype == TRJ_BF16;
-  if (B <= PREP_MAX_SEQS) {
+  const bool bf16 = dtype == TRJ_BF16, self = bf16 && B == 1;  // one sequence: the kernel checks it itself
+  if (self) {
+  } else if (B <= PREP_MAX_SEQS) {
     const StepPrep p{parent, node_off, kv_off, prefix_len, B, T, s_pool, max_seq_slots, w.depth, w.anc, w.status,
                      w.row_slot, w.row_pos, w.row_seq, nullptr, head_dim, 0.f, w.items, w.attn_rows, w.attn_qg,
                      w.attn_bpwg, w.attn_ns,
@@ -466,7 +467,7 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
     return launch_tree_attn_bf16((const uint16_t*)q, (const uint16_t*)k_layer,
                                  (const uint16_t*)v_layer, w.anc, node_off, kv_off, prefix_len,
                                  w.status, w.items, B, T, n_heads, n_kv_heads, head_dim, s_pool, max_seq_slots, scale,
-                                 w.attn, 0, 0, (uint16_t*)out, st);
+                                 w.attn, 0, 0, (uint16_t*)out, self ? parent : nullptr, w.status, st);
   }
   return launch_tree_attn_f32((const float*)q, (const float*)k_layer, (const float*)v_layer, w.anc,
                               w.row_seq, node_off, kv_off, prefix_len, w.status, T, n_heads,
@@ -690,7 +691,7 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
       if (kv_only) return TRJ_OK;
       TRJ_TRY(launch_tree_attn_bf16(w.q, kl, vl, w.t.anc, node_off, kv_off, prefix_len, status_dev,
                                     w.t.items, B, T, H, Hkv, dh, s_pool, max_seq_slots, scale, w.t.attn, 1, tp,
-                                    w.op, st));
+                                    w.op, nullptr, nullptr, st));
       { ProfScope ps_(KC_GEMM_O, st); TRJ_TRY(launch_gemm_store_f32(w.op, (const uint16_t*)lw.wo, T, tp, hd, d, sk_o, w.partial, st)); }
       { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_o, w.x, lw.g_ffn, T, d, tp, w.hp, w.ssq, st)); }
       { ProfScope ps_(KC_GEMM_GATE_UP, st); TRJ_TRY(launch_gemm_gate_up(w.hp, (const uint16_t*)lw.w_gate_up, tp, d, F, rs, w.act, st)); }

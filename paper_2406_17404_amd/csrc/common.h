@@ -102,8 +102,19 @@ __device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uin
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
                  : "memory");
 }
+// 4 bytes per lane instead, for arrays that start anywhere a word may
+__device__ __forceinline__ void load_words_to_lds(const void* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(base), "s"(lds)
+               : "memory");
+}
 __device__ __forceinline__ void copy_to_lds(const void* base, uint32_t voff, void* lane_dst) {
   *static_cast<u32x4*>(lane_dst) = *reinterpret_cast<const u32x4*>(static_cast<const uint8_t*>(base) + voff);
+}
+
+// per-node values of a tree on one wavefront, two nodes per lane (node = lane and lane + 64):
+__device__ inline int from_node(const int (&v)[2], int node) {  // the value of `node`, any lane's choice
+  const int a = __shfl(v[0], node & 63), b = __shfl(v[1], node & 63);
+  return node < 64 ? a : b;
 }
 
 // ---- error bookkeeping (defined in api.hip)

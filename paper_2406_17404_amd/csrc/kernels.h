@@ -201,12 +201,15 @@ AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_s
 size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots);
 size_t attn_bf16_item_words(int B, int T, int n_heads, int max_seq_slots);
 int launch_zero_bytes(void* p, size_t bytes, hipStream_t st);
+// parent (one sequence, plain `out`): no prologue launch came before, the kernel checks the
+// sequence itself, writes its status and the rows it does not own; anc and items are not read
 int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint16_t* v_layer,
                           const uint64_t* anc, const int32_t* node_off,
                           const int32_t* kv_off, const int32_t* prefix_len,
                           const int32_t* status_dev, const int32_t* items, int B, int T,
                           int n_heads, int n_kv_heads, int dh, int s_pool, int max_seq_slots,
-                          float scale, float* ws, int tiled, int tp, uint16_t* out, hipStream_t st);
+                          float scale, float* ws, int tiled, int tp, uint16_t* out, const int32_t* parent,
+                          int32_t* status, hipStream_t st);
 
 // api.hip: the forward pass behind tr_verify_step (with_head == false: decoder layers
 // only, for prompt passes), its workspace need, and the model-descriptor check

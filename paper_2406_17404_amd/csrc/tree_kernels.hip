@@ -194,7 +194,7 @@ int launch_tree_prep(const int32_t* parent, const int32_t* node_off, const int32
 // tree, which is small enough (at most 128 parents) to be worked out again by every workgroup
 // that needs it.  A launch of its own for each piece costs 2-5 us of dispatch and drain for
 // next to no work: clear, tree checks, rotary table, work list and embedding together 19 us of
-// a step, in one launch 7 us (5 rows; attention alone 8.5 -> 4.5 us).  Roles by workgroup id:
+// a step, in one launch 7 us (5 rows).  Roles by workgroup id:
 //   B * chunks   sequence s, rows 16c..: tree checks, depth and ancestor bits by pointer
 //                doubling (7 rounds at most, where walking the parents of a 128-node chain
 //                took 14 us); chunk 0 writes the tree's rows, every chunk the rotary table of
@@ -565,10 +565,6 @@ struct Accepted {
   int depth, best, bonus;  // depth of the best node, -1 for a malformed sequence; uniform
   int path[2];             // nodes lane and lane + 64 of the path, root first; -1 behind its end
 };
-__device__ inline int from_node(const int (&v)[2], int node) {  // v of `node`, any lane's choice
-  const int a = __shfl(v[0], node & 63), b = __shfl(v[1], node & 63);
-  return node < 64 ? a : b;
-}
 __device__ inline Accepted accept_sequence(const int32_t* __restrict__ argmax, const int32_t* __restrict__ tok,
                                            const int32_t* __restrict__ parent, const int32_t* __restrict__ node_off,
                                            int T, bool known_bad, int s) {

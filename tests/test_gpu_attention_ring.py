@@ -85,3 +85,49 @@ def test_projection_operands_at_any_alignment(which, T, n_in, n_out):
     torch.cuda.synchronize()
     # bf16 products are exact in fp32: only the order of at most 1040 additions differs
     assert rel_err(y.cpu().numpy(), x.astype(np.float64) @ w.astype(np.float64).T) <= 1e-5
+
+
+@pytest.mark.parametrize("what", ["good", "inner rows", "second root", "child before parent", "slots", "no rows",
+                                  "too many rows"])
+@pytest.mark.parametrize("L,n", [(40, 20), (900, 64), (1450, 128)])
+def test_one_sequence_checked_by_the_attention_kernel(what, L, n):
+    """A single sequence has no launch of its own for the tree's checks: rows that no valid
+    sequence owns read as zeros, deep trees need every doubling round."""
+    H, dh = 2, 64
+    for tree in (I.tree_chain(n), I.tree_random(n, np.random.default_rng(n))):
+        c = case(77 + L, H, dh, L, n, "bf16", np.asarray(tree, np.int32))
+        batch = Batch([c[3]], [L])
+        kp, vp = np.zeros((H, batch.s_pool * dh), np.float32), np.zeros((H, batch.s_pool * dh), np.float32)
+        layouts.kv_to_pool(c[1].astype(np.float32), c[2].astype(np.float32), batch.s_pool, int(batch.kv_off_h[0]),
+                           kp, vp)
+        before, after = (3, 4) if what == "inner rows" and n + 7 <= 128 else (0, 0)
+        T = before + n + after
+        parent = np.zeros(T, np.int32)
+        parent[before:before + n] = c[3]
+        off, prefix = [before, before + n], L
+        if what == "second root":
+            parent[n // 2] = -1
+        elif what == "child before parent":
+            parent[n - 1] = n - 1
+        elif what == "slots":
+            prefix = batch.s_pool
+        elif what == "no rows":
+            off = [n, n]
+        elif what == "too many rows":
+            off = [0, T + 1]
+        q = np.zeros((T, H, dh), np.float32)
+        q[before:before + n] = c[0]
+        i32 = lambda a: torch.tensor(a, dtype=torch.int32, device=DEV)
+        out = torch.full((T, H, dh), float("nan"), dtype=torch.bfloat16, device=DEV)
+        ws = torch.empty(b.tree_attention_workspace_bytes(1, T, H, dh, batch.max_seq_slots, b.BF16),
+                         dtype=torch.uint8, device=DEV)
+        b.tree_attention(to_dev(q, torch.bfloat16), to_dev(kp, torch.bfloat16), to_dev(vp, torch.bfloat16), i32(parent),
+                         i32(off), batch.kv_off, i32([prefix]), 1, T, H, dh, batch.s_pool, batch.max_seq_slots, b.BF16,
+                         1.0 / math.sqrt(dh), ws, out, n_kv_heads=H)
+        torch.cuda.synchronize()
+        got = out.float().cpu().numpy()
+        if what in ("good", "inner rows"):
+            assert rel_err(got[before:before + n], O.tree_attention(*c)) <= TOL["bf16"]
+            assert not got[:before].any() and not got[before + n:].any()
+        else:
+            assert not got.any()
