@@ -582,6 +582,13 @@ int32_t trj_dev_gemm_plan(int32_t T, int32_t n_in, int32_t n_out, int32_t fused,
 }  // extern "C"
 
 namespace trj {
+// a projection into the residual stream: k-split images that launch_reduce_norm adds, or (one
+// split) added at once
+static int add_projection(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out, int split,
+                          float* partial, float* x, hipStream_t st) {
+  return split > 1 ? launch_gemm_store_f32(xp, w, T, tp, n_in, n_out, split, partial, st)
+                   : launch_gemm_residual(xp, w, T, tp, n_in, n_out, x, st);
+}
 // The forward pass over the tree rows; with_head == false stops after the last decoder
 // layer (the tree's K/V are in the pool, nothing else is produced), which is what a
 // prompt pass needs.
@@ -692,12 +699,12 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
       TRJ_TRY(launch_tree_attn_bf16(w.q, kl, vl, w.t.anc, node_off, kv_off, prefix_len, status_dev,
                                     w.t.items, B, T, H, Hkv, dh, s_pool, max_seq_slots, scale, w.t.attn, 1, tp,
                                     w.op, nullptr, nullptr, st));
-      { ProfScope ps_(KC_GEMM_O, st); TRJ_TRY(launch_gemm_store_f32(w.op, (const uint16_t*)lw.wo, T, tp, hd, d, sk_o, w.partial, st)); }
-      { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_o, w.x, lw.g_ffn, T, d, tp, w.hp, w.ssq, st)); }
+      { ProfScope ps_(KC_GEMM_O, st); TRJ_TRY(add_projection(w.op, (const uint16_t*)lw.wo, T, tp, hd, d, sk_o, w.partial, w.x, st)); }
+      { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_o > 1 ? sk_o : 0, w.x, lw.g_ffn, T, d, tp, w.hp, w.ssq, st)); }
       { ProfScope ps_(KC_GEMM_GATE_UP, st); TRJ_TRY(launch_gemm_gate_up(w.hp, (const uint16_t*)lw.w_gate_up, tp, d, F, rs, w.act, st)); }
-      { ProfScope ps_(KC_GEMM_DOWN, st); TRJ_TRY(launch_gemm_store_f32(w.act, (const uint16_t*)lw.w_down, T, tp, F, d, sk_d, w.partial, st)); }
+      { ProfScope ps_(KC_GEMM_DOWN, st); TRJ_TRY(add_projection(w.act, (const uint16_t*)lw.w_down, T, tp, F, d, sk_d, w.partial, w.x, st)); }
       const float* g_next = l + 1 < m.n_layers ? weights->h_layers[l + 1].g_attn : weights->g_final;
-      { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_d, w.x, g_next, T, d, tp, w.hp, w.ssq, st)); }
+      { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_d > 1 ? sk_d : 0, w.x, g_next, T, d, tp, w.hp, w.ssq, st)); }
     }
     ProfScope ps_(KC_GEMM_LM, st);
     TRJ_TRY(launch_gemm_lm(w.hp, (const uint16_t*)weights->w_lm, T, tp, d, V, rs, logits, w.cand, argmax_out, st));

@@ -1,4 +1,4 @@
-// One token row's embedding, as a piece of a launch that does other things too: in bf16 mode
+// Token rows' embedding, as a piece of a launch that does other things too: in bf16 mode
 // with the first projection's input, exactly what reduce_norm_kernel writes for a row that
 // comes from the embedding table (same column parts, same order of every sum).
 #pragma once
@@ -7,12 +7,18 @@
 
 namespace trj {
 
-inline int embed_blocks(const EmbedRow& e) { return e.x ? (e.hp ? e.tp : e.T) : 0; }
+// rows of a workgroup of PREP_THREADS: in bf16 as many as fit side by side (d = 4096: two)
+__host__ __device__ inline int embed_rows(const EmbedRow& e) {
+  return e.hp ? PREP_THREADS / (e.parts * e.part_threads) : 1;
+}
+inline int embed_blocks(const EmbedRow& e) {
+  return e.x ? ((e.hp ? e.tp : e.T) + embed_rows(e) - 1) / embed_rows(e) : 0;
+}
 
-// one workgroup of PREP_THREADS; thread `tid` owns 8 columns (bf16: at most 8192 of them)
-__device__ inline void embed_row(const EmbedRow& e, int t) {
-  const int tid = threadIdx.x;
-  if (!e.hp) {  // fp32: the row alone
+// workgroup `block` of PREP_THREADS; a thread owns 8 columns (bf16: at most 8192 of them)
+__device__ inline void embed_row(const EmbedRow& e, int block) {
+  if (!e.hp) {  // fp32: one row alone
+    const int tid = threadIdx.x, t = block;
     int id = e.tok[t];
     id = id < 0 ? 0 : (id >= e.vocab ? e.vocab - 1 : id);
     const float* row = static_cast<const float*>(e.embed) + (size_t)id * e.d;
@@ -20,8 +26,10 @@ __device__ inline void embed_row(const EmbedRow& e, int t) {
     return;
   }
   __shared__ float wsum[PREP_THREADS / WAVE];
-  const int part = tid / e.part_threads;  // parts are whole wavefronts
-  const bool live = part < e.parts && tid < (e.d >> 3);
+  const int row_threads = e.parts * e.part_threads, sub = threadIdx.x / row_threads;
+  const int tid = threadIdx.x - sub * row_threads;  // within the row; parts are whole wavefronts
+  const int t = block * embed_rows(e) + sub;
+  const bool mine = sub < embed_rows(e) && t < e.tp, live = mine && tid < (e.d >> 3);
   float ss = 0.f;
   if (t >= e.T) {
     const u32x4 z = {0, 0, 0, 0};
@@ -46,10 +54,10 @@ __device__ inline void embed_row(const EmbedRow& e, int t) {
     for (int i = 0; i < 4; ++i) ss += a[i] * a[i] + b[i] * b[i];
   }
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-  if ((tid & 63) == 0) wsum[tid >> 6] = ss;
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
   __syncthreads();
-  if (tid < e.parts) {
-    const int w0 = tid * (e.part_threads / WAVE);
+  if (mine && tid < e.parts) {
+    const int w0 = (sub * row_threads + tid * e.part_threads) / WAVE;
     float tot = 0.f;
     for (int w = 0; w < e.part_threads / WAVE; ++w) tot += wsum[w0 + w];
     e.ssq[(size_t)tid * e.tp + t] = tot;

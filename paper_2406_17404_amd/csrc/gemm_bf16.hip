@@ -146,11 +146,14 @@ int gemm_bf16_split_k(int n_out, int tp, int n_in) {
   const int ntiles = n_out >> 5, ttiles = tp >> 5, ksteps = n_in >> 4;
   int sk = 1;
   if (many_rows(tp)) {
-    // every further split is one more fp32 image written and read again: 6.7 us at 1024 x 4096
+    // us at 1024 x 4096 behind the product: an unsplit one is added to the residual stream in its
+    // epilogue and the next kernel only reads it (8), split ones are images to write, read again
+    // and add (30 for two, 50 for four).  With the output projection unsplit at 1024 rows:
+    // 41.0 + 19.8 us for the sum -> 47.5 + 10.1
     float best = 0.f;
     for (int s : {1, 2, 4}) {
       const float cost = many_cost(plan_many(ttiles, ntiles, ksteps, s), ttiles, ntiles, ksteps, s) +
-                         6.7f * s * (ttiles / 32.f) * (ntiles / 128.f);
+                         (s == 1 ? 8.f : 10.f + 10.f * s) * (ttiles / 32.f) * (ntiles / 128.f);
       if (s == 1 || cost < best) { best = cost; sk = s; }
     }
   } else {

@@ -171,6 +171,9 @@ int gemm_bf16_clamp_split(int n_out, int tp, int n_in, int split_k);
 void gemm_bf16_describe_plan(int tp, int n_in, int n_out, int split_k, int32_t out[6]);
 int launch_gemm_store_f32(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in,
                           int n_out, int split_k, float* y, hipStream_t st);
+// x += the whole product (no k-split)
+int launch_gemm_residual(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out, float* x,
+                         hipStream_t st);
 size_t gemm_lm_argmax_scratch_bytes(int T, int n_out);
 // fp32 logits (null: none) and the greedy argmax of every row, from candidates of the epilogue
 // (cand null: the logits alone)
@@ -183,6 +186,7 @@ int launch_gemm_qkv(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_
                     int n_kv_heads, int dh, int s_pool, const RowScale& rs, const float2* cs,
                     const int32_t* cs_row, const int32_t* row_slot, uint16_t* q, uint16_t* k_layer,
                     uint16_t* v_layer, hipStream_t st);
+// n_split == 0: x is complete already and only read.
 // x[t] = E[tok[t]] (more than PREP_MAX_SEQS sequences), or x[t] += the split-k partial sums; hp = bf16(x * g) tiled and the
 // rows' partial sums of squares for the consumer's RowScale, one launch
 int launch_embed_norm(const uint16_t* embed, const int32_t* tok, int T, int d, int vocab, float* x,
