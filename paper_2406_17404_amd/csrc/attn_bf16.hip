@@ -562,18 +562,6 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
   }
 }
 
-// zero fill (rows of malformed sequences and the padding rows of the tiled output)
-__global__ void zero_u32_kernel(uint32_t* p, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-int launch_zero_bytes(void* p, size_t bytes, hipStream_t st) {
-  size_t n = bytes / 4;
-  if (n == 0) return TRJ_OK;
-  zero_u32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>((uint32_t*)p, n);
-  return check_launch();
-}
-
 // Launch shape: query tiles per workgroup, query groups, blocks per workgroup, splits.
 AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_slots) {
   AttnPlan p;

@@ -128,7 +128,6 @@ inline int check_launch() {
   return TRJ_OK;
 }
 
-inline size_t elem_bytes(int dtype) { return dtype == TRJ_BF16 ? 2 : 4; }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 }  // namespace trj

@@ -204,7 +204,6 @@ struct AttnPlan {
 AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_slots);
 size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots);
 size_t attn_bf16_item_words(int B, int T, int n_heads, int max_seq_slots);
-int launch_zero_bytes(void* p, size_t bytes, hipStream_t st);
 // parent (one sequence, plain `out`): no prologue launch came before, the kernel checks the
 // sequence itself, writes its status and the rows it does not own; anc and items are not read
 int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint16_t* v_layer,
