@@ -37,6 +37,7 @@
 namespace trj {
 
 constexpr float NEG_BIG = -1e30f;
+constexpr float SOFTMAX_LAG = 8.f;  // see softmax_tile_prefix; smaller weights are below a bf16 step of the largest
 
 struct AttnArgs {
   const uint16_t* q;
@@ -58,6 +59,7 @@ struct AttnArgs {
   const int32_t* items;
   const int32_t* n_items;
   float scale_log2e;
+  float lag;  // of the softmax reference behind the running maximum, log2
   // un-normalised partials, one per (sequence, query tile, head, split), stored as the
   // image of the wavefront's accumulator registers: element (mt*16 + v)*64 + lane, so that
   // every store and every load of the merge kernel is a contiguous 256-byte row
@@ -75,20 +77,29 @@ struct AttnArgs {
 
 
 // Online-softmax update of one query tile with one block of 32 keys: S^T accumulators in,
-// packed bf16 probabilities out (the B operand of the second product), running max m and
-// sum l of this lane's query updated, `alpha` = factor for the O accumulators.
-//
+// packed bf16 probabilities out (the B operand of the second product), running maximum `top`,
+// reference m and sum l of this lane's query updated, `alpha` = factor for the O accumulators.
+// Weights are 2^(score - m).  The key whose score is m has weight 1, which bf16 holds exactly,
+// and the largest weights are what rounding to bf16 costs precision on: the more keys set the
+// reference, the closer the result.  With lag 0 the reference is the running maximum, set by a
+// few keys per stream.  With lag > 0 every block's largest key sets it, down to 2^-lag of the
+// running maximum (below, rounding no longer matters), at the price of rescaling O at every
+// block: for walks that have fewer streams or splits than a sequence of that size could have.
+// Error against 64 bits of 16 rows on 512 slots: eight streams 2.02e-3, four 2.06e-3 without
+// lag, 2.02e-3 with; twelve sequences of 80 rows on up to 2048 slots with two unsplit streams
+// 2.175e-3 without, 2.02e-3 with, with four streams 2.135e-3.
 // Blocks that lie wholly in the prefix (all but the last few of a sequence) take this
 // lean form: no visibility tests; the max works on the raw scores and the scale
 // (log2 e / sqrt(dh), > 0) goes into one fused multiply-add per key; v_exp_f32 directly
 // (results below the normal range flush to zero, as they should).
-__device__ inline void softmax_tile_prefix(const f32x16& sacc, float scale, float& m, float& l,
+__device__ inline void softmax_tile_prefix(const f32x16& sacc, float scale, float lag, float& top, float& m, float& l,
                                            float& alpha, u32x4 (&pk)[2]) {
   float mx = sacc[0];
 #pragma unroll
   for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
   mx = fmaxf(mx, __shfl_xor(mx, 32));
-  const float m_new = fmaxf(m, mx * scale);
+  top = fmaxf(top, mx * scale);
+  const float m_new = fmaxf(mx * scale, top - lag);
   alpha = __builtin_amdgcn_exp2f(m - m_new);
   float lsum = 0.f;
   float p[16];
@@ -109,7 +120,7 @@ __device__ inline void softmax_tile_prefix(const f32x16& sacc, float scale, floa
 // which keys a query sees; a key that is not visible contributes exactly 0, also while
 // nothing is visible yet (m == NEG_BIG).
 __device__ inline void softmax_tile_tree(const f32x16& sacc, int key0, int hh, int L, uint64_t anc0,
-                                         uint64_t anc1, float scale, float& m, float& l,
+                                         uint64_t anc1, float scale, float lag, float& top, float& m, float& l,
                                          float& alpha, u32x4 (&pk)[2]) {
   float sv[16];
   float mx = NEG_BIG;
@@ -121,7 +132,8 @@ __device__ inline void softmax_tile_tree(const f32x16& sacc, int key0, int hh, i
     mx = fmaxf(mx, sv[v]);
   }
   mx = fmaxf(mx, __shfl_xor(mx, 32));
-  const float m_new = fmaxf(m, mx);
+  top = fmaxf(top, mx);
+  const float m_new = fmaxf(mx, top - lag);
   alpha = exp2f(m - m_new);
   float lsum = 0.f;
   float p[16];
@@ -297,7 +309,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   for (int mt = 0; mt < MTV; ++mt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[mt][v] = 0.f;
-  float m = NEG_BIG, l = 0.f;
+  float top = NEG_BIG, m = NEG_BIG, l = 0.f;
   u32x4 kreg[KSTEPS], vreg[2 * MTV];
   auto read = [&](u32x4 (&r)[KSTEPS], int sl) {
 #pragma unroll
@@ -383,9 +395,9 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
     if (live) {
       read(vreg, cur + 1);
       if (key0 + 32 > L)  // uniform
-        softmax_tile_tree(sacc, key0, hh, L, anc0, anc1, a.scale_log2e, m, l, alpha, pk);
+        softmax_tile_tree(sacc, key0, hh, L, anc0, anc1, a.scale_log2e, a.lag, top, m, l, alpha, pk);
       else
-        softmax_tile_prefix(sacc, a.scale_log2e, m, l, alpha, pk);
+        softmax_tile_prefix(sacc, a.scale_log2e, a.lag, top, m, l, alpha, pk);
     }
     attn_wait<(AHEAD == 0 ? 0 : (AHEAD < D ? 2 * AHEAD - 1 : 2 * (D - 1))) * HP, MEET>();
     if constexpr (AHEAD == D) request(vp, cur + 1);
@@ -594,10 +606,15 @@ AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_s
   const int min_b = tune().attn_min_bpw > 0 ? tune().attn_min_bpw * (p.ntw == 4 ? 2 : 4)
                                             : (p.ntw == 4 || (p.ntw == 2 && nmax <= 64) ? 4 : 8);
   if (b < min_b) b = min_b;
+  // one and four tiles have half the key streams that workgroups of eight wavefronts could have
+  p.lag = p.ntw == 2 ? 0.f : SOFTMAX_LAG;
   // up to 16 blocks (four per stream) the walk is shorter than the merge launch that a split
   // needs: 16 rows on 300 slots 11.9 against 13.6 us a call, 64 rows on 128 12.9 against 15.1,
   // on 512 (18 blocks) 17.2 against 15.9
-  if (tune().attn_min_bpw == 0 && nb <= 16) b = nb;
+  if (tune().attn_min_bpw == 0 && nb <= 16 && b < nb) {
+    b = nb;
+    p.lag = SOFTMAX_LAG;
+  }
   if (b > nb) b = nb;
   p.bpwg = b;
   p.nsplit_max = (nb + b - 1) / b;
@@ -641,7 +658,7 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
   float* pl = pm + parts * 32;
   AttnArgs a{q, k_layer, v_layer, anc, node_off, kv_off, prefix_len, status_dev, n_heads, n_heads / n_kv_heads,
              s_pool, bpwg, nsplit_max, qg_max, B * qg_max * nsplit_max * n_kv_heads, items,
-             items + (size_t)B * qg_max * nsplit_max * 8, scale * 1.4426950408889634f, po, pm, pl, tiles_per_seq, out, tiled, tp,
+             items + (size_t)B * qg_max * nsplit_max * 8, scale * 1.4426950408889634f, p.lag, po, pm, pl, tiles_per_seq, out, tiled, tp,
              parent, status, T, max_seq_slots};
   if (parent && (B != 1 || tiled)) return TRJ_ERR_BAD_SHAPE;
   const int group = n_heads / n_kv_heads;

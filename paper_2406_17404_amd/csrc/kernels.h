@@ -200,6 +200,7 @@ int launch_tile_activation(const uint16_t* x, int T, int n, int tp, uint16_t* xp
 struct AttnPlan {
   int ntw, qg_max;       // query tiles of 32 rows per workgroup, groups of them per sequence at most
   int bpwg, nsplit_max;  // 32-slot blocks per workgroup, key splits per sequence at most
+  float lag;             // how far the softmax reference may fall behind the running maximum (log2)
 };
 AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_slots);
 size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots);
