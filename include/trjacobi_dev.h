@@ -35,15 +35,24 @@ int32_t trj_linear(const void* x, const void* w_packed, int32_t T, int32_t n_in,
  * grid k-splits, 1 if the many-rows kernel (packed batches) is used. */
 int32_t trj_dev_gemm_plan(int32_t T, int32_t n_in, int32_t n_out, int32_t fused, int32_t* h_plan);
 
+/* The launch plan of a bf16 attention over B sequences with T rows in all.  shared_kv != 0:
+ * several query heads per K/V head.  h_plan[6] (HOST): query tiles per workgroup, query groups
+ * per sequence, 32-slot blocks per workgroup, key splits, 1 if K/V go through rings in LDS
+ * (operands on multiples of 16 bytes), 1 if every block's largest key sets the softmax
+ * reference. */
+int32_t trj_dev_attn_plan(int32_t B, int32_t T, int32_t n_heads, int32_t head_dim, int32_t shared_kv,
+                          int32_t max_seq_slots, int32_t* h_plan);
+
 /* Launch-shape knobs for experiments: "gemm_target_wgs" (workgroups a split-k projection
  * is split up to), "max_split_k", "gemm_cfg" (0: choose the workgroup shape per
  * projection, 1..6 force one), "gemm_big_t" (padded token rows from which the packed-batch
  * projection kernel is used, 0: never), "gemm_big_wt" (row tiles per wavefront of that
  * kernel: 2, 4, or 0 to choose per projection), "attn_target_wgs" (attention workgroups aimed at
  * per launch), "attn_min_bpw" (32-slot blocks per key stream, at least; 0 = chosen from the tree
- * size), "attn_xchg_min_blocks" (accepted, without effect: the wavefronts of a key stream always
- * share its loads).  Results do not
- * depend on them beyond fp32 summation order.  Unknown name: TRJ_ERR_BAD_SHAPE. */
+ * size), "attn_xchg_min_blocks" (32-slot blocks of 32 heads per query tile from which the
+ * wavefronts of a key stream share its K/V through rings in LDS, heads of 128 that share no
+ * K/V; 1: always).  Results do not depend on them beyond fp32 summation order and, in the
+ * attention, which keys set the softmax reference.  Unknown name: TRJ_ERR_BAD_SHAPE. */
 int32_t trj_set_tunable(const char* name, int32_t value);
 
 /* Per-kernel timing for benchmarks.  Between trj_profile_begin(kernel_class, capacity)

@@ -72,6 +72,7 @@ _SIGS = {
     "trj_read_probe": (_i32, [_vp, _sz, _vp, _vp]),
     "trj_dev_device_info": (_i32, [_ip]),
     "trj_dev_gemm_plan": (_i32, [_i32, _i32, _i32, _i32, _ip]),
+    "trj_dev_attn_plan": (_i32, [_i32, _i32, _i32, _i32, _i32, _i32, _ip]),
     "trj_workspace_bytes": (_i32, [C.POINTER(ModelDesc), _i32, _i32, _i32, C.POINTER(_sz)]),
     "trj_pack_weight": (_i32, [_vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp]),
     "trj_kv_pack": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp]),
@@ -202,6 +203,12 @@ def trj_dev_gemm_plan(T: int, n_in: int, n_out: int, fused: bool) -> dict:
     _check("trj_dev_gemm_plan", lib().trj_dev_gemm_plan(T, n_in, n_out, int(fused), out))
     return dict(zip(("token_tiles", "row_tiles", "k_parts", "tiles_per_wave", "split_k", "many_rows"),
                     (int(v) for v in out)))
+
+
+def trj_dev_attn_plan(B: int, T: int, n_heads: int, head_dim: int, shared_kv: bool, max_seq_slots: int) -> dict:
+    out = (C.c_int32 * 6)()
+    _check("trj_dev_attn_plan", lib().trj_dev_attn_plan(B, T, n_heads, head_dim, int(shared_kv), max_seq_slots, out))
+    return dict(zip(("tiles", "groups", "blocks", "splits", "ring", "lag"), (int(v) for v in out)))
 
 
 def trj_workspace_bytes(desc: ModelDesc, t_max: int, b_max: int, l_max: int) -> int:

@@ -93,9 +93,9 @@ static void carve_tree(Carver& c, int dtype, int B, int T, int H, int Hkv, int d
   w->items = nullptr;
   w->attn_rows = w->attn_qg = w->attn_bpwg = w->attn_ns = 0;
   if (dtype == TRJ_BF16) {
-    const AttnPlan p = attn_bf16_plan(B, T, H, H != Hkv, max_seq_slots);
+    const AttnPlan p = attn_bf16_plan(B, T, H, dh, H != Hkv, max_seq_slots);
     w->attn = c.take<float>(attn_bf16_ws_floats(B, T, H, dh, max_seq_slots));
-    w->items = c.take<int32_t>(attn_bf16_item_words(B, T, H, max_seq_slots));
+    w->items = c.take<int32_t>(attn_bf16_item_words(B, T, H, dh, max_seq_slots));
     w->attn_rows = 32 * p.ntw;
     w->attn_qg = p.qg_max;
     w->attn_bpwg = p.bpwg;
@@ -576,6 +576,19 @@ int32_t trj_dev_gemm_plan(int32_t T, int32_t n_in, int32_t n_out, int32_t fused,
   TuneScope tune_scope;
   const int tp = padded_rows(T);
   gemm_bf16_describe_plan(tp, n_in, n_out, fused ? 1 : gemm_bf16_split_k(n_out, tp, n_in), h_plan);
+  return TRJ_OK;
+}
+
+int32_t trj_dev_attn_plan(int32_t B, int32_t T, int32_t n_heads, int32_t head_dim, int32_t shared_kv,
+                          int32_t max_seq_slots, int32_t* h_plan) {
+  if (!h_plan) return TRJ_ERR_NULLPTR;
+  if (B < 1 || T < B || (long)T > (long)B * TRJ_N_MAX || n_heads < 1 || (head_dim != 64 && head_dim != 128) ||
+      max_seq_slots < 1)
+    return TRJ_ERR_BAD_SHAPE;
+  TuneScope tune_scope;
+  const AttnPlan p = attn_bf16_plan(B, T, n_heads, head_dim, shared_kv != 0, max_seq_slots);
+  const int32_t v[6] = {p.ntw, p.qg_max, p.bpwg, p.nsplit_max, p.ring, p.lag > 0.f};
+  memcpy(h_plan, v, sizeof(v));
   return TRJ_OK;
 }
 

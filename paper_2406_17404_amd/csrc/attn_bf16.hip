@@ -14,13 +14,17 @@
 //
 // What bounds it: on long sequences the rate at which K/V arrive, i.e. how much is in flight
 // and that no byte is asked for twice; on short ones (up to about 1000 slots) some 9 us of
-// launch, first loads, merge and stores.  A key stream's wavefronts share a ring of D blocks in
-// LDS that the loads fill without passing through registers; each wavefront fetches its part
-// of every half block, K of block i+D as soon as K of block i has been read by all of them.
-// (Register prefetch, the form before, held one block per wavefront, and the two tiles of a
-// stream each loaded it: 64 rows on 8192 slots of 32 heads with cold caches 57 -> 31 us, 128
-// rows, where two such workgroups read it, 60 -> 39; 16 packed sequences 118 -> 106; 16 rows
-// on 512 slots 8.6 -> 7.9.)  Loads of blocks that no other workgroup reads carry the
+// launch, first loads, merge and stores.  Two forms of the walk, chosen by the launch plan
+// (figures at attn_bf16_plan):
+//  - registers: every wavefront loads its blocks by itself, the next K while this block's
+//    softmax and P*V run and the next V behind them.  No wavefront waits for another before the
+//    merge; the tiles of a stream find each other's blocks in the caches.
+//  - rings: a key stream's wavefronts share a ring of D blocks in LDS that the loads fill without
+//    passing through registers; each fetches its part of every half block, K of block i+D as
+//    soon as K of block i has been read by all of them.  More is in flight and each byte is
+//    asked for once, which pays for the two meetings per block and the second way through LDS
+//    where K/V stream from HBM.
+// Loads of blocks that no other workgroup (rings) or wavefront (registers) reads carry the
 // streaming hint.
 // The wavefronts of a workgroup merge their (m, l, O) through LDS in a fixed order.  If
 // the workgroup covers the whole sequence it writes the normalised rows; otherwise it
@@ -177,21 +181,24 @@ __device__ __forceinline__ void attn_wait() {
   else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
-// NTW query tiles x KS key streams of wavefronts; a stream's ring holds D blocks.  ALIGNED: all
-// operands start at multiples of 16 bytes (else they are copied through registers).
+// NTW query tiles x KS key streams of wavefronts.  RING: a stream's blocks come through a ring of
+// D blocks in LDS; all operands start at multiples of 16 bytes.  Otherwise every wavefront loads
+// its blocks into registers by itself, the next K while this block's softmax and P*V run and the
+// next V behind them, and never meets the others before the merge; operands may start anywhere.
 // SELF: one sequence and no prologue launch: every workgroup checks the sequence and works the
-// ancestor bits out for itself (parents in LDS behind the queries, pointer doubling on the
-// lanes of each wavefront, under 1 us), which saves a launch of 4.4 us.
-template <int DH, int NTW, int KS, int D, bool ALIGNED, bool SELF>
+// ancestor bits out for itself (pointer doubling on the lanes of each wavefront), which saves a
+// launch of 5 to 6 us for 0.4 to 2 us more in this one (5 rows on 1024 slots 11.6 against 10.8
+// us, 64 rows 17.2 against 15.6).
+template <int DH, int NTW, int KS, int D, bool RING, bool SELF>
 __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArgs a) {
-  constexpr int KSTEPS = DH / 16, MTV = DH / 32, RING = 2 * D;
+  constexpr int KSTEPS = DH / 16, MTV = DH / 32, SLOTS = 2 * D;
   constexpr int OW = MTV * 16 * 64;     // floats of one wavefront's O tile
   constexpr int HALF = KSTEPS;          // 1-KiB pieces of a block's K, and of its V
   constexpr int HP = HALF / NTW;        // of these, requested by one wavefront
   constexpr int SLOT = HALF * 1024;     // bytes of a ring slot
   constexpr bool MEET = NTW > 1;
   static_assert(D == 2 || D == 3, "the tail below");
-  extern __shared__ __align__(16) uint8_t smem[];  // rings: KS x RING slots; then the parts handed over
+  extern __shared__ __align__(16) uint8_t smem[];  // rings: KS x SLOTS slots; then the parts handed over
   __shared__ float sm_m[KS * NTW][32], sm_l[KS * NTW][32];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -250,59 +257,13 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   // loads carry the streaming hint; with a second reader through L2 it costs a second trip to HBM
   const bool stream = a.group == 1 && !several;
 
-  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem;
-  const uint32_t ring = __builtin_amdgcn_readfirstlane(lds0 + ks * RING * SLOT);
-  uint8_t* ring_w = smem + (size_t)ks * RING * SLOT + lane * 16;
-  const u32x4* ring_r = reinterpret_cast<const u32x4*>(ring_w);
   const size_t plane = (size_t)(head / a.group) * a.s_pool * DH;  // the group's K/V head
   // this stream's blocks: b0 + ks, b0 + ks + KS, ..
-  const int nblk = b0 + ks < b1 ? (b1 - b0 - ks + KS - 1) / KS : 0, rounds = (b1 - b0 + KS - 1) / KS;
-  const size_t first = (size_t)(blk_base + b0 + ks) * SLOT + nt * HP * 1024;
-  const uint8_t* kp = reinterpret_cast<const uint8_t*>(a.k_layer + plane) + first;
-  const uint8_t* vp = reinterpret_cast<const uint8_t*>(a.v_layer + plane) + first;
-  auto request = [&](const uint8_t*& p, int sl) {  // this wavefront's pieces of the next K (or V) into slot sl
-    const uint32_t dst = ring + sl * SLOT + nt * HP * 1024;
-#pragma unroll
-    for (int k = 0; k < HP; ++k) {
-      if constexpr (!ALIGNED) copy_to_lds(p + k * 1024, lane * 16, ring_w + sl * SLOT + (nt * HP + k) * 1024);
-      else if (stream) load_to_lds<true>(p + k * 1024, lane * 16, dst + k * 1024);
-      else load_to_lds<false>(p + k * 1024, lane * 16, dst + k * 1024);
-    }
-    p += (size_t)KS * SLOT;
-  };
-
-  // The queries (as operands of the first product) and their ancestor bits come through LDS
-  // too: registers that the compiler had loaded itself it would wait for together with the
-  // whole ring.  The streams share them, each fetching its part of every tile.  Rows past the
-  // tree's end read the last row instead (never stored, always finite) and see no tree node.
+  const int nblk = b0 + ks < b1 ? (b1 - b0 - ks + KS - 1) / KS : 0;
+  // rows past the tree's end read the last row instead (never stored, always finite) and see no
+  // tree node; a wavefront without any row computes nothing
   const int qi = (qg * NTW + nt) * 32 + n32, qc = min(qi, n - 1);
-  constexpr int QAT = KS * RING * SLOT, ANC_AT = QAT + NTW * SLOT, QP = KSTEPS / KS;
-  {
-    auto fetch = [&](const void* base, uint32_t voff, int at) {
-      if constexpr (ALIGNED) load_to_lds<false>(base, voff, __builtin_amdgcn_readfirstlane(lds0 + at));
-      else copy_to_lds(base, voff, smem + at + lane * 16);
-    };
-    const uint16_t* qh = a.q + ((size_t)r0 * a.n_heads + head) * DH;
-#pragma unroll
-    for (int j = 0; j < QP; ++j) {
-      const int k = ks * QP + j;
-      fetch(qh, (uint32_t)(qc * a.n_heads * DH + hh * 8 + 16 * k) * 2, QAT + nt * SLOT + k * 1024);
-    }
-    if constexpr (SELF) {
-      if (wv == 0) {
-        load_words_to_lds(a.parent + r0, min(lane, n - 1) * 4, __builtin_amdgcn_readfirstlane(lds0 + ANC_AT));
-        load_words_to_lds(a.parent + r0, min(lane + 64, n - 1) * 4, __builtin_amdgcn_readfirstlane(lds0 + ANC_AT + 256));
-      }
-    } else if (ks == 0) {
-      fetch(a.anc + 2 * (size_t)r0, (uint32_t)qc * 16, ANC_AT + nt * 1024);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < D; ++i)
-    if (i < nblk) {
-      request(kp, 2 * i);
-      request(vp, 2 * i + 1);
-    }
+  const bool live = (qg * NTW + nt) * 32 < n;
 
   f32x16 o[MTV];
 #pragma unroll
@@ -310,100 +271,25 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[mt][v] = 0.f;
   float top = NEG_BIG, m = NEG_BIG, l = 0.f;
-  u32x4 kreg[KSTEPS], vreg[2 * MTV];
-  auto read = [&](u32x4 (&r)[KSTEPS], int sl) {
-#pragma unroll
-    for (int k = 0; k < KSTEPS; ++k) r[k] = ring_r[(sl * HALF + k) * 64];
-  };
-  // queries, bits and K of the first block: behind it its V and the blocks already requested
-  if (nblk >= D) attn_wait<(2 * D - 1) * HP, true>();
-  else if (D > 2 && nblk == 2) attn_wait<3 * HP, true>();
-  else if (nblk == 1) attn_wait<HP, true>();
-  else attn_wait<0, true>();
   bf16x8 qreg[KSTEPS];
-#pragma unroll
-  for (int k = 0; k < KSTEPS; ++k)
-    qreg[k] = __builtin_bit_cast(bf16x8, reinterpret_cast<const u32x4*>(smem + QAT + nt * SLOT)[k * 64 + lane]);
+  u32x4 kreg[KSTEPS], vreg[2 * MTV];  // 1-KiB pieces of a block; V piece mt * 2 + kg
   uint64_t anc0, anc1;
-  if constexpr (SELF) {
-    const int32_t* par = reinterpret_cast<const int32_t*>(smem + ANC_AT);
-    int jump[2], b[4][2];  // nearest ancestor whose bit is not in the row yet (255: none); the row's words
-    bool bad = false;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int i = lane + 64 * h, p = i < n ? par[i] : -1;
-      bad = bad || (i < n && (i == 0 ? p != -1 : (p < 0 || p >= i)));
-      jump[h] = p < 0 ? 255 : p & 127;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) b[w][h] = i >> 5 == w ? (int)(1u << (i & 31)) : 0;
-    }
-    if (__ballot(bad)) {  // the same in every wavefront; nothing may arrive after the end
-      attn_wait<0, true>();
-      if (sp == 0) zero_rows(r0 + qg * 32 * NTW, min(r0 + n, r0 + (qg + 1) * 32 * NTW));
-      if (sp == 0 && qg == 0 && head == 0 && tid == 0) a.status[0] = 1;
-      return;
-    }
-    if (sp == 0 && qg == 0 && head == 0 && tid == 0) a.status[0] = 0;
-    while (__ballot(jump[0] != 255 || jump[1] != 255)) {
-      int u[5][2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        u[4][h] = from_node(jump, jump[h] & 127);
-#pragma unroll
-        for (int w = 0; w < 4; ++w) u[w][h] = from_node(b[w], jump[h] & 127);
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (jump[h] == 255) continue;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) b[w][h] |= u[w][h];
-        jump[h] = u[4][h];
-      }
-    }
-    uint32_t r[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) r[w] = qi < n ? (uint32_t)from_node(b[w], qc) : 0u;
-    anc0 = (uint64_t)r[1] << 32 | r[0];
-    anc1 = (uint64_t)r[3] << 32 | r[2];
-  } else {
-    const u32x4 bits = reinterpret_cast<const u32x4*>(smem + ANC_AT + nt * 1024)[lane];
-    anc0 = qi < n ? (uint64_t)bits[1] << 32 | bits[0] : 0;
-    anc1 = qi < n ? (uint64_t)bits[3] << 32 | bits[2] : 0;
-  }
-  // Block i of this stream: its K is in kreg; its V and the next blocks are on the way (slots
-  // 2(i%D)+1, ..).  AHEAD: blocks behind it, D when there are at least as many; then block i+D
-  // is requested into the slots that get free.  V is read under S^T and softmax, the next K
-  // under P*V; at every wait 2(D-1) half blocks of the stream stay in flight.  A wavefront
-  // without a row only requests and meets.
-  const bool live = (qg * NTW + nt) * 32 < n;
-  int cur = 0;  // slot of this block's K
-  auto block = [&](int i, auto ahead_c) {
-    constexpr int AHEAD = decltype(ahead_c)::value;
-    const int key0 = (b0 + ks + i * KS) * 32, next = cur + 2 == RING ? 0 : cur + 2;
+  auto scores = [&]() {
     f32x16 sacc;
-    if (live) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
+    for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
 #pragma unroll
-      for (int k = 0; k < KSTEPS; ++k)
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[k]), qreg[k], sacc, 0, 0, 0);
-    }
-    attn_wait<(AHEAD < D ? 2 * AHEAD : 2 * (D - 1)) * HP, MEET>();
-    if constexpr (AHEAD == D) request(kp, cur);
-    float alpha;
-    u32x4 pk[2];
-    if (live) {
-      read(vreg, cur + 1);
-      if (key0 + 32 > L)  // uniform
-        softmax_tile_tree(sacc, key0, hh, L, anc0, anc1, a.scale_log2e, a.lag, top, m, l, alpha, pk);
-      else
-        softmax_tile_prefix(sacc, a.scale_log2e, a.lag, top, m, l, alpha, pk);
-    }
-    attn_wait<(AHEAD == 0 ? 0 : (AHEAD < D ? 2 * AHEAD - 1 : 2 * (D - 1))) * HP, MEET>();
-    if constexpr (AHEAD == D) request(vp, cur + 1);
-    cur = next;
-    if (!live) return;
-    if constexpr (AHEAD > 0) read(kreg, next);
+    for (int k = 0; k < KSTEPS; ++k)
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[k]), qreg[k], sacc, 0, 0, 0);
+    return sacc;
+  };
+  auto softmax = [&](const f32x16& sacc, int key0, float& alpha, u32x4 (&pk)[2]) {
+    if (key0 + 32 > L)  // uniform
+      softmax_tile_tree(sacc, key0, hh, L, anc0, anc1, a.scale_log2e, a.lag, top, m, l, alpha, pk);
+    else
+      softmax_tile_prefix(sacc, a.scale_log2e, a.lag, top, m, l, alpha, pk);
+  };
+  auto add_values = [&](int key0, float alpha, const u32x4 (&pk)[2]) {
     if (key0 + 32 > total) {
       // slots past the sequence's last row may hold anything (NaN bit patterns too):
       // clear them in the V operand, their probabilities are exactly zero
@@ -427,19 +313,211 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
         o[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vreg[mt * 2 + kg]),
                                                         __builtin_bit_cast(bf16x8, pk[kg]), o[mt], 0, 0, 0);
   };
-  if (nblk > 0) {
-    read(kreg, 0);
-    int i = 0;
-    for (; i + D < nblk; ++i) block(i, std::integral_constant<int, D>{});
-    if constexpr (D > 2) {
-      if (nblk - 1 - i >= 2) block(i++, std::integral_constant<int, 2>{});
+  // SELF: the ancestor bits from the parents, par[h] = parent of node lane + 64 h (anything
+  // from node n on); false if the tree is malformed (the same in every wavefront)
+  auto own_bits = [&](const int (&par)[2]) -> bool {
+    int jump[2], b[4][2];  // nearest ancestor whose bit is not in the row yet (255: none); the row's words
+    bool bad = false;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = lane + 64 * h, p = i < n ? par[h] : -1;
+      bad = bad || (i < n && (i == 0 ? p != -1 : (p < 0 || p >= i)));
+      jump[h] = p < 0 ? 255 : p & 127;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) b[w][h] = i >> 5 == w ? (int)(1u << (i & 31)) : 0;
     }
-    if (nblk - 1 - i >= 1) block(i++, std::integral_constant<int, 1>{});
-    block(i, std::integral_constant<int, 0>{});
-  }
-  if (MEET && nblk < rounds) {  // a stream with a block less than the others meets them as often
-    attn_wait<0, MEET>();
-    attn_wait<0, MEET>();
+    if (__ballot(bad)) return false;
+    while (__ballot(jump[0] != 255 || jump[1] != 255)) {
+      int u[5][2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        u[4][h] = from_node(jump, jump[h] & 127);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) u[w][h] = from_node(b[w], jump[h] & 127);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (jump[h] == 255) continue;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) b[w][h] |= u[w][h];
+        jump[h] = u[4][h];
+      }
+    }
+    uint32_t r[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) r[w] = qi < n ? (uint32_t)from_node(b[w], qc) : 0u;
+    anc0 = (uint64_t)r[1] << 32 | r[0];
+    anc1 = (uint64_t)r[3] << 32 | r[2];
+    return true;
+  };
+  auto self_status = [&](bool ok) {  // the verdict on the tree, and zeros for its rows if it is malformed
+    if (sp != 0) return;
+    if (!ok) zero_rows(r0 + qg * 32 * NTW, min(r0 + n, r0 + (qg + 1) * 32 * NTW));
+    if (qg == 0 && head == 0 && tid == 0) a.status[0] = !ok;
+  };
+
+  if constexpr (RING) {
+    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem;
+    const uint32_t ring = __builtin_amdgcn_readfirstlane(lds0 + ks * SLOTS * SLOT);
+    const u32x4* ring_r = reinterpret_cast<const u32x4*>(smem + (size_t)ks * SLOTS * SLOT + lane * 16);
+    const int rounds = (b1 - b0 + KS - 1) / KS;
+    const size_t first = (size_t)(blk_base + b0 + ks) * SLOT + nt * HP * 1024;
+    const uint8_t* kp = reinterpret_cast<const uint8_t*>(a.k_layer + plane) + first;
+    const uint8_t* vp = reinterpret_cast<const uint8_t*>(a.v_layer + plane) + first;
+    auto request = [&](const uint8_t*& p, int sl) {  // this wavefront's pieces of the next K (or V) into slot sl
+      const uint32_t dst = ring + sl * SLOT + nt * HP * 1024;
+#pragma unroll
+      for (int k = 0; k < HP; ++k) {
+        if (stream) load_to_lds<true>(p + k * 1024, lane * 16, dst + k * 1024);
+        else load_to_lds<false>(p + k * 1024, lane * 16, dst + k * 1024);
+      }
+      p += (size_t)KS * SLOT;
+    };
+
+    // The queries (as operands of the first product) and their ancestor bits come through LDS
+    // too: registers that the compiler had loaded itself it would wait for together with the
+    // whole ring.  The streams share them, each fetching its part of every tile.
+    constexpr int QAT = KS * SLOTS * SLOT, ANC_AT = QAT + NTW * SLOT, QP = KSTEPS / KS;
+    {
+      auto fetch = [&](const void* base, uint32_t voff, int at) {
+        load_to_lds<false>(base, voff, __builtin_amdgcn_readfirstlane(lds0 + at));
+      };
+      const uint16_t* qh = a.q + ((size_t)r0 * a.n_heads + head) * DH;
+#pragma unroll
+      for (int j = 0; j < QP; ++j) {
+        const int k = ks * QP + j;
+        fetch(qh, (uint32_t)(qc * a.n_heads * DH + hh * 8 + 16 * k) * 2, QAT + nt * SLOT + k * 1024);
+      }
+      if constexpr (SELF) {
+        if (wv == 0) {
+          load_words_to_lds(a.parent + r0, min(lane, n - 1) * 4, __builtin_amdgcn_readfirstlane(lds0 + ANC_AT));
+          load_words_to_lds(a.parent + r0, min(lane + 64, n - 1) * 4, __builtin_amdgcn_readfirstlane(lds0 + ANC_AT + 256));
+        }
+      } else if (ks == 0) {
+        fetch(a.anc + 2 * (size_t)r0, (uint32_t)qc * 16, ANC_AT + nt * 1024);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+      if (i < nblk) {
+        request(kp, 2 * i);
+        request(vp, 2 * i + 1);
+      }
+
+    auto read = [&](u32x4 (&r)[KSTEPS], int sl) {
+#pragma unroll
+      for (int k = 0; k < KSTEPS; ++k) r[k] = ring_r[(sl * HALF + k) * 64];
+    };
+    // queries, bits and K of the first block: behind it its V and the blocks already requested
+    if (nblk >= D) attn_wait<(2 * D - 1) * HP, true>();
+    else if (D > 2 && nblk == 2) attn_wait<3 * HP, true>();
+    else if (nblk == 1) attn_wait<HP, true>();
+    else attn_wait<0, true>();
+#pragma unroll
+    for (int k = 0; k < KSTEPS; ++k)
+      qreg[k] = __builtin_bit_cast(bf16x8, reinterpret_cast<const u32x4*>(smem + QAT + nt * SLOT)[k * 64 + lane]);
+    if constexpr (SELF) {
+      const int32_t* words = reinterpret_cast<const int32_t*>(smem + ANC_AT);
+      const int par[2] = {words[lane], words[lane + 64]};
+      const bool ok = own_bits(par);
+      if (!ok) attn_wait<0, true>();  // nothing may arrive after the end
+      self_status(ok);
+      if (!ok) return;
+    } else {
+      const u32x4 bits = reinterpret_cast<const u32x4*>(smem + ANC_AT + nt * 1024)[lane];
+      anc0 = qi < n ? (uint64_t)bits[1] << 32 | bits[0] : 0;
+      anc1 = qi < n ? (uint64_t)bits[3] << 32 | bits[2] : 0;
+    }
+    // Block i of this stream: its K is in kreg; its V and the next blocks are on the way (slots
+    // 2(i%D)+1, ..).  AHEAD: blocks behind it, D when there are at least as many; then block i+D
+    // is requested into the slots that get free.  V is read under S^T and softmax, the next K
+    // under P*V; at every wait 2(D-1) half blocks of the stream stay in flight.  A wavefront
+    // without a row only requests and meets.
+    int cur = 0;  // slot of this block's K
+    auto block = [&](int i, auto ahead_c) {
+      constexpr int AHEAD = decltype(ahead_c)::value;
+      const int key0 = (b0 + ks + i * KS) * 32, next = cur + 2 == SLOTS ? 0 : cur + 2;
+      f32x16 sacc;
+      if (live) sacc = scores();
+      attn_wait<(AHEAD < D ? 2 * AHEAD : 2 * (D - 1)) * HP, MEET>();
+      if constexpr (AHEAD == D) request(kp, cur);
+      float alpha;
+      u32x4 pk[2];
+      if (live) {
+        read(vreg, cur + 1);
+        softmax(sacc, key0, alpha, pk);
+      }
+      attn_wait<(AHEAD == 0 ? 0 : (AHEAD < D ? 2 * AHEAD - 1 : 2 * (D - 1))) * HP, MEET>();
+      if constexpr (AHEAD == D) request(vp, cur + 1);
+      cur = next;
+      if (!live) return;
+      if constexpr (AHEAD > 0) read(kreg, next);
+      add_values(key0, alpha, pk);
+    };
+    if (nblk > 0) {
+      read(kreg, 0);
+      int i = 0;
+      for (; i + D < nblk; ++i) block(i, std::integral_constant<int, D>{});
+      if constexpr (D > 2) {
+        if (nblk - 1 - i >= 2) block(i++, std::integral_constant<int, 2>{});
+      }
+      if (nblk - 1 - i >= 1) block(i++, std::integral_constant<int, 1>{});
+      block(i, std::integral_constant<int, 0>{});
+    }
+    if (MEET && nblk < rounds) {  // a stream with a block less than the others meets them as often
+      attn_wait<0, MEET>();
+      attn_wait<0, MEET>();
+    }
+  } else {
+    const u32x4* kb = reinterpret_cast<const u32x4*>(a.k_layer + plane) + (size_t)(blk_base + b0 + ks) * KSTEPS * 64 + lane;
+    const u32x4* vb = reinterpret_cast<const u32x4*>(a.v_layer + plane) + (size_t)(blk_base + b0 + ks) * KSTEPS * 64 + lane;
+    auto load = [&](u32x4 (&r)[KSTEPS], const u32x4*& p) {
+#pragma unroll
+      for (int k = 0; k < KSTEPS; ++k) {
+        // the wavefronts of a stream load the same blocks: with the hint each from HBM again
+        if (NTW == 1 && stream) r[k] = __builtin_nontemporal_load(p + k * 64);
+        else r[k] = p[k * 64];
+      }
+      p += (size_t)KS * KSTEPS * 64;
+    };
+    const uint16_t* qp = a.q + ((size_t)(r0 + qc) * a.n_heads + head) * DH + hh * 8;
+#pragma unroll
+    for (int k = 0; k < KSTEPS; ++k) qreg[k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * k));
+    int par[2];
+    if constexpr (SELF) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) par[h] = a.parent[r0 + min(lane + 64 * h, n - 1)];
+    } else {
+      anc0 = a.anc[2 * (size_t)(r0 + qc)];
+      anc1 = a.anc[2 * (size_t)(r0 + qc) + 1];
+    }
+    const int mine = live ? nblk : 0;
+    if (mine > 0) {
+      load(kreg, kb);
+      load(vreg, vb);
+    }
+    if constexpr (SELF) {
+      const bool ok = own_bits(par);
+      self_status(ok);
+      if (!ok) return;
+    } else if (qi >= n) {
+      anc0 = anc1 = 0;
+    }
+    // the last block has a copy of the code to itself: behind a condition the compiler would wait
+    // for all loads wherever it waits for some
+    auto block = [&](int i, auto more_c) {
+      constexpr bool MORE = decltype(more_c)::value;
+      const int key0 = (b0 + ks + i * KS) * 32;
+      const f32x16 sacc = scores();
+      if constexpr (MORE) load(kreg, kb);  // in flight during the softmax and P*V
+      float alpha;
+      u32x4 pk[2];
+      softmax(sacc, key0, alpha, pk);
+      add_values(key0, alpha, pk);
+      if constexpr (MORE) load(vreg, vb);  // in flight during the next S^T and softmax
+    };
+    for (int i = 0; i + 1 < mine; ++i) block(i, std::true_type{});
+    if (mine > 0) block(mine - 1, std::false_type{});
   }
 
   // ---- merge the KS key streams of every query tile (fixed order, deterministic)
@@ -574,26 +652,53 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
   }
 }
 
-// Launch shape: query tiles per workgroup, query groups, blocks per workgroup, splits.
-AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_slots) {
+// Launch shape: form of the walk, query tiles per workgroup, query groups, blocks per workgroup,
+// splits.  Figures: us of the attention kernel with its merge in a step of 12 layers, where K/V
+// come from HBM, 32 heads of 128; R register form, 2r / 4r ring with two / four tiles.
+AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int max_seq_slots) {
   AttnPlan p;
   const int nmax = T < TRJ_N_MAX ? T : TRJ_N_MAX;
   int nb = (max_seq_slots + 31) / 32;
   if (nb < 1) nb = 1;
-  // Query tiles per workgroup: one or two with four key streams, and four with two streams for
-  // trees of more than 64 rows (on average) on long sequences, whose K/V is then read once; as
-  // two groups of two tiles both groups wait for HBM (32 heads, 128 rows on 4096 slots 39.5
-  // against 29.7 us, on 1536 24.4 against 21.0, on 1024 the shorter walks win: 18.9 against
-  // 20.4).  Query heads that share K/V find it in L2 either way (27.8 against 29.2 on 4096).
+  // The ring pays where so many blocks stream from HBM that it matters how much is in flight
+  // and that none is asked for twice: from 1536 (block, head) pairs of 16 KiB per query tile,
+  // as blocks with more queries are worked on for longer.  Query heads that share K/V find it
+  // in L2, and halves of it (heads of 64) arrive in time anyway.
+  //   rows x slots        5x1024 5x2048 5x4096 33x2048 33x4096 97x1024 97x2048 97x4096
+  //   pairs / 1536 tiles    0.7   1.4    2.7     0.7     1.4     0.2     0.3     0.7
+  //   ring (2 tiles)       12.7   15.5   20.3    18.0    22.6    20.2    24.6    31.0
+  //   R                    12.3   15.3   20.6    17.5    23.3    18.2    22.3    30.1
+  // 16 packed sequences of 64 rows, up to 2048 slots: ring 69.6, R 85.7; four query heads per
+  // K/V head, 97 rows on 4096 slots: ring 30.8, R 28.2, 16 sequences of 16 rows 72.1, 63.1.
+  // Heads of 64 with one tile are the exception: two short blocks in flight from the start save
+  // 1 us of a call at every length (16 heads, 512 slots: 11.4, 12.6).
+  const int tiles = T > 64 * B ? 4 : T > 32 * B ? 2 : 1;  // on average: the sizes are device data
+  const long pairs = (long)nb * B * n_heads, xchg = tune().attn_xchg_min_blocks;
+  const long least = xchg > 1 ? 32 * xchg * tiles : 0;    // 48 blocks of 32 heads per tile
+  p.ring = !shared_kv && (dh == 128 ? pairs >= least : nmax <= 32);
+  // Query tiles per workgroup: one or two with four key streams; and four with two streams, so
+  // that a tree of more than 64 rows needs no second pass over the sequence, where this fills
+  // the chip evenly: one sequence's splits do, several sequences' ragged ones only down to two
+  // (and with every tile full the two streams take longer than two workgroups), unsplit ones
+  // from one and a half rounds on.  4r against 2r: 69 rows on 4096 slots 26.8, 28.7; four
+  // sequences of 69 rows 40.7, 46.5, of 128 66.1, 61.8; two of 97 35.1, 33.4; three (three
+  // quarters of the chip) of 128 44.3, 37.5; eight of 128 62.2, 57.3; twelve of 128 115, 135.
+  p.ntw = nmax <= 32 ? 1 : 2;
+  const long target = tune().attn_target_wgs;
+  if (p.ring && tiles == 4) {
+    const long cols = (long)B * n_heads, split = cols < target ? target / cols : 1;
+    const bool even = split == 1 ? 2 * cols >= 3 * target
+                                 : 8 * cols * split >= 7 * target && (B == 1 || (split == 2 && T <= 112 * B));
+    if (even) p.ntw = 4;
+  }
   // A sequence with more rows than a workgroup takes has several groups.
-  p.ntw = nmax <= 32 ? 1 : (!shared_kv && T > 64 * B && nb >= 44 ? 4 : 2);
   p.qg_max = (nmax + 32 * p.ntw - 1) / (32 * p.ntw);
   // the host does not know the trees' sizes (they are device data): the number of work
   // items lies between max(B, T / rows per item) and B * qg_max; the lower figure sizes
   // the split (too few workgroups cost more than too many), the upper one the launch
   const int rows = 32 * p.ntw;
   const int items_est = B > (T + rows - 1) / rows ? B : (T + rows - 1) / rows;
-  const long cols = (long)items_est * n_heads, target = tune().attn_target_wgs;
+  const long cols = (long)items_est * n_heads;
   int b;
   if (p.ntw == 4) {  // whole rounds of workgroups at most: a split is four tiles' partials
     const long split = cols < target ? target / cols : 1;
@@ -625,16 +730,16 @@ AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_s
 size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots) {
   size_t most = 64;  // no partials needed when every sequence fits one workgroup
   for (bool shared : {false, true}) {
-    const AttnPlan p = attn_bf16_plan(B, T, n_heads, shared, max_seq_slots);
+    const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, shared, max_seq_slots);
     const size_t n = p.nsplit_max > 1 ? (size_t)B * p.qg_max * p.ntw * n_heads * p.nsplit_max * (dh / 32 * 1024 + 64) : 0;
     most = n > most ? n : most;
   }
   return most;
 }
-size_t attn_bf16_item_words(int B, int T, int n_heads, int max_seq_slots) {
+size_t attn_bf16_item_words(int B, int T, int n_heads, int dh, int max_seq_slots) {
   size_t most = 0;
   for (bool shared : {false, true}) {
-    const AttnPlan p = attn_bf16_plan(B, T, n_heads, shared, max_seq_slots);
+    const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, shared, max_seq_slots);
     const size_t n = (size_t)B * p.qg_max * p.nsplit_max * 8 + 8;
     most = n > most ? n : most;
   }
@@ -649,7 +754,7 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
                           float scale, float* ws, int tiled, int tp, uint16_t* out, const int32_t* parent,
                           int32_t* status, hipStream_t st) {
   if (dh != 64 && dh != 128) return TRJ_ERR_BAD_SHAPE;
-  const AttnPlan p = attn_bf16_plan(B, T, n_heads, n_heads != n_kv_heads, max_seq_slots);
+  const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, n_heads != n_kv_heads, max_seq_slots);
   const int ntw = p.ntw, qg_max = p.qg_max, bpwg = p.bpwg, nsplit_max = p.nsplit_max;
   const int tiles_per_seq = qg_max * ntw;
   size_t parts = nsplit_max > 1 ? (size_t)B * tiles_per_seq * n_heads * nsplit_max : 0;
@@ -665,13 +770,14 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
   dim3 grid((B * qg_max * n_kv_heads * nsplit_max + 7) / 8 * 8 * group);
   {
     ProfScope ps_(KC_ATTN, st);
-    const bool aligned = (((uintptr_t)q | (uintptr_t)k_layer | (uintptr_t)v_layer | (uintptr_t)anc) & 15) == 0;
-#define TRJ_ATTN_A(DH, Q, KS, D, AL, SELF)                                                      \
+    // loads without registers need operands on multiples of 16 bytes
+    const bool ring = p.ring && (((uintptr_t)q | (uintptr_t)k_layer | (uintptr_t)v_layer | (uintptr_t)anc) & 15) == 0;
+#define TRJ_ATTN_A(DH, Q, KS, D, RING, SELF)                                                      \
   do {                                                                                          \
     constexpr size_t rings = (size_t)(KS * 2 * D + Q) * DH * 64 + Q * 1024;                     \
     constexpr size_t handed = (size_t)Q * DH * (KS - 1) * 128;                                  \
-    constexpr size_t lds = rings > handed ? rings : handed;                                     \
-    auto kern = tree_attn_bf16_kernel<DH, Q, KS, D, AL, SELF>;                                  \
+    constexpr size_t lds = RING && rings > handed ? rings : handed;                                     \
+    auto kern = tree_attn_bf16_kernel<DH, Q, KS, D, RING, SELF>;                                  \
     static bool big_lds_allowed = false; /* one-time, per instantiation */                      \
     if (!big_lds_allowed) {                                                                     \
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                            \
@@ -680,17 +786,22 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
     }                                                                                           \
     kern<<<grid, KS * Q * 64, lds, st>>>(a);                                                    \
   } while (0)
-#define TRJ_ATTN(DH, Q, KS, D)                                                                  \
+#define TRJ_ATTN(DH, Q, KS, D, RING)                                                            \
   do {                                                                                          \
-    if (aligned && !parent) TRJ_ATTN_A(DH, Q, KS, D, true, false);                              \
-    else if (aligned) TRJ_ATTN_A(DH, Q, KS, D, true, true);                                     \
-    else if (!parent) TRJ_ATTN_A(DH, Q, KS, D, false, false);                                   \
-    else TRJ_ATTN_A(DH, Q, KS, D, false, true);                                                 \
+    if (parent) TRJ_ATTN_A(DH, Q, KS, D, RING, true);                                           \
+    else TRJ_ATTN_A(DH, Q, KS, D, RING, false);                                                 \
   } while (0)
     if (dh == 128) {
-      if (ntw == 1) TRJ_ATTN(128, 1, 4, 2); else if (ntw == 2) TRJ_ATTN(128, 2, 4, 2); else TRJ_ATTN(128, 4, 2, 3);
+      if (ring && ntw == 1) TRJ_ATTN(128, 1, 4, 2, true);
+      else if (ring && ntw == 2) TRJ_ATTN(128, 2, 4, 2, true);
+      else if (ring) TRJ_ATTN(128, 4, 2, 3, true);
+      else if (ntw == 1) TRJ_ATTN(128, 1, 4, 2, false);
+      else if (ntw == 2) TRJ_ATTN(128, 2, 4, 2, false);
+      else TRJ_ATTN(128, 4, 2, 3, false);  // planned for the ring, operands off the grid
     } else {
-      if (ntw == 1) TRJ_ATTN(64, 1, 4, 2); else if (ntw == 2) TRJ_ATTN(64, 2, 4, 2); else TRJ_ATTN(64, 4, 2, 3);
+      if (ring) TRJ_ATTN(64, 1, 4, 2, true);
+      else if (ntw == 1) TRJ_ATTN(64, 1, 4, 2, false);
+      else TRJ_ATTN(64, 2, 4, 2, false);
     }
 #undef TRJ_ATTN
 #undef TRJ_ATTN_A

@@ -12,7 +12,7 @@ struct Tunables {
   int gemm_big_t = 256;        // padded token rows from which wavefronts own two row tiles (0: never)
   int attn_target_wgs = 256;   // attention workgroups per launch aimed at (one per CU)
   int gemm_big_wt = 0;         // row tiles per wavefront of the many-rows kernel (2, 4; 0 = choose)
-  int attn_xchg_min_blocks = 48;  // no effect any more: the wavefronts of a key stream always share their loads
+  int attn_xchg_min_blocks = 48;  // blocks of 32 heads per query tile from which K/V go through rings (1: always)
   int attn_min_bpw = 0;        // 32-slot blocks per key stream, at least (0: chosen from the tree size)
 };
 // trj_set_tunable writes the process-wide set; every entry point copies it once on entry
@@ -200,11 +200,12 @@ int launch_tile_activation(const uint16_t* x, int T, int n, int tp, uint16_t* xp
 struct AttnPlan {
   int ntw, qg_max;       // query tiles of 32 rows per workgroup, groups of them per sequence at most
   int bpwg, nsplit_max;  // 32-slot blocks per workgroup, key splits per sequence at most
+  bool ring;             // K/V through rings in LDS, else registers
   float lag;             // how far the softmax reference may fall behind the running maximum (log2)
 };
-AttnPlan attn_bf16_plan(int B, int T, int n_heads, bool shared_kv, int max_seq_slots);
+AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int max_seq_slots);
 size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots);
-size_t attn_bf16_item_words(int B, int T, int n_heads, int max_seq_slots);
+size_t attn_bf16_item_words(int B, int T, int n_heads, int dh, int max_seq_slots);
 // parent (one sequence, plain `out`): no prologue launch came before, the kernel checks the
 // sequence itself, writes its status and the rows it does not own; anc and items are not read
 int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint16_t* v_layer,

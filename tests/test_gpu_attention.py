@@ -231,8 +231,8 @@ def test_packed_batch_with_splits_ties_and_both_query_groups():
 
 @pytest.fixture
 def pair_exchange():
-    """Launch shape in which the two wavefronts of a key stream split the loads of every
-    K/V block and hand halves to each other (normally chosen only for long prefixes)."""
+    """Launch plan in which the two wavefronts of a key stream share the loads of every K/V
+    block through a ring in LDS (heads of 128; normally chosen only for long prefixes)."""
     b.trj_set_tunable("attn_xchg_min_blocks", 1)
     yield
     b.trj_set_tunable("attn_xchg_min_blocks", 48)

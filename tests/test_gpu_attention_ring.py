@@ -1,7 +1,8 @@
-"""The bf16 attention's ring of K/V blocks at its edges: key streams with no, one and a few
-blocks (fewer and more than the ring holds), four query tiles per workgroup with idle and
-ragged ones, batches that mix tree sizes, and operands that do not start at a multiple of 16
-bytes (which the loads straight to LDS cannot take), for the projections too."""
+"""The bf16 attention's two forms, K/V through rings in LDS and through registers, at their
+edges: key streams with no, one and a few blocks (fewer and more than the ring holds), four
+query tiles per workgroup with idle and ragged ones, batches that mix tree sizes, and operands
+that do not start at a multiple of 16 bytes (which the loads straight to LDS cannot take), for
+the projections too."""
 import math
 
 import numpy as np
@@ -16,30 +17,49 @@ from paper_2406_17404_amd import inputs as I
 from test_gpu_attention import TOL, case, run_attention
 
 pytestmark = pytest.mark.gpu
+KNOBS = {"attn_target_wgs": 256, "attn_min_bpw": 0, "attn_xchg_min_blocks": 48}
+
+
+@pytest.fixture
+def knobs():
+    """Sets launch-plan knobs; the form: attn_xchg_min_blocks 1 always rings, 1 << 20 never."""
+    def put(**values):
+        for name, value in values.items():
+            b.trj_set_tunable(name, value)
+    yield put
+    put(**KNOBS)
+
 
 
 @pytest.mark.parametrize("H,dh,L,n", [
-    (2, 128, 1400, 65), (1, 64, 1407, 128), (2, 128, 1536, 97), (1, 128, 2047, 69),   # four tiles
-    (2, 128, 1000, 33), (1, 64, 700, 64), (2, 128, 600, 17)])                         # two, one
-def test_streams_with_few_and_many_blocks(H, dh, L, n):
+    (2, 128, 1400, 65), (1, 64, 1407, 128), (2, 128, 1536, 97), (1, 128, 2047, 69),   # four tiles (heads of 128)
+    (2, 128, 1000, 33), (1, 64, 700, 64), (2, 128, 600, 17), (3, 64, 650, 20)])       # two, one
+def test_streams_with_few_and_many_blocks(knobs, H, dh, L, n):
     c = case(3 * L + n, H, dh, L, n, "bf16")
     want = O.tree_attention(*c)
-    try:
-        for wgs, blocks in ((1, 0), (8, 1), (24, 1), (64, 1), (4096, 1), (4096, 3)):
-            b.trj_set_tunable("attn_target_wgs", wgs)
-            b.trj_set_tunable("attn_min_bpw", blocks)
-            got = run_attention("bf16", H, dh, [c])[0]
-            assert np.isfinite(got).all(), (wgs, blocks)
-            assert rel_err(got, want) <= TOL["bf16"], (wgs, blocks)
-    finally:
-        b.trj_set_tunable("attn_target_wgs", 256)
-        b.trj_set_tunable("attn_min_bpw", 0)
+    for wgs, blocks in ((1, 0), (8, 1), (24, 1), (64, 1), (4096, 1), (4096, 3)):
+        got = []
+        for least in (1, 1 << 20):
+            knobs(attn_target_wgs=wgs, attn_min_bpw=blocks, attn_xchg_min_blocks=least)
+            plan = b.trj_dev_attn_plan(1, n, H, dh, False, L + n)
+            assert plan["ring"] == (least == 1 and dh == 128 or n <= 32 and dh == 64)
+            four = plan["ring"] and n > 64 and (wgs > H or 2 * H >= 3 * wgs)   # unsplit: not one round of workgroups
+            assert plan["tiles"] == (4 if four else 1 if n <= 32 else 2)
+            got.append(run_attention("bf16", H, dh, [c])[0])
+            assert np.isfinite(got[-1]).all(), (wgs, blocks, least)
+            assert rel_err(got[-1], want) <= TOL["bf16"], (wgs, blocks, least)
+        if n <= 64:   # the same streams, in the same order: the same bits in either form
+            assert np.array_equal(got[0], got[1]), (wgs, blocks)
 
 
-def test_batch_of_large_and_small_trees_takes_four_tiles():
+@pytest.mark.parametrize("wgs", [8, 24, 256])   # four tiles unsplit, in two splits, two tiles
+def test_batch_of_large_and_small_trees(knobs, wgs):
     sizes, lens = [128, 128, 33, 97, 1, 96], [1500, 3, 1411, 0, 900, 64]
     cases = [case(70 + s, 2, 128, L, n, "bf16") for s, (n, L) in enumerate(zip(sizes, lens))]
     assert sum(sizes) > 64 * len(sizes)
+    knobs(attn_target_wgs=wgs, attn_xchg_min_blocks=1)
+    plan = b.trj_dev_attn_plan(6, sum(sizes), 2, 128, False, 1628)
+    assert plan["ring"] == 1 and plan["tiles"] == (4 if wgs < 256 else 2)
     for g, c in zip(run_attention("bf16", 2, 128, cases, align=32), cases):
         assert rel_err(g, O.tree_attention(*c)) <= TOL["bf16"]
 
@@ -53,8 +73,9 @@ def shifted(a, dtype, by):
 
 @pytest.mark.parametrize("which", ["q", "k", "v", "workspace"])
 @pytest.mark.parametrize("L,n", [(100, 20), (300, 50), (1450, 80)])
-def test_attention_operands_at_any_alignment(which, L, n):
+def test_attention_operands_at_any_alignment(knobs, which, L, n):
     H, dh = 2, 128
+    knobs(attn_xchg_min_blocks=1)   # the plan is the ring's, with one, two and four tiles
     c = case(9 + L, H, dh, L, n, "bf16")
     batch = Batch([c[3]], [L])
     kp, vp = np.zeros((H, batch.s_pool * dh), np.float32), np.zeros((H, batch.s_pool * dh), np.float32)
@@ -90,10 +111,12 @@ def test_projection_operands_at_any_alignment(which, T, n_in, n_out):
 @pytest.mark.parametrize("what", ["good", "inner rows", "second root", "child before parent", "slots", "no rows",
                                   "too many rows"])
 @pytest.mark.parametrize("L,n", [(40, 20), (900, 64), (1450, 128)])
-def test_one_sequence_checked_by_the_attention_kernel(what, L, n):
+@pytest.mark.parametrize("dh,least", [(64, 48), (128, 1), (128, 1 << 20)])
+def test_one_sequence_checked_by_the_attention_kernel(knobs, what, L, n, dh, least):
     """A single sequence has no launch of its own for the tree's checks: rows that no valid
     sequence owns read as zeros, deep trees need every doubling round."""
-    H, dh = 2, 64
+    H = 2
+    knobs(attn_xchg_min_blocks=least)
     for tree in (I.tree_chain(n), I.tree_random(n, np.random.default_rng(n))):
         c = case(77 + L, H, dh, L, n, "bf16", np.asarray(tree, np.int32))
         batch = Batch([c[3]], [L])
