@@ -216,7 +216,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   const int head = (kvg % n_kv) * a.group + slot % a.group;
   const int item = kvg / n_kv;
   int s, qg, r0, n, L, blk_base, sp;
-  bool several;  // another query group of the sequence reads the same blocks
+  bool several;  // another query group or sequence reads the same blocks
   auto zero_rows = [&](int t0, int t1) {  // rows without a valid sequence read as zeros (this head's part)
     const u32x2 z = {0, 0};
     for (int i = tid; i < (t1 - t0) * (DH / 4); i += KS * NTW * 64)
@@ -253,8 +253,9 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   if (sp >= nsplit || qg * 32 * NTW >= n) return;  // uniform as well
   const int b0 = sp * a.bpwg, b1 = min(nb, b0 + a.bpwg);
   const int n32 = lane & 31, hh = lane >> 5;
-  // no other workgroup reads these blocks (one query group, one query head per K/V head): the
-  // loads carry the streaming hint; with a second reader through L2 it costs a second trip to HBM
+  // no other workgroup reads these blocks (one query group, no sequence with the same slots, one
+  // query head per K/V head): the loads carry the streaming hint; with a second reader through
+  // L2 it costs a second trip to HBM
   const bool stream = a.group == 1 && !several;
 
   const size_t plane = (size_t)(head / a.group) * a.s_pool * DH;  // the group's K/V head

@@ -83,7 +83,7 @@ struct EmbedRow {
 int launch_step_prep(const StepPrep& a, const EmbedRow& e, hipStream_t st);
 // List of the (sequence, key split, query group) triples that exist, for the bf16 attention
 // launch: n records of 8 words {sequence, group, first row, rows, prefix length,
-// kv_off / 32, split, 1 if the sequence has more than one group}, sequences ordered by length (prefix + tree), longest first, when
+// kv_off / 32, split, 1 if another group or sequence reads the same slots}, sequences ordered by length (prefix + tree), longest first, when
 // B <= 1024 (else in index order); word 8 * B * qg_max * nsplit_max holds n.  Sequences
 // whose status is not 0 are left out.  Must follow launch_tree_prep on the stream.
 int launch_attn_items(const int32_t* node_off, const int32_t* prefix_len, const int32_t* kv_off,

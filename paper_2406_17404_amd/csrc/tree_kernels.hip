@@ -98,12 +98,19 @@ __global__ void prep_clear_kernel(int32_t* depth, int32_t* anc_words, int32_t* r
 // over the chunk gives every sequence its place.  With one
 // chunk (B <= 1024) the sequences are first ranked by length, longest first (ties by
 // index), so that the long ones start early and the launch ends evenly.
+// The last word of an item: another query group of the sequence, or another sequence (a prompt
+// pass packs chunks of one prompt that share its slots; up to 1024 sequences are compared),
+// reads the same blocks.
+__device__ inline bool slots_meet(int slot0, int len, int other0, int other_len) {  // len < 0: no valid sequence
+  return len > 0 && other_len > 0 && slot0 < other0 + other_len && other0 < slot0 + len;
+}
 __device__ inline void attn_items_body(
     const int32_t* __restrict__ node_off, const int32_t* __restrict__ prefix_len,
     const int32_t* __restrict__ kv_off, const int32_t* __restrict__ status, int B,
     int rows_per_item, int qg_max, int blocks_per_item, int nsplit_max,
     int32_t* __restrict__ items, int32_t* key, int32_t* cnt, int32_t* scan) {
   const int tid = threadIdx.x;
+  __shared__ int32_t first[1024];
   int carry = 0;
   for (int base = 0; base < B; base += 1024) {
     const int s = base + tid;
@@ -118,11 +125,17 @@ __device__ inline void attn_items_body(
     if (nsp > nsplit_max) nsp = nsplit_max;
     const int nq = len < 0 ? 0 : ng * nsp;
     int place = tid;  // position of this sequence within the chunk
+    bool common = false;
     if (B <= 1024) {
+      const int slot0 = nq > 0 ? kv_off[s] : 0;
       key[tid] = len;
+      first[tid] = slot0;
       __syncthreads();
       place = 0;
-      for (int j = 0; j < B; ++j) place += key[j] > len || (key[j] == len && j < tid);
+      for (int j = 0; j < B; ++j) {
+        place += key[j] > len || (key[j] == len && j < tid);
+        common = common || (j != tid && slots_meet(slot0, len, first[j], key[j]));
+      }
     }
     __syncthreads();
     if (s < B) cnt[place] = nq;
@@ -147,7 +160,7 @@ __device__ inline void attn_items_body(
         rec[4] = len - n;
         rec[5] = kv_off[s] >> 5;
         rec[6] = j / ng;
-        rec[7] = ng > 1;  // another query group of the sequence reads the same blocks
+        rec[7] = ng > 1 || common;
       }
     }
     carry += scan[1023];
@@ -278,30 +291,38 @@ __device__ inline void prep_sequence(const StepPrep& a, int s, int chunk) {
 }
 
 // The attention work list for up to PREP_MAX_SEQS sequences: the records of attn_items_body,
-// one thread per record instead of one per sequence.  ok[s]: LDS or global.
+// one thread per record instead of one per sequence.  bad[s] (LDS or global): no record.
 __device__ inline void few_items_body(const int32_t* node_off, const int32_t* prefix_len, const int32_t* kv_off,
                                       const int32_t* bad, int B, int rows_per_item, int qg_max,
                                       int blocks_per_item, int nsplit_max, int32_t* items) {
   __shared__ int32_t len[PREP_MAX_SEQS], order[PREP_MAX_SEQS], groups[PREP_MAX_SEQS], end[PREP_MAX_SEQS];
+  __shared__ int32_t first[PREP_MAX_SEQS], shared[PREP_MAX_SEQS];
   const int tid = threadIdx.x;
-  int n = 0, l = -1;
+  int n = 0, l = -1, slot0 = 0;
   if (tid < PREP_MAX_SEQS) {
     if (tid < B && bad[tid] == 0) {
       n = node_off[tid + 1] - node_off[tid];
       l = prefix_len[tid] + n;
+      slot0 = kv_off[tid];
     }
     len[tid] = l;
+    first[tid] = slot0;
     order[tid] = tid;  // places past the last sequence: nothing
     groups[tid] = end[tid] = 0;
   }
   __syncthreads();
   if (tid < B) {
     int place = 0;
-    for (int j = 0; j < B; ++j) place += len[j] > l || (len[j] == l && j < tid);
+    bool common = false;
+    for (int j = 0; j < B; ++j) {
+      place += len[j] > l || (len[j] == l && j < tid);
+      common = common || (j != tid && slots_meet(slot0, l, first[j], len[j]));
+    }
     const int ng = min((n + rows_per_item - 1) / rows_per_item, qg_max);
     const int nsp = min((((l + 31) >> 5) + blocks_per_item - 1) / blocks_per_item, nsplit_max);
     order[place] = tid;
     groups[place] = ng;
+    shared[tid] = ng > 1 || common;
     end[place] = l < 0 ? 0 : ng * nsp;
   }
   __syncthreads();
@@ -326,9 +347,9 @@ __device__ inline void few_items_body(const int32_t* node_off, const int32_t* pr
     rec[2] = node_off[s];
     rec[3] = rows;
     rec[4] = len[s] - rows;
-    rec[5] = kv_off[s] >> 5;
+    rec[5] = first[s] >> 5;
     rec[6] = j / ng;
-    rec[7] = ng > 1;  // another query group of the sequence reads the same blocks
+    rec[7] = shared[s];
   }
   if (tid == 0) items[(size_t)B * qg_max * nsplit_max * 8] = total;
 }
