@@ -116,10 +116,10 @@ int launch_argmax(const float* logits, int T, int V, int32_t* out, hipStream_t s
 int launch_accept(const int32_t* argmax, const int32_t* tok, const int32_t* parent, const int32_t* node_off, int B,
                   int T, int32_t* accept_len, int32_t* best_node, int32_t* path, int32_t* bonus_tok,
                   int32_t* status_dev, hipStream_t st);
-// both of a step; status_dev as the prologue wrote it
+// both of a step; status_dev: as the prologue wrote it, 1 is added for a malformed parent[]
 int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const int32_t* argmax, const int32_t* tok,
                           const int32_t* parent, const int32_t* node_off, const int32_t* kv_off,
-                          const int32_t* prefix_len, const int32_t* status_dev, int B, int T, int n_layers,
+                          const int32_t* prefix_len, int32_t* status_dev, int B, int T, int n_layers,
                           int n_heads, int dh, int s_pool, int dtype, int32_t* accept_len, int32_t* best_node,
                           int32_t* path, int32_t* bonus_tok, int32_t* new_len, hipStream_t st);
 int launch_kv_compact(void* k_pool, void* v_pool, size_t layer_stride, const int32_t* path,

@@ -729,13 +729,13 @@ int launch_kv_compact(void* k_pool, void* v_pool, size_t layer_stride, const int
 }
 
 // Acceptance and compaction of a step in one launch: every plane's workgroup works the path
-// out for itself (three 512-byte reads and a few rounds in LDS) instead of waiting for a launch
+// out for itself (three 512-byte reads and a few rounds on registers) instead of waiting for a launch
 // that does only this; plane 0 writes it out.  Tail of a step 9.4 -> 5.0 us.
 template <typename E>
 __global__ __launch_bounds__(TRJ_N_MAX) void accept_compact_kernel(
     E* __restrict__ k_pool, E* __restrict__ v_pool, size_t layer_stride, const int32_t* __restrict__ argmax,
     const int32_t* __restrict__ tok, const int32_t* __restrict__ parent, const int32_t* __restrict__ node_off,
-    const int32_t* __restrict__ kv_off, const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ status_dev,
+    const int32_t* __restrict__ kv_off, const int32_t* __restrict__ prefix_len, int32_t* status_dev,
     int T, int n_heads, int dh, int s_pool, int32_t* __restrict__ accept_len, int32_t* __restrict__ best_node,
     int32_t* __restrict__ path, int32_t* __restrict__ bonus_tok, int32_t* __restrict__ new_len) {
   __shared__ int32_t pth[TRJ_N_MAX];
@@ -743,11 +743,16 @@ __global__ __launch_bounds__(TRJ_N_MAX) void accept_compact_kernel(
   const int s = blockIdx.x, plane = blockIdx.y;
   const int L = prefix_len[s], ko = kv_off[s];
   if (threadIdx.x < WAVE) {
-    // the prologue's verdict on tree and slots stands and is not written again (every plane reads it)
+    // the prologue's verdict on tree and slots stands; what only parent[] shows (a prepared template
+    // is not compared with it) is added.  Every plane reads the word while plane 0 may write it and
+    // comes to the same end with either value.
     const Accepted r = accept_sequence(argmax, tok, parent, node_off, T, status_dev[s] != 0, s);
     if (plane == 0) {
       accept_store(r, s, accept_len, best_node, path, bonus_tok);
-      if (threadIdx.x == 0) new_len[s] = r.depth < 0 ? L : L + r.depth + 1;
+      if (threadIdx.x == 0) {
+        new_len[s] = r.depth < 0 ? L : L + r.depth + 1;
+        if (r.depth < 0) status_dev[s] = 1;
+      }
     }
     pth[threadIdx.x] = r.path[0];
     pth[threadIdx.x + WAVE] = r.path[1];
@@ -762,7 +767,7 @@ __global__ __launch_bounds__(TRJ_N_MAX) void accept_compact_kernel(
 
 int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const int32_t* argmax, const int32_t* tok,
                           const int32_t* parent, const int32_t* node_off, const int32_t* kv_off,
-                          const int32_t* prefix_len, const int32_t* status_dev, int B, int T, int n_layers,
+                          const int32_t* prefix_len, int32_t* status_dev, int B, int T, int n_layers,
                           int n_heads, int dh, int s_pool, int dtype, int32_t* accept_len, int32_t* best_node,
                           int32_t* path, int32_t* bonus_tok, int32_t* new_len, hipStream_t st) {
   dim3 grid(B, n_layers * n_heads);

@@ -120,6 +120,28 @@ def test_malformed_tree_in_the_template_and_bad_slot_ranges():
     assert list(res4["status"]) == [0, 1, 1, 1]      # sequence 1: malformed in the template; 2, 3: other ranges
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_parents_that_do_not_belong_to_the_template(dtype):
+    """The acceptance rule still reads parent[]: a malformed one marks its sequence although the
+    prepared tree is good, and leaves the others alone."""
+    shape = I.ModelShape(2, 256, 4, 64, 512, 512, dtype)
+    w = I.gen_weights(shape, 303)
+    trees = [I.tree_c0(), I.tree_c0(), I.tree_c0()]
+    toks = [I.gen_tokens(shape.vocab, 15, 303, "tree", s) for s in range(3)]
+    Ls = [40, 10, 70]
+    pkvs = [prefix_normal(shape, 303, s, L) for s, L in enumerate(Ls)]
+    desc, dw = device_weights(shape, w)
+    batch = Batch(trees, Ls, toks)
+    tmpl = make_template(desc, batch, 128)
+    batch.parent[15 + 7] = 9                       # sequence 1, behind its child
+    kp, vp = pools_for(shape, batch, Ls, pkvs)
+    res = run_step(shape, desc, dw, batch, kp, vp, tmpl=tmpl, max_pos=128)
+    assert list(res["status"]) == [0, 1, 0]
+    assert res["accept_len"][1] == -1 and res["best"][1] == -1 and res["new_len"][1] == Ls[1]
+    assert (res["path"][1] == -1).all()
+    check_against_oracle(shape, w, res, batch, trees, toks, Ls, pkvs, TOL[dtype], skip=(1,))
+
+
 def test_template_host_side_errors():
     shape = I.ModelShape(2, 512, 4, 128, 1408, 1024, "bf16")
     desc = b.make_desc(shape)
