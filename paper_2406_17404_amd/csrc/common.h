@@ -91,8 +91,7 @@ __device__ inline void lds_barrier() {
 // (uniform; lane l's 16 bytes land at lds + 16 l).  Has no destination register; completion
 // is counted by vmcnt, in order with the wavefront's other loads.  (m0 is written here and
 // read by the next instruction; nothing the compiler emits in these kernels uses it.)
-// Both addresses must be multiples of 16; copy_to_lds is the form for those that are not, at
-// the price of registers and a wait.
+// Both addresses must be multiples of 16.
 template <bool NT>
 __device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
   if constexpr (NT)
@@ -107,10 +106,6 @@ __device__ __forceinline__ void load_words_to_lds(const void* base, uint32_t vof
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(base), "s"(lds)
                : "memory");
 }
-__device__ __forceinline__ void copy_to_lds(const void* base, uint32_t voff, void* lane_dst) {
-  *static_cast<u32x4*>(lane_dst) = *reinterpret_cast<const u32x4*>(static_cast<const uint8_t*>(base) + voff);
-}
-
 // per-node values of a tree on one wavefront, two nodes per lane (node = lane and lane + 64):
 __device__ inline int from_node(const int (&v)[2], int node) {  // the value of `node`, any lane's choice
   const int a = __shfl(v[0], node & 63), b = __shfl(v[1], node & 63);

@@ -94,7 +94,13 @@ __device__ __forceinline__ void wait_and_meet() {
 // behind the LDS read makes the wavefront wait for the read there (22016 x 4096 at 128 rows
 // 56.0 against 48.6 us).
 //
-// ALIGNED: xp and w start at multiples of 16 bytes (else they are copied through registers).
+// ALIGNED: xp and w start at multiples of 16 bytes, as loads to LDS need.  Else the pieces of a
+// phase wait in registers from its request to the end of the next phase, when they are written
+// to their buffer in front of the barrier: one phase in flight besides the two in LDS, so
+// phases are long where they are small (8 k-steps up to 32 rows: 22016 x 4096 41 against 48 us;
+// beyond, 4 leave room for a second workgroup on the compute unit: 128 rows 64 against 88).
+// 22016 x 4096 with weights one element off: 64 rows 45 us (33 aligned), 1024 rows 264 (181);
+// copied to LDS at once and waited for, in one shape for all rows: 64 and 750.
 template <int RT, int CT, int KW, int WT, int MT, int PH, int NB, bool NT, bool ALIGNED, class Epi>
 __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs a, Epi epi) {
   constexpr int NW = RT * CT * KW, WR = RT * WT, XC = CT * MT, WS = PH / KW;
@@ -144,6 +150,19 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
   const bool tail = ksteps % PH != 0;
   int iph = ph0;                         // next phase to request
   uint32_t ibuf = lds0 + wv * 1024;      // this wavefront's first piece in its buffer
+  u32x4 held[ALIGNED ? 1 : PL];          // pieces of the youngest phase, and where they belong
+  uint32_t hbuf = 0;
+  bool holds = false;
+  auto store_held = [&]() {
+    if constexpr (!ALIGNED) {
+      if (!holds) return;  // uniform
+#pragma unroll
+      for (int j = 0; j < PL; ++j)
+        if (REM == 0 || j < PL - 1 || j * NW + wv < P)
+          *reinterpret_cast<u32x4*>(smem + (hbuf - lds0) + j * NW * 1024 + lane * 16) = held[j];
+      holds = false;
+    }
+  };
   auto request = [&]() {
     if (iph == nph - 1 && tail) {
 #pragma unroll
@@ -153,13 +172,15 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
     for (int j = 0; j < PL; ++j) {
       const int p = j * NW + wv;
       if (REM != 0 && j == PL - 1 && p >= P) break;
-      if constexpr (!ALIGNED) {  // waited for at once and counted by nobody: the waits below only get stricter
-        copy_to_lds(p < XP ? xs : ws, voff[j], smem + (ibuf - lds0) + j * NW * 1024 + lane * 16);
+      if constexpr (!ALIGNED) {
+        held[j] = *reinterpret_cast<const u32x4*>((p < XP ? xs : ws) + voff[j]);
         continue;
       }
       if ((j + 1) * NW <= XP || (j * NW < XP && p < XP)) load_to_lds<false>(xs, voff[j], ibuf + j * NW * 1024);
       else load_to_lds<NT>(ws, voff[j], ibuf + j * NW * 1024);
     }
+    hbuf = ibuf;
+    holds = true;
     xs += xstep;
     ws += PH * 1024;
     ++iph;
@@ -167,6 +188,7 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
   };
   auto wait_younger = [&](auto k_c) {  // everything but the youngest K phases has landed
     constexpr int K = decltype(k_c)::value;
+    store_held();
     if (REM == 0 || wv < REM) wait_and_meet<K * PL>();
     else wait_and_meet<K * (PL - 1)>();
   };
@@ -241,7 +263,10 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
   if (ALIGNED || n > 0) {
-    for (int p = 0; p < NB && p < n; ++p) request();
+    for (int p = 0; p < NB && p < n; ++p) {
+      request();
+      store_held();
+    }
     if (n >= NB) wait_younger(std::integral_constant<int, NB - 1>{});
     else if (NB > 3 && n == 3) wait_younger(k2);
     else if (NB > 2 && n == 2) wait_younger(k1);
@@ -363,8 +388,18 @@ static int launch_gemm(const uint16_t* xp, const uint16_t* w, int tp, int n_in, 
                        const Epi& epi, hipStream_t st) {
   if (tp < 32 || (tp & 31) || (n_in & 15) || (n_out & 31)) return TRJ_ERR_BAD_SHAPE;
   const GemmPlan g = plan_gemm(tp, n_in, n_out, split_k);
-  if ((((uintptr_t)xp | (uintptr_t)w) & 15) != 0) {  // one shape for callers' odd pointers
-    launch_ring_t<2, 1, 2, 1, 1, gemm_phase(GS_2x2), 2, false, false>(xp, w, tp, n_in, n_out, g.split_k, epi, st);
+  if ((((uintptr_t)xp | (uintptr_t)w) & 15) != 0) {  // callers' odd pointers
+#define TRJ_HELD(RT, CT, KW, WT, MT, PH) \
+  launch_ring_t<RT, CT, KW, WT, MT, PH, 2, false, false>(xp, w, tp, n_in, n_out, g.split_k, epi, st)
+    if (g.shape == GS_MANY_8x8) TRJ_HELD(2, 4, 1, 4, 2, 4);
+    else if (g.shape == GS_MANY_4x8) TRJ_HELD(2, 2, 1, 2, 4, 3);
+    else if (g.shape == GS_MANY_4x4) TRJ_HELD(2, 2, 1, 2, 2, 4);
+    else if (g.many) TRJ_HELD(2, 1, 4, 1, 4, 8);
+    else if (g.mt == 1) TRJ_HELD(2, 1, 2, 1, 1, 8);
+    else if (g.mt == 2) TRJ_HELD(2, 1, 2, 1, 2, 4);
+    else if (g.mt == 3) TRJ_HELD(2, 1, 2, 1, 3, 4);
+    else TRJ_HELD(2, 1, 2, 1, 4, 4);
+#undef TRJ_HELD
     return check_launch();
   }
   switch (g.shape) {
