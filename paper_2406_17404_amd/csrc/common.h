@@ -89,22 +89,21 @@ __device__ inline void lds_barrier() {
 
 // 1 KiB from global memory (uniform base, 16 bytes per lane at `voff`) to LDS at byte `lds`
 // (uniform; lane l's 16 bytes land at lds + 16 l).  Has no destination register; completion
-// is counted by vmcnt, in order with the wavefront's other loads.  (m0 is written here and
-// read by the next instruction; nothing the compiler emits in these kernels uses it.)
+// is counted by vmcnt, in order with the wavefront's other loads.  m0 holds the LDS address.
 // Both addresses must be multiples of 16.
 template <bool NT>
 __device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
   if constexpr (NT)
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "s"(lds)
-                 : "memory");
+                 : "memory", "m0");
   else
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
-                 : "memory");
+                 : "memory", "m0");
 }
 // 4 bytes per lane instead, for arrays that start anywhere a word may
 __device__ __forceinline__ void load_words_to_lds(const void* base, uint32_t voff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(base), "s"(lds)
-               : "memory");
+               : "memory", "m0");
 }
 // per-node values of a tree on one wavefront, two nodes per lane (node = lane and lane + 64):
 __device__ inline int from_node(const int (&v)[2], int node) {  // the value of `node`, any lane's choice
