@@ -89,8 +89,11 @@ __device__ inline void lds_barrier() {
 
 // 1 KiB from global memory (uniform base, 16 bytes per lane at `voff`) to LDS at byte `lds`
 // (uniform; lane l's 16 bytes land at lds + 16 l).  Has no destination register; completion
-// is counted by vmcnt, in order with the wavefront's other loads.  m0 holds the LDS address.
+// is counted by vmcnt, in order with the wavefront's other loads.  m0 holds the LDS address
+// (the compiler's note that m0 may not be preserved behind the statement is what is wanted).
 // Both addresses must be multiples of 16.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <bool NT>
 __device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
   if constexpr (NT)
@@ -105,6 +108,8 @@ __device__ __forceinline__ void load_words_to_lds(const void* base, uint32_t vof
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(base), "s"(lds)
                : "memory", "m0");
 }
+#pragma clang diagnostic pop
+
 // per-node values of a tree on one wavefront, two nodes per lane (node = lane and lane + 64):
 __device__ inline int from_node(const int (&v)[2], int node) {  // the value of `node`, any lane's choice
   const int a = __shfl(v[0], node & 63), b = __shfl(v[1], node & 63);
