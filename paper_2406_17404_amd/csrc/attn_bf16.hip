@@ -779,12 +779,8 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
     constexpr size_t handed = (size_t)Q * DH * (KS - 1) * 128;                                  \
     constexpr size_t lds = RING && rings > handed ? rings : handed;                                     \
     auto kern = tree_attn_bf16_kernel<DH, Q, KS, D, RING, SELF>;                                  \
-    static bool big_lds_allowed = false; /* one-time, per instantiation */                      \
-    if (!big_lds_allowed) {                                                                     \
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                            \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);          \
-      big_lds_allowed = true;                                                                   \
-    }                                                                                           \
+    static DeviceOnce once; /* per instantiation */                                             \
+    allow_lds(once, kern, lds);                                                                 \
     kern<<<grid, KS * Q * 64, lds, st>>>(a);                                                    \
   } while (0)
 #define TRJ_ATTN(DH, Q, KS, D, RING)                                                            \

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/trjacobi.h"
+#include "device_once.h"
 
 namespace trj {
 
@@ -125,6 +126,18 @@ inline int check_launch() {
     return TRJ_ERR_HIP;
   }
   return TRJ_OK;
+}
+
+// Lets a kernel take `bytes` of dynamic LDS on the current device (from 64 KiB on it must be
+// asked for, on each device); without the permission the launch itself reports the error.
+template <class K>
+inline void allow_lds(DeviceOnce& once, K* kern, size_t bytes) {
+  int dev = -1;
+  (void)hipGetDevice(&dev);
+  once.run(dev, [&] {
+    return (int)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)bytes);
+  });
 }
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

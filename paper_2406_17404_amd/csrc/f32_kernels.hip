@@ -322,12 +322,8 @@ int launch_tree_attn_f32(const float* q, const float* k_layer, const float* v_la
                          int s_pool, int max_slots, float scale, float* out, hipStream_t st) {
   if ((size_t)(dh + max_slots) * sizeof(float) > 64 * 1024) return TRJ_ERR_BAD_SHAPE;
   const size_t lds = attn_f32_lds(dh, max_slots);
-  static bool big_lds_allowed = false;  // one-time: a little more than 64 KiB at the limit
-  if (!big_lds_allowed) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(tree_attn_f32_kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-    big_lds_allowed = true;
-  }
+  static DeviceOnce once;
+  allow_lds(once, tree_attn_f32_kernel, 96 * 1024);  // a little more than 64 KiB at the limit
   dim3 grid(T, n_heads);
   tree_attn_f32_kernel<<<grid, FA_THREADS, lds, st>>>(q, k_layer, v_layer, anc, row_seq, node_off,
                                               kv_off, prefix_len, status_dev, n_heads,

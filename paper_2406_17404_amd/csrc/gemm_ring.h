@@ -358,12 +358,8 @@ static void launch_ring_t(const uint16_t* xp, const uint16_t* w, int tp, int n_i
   constexpr size_t lds = lds_x > lds_r ? lds_x : lds_r;
   static_assert(lds <= 160 * 1024, "LDS");
   auto kern = gemm_ring_kernel<RT, CT, KW, WT, MT, PH, NB, NT, ALIGNED, Epi>;
-  static bool big_lds_allowed = false;  // one-time, per instantiation
-  if (!big_lds_allowed) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              160 * 1024);
-    big_lds_allowed = true;
-  }
+  static DeviceOnce once;  // per instantiation
+  allow_lds(once, kern, 160 * 1024);
   kern<<<grid, RT * CT * KW * 64, lds, st>>>(a, epi);
 }
 template <int M, class Epi>
