@@ -81,7 +81,7 @@ struct StepWs {
   float *qf, *of, *actf;
 };
 
-static void carve_tree(Carver& c, int dtype, int B, int T, int H, int Hkv, int dh, int max_seq_slots,
+static void carve_tree(Carver& c, int dtype, int B, int T, int H, bool shared_kv, int dh, int max_seq_slots,
                        TreeWs* w) {
   w->depth = c.take<int32_t>(T);
   w->row_slot = c.take<int32_t>(T);
@@ -93,7 +93,7 @@ static void carve_tree(Carver& c, int dtype, int B, int T, int H, int Hkv, int d
   w->items = nullptr;
   w->attn_rows = w->attn_qg = w->attn_bpwg = w->attn_ns = 0;
   if (dtype == TRJ_BF16) {
-    const AttnPlan p = attn_bf16_plan(B, T, H, dh, H != Hkv, max_seq_slots);
+    const AttnPlan p = attn_bf16_plan(B, T, H, dh, shared_kv, max_seq_slots);
     w->attn = c.take<float>(attn_bf16_ws_floats(B, T, H, dh, max_seq_slots));
     w->items = c.take<int32_t>(attn_bf16_item_words(B, T, H, dh, max_seq_slots));
     w->attn_rows = 32 * p.ntw;
@@ -103,10 +103,11 @@ static void carve_tree(Carver& c, int dtype, int B, int T, int H, int Hkv, int d
   }
 }
 
+static bool model_shares_kv(const trj_model_desc& m) { return m.n_kv_heads && m.n_kv_heads != m.n_heads; }
 static void carve_step(Carver& c, const trj_model_desc& m, int B, int T, int max_seq_slots,
-                       bool head_scratch, StepWs* w) {
+                       bool head_scratch, bool shared_kv, StepWs* w) {
   const int d = m.d_model, hd = m.n_heads * m.head_dim, F = m.d_ffn;
-  carve_tree(c, m.dtype, B, T, m.n_heads, m.n_kv_heads ? m.n_kv_heads : m.n_heads, m.head_dim, max_seq_slots, &w->t);
+  carve_tree(c, m.dtype, B, T, m.n_heads, shared_kv, m.head_dim, max_seq_slots, &w->t);
   w->cs = c.take<float2>((size_t)T * (m.head_dim / 2));
   w->x = c.take<float>((size_t)T * d);
   // the head's own scratch: the fp32 mode's logits (if the caller keeps none), the bf16 mode's
@@ -275,7 +276,7 @@ int32_t trj_workspace_bytes(const trj_model_desc* desc, int32_t t_max, int32_t b
   TuneScope tune_scope;
   Carver c(nullptr);
   StepWs w;
-  carve_step(c, *desc, b_max, t_max, l_max, true, &w);
+  carve_step(c, *desc, b_max, t_max, l_max, true, model_shares_kv(*desc), &w);
   *h_bytes = align_up(c.off, 256);
   return TRJ_OK;
 }
@@ -436,14 +437,14 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
   if (static_ws) {  // sizes first: nothing is touched when the call does not fit the array
     Carver need(nullptr);
     TreeWs wn;
-    carve_tree(need, dtype, B, T, n_heads, n_kv_heads, head_dim, max_seq_slots, &wn);
+    carve_tree(need, dtype, B, T, n_heads, n_heads != n_kv_heads, head_dim, max_seq_slots, &wn);
     if (need.off > (size_t)TRJ_STATIC_SCRATCH_BYTES) return TRJ_ERR_WORKSPACE_TOO_SMALL;
     TRJ_TRY(static_scratch(&workspace));
     ws_bytes = TRJ_STATIC_SCRATCH_BYTES;
   }
   Carver c(workspace);
   TreeWs w;
-  carve_tree(c, dtype, B, T, n_heads, n_kv_heads, head_dim, max_seq_slots, &w);
+  carve_tree(c, dtype, B, T, n_heads, n_heads != n_kv_heads, head_dim, max_seq_slots, &w);
   if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = dtype == TRJ_BF16, self = bf16 && B == 1;  // one sequence: the kernel checks it itself
@@ -466,7 +467,7 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
   if (bf16) {
     return launch_tree_attn_bf16((const uint16_t*)q, (const uint16_t*)k_layer,
                                  (const uint16_t*)v_layer, w.anc, node_off, kv_off, prefix_len,
-                                 w.status, w.items, B, T, n_heads, n_kv_heads, head_dim, s_pool, max_seq_slots, scale,
+                                 w.status, w.items, B, T, n_heads, n_kv_heads, n_heads != n_kv_heads, head_dim, s_pool, max_seq_slots, scale,
                                  w.attn, 0, 0, (uint16_t*)out, self ? parent : nullptr, w.status, st);
   }
   return launch_tree_attn_f32((const float*)q, (const float*)k_layer, (const float*)v_layer, w.anc,
@@ -484,7 +485,7 @@ int32_t tree_attention_workspace_bytes(int32_t B, int32_t T, int32_t n_heads, in
   TuneScope tune_scope;
   Carver c(nullptr);
   TreeWs w;
-  carve_tree(c, dtype, B, T, n_heads, n_heads, head_dim, max_seq_slots, &w);  // the same for any K/V heads
+  carve_tree(c, dtype, B, T, n_heads, false, head_dim, max_seq_slots, &w);  // the same with shared K/V
   *h_bytes = align_up(c.off, 256);
   return TRJ_OK;
 }
@@ -637,10 +638,12 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
   Carver c(workspace);
   StepWs w;
   const bool bf16 = m.dtype == TRJ_BF16;
-  carve_step(c, m, B, T, max_seq_slots, with_head && (bf16 || !logits), &w);
+  // heads of a group read the same K/V, and so do the chunks of a prompt that a pass packs
+  const bool shared_kv = model_shares_kv(m) || (!with_head && B > 1);
+  carve_step(c, m, B, T, max_seq_slots, with_head && (bf16 || !logits), shared_kv, &w);
   if (c.off > ws_bytes && bf16 && logits) {  // no room for the candidates: argmax of the written logits
     c = Carver(workspace);
-    carve_step(c, m, B, T, max_seq_slots, false, &w);
+    carve_step(c, m, B, T, max_seq_slots, false, shared_kv, &w);
   }
   if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   float* lg = logits ? logits : w.logits;
@@ -710,7 +713,7 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
                               cs_row, w.t.row_slot, kv_only ? nullptr : w.q, kl, vl, st)); }
       if (kv_only) return TRJ_OK;
       TRJ_TRY(launch_tree_attn_bf16(w.q, kl, vl, w.t.anc, node_off, kv_off, prefix_len, status_dev,
-                                    w.t.items, B, T, H, Hkv, dh, s_pool, max_seq_slots, scale, w.t.attn, 1, tp,
+                                    w.t.items, B, T, H, Hkv, shared_kv, dh, s_pool, max_seq_slots, scale, w.t.attn, 1, tp,
                                     w.op, nullptr, nullptr, st));
       { ProfScope ps_(KC_GEMM_O, st); TRJ_TRY(add_projection(w.op, (const uint16_t*)lw.wo, T, tp, hd, d, sk_o, w.partial, w.x, st)); }
       { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_o > 1 ? sk_o : 0, w.x, lw.g_ffn, T, d, tp, w.hp, w.ssq, st)); }
@@ -750,7 +753,7 @@ size_t step_workspace_bytes(const trj_model_desc& m, int B, int T, int max_seq_s
   TuneScope tune_scope;
   Carver c(nullptr);
   StepWs w;
-  carve_step(c, m, B, T, max_seq_slots, true, &w);
+  carve_step(c, m, B, T, max_seq_slots, true, model_shares_kv(m), &w);
   return c.off + 256;
 }
 int check_model(const trj_model_desc* m) { return check_desc(m); }

@@ -664,7 +664,8 @@ AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int m
   // The ring pays where so many blocks stream from HBM that it matters how much is in flight
   // and that none is asked for twice: from 1536 (block, head) pairs of 16 KiB per query tile,
   // as blocks with more queries are worked on for longer.  Query heads that share K/V find it
-  // in L2, and halves of it (heads of 64) arrive in time anyway.
+  // in L2, as do the chunks of a prompt (1000 tokens: ring 29.8, R 27.2), and halves of it
+  // (heads of 64) arrive in time anyway.
   //   rows x slots        5x1024 5x2048 5x4096 33x2048 33x4096 97x1024 97x2048 97x4096
   //   pairs / 1536 tiles    0.7   1.4    2.7     0.7     1.4     0.2     0.3     0.7
   //   ring (2 tiles)       12.7   15.5   20.3    18.0    22.6    20.2    24.6    31.0
@@ -751,11 +752,11 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
                           const uint64_t* anc, const int32_t* node_off,
                           const int32_t* kv_off, const int32_t* prefix_len,
                           const int32_t* status_dev, const int32_t* items, int B, int T,
-                          int n_heads, int n_kv_heads, int dh, int s_pool, int max_seq_slots,
+                          int n_heads, int n_kv_heads, bool shared_kv, int dh, int s_pool, int max_seq_slots,
                           float scale, float* ws, int tiled, int tp, uint16_t* out, const int32_t* parent,
                           int32_t* status, hipStream_t st) {
   if (dh != 64 && dh != 128) return TRJ_ERR_BAD_SHAPE;
-  const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, n_heads != n_kv_heads, max_seq_slots);
+  const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, shared_kv, max_seq_slots);
   const int ntw = p.ntw, qg_max = p.qg_max, bpwg = p.bpwg, nsplit_max = p.nsplit_max;
   const int tiles_per_seq = qg_max * ntw;
   size_t parts = nsplit_max > 1 ? (size_t)B * tiles_per_seq * n_heads * nsplit_max : 0;

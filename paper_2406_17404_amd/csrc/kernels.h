@@ -203,6 +203,7 @@ struct AttnPlan {
   bool ring;             // K/V through rings in LDS, else registers
   float lag;             // how far the softmax reference may fall behind the running maximum (log2)
 };
+// shared_kv: several workgroups besides a sequence's query groups read the same K/V
 AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int max_seq_slots);
 size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots);
 size_t attn_bf16_item_words(int B, int T, int n_heads, int dh, int max_seq_slots);
@@ -212,7 +213,7 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
                           const uint64_t* anc, const int32_t* node_off,
                           const int32_t* kv_off, const int32_t* prefix_len,
                           const int32_t* status_dev, const int32_t* items, int B, int T,
-                          int n_heads, int n_kv_heads, int dh, int s_pool, int max_seq_slots,
+                          int n_heads, int n_kv_heads, bool shared_kv, int dh, int s_pool, int max_seq_slots,
                           float scale, float* ws, int tiled, int tp, uint16_t* out, const int32_t* parent,
                           int32_t* status, hipStream_t st);
 
