@@ -99,7 +99,9 @@ def test_eos_stops_generation_and_is_kept():
     assert toks == full[:cut] == want["tokens"] and steps == want["n_steps"]
 
 
-@pytest.mark.parametrize("seed,n,r,plen,max_new", [(0, 16, 4, 6, 24), (1, 64, 5, 150, 16), (2, 33, 0, 40, 16)])
+@pytest.mark.parametrize("seed,n,r,plen,max_new", [(0, 16, 4, 6, 24), (1, 64, 5, 150, 16), (2, 33, 0, 40, 16),
+                                                    # two prompt passes, the second on a shared prefix
+                                                    (3, 20, 3, 1500, 8)])
 def test_bf16_loop_against_oracle_loop(seed, n, r, plen, max_new):
     """bf16 rounding can flip a near tie, after which the two runs follow different (both
     valid) continuations: equal up to the first difference, and at that point the fp64

@@ -401,3 +401,44 @@ def test_argmax_in_the_lm_head_epilogue_equals_argmax_of_the_logits(n_rows, many
     for k in ("accept_len", "best", "bonus", "new_len", "status", "path"):
         assert np.array_equal(fused[k], with_logits[k]), k
     assert np.array_equal(fused["k_pool"], with_logits["k_pool"], equal_nan=True)
+
+
+def test_workspace_without_room_for_the_argmax_candidates():
+    """A bf16 step that writes logits can do without the candidates of the LM head's epilogue:
+    a workspace smaller by them gives the same results through the argmax of the logits; any
+    less, or no logits, and the call is refused."""
+    import torch
+    from gpu_util import DEV
+    shape = I.ModelShape(2, 256, 4, 64, 512, 2048, "bf16")
+    w = I.gen_weights(shape, 350)
+    rng = np.random.default_rng(350)
+    trees, Ls = [I.tree_random(33, rng), I.tree_c0()], [70, 5]
+    toks = [I.gen_tokens(shape.vocab, len(t), 350, "tree", s) for s, t in enumerate(trees)]
+    desc, dw = device_weights(shape, w)
+    batch = Batch(trees, Ls, toks)
+    planes = shape.n_heads * batch.s_pool * shape.head_dim
+    full = b.trj_workspace_bytes(desc, batch.T, batch.B, batch.max_seq_slots)
+    less = full - (batch.T * shape.vocab // 32 * 8 + 255) // 256 * 256
+
+    def step(ws_bytes, with_logits):
+        g = torch.Generator(device=DEV).manual_seed(1)
+        kp, vp = (torch.randn(shape.n_layers, planes, device=DEV, generator=g).to(torch.bfloat16) for _ in "kv")
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+        logits = torch.zeros(batch.T, shape.vocab, device=DEV) if with_logits else None
+        out = [torch.full((n,), -7, dtype=torch.int32, device=DEV) for n in [batch.T] + [batch.B] * 5]
+        path = torch.full((batch.B, b.N_MAX), -7, dtype=torch.int32, device=DEV)
+        b.tr_verify_step(desc, dw.struct, kp, vp, planes, batch.s_pool, batch.tok, batch.parent, batch.node_off,
+                         batch.kv_off, batch.prefix, batch.B, batch.T, batch.max_seq_slots, ws, logits, out[0], out[1],
+                         out[2], path, out[3], out[4], out[5])
+        torch.cuda.synchronize()
+        return out + [path, kp.float(), vp.float()] + ([logits] if with_logits else [])
+
+    want, got = step(full, True), step(less, True)
+    for i, (x, y) in enumerate(zip(want, got)):
+        assert torch.equal(x, y), i
+    for x, y in zip(want, step(full, False)):
+        assert torch.equal(x, y)
+    for size, with_logits in ((less - 256, True), (less, False)):
+        with pytest.raises(b.TrjError) as e:
+            step(size, with_logits)
+        assert e.value.status == -5

@@ -1,12 +1,15 @@
-"""The one-launch prologue (tree checks by pointer doubling, rotary table, work list, rows
-without a valid sequence, embedding) on both sides of the number of sequences it takes."""
+"""The one-launch prologue on both sides of the number of sequences it takes: in attention
+calls the tree checks by pointer doubling, the work list and the rows without a valid sequence
+(a single bf16 sequence has no prologue, the attention kernel checks it), in whole steps the
+rotary table and the embedding as well."""
 import numpy as np
 import pytest
 
-from gpu_util import rel_err
+from gpu_util import Batch, device_weights, rel_err, run_step
 from oracle import tr_oracle as O
 from paper_2406_17404_amd import inputs as I
 from test_gpu_attention import TOL, case, run_attention
+from test_gpu_template import check_against_oracle, pools_for, prefix_normal
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +39,25 @@ def test_sequences_around_the_limit_with_deep_trees_and_malformed_ones(dtype, B)
             assert not g.any(), s
         else:
             assert rel_err(g, O.tree_attention(*c)) <= TOL[dtype], s
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B", [64, 65])
+def test_steps_around_the_limit(dtype, B):
+    shape = I.ModelShape(2, 128, 2, 64, 256, 256, dtype)
+    w = I.gen_weights(shape, 340)
+    rng = np.random.default_rng(B)
+    sizes = [int(rng.choice([1, 2, 5, 17, 33])) for _ in range(B)]
+    trees = [I.tree_random(n, rng) for n in sizes]
+    sizes[9] = 5
+    trees[9] = np.array([-1, 0, 3, 1, 0], np.int32)      # a parent behind its child
+    Ls = [int(rng.integers(0, 60)) for _ in range(B)]
+    toks = [I.gen_tokens(shape.vocab, n, 340, "tree", s) for s, n in enumerate(sizes)]
+    pkvs = [prefix_normal(shape, 340, s, L) if L else None for s, L in enumerate(Ls)]
+    desc, dw = device_weights(shape, w)
+    batch = Batch(trees, Ls, toks)
+    kp, vp = pools_for(shape, batch, Ls, pkvs)
+    res = run_step(shape, desc, dw, batch, kp, vp)
+    assert list(np.flatnonzero(res["status"])) == [9]
+    assert res["accept_len"][9] == -1 and res["new_len"][9] == Ls[9]
+    check_against_oracle(shape, w, res, batch, trees, toks, Ls, pkvs, TOL[dtype], skip=(9,))
