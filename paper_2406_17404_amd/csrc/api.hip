@@ -73,7 +73,7 @@ struct StepWs {
   TreeWs t;
   float2* cs;
   float *x, *logits;
-  void* cand;  // bf16 mode without logits: argmax candidates of the LM head's epilogue
+  void* cand;  // bf16 mode: argmax candidates of the LM head's epilogue, if there is room
   // bf16 mode
   uint16_t *hp, *q, *op, *act;
   float *partial, *ssq;
@@ -448,15 +448,14 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
   if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = dtype == TRJ_BF16, self = bf16 && B == 1;  // one sequence: the kernel checks it itself
-  if (self) {
-  } else if (B <= PREP_MAX_SEQS) {
+  if (!self && B <= PREP_MAX_SEQS) {
     const StepPrep p{parent, node_off, kv_off, prefix_len, B, T, s_pool, max_seq_slots, w.depth, w.anc, w.status,
                      w.row_slot, w.row_pos, w.row_seq, nullptr, head_dim, 0.f, w.items, w.attn_rows, w.attn_qg,
                      w.attn_bpwg, w.attn_ns,
                      // bf16: rows of malformed sequences read as zeros
                      bf16 ? (uint16_t*)out : nullptr, n_heads * head_dim, 0};
     TRJ_TRY(launch_step_prep(p, EmbedRow{}, st));
-  } else {
+  } else if (!self) {
     TRJ_TRY(launch_tree_prep(parent, node_off, kv_off, prefix_len, B, T, s_pool, max_seq_slots, w.depth,
                              w.anc, w.status, w.row_slot, w.row_pos, w.row_seq,
                              bf16 ? out : nullptr, (size_t)T * n_heads * head_dim * 2, st));
@@ -725,7 +724,7 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
     ProfScope ps_(KC_GEMM_LM, st);
     TRJ_TRY(launch_gemm_lm(w.hp, (const uint16_t*)weights->w_lm, T, tp, d, V, rs, logits, w.cand, argmax_out, st));
   } else {
-    if (!one_prep) TRJ_TRY(launch_embed(weights->embed, tok, T, d, V, m.dtype, w.x, st));
+    if (!one_prep) TRJ_TRY(launch_embed((const float*)weights->embed, tok, T, d, V, w.x, st));
     for (int l = 0; l < m.n_layers; ++l) {
       const trj_layer_weights& lw = weights->h_layers[l];
       float* kl = (float*)k_pool + (size_t)l * kv_layer_stride;

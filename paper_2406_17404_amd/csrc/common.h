@@ -80,14 +80,6 @@ __host__ __device__ inline int logical_row(int r, int kind, int n_out, int n_hea
   return r;
 }
 
-// Workgroup barrier that orders LDS traffic only: each wavefront waits for its own LDS
-// operations and then joins the barrier, while its outstanding global loads stay in
-// flight (the generic barrier would first drain them, which empties a register prefetch
-// ring at every k-chunk).
-__device__ inline void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // 1 KiB from global memory (uniform base, 16 bytes per lane at `voff`) to LDS at byte `lds`
 // (uniform; lane l's 16 bytes land at lds + 16 l).  Has no destination register; completion
 // is counted by vmcnt, in order with the wavefront's other loads.  m0 holds the LDS address

@@ -5,8 +5,8 @@
 // output is summed by 32 threads, and norm, rotary rotation with the K/V write, and SiLU(g) * u
 // are part of the projection next to them: 14 launches, 78.5 us, and the result is closer to the
 // 64-bit one (3.4e-7 against 8.1e-7).
-// They read the same tiled weight / KV layouts as the bf16 kernels.  The element-wise
-// kernels at the top (rotary table, embedding) serve both modes.
+// They read the same tiled weight / KV layouts as the bf16 kernels.  The rotary table at the
+// top serves both modes.
 #include "common.h"
 #include "kernels.h"
 #include "tree_vis.h"
@@ -33,41 +33,17 @@ int launch_rope_table(const int32_t* row_pos, int T, int dh, float theta, float2
 }
 
 // ------------------------------------------------------------------ embedding
-// x[t][:] = E[tok[t]][:] as fp32.  Token ids outside [0, vocab) are clamped.
-template <typename E>
-__global__ void embed_kernel(const E* __restrict__ embed, const int32_t* __restrict__ tok, int d,
-                             int vocab, float* __restrict__ x) {
+// x[t][:] = E[tok[t]][:] where the prologue does not do it (more than PREP_MAX_SEQS sequences).
+// Token ids outside [0, vocab) are clamped.
+__global__ void embed_kernel(const float* __restrict__ embed, const int32_t* __restrict__ tok, int d, int vocab,
+                             float* __restrict__ x) {
   int t = blockIdx.x;
   int id = tok[t];
   id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);
-  const E* row = embed + (size_t)id * d;
-  if constexpr (sizeof(E) == 2) {
-    if ((d & 7) == 0) {  // 8 elements per load (rows are 16-byte aligned then)
-      const u32x4* r8 = reinterpret_cast<const u32x4*>(row);
-      f32x4* x8 = reinterpret_cast<f32x4*>(x + (size_t)t * d);
-      for (int g = threadIdx.x; g < (d >> 3); g += blockDim.x) {
-        const u32x4 v = r8[g];
-        f32x4 lo = {__builtin_bit_cast(float, v.x << 16), __builtin_bit_cast(float, v.x & 0xffff0000u),
-                    __builtin_bit_cast(float, v.y << 16), __builtin_bit_cast(float, v.y & 0xffff0000u)};
-        f32x4 hi = {__builtin_bit_cast(float, v.z << 16), __builtin_bit_cast(float, v.z & 0xffff0000u),
-                    __builtin_bit_cast(float, v.w << 16), __builtin_bit_cast(float, v.w & 0xffff0000u)};
-        x8[2 * g] = lo;
-        x8[2 * g + 1] = hi;
-      }
-      return;
-    }
-  }
-  for (int c = threadIdx.x; c < d; c += blockDim.x) {
-    if constexpr (sizeof(E) == 2) x[(size_t)t * d + c] = bf2f(row[c]);
-    else x[(size_t)t * d + c] = row[c];
-  }
+  for (int c = threadIdx.x; c < d; c += blockDim.x) x[(size_t)t * d + c] = embed[(size_t)id * d + c];
 }
-int launch_embed(const void* embed, const int32_t* tok, int T, int d, int vocab, int dtype,
-                 float* x, hipStream_t st) {
-  if (dtype == TRJ_BF16)
-    embed_kernel<uint16_t><<<T, 512, 0, st>>>((const uint16_t*)embed, tok, d, vocab, x);
-  else
-    embed_kernel<float><<<T, 256, 0, st>>>((const float*)embed, tok, d, vocab, x);
+int launch_embed(const float* embed, const int32_t* tok, int T, int d, int vocab, float* x, hipStream_t st) {
+  embed_kernel<<<T, 256, 0, st>>>(embed, tok, d, vocab, x);
   return check_launch();
 }
 

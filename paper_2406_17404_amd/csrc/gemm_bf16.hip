@@ -37,8 +37,8 @@ static GemmShape plan_few(int mt, int ntiles, int ksteps, int split, int* rows, 
   int best = 1;
   long best_cost = -1;
   for (int n : {1, 2, 3, 4, 16}) {
-    // four token tiles: three row tiles measured 40.5 against 43.0 us (22016 x 4096); four are
-    // the documented plan of that workload
+    // four token tiles: three row tiles measured faster (22016 x 4096: 40.5 against 43.0 us), but
+    // four row tiles are the documented plan of that workload, which is kept
     if (n == 3 && mt == 4) continue;
     const long cost = ((long)(ntiles + n - 1) / n * split + 255) / 256 * (n + mt);
     if (best_cost < 0 || cost < best_cost) { best = n; best_cost = cost; }
@@ -49,8 +49,10 @@ static GemmShape plan_few(int mt, int ntiles, int ksteps, int split, int* rows, 
   if (best == 16) return GS_16;
   if (best == 1) { *kw = 4; return GS_1x4; }
   if (best == 3) { *kw = 2; return GS_3x2; }
-  // two row tiles: four k-parts pay on long k ranges only (12288 x 4096 at 32 rows 18.8 against
-  // 18.9 us; 4096 x 4096 split four ways at 128 rows 12.8 against 11.8)
+  // two row tiles: four k-parts do not pay on short k ranges (4096 x 4096 split four ways at 128
+  // rows 12.8 against 11.8 us) and hardly on long ones (12288 x 4096 at 32 rows 18.8 against
+  // 18.9); at 128 rows two measured faster there too (27.8 against 30.6), but four are the
+  // documented plan of that workload, which is kept
   if (best == 2) { *kw = ksteps / split >= 128 ? 4 : 2; return *kw == 4 ? GS_2x4 : GS_2x2; }
   if (mt < 4 || split > 1) return GS_4x1;  // 64 rows, 32000 x 4096: 45.7 against 45.4 us with two k-parts
   *kw = 2;                                 // 128 rows, 28672 x 4096: 44.7 against 45.1
@@ -181,8 +183,8 @@ int launch_gemm_store_f32(const uint16_t* xp, const uint16_t* w, int T, int tp, 
 // bf16(x * g) in the tiled activation layout, NOT yet divided by the row's norm: each
 // workgroup owns one column part (about 1024 columns) of one token row and writes that part's sum of x^2 to
 // ssq[part][t]; the consuming projection divides (RowScale).  Rows t >= T of the padded tile
-// are written as zeros.  Without partials the row comes from the embedding table instead
-// (x[t] = E[tok[t]], ids outside [0, vocab) clamped).
+// are written as zeros.  Without partials x is only read; with an embedding table the row comes
+// from it instead (x[t] = E[tok[t]], ids outside [0, vocab) clamped).
 constexpr int RN_MAX_THREADS = 256, RN_SB = 8;
 // column parts of a row: about 1024 columns each, at most RS_MAX_PARTS
 int reduce_norm_parts(int d) {

@@ -8,7 +8,7 @@ namespace trj {
 struct Tunables {
   int gemm_target_wgs = 256;   // split-k is raised until a GEMM has this many workgroups
   int max_split_k = 8;
-  int gemm_cfg = 0;            // 0: choose the workgroup shape per GEMM; 1..4 force one
+  int gemm_cfg = 0;            // 0: choose the workgroup shape per GEMM; 1..6 force one
   int gemm_big_t = 256;        // padded token rows from which wavefronts own two row tiles (0: never)
   int attn_target_wgs = 256;   // attention workgroups per launch aimed at (one per CU)
   int gemm_big_wt = 0;         // row tiles per wavefront of the many-rows kernel (2, 4; 0 = choose)
@@ -135,8 +135,7 @@ int launch_pack_weight(void* dst, const void* src, int n_out, int n_in, int dtyp
 // f32_kernels.hip
 int launch_rope_table(const int32_t* row_pos, int T, int dh, float theta, float2* cs,
                       hipStream_t st);
-int launch_embed(const void* embed, const int32_t* tok, int T, int d, int vocab, int dtype,
-                 float* x, hipStream_t st);
+int launch_embed(const float* embed, const int32_t* tok, int T, int d, int vocab, float* x, hipStream_t st);
 // g: RMSNorm's gain, applied to x with its division (null: x as it is); add_to: y += instead of y =
 int launch_gemm_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_out, int add_to,
                     float* y, hipStream_t st);
@@ -186,9 +185,9 @@ int launch_gemm_qkv(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_
                     int n_kv_heads, int dh, int s_pool, const RowScale& rs, const float2* cs,
                     const int32_t* cs_row, const int32_t* row_slot, uint16_t* q, uint16_t* k_layer,
                     uint16_t* v_layer, hipStream_t st);
-// n_split == 0: x is complete already and only read.
-// x[t] = E[tok[t]] (more than PREP_MAX_SEQS sequences), or x[t] += the split-k partial sums; hp = bf16(x * g) tiled and the
-// rows' partial sums of squares for the consumer's RowScale, one launch
+// x[t] = E[tok[t]] (more than PREP_MAX_SEQS sequences), or x[t] += the split-k partial sums
+// (n_split == 0: x is complete already and only read); hp = bf16(x * g) tiled and the rows'
+// partial sums of squares for the consumer's RowScale, one launch
 int launch_embed_norm(const uint16_t* embed, const int32_t* tok, int T, int d, int vocab, float* x,
                       const float* g, int tp, uint16_t* hp, float* ssq, hipStream_t st);
 int launch_reduce_norm(const float* partial, int n_split, float* x, const float* g, int T, int d,

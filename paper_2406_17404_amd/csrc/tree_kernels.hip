@@ -240,7 +240,8 @@ int launch_tree_prep(const int32_t* parent, const int32_t* node_off, const int32
 //   1            validity of all sequences, the attention work list, rows that no valid
 //                sequence covers
 //   tp - T       padding rows of the attention output
-//   tp           embedding and first norm input of one row (bf16), or the embedding (fp32)
+//   tp / rows    embedding and first norm input of embed_rows rows (bf16), or T: the embedding
+//                of one row (fp32)
 // Above PREP_MAX_SEQS the launches stay separate: the one workgroup that sees all sequences
 // would take longer than they do.
 __device__ inline void zero_row(const StepPrep& a, int t, int first, int stride) {
@@ -473,7 +474,7 @@ __global__ __launch_bounds__(1024) void tmpl_step_prep_kernel(
     int blocks_per_item, int nsplit_max, int32_t* __restrict__ items, uint32_t* __restrict__ zero,
     size_t zero_words, int zero_wgs, EmbedRow e) {
   const int tid = threadIdx.x;
-  if (blockIdx.x > zero_wgs) {  // embedding and first norm input, one row each
+  if (blockIdx.x > zero_wgs) {  // embedding and first norm input, embed_rows rows each
     embed_row(e, blockIdx.x - 1 - zero_wgs);
     return;
   }
@@ -542,7 +543,8 @@ int launch_template_step_prep(const TemplateView& v, const int32_t* node_off, co
 // One workgroup per row; lowest index wins ties; NaN never compares greater.
 // One workgroup per row; every thread keeps ARGMAX_UNROLL 16-byte loads in flight (the row
 // is read once, so the kernel is a latency chain unless the loads are batched: a row of 32000
-// is one batch of eight, 64 such rows 7.2 -> 6.5 us).
+// is one batch of eight, 64 such rows 7.0 -> 6.5 us in the kernel; accept_path with kv_compact,
+// three launches, does not show it).
 constexpr int ARGMAX_THREADS = 1024, ARGMAX_UNROLL = 8;
 __device__ inline void amax_merge(float& bv, int& bi, float v, int i) {
   if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
@@ -601,8 +603,8 @@ int launch_argmax(const float* logits, int T, int V, int32_t* out, hipStream_t s
 // lane + 64): node i is accepted when its token is the prediction at its parent and the parent
 // is accepted (the root always is); best = max over accepted nodes of (depth, -index).  Depth
 // and acceptance come by pointer doubling on registers passed between lanes, at most 7 rounds
-// and no barrier (64 rows: walking the parents in LDS 3.1 us a launch, doubling in LDS with
-// barriers 4.3, this 3.0; a 128-node chain takes 127 steps to walk).
+// and no barrier (64 rows, the kernel alone: walking the parents in LDS 2.9 us, doubling in LDS
+// with barriers 4.3, this 2.7; a 128-node chain takes 127 steps to walk).
 struct Accepted {
   int depth, best, bonus;  // depth of the best node, -1 for a malformed sequence; uniform
   int path[2];             // nodes lane and lane + 64 of the path, root first; -1 behind its end
