@@ -49,9 +49,9 @@ int32_t trj_dev_attn_plan(int32_t B, int32_t T, int32_t n_heads, int32_t head_di
  * projection kernel is used, 0: never), "gemm_big_wt" (row tiles per wavefront of that
  * kernel: 2, 4, or 0 to choose per projection), "attn_target_wgs" (attention workgroups aimed at
  * per launch), "attn_min_bpw" (32-slot blocks per key stream, at least; 0 = chosen from the tree
- * size), "attn_xchg_min_blocks" (32-slot blocks of 32 heads per query tile from which the
- * wavefronts of a key stream share its K/V through rings in LDS, heads of 128 that share no
- * K/V; 1: always).  Results do not depend on them beyond fp32 summation order and, in the
+ * size), "attn_xchg_min_blocks" (32-slot blocks of 32 heads from which the wavefronts of a
+ * key stream share its K/V through rings in LDS for one query tile, twice as many for two and
+ * 8/3 as many for more; heads of 128 that share no K/V; 1: always).  Results do not depend on them beyond fp32 summation order and, in the
  * attention, which keys set the softmax reference.  Unknown name: TRJ_ERR_BAD_SHAPE. */
 int32_t trj_set_tunable(const char* name, int32_t value);
 

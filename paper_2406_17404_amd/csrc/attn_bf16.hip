@@ -662,21 +662,23 @@ AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int m
   int nb = (max_seq_slots + 31) / 32;
   if (nb < 1) nb = 1;
   // The ring pays where so many blocks stream from HBM that it matters how much is in flight
-  // and that none is asked for twice: from 1536 (block, head) pairs of 16 KiB per query tile,
-  // as blocks with more queries are worked on for longer.  Query heads that share K/V find it
+  // and that none is asked for twice: from 48 blocks of 32 heads (of 16 KiB each) for one query
+  // tile, 96 for two and 128 for more, as blocks with more queries are worked on for longer
+  // and four tiles then share them.  Query heads that share K/V find it
   // in L2, as do the chunks of a prompt (1000 tokens: ring 29.8, R 27.2), and halves of it
   // (heads of 64) arrive in time anyway.
   //   rows x slots        5x1024 5x2048 5x4096 33x2048 33x4096 97x1024 97x2048 97x4096
-  //   pairs / 1536 tiles    0.7   1.4    2.7     0.7     1.4     0.2     0.3     0.7
-  //   ring (2 tiles)       12.7   15.5   20.3    18.0    22.6    20.2    24.6    31.0
+  //   blocks / limit        0.7   1.4    2.7     0.7     1.4     0.3     0.5     1.0
+  //   ring                 12.7   15.5   20.3    18.0    22.6    20.2    24.6  4r 31.1
   //   R                    12.3   15.3   20.6    17.5    23.3    18.2    22.3    30.1
+  // (69 rows on 4096: 4r 26.4, R 27.8; 128 with K/V of three inputs in turn: 4r 25.5, R 26.4.)
   // 16 packed sequences of 64 rows, up to 2048 slots: ring 69.6, R 85.7; four query heads per
   // K/V head, 97 rows on 4096 slots: ring 30.8, R 28.2, 16 sequences of 16 rows 72.1, 63.1.
   // Heads of 64 with one tile are the exception: two short blocks in flight from the start save
   // 1 us of a call at every length (16 heads, 512 slots: 11.4, 12.6).
   const int tiles = T > 64 * B ? 4 : T > 32 * B ? 2 : 1;  // on average: the sizes are device data
   const long pairs = (long)nb * B * n_heads, xchg = tune().attn_xchg_min_blocks;
-  const long least = xchg > 1 ? 32 * xchg * tiles : 0;    // 48 blocks of 32 heads per tile
+  const long least = xchg > 1 ? 32 * xchg * (tiles == 4 ? 8 : 3 * tiles) / 3 : 0;
   p.ring = !shared_kv && (dh == 128 ? pairs >= least : nmax <= 32);
   // Query tiles per workgroup: one or two with four key streams; and four with two streams, so
   // that a tree of more than 64 rows needs no second pass over the sequence, where this fills

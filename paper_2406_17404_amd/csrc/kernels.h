@@ -12,7 +12,7 @@ struct Tunables {
   int gemm_big_t = 256;        // padded token rows from which wavefronts own two row tiles (0: never)
   int attn_target_wgs = 256;   // attention workgroups per launch aimed at (one per CU)
   int gemm_big_wt = 0;         // row tiles per wavefront of the many-rows kernel (2, 4; 0 = choose)
-  int attn_xchg_min_blocks = 48;  // blocks of 32 heads per query tile from which K/V go through rings (1: always)
+  int attn_xchg_min_blocks = 48;  // blocks of 32 heads from which K/V go through rings, one query tile (1: always)
   int attn_min_bpw = 0;        // 32-slot blocks per key stream, at least (0: chosen from the tree size)
 };
 // trj_set_tunable writes the process-wide set; every entry point copies it once on entry

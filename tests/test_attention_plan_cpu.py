@@ -33,7 +33,7 @@ def test_every_plan_covers_its_rows_and_slots_and_fits_the_workspace():
     (1, 97, 1024 + 97, 32, 128, False, 0, 2), (1, 128, 512 + 128, 32, 128, False, 0, 2),
     (1, 97, 4096 + 97, 32, 128, True, 0, 2), (16, 16, 4112, 32, 128, True, 0, 2), (1, 64, 1088, 32, 128, False, 0, 2),
     (1, 5, 782, 32, 128, False, 0, 1), (1, 64, 8256, 32, 128, False, 1, 2), (16, 64, 4160, 32, 128, False, 1, 2),
-    (1, 100, 8292, 32, 128, False, 1, 4), (16, 69, 2117, 32, 128, False, 1, 4), (4, 69, 2117, 32, 128, False, 1, 4),
+    (1, 100, 8292, 32, 128, False, 1, 4), (1, 128, 4224, 32, 128, False, 1, 4), (1, 128, 2176, 32, 128, False, 0, 2), (16, 69, 2117, 32, 128, False, 1, 4), (4, 69, 2117, 32, 128, False, 1, 4),
     (3, 128, 2176, 32, 128, False, 1, 2), (4, 128, 4224, 32, 128, False, 1, 2), (8, 97, 4193, 32, 128, False, 1, 2),
     (12, 97, 4193, 16, 64, False, 0, 2), (1, 16, 528, 16, 64, False, 1, 1)])
 def test_form_and_tiles(B, n, slots, H, dh, shared, ring, tiles):
