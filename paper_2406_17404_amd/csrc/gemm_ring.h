@@ -137,6 +137,20 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
   const uint8_t* xs = reinterpret_cast<const uint8_t*>(a.xp) + ((size_t)ph0 * PH * ttiles + tt0) * 1024;
   const uint8_t* ws = reinterpret_cast<const uint8_t*>(a.w) + ((size_t)tile0 * ksteps + (size_t)ph0 * PH) * 1024;
   const size_t xstep = (size_t)PH * ttiles * 1024;
+  // Few rows: every workgroup starts at another phase of its k range (spread by the golden ratio)
+  // and goes round.  In step, all of them would ask the same memory channels for W (row tiles lie
+  // whole multiples of 4 KiB apart), and activations that the launch before has just written would
+  // miss in a die's L2 for all its workgroups at once; spread out, each fetches its share for the
+  // others.  Up to 1 MiB of activations (128 x 4096), which stay in the L2 together; not with a
+  // single row tile, where activations are most of what is read; and where all phases are whole.
+  // In the step, us: 22016 x 4096 at 128 rows 49.0 -> 44.6, 12288 x 4096 at 128 35.3 -> 34.3, at 64
+  // 25.7 -> 25.2, 128256 x 4096 at 96 180 -> 166, 32000 x 4096 at 64 47.5 -> 45.1, 4096 x 4096 at
+  // 32 9.1 -> 7.8.  Left out: 4096 x 11008 at 128 rows 26.9 -> 27.3, 6144 x 4096 at 96 23.4 -> 23.9.
+  const bool tail = ksteps % PH != 0;
+  const bool spread = NT && WR > 1 && !tail && a.tp * a.n_in <= 1 << 19;
+  const int rot = spread ? (int)(((blockIdx.x >> 3) * 40503u + (blockIdx.x & 7) * 8192u & 0xffffu) * n >> 16) : 0;
+  xs += rot * xstep;
+  ws += (size_t)rot * PH * 1024;
   // piece p of a phase: X (k-step p / XC, token tile p % XC), then W (row tile, k-step);
   // tiles past the matrix' end and k-steps past kmax are read from the last one instead
   auto piece = [&](int p, int kmax) -> uint32_t {
@@ -147,8 +161,7 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
   uint32_t voff[PL];
 #pragma unroll
   for (int j = 0; j < PL; ++j) voff[j] = piece(min(j * NW + wv, P - 1), PH - 1);
-  const bool tail = ksteps % PH != 0;
-  int iph = ph0;                         // next phase to request
+  int iph = ph0;                         // requests made, from ph0 on
   uint32_t ibuf = lds0 + wv * 1024;      // this wavefront's first piece in its buffer
   u32x4 held[ALIGNED ? 1 : PL];          // pieces of the youngest phase, and where they belong
   uint32_t hbuf = 0;
@@ -184,6 +197,10 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
     xs += xstep;
     ws += PH * 1024;
     ++iph;
+    if (NT && iph == ph0 + n - rot) {  // round
+      xs -= n * xstep;
+      ws -= (size_t)n * PH * 1024;
+    }
     ibuf = ibuf + BUF >= lds0 + NB * BUF ? ibuf + BUF - NB * BUF : ibuf + BUF;
   };
   auto wait_younger = [&](auto k_c) {  // everything but the youngest K phases has landed
