@@ -187,8 +187,8 @@ __device__ __forceinline__ void attn_wait() {
 // next V behind them, and never meets the others before the merge; operands may start anywhere.
 // SELF: one sequence and no prologue launch: every workgroup checks the sequence and works the
 // ancestor bits out for itself (pointer doubling on the lanes of each wavefront), which saves a
-// launch of 5 to 6 us for 0.4 to 2 us more in this one (5 rows on 1024 slots 11.6 against 10.8
-// us, 64 rows 17.2 against 15.6).
+// launch of 5 to 6 us.  The parents are asked for first and the bits worked out only by streams
+// that come to the tree (see own_bits).
 template <int DH, int NTW, int KS, int D, bool RING, bool SELF>
 __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArgs a) {
   constexpr int KSTEPS = DH / 16, MTV = DH / 32, SLOTS = 2 * D;
@@ -315,40 +315,59 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
                                                         __builtin_bit_cast(bf16x8, pk[kg]), o[mt], 0, 0, 0);
   };
   // SELF: the ancestor bits from the parents, par[h] = parent of node lane + 64 h (anything
-  // from node n on); false if the tree is malformed (the same in every wavefront)
+  // from node n on); false if the tree is malformed (the same in every wavefront).  Only streams
+  // that come to the tree's own slots need the bits, and trees of up to 64 nodes only half of the
+  // work.  Parents behind the queries and all bits in every wavefront took, us of a call: 16 rows on
+  // 512 slots 13.3 (now 12.1), 32 on 900 15.6 (14.5), 64 on 8192 36.7 (35.2).
+  const bool meets_tree = nblk > 0 && (b0 + ks + (nblk - 1) * KS) * 32 + 32 > L;  // uniform
+  auto bits_of = [&](const int (&par)[2], auto halves_c) {
+    constexpr int HV = decltype(halves_c)::value, W = 2 * HV;  // nodes per lane, words of a row
+    int jump[2], b[W][2];  // nearest ancestor whose bit is not in the row yet (255: none); the row's words
+    auto value = [&](const int (&v)[2], int node) { return HV == 1 ? __shfl(v[0], node & 63) : from_node(v, node); };
+#pragma unroll
+    for (int h = 0; h < HV; ++h) {
+      const int i = lane + 64 * h, p = i < n ? par[h] : -1;
+      jump[h] = p < 0 ? 255 : p & 127;
+#pragma unroll
+      for (int w = 0; w < W; ++w) b[w][h] = i >> 5 == w ? (int)(1u << (i & 31)) : 0;
+    }
+    while (__ballot(jump[0] != 255 || (HV > 1 && jump[HV - 1] != 255))) {
+      int u[W + 1][2];
+#pragma unroll
+      for (int h = 0; h < HV; ++h) {
+        u[W][h] = value(jump, jump[h] & 127);
+#pragma unroll
+        for (int w = 0; w < W; ++w) u[w][h] = value(b[w], jump[h] & 127);
+      }
+#pragma unroll
+      for (int h = 0; h < HV; ++h) {
+        if (jump[h] == 255) continue;
+#pragma unroll
+        for (int w = 0; w < W; ++w) b[w][h] |= u[w][h];
+        jump[h] = u[W][h];
+      }
+    }
+    uint32_t r[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const int word = value(b[w], qc);
+      r[w] = qi < n ? (uint32_t)word : 0u;
+    }
+    anc0 = (uint64_t)r[1] << 32 | r[0];
+    anc1 = (uint64_t)r[3] << 32 | r[2];
+  };
   auto own_bits = [&](const int (&par)[2]) -> bool {
-    int jump[2], b[4][2];  // nearest ancestor whose bit is not in the row yet (255: none); the row's words
     bool bad = false;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int i = lane + 64 * h, p = i < n ? par[h] : -1;
-      bad = bad || (i < n && (i == 0 ? p != -1 : (p < 0 || p >= i)));
-      jump[h] = p < 0 ? 255 : p & 127;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) b[w][h] = i >> 5 == w ? (int)(1u << (i & 31)) : 0;
+      const int i = lane + 64 * h;
+      bad = bad || (i < n && (i == 0 ? par[h] != -1 : (par[h] < 0 || par[h] >= i)));
     }
     if (__ballot(bad)) return false;
-    while (__ballot(jump[0] != 255 || jump[1] != 255)) {
-      int u[5][2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        u[4][h] = from_node(jump, jump[h] & 127);
-#pragma unroll
-        for (int w = 0; w < 4; ++w) u[w][h] = from_node(b[w], jump[h] & 127);
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (jump[h] == 255) continue;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) b[w][h] |= u[w][h];
-        jump[h] = u[4][h];
-      }
-    }
-    uint32_t r[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) r[w] = qi < n ? (uint32_t)from_node(b[w], qc) : 0u;
-    anc0 = (uint64_t)r[1] << 32 | r[0];
-    anc1 = (uint64_t)r[3] << 32 | r[2];
+    anc0 = anc1 = 0;
+    if (!meets_tree) return true;
+    if (n <= 64) bits_of(par, std::integral_constant<int, 1>{});
+    else bits_of(par, std::integral_constant<int, 2>{});
     return true;
   };
   auto self_status = [&](bool ok) {  // the verdict on the tree, and zeros for its rows if it is malformed
@@ -482,13 +501,14 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       p += (size_t)KS * KSTEPS * 64;
     };
     const uint16_t* qp = a.q + ((size_t)(r0 + qc) * a.n_heads + head) * DH + hh * 8;
-#pragma unroll
-    for (int k = 0; k < KSTEPS; ++k) qreg[k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * k));
     int par[2];
-    if constexpr (SELF) {
+    if constexpr (SELF) {  // first: they are needed first
 #pragma unroll
       for (int h = 0; h < 2; ++h) par[h] = a.parent[r0 + min(lane + 64 * h, n - 1)];
-    } else {
+    }
+#pragma unroll
+    for (int k = 0; k < KSTEPS; ++k) qreg[k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * k));
+    if constexpr (!SELF) {
       anc0 = a.anc[2 * (size_t)(r0 + qc)];
       anc1 = a.anc[2 * (size_t)(r0 + qc) + 1];
     }
@@ -597,35 +617,50 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
 // thread (lane, mt, half) owns the 8 accumulator registers v = 8*half .. 8*half+7 of tile mt
 // that lane `lane` of the attention wavefront held, i.e. query lane%32, 8 columns.  The loads
 // of a batch of splits are all issued together (clamped, never predicated).
-template <int DH>
+template <int DH, int CB>
 __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
-  constexpr int CB = 8, MTV = DH / 32, OW = MTV * 16 * 64;
+  constexpr int MTV = DH / 32, OW = MTV * 16 * 64;
   const int tile = blockIdx.x % a.tiles_per_seq, s = blockIdx.x / a.tiles_per_seq;
   const int head = blockIdx.y;
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int mt = grp >> 1, v0 = (grp & 1) * 8;
   if (mt >= MTV) return;
-  if (a.status_dev[s] != 0) return;  // rows of malformed sequences stay zero
-  const int r0 = a.node_off[s], n = a.node_off[s + 1] - r0;
-  if (tile * 32 >= n) return;
-  const int nb = (a.prefix_len[s] + n + 31) >> 5;
-  const int nsplit = (nb + a.bpwg - 1) / a.bpwg;
-  if (nsplit == 1) return;  // written by the attention kernel itself
   const int n32 = lane & 31, hh = lane >> 5;
   const size_t base = (((size_t)s * a.tiles_per_seq + tile) * a.n_heads + head) * a.nsplit_max;
-  float mrun = NEG_BIG, lrun = 0.f;
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int k0 = 0; k0 < nsplit; k0 += CB) {
-    float ms[CB], ls[CB], x[CB][8];
+  // The first splits' partials are asked for together with what says how many there are: waiting
+  // for one after the other was a third of this launch (4.2 -> 3.1 us for three splits of 16 rows).
+  // Splits that do not exist are left out of maximum and sum, whatever their memory holds.
+  const int status = a.status_dev[s], r0 = a.node_off[s], r1 = a.node_off[s + 1], L = a.prefix_len[s];
+  float ms[CB], ls[CB], x[CB][8];
+  auto load = [&](int k0, int last) {
 #pragma unroll
     for (int j = 0; j < CB; ++j) {
-      const int k = min(k0 + j, nsplit - 1);
+      const int k = min(k0 + j, last);
       ms[j] = a.pm[(base + k) * 32 + n32];
       ls[j] = a.pl[(base + k) * 32 + n32];
       const float* img = a.po + (base + k) * OW + (mt * 16 + v0) * 64 + lane;
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[j][e] = img[e * 64];
     }
+  };
+  load(0, a.nsplit_max - 1);
+  const int n = r1 - r0;
+  if (status != 0 || tile * 32 >= n) return;  // rows of malformed sequences stay zero
+  const int nb = (L + n + 31) >> 5;
+  const int nsplit = (nb + a.bpwg - 1) / a.bpwg;
+  if (nsplit == 1) return;  // written by the attention kernel itself
+  float mrun = NEG_BIG, lrun = 0.f;
+  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int k0 = 0; k0 < nsplit; k0 += CB) {
+    if (k0 > 0) load(k0, nsplit - 1);
+#pragma unroll
+    for (int j = 0; j < CB; ++j)
+      if (k0 + j >= nsplit) {
+        ms[j] = NEG_BIG;
+        ls[j] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[j][e] = 0.f;
+      }
     float mb = mrun;
 #pragma unroll
     for (int j = 0; j < CB; ++j) mb = fmaxf(mb, ms[j]);
@@ -635,7 +670,7 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
     for (int e = 0; e < 8; ++e) acc[e] *= resc;
 #pragma unroll
     for (int j = 0; j < CB; ++j) {
-      const float wgt = k0 + j < nsplit ? exp2f(ms[j] - mb) : 0.f;
+      const float wgt = exp2f(ms[j] - mb);
       lrun += wgt * ls[j];
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] += wgt * x[j][e];
@@ -810,8 +845,10 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
   if (rc || nsplit_max == 1) return rc;
   ProfScope ps_(KC_ATTN_COMBINE, st);
   dim3 cgrid(B * tiles_per_seq, n_heads);
-  if (dh == 128) attn_combine_kernel<128><<<cgrid, 512, 0, st>>>(a);
-  else attn_combine_kernel<64><<<cgrid, 512, 0, st>>>(a);
+  if (dh == 128 && nsplit_max <= 4) attn_combine_kernel<128, 4><<<cgrid, 512, 0, st>>>(a);
+  else if (dh == 128) attn_combine_kernel<128, 8><<<cgrid, 512, 0, st>>>(a);
+  else if (nsplit_max <= 4) attn_combine_kernel<64, 4><<<cgrid, 512, 0, st>>>(a);
+  else attn_combine_kernel<64, 8><<<cgrid, 512, 0, st>>>(a);
   return check_launch();
 }
 
