@@ -13,8 +13,10 @@
 // The ancestor bit rows mask only the blocks that overlap the tree's own slots.
 //
 // What bounds it: on long sequences the rate at which K/V arrive, i.e. how much is in flight
-// and that no byte is asked for twice; on short ones (up to about 1000 slots) some 9 us of
-// launch, first loads, merge and stores.  Two forms of the walk, chosen by the launch plan
+// and that no byte is asked for twice; on short ones (up to about 1000 slots) some 8 us of
+// launch, first loads, merge and stores, one after the other (100 slots x 5 rows, from the first
+// workgroup's start: sequence known 1.0 us, parents there 2.7, K there 3.3, the tree's block done
+// 6.2, streams merged 6.9, stored 7.9).  Three forms of the walk, chosen by the launch plan
 // (figures at attn_bf16_plan):
 //  - registers: every wavefront loads its blocks by itself, the next K while this block's
 //    softmax and P*V run and the next V behind them.  No wavefront waits for another before the
@@ -24,6 +26,8 @@
 //    soon as K of block i has been read by all of them.  More is in flight and each byte is
 //    asked for once, which pays for the two meetings per block and the second way through LDS
 //    where K/V stream from HBM.
+//  - at once: up to two blocks per stream, all requested together into LDS, with one meeting for
+//    K and one for V.
 // Loads of blocks that no other workgroup (rings) or wavefront (registers) reads carry the
 // streaming hint.
 // The wavefronts of a workgroup merge their (m, l, O) through LDS in a fixed order.  If
@@ -40,6 +44,7 @@
 
 namespace trj {
 
+enum AttnForm { AF_REGISTERS, AF_RING, AF_ONCE };  // see the top
 constexpr float NEG_BIG = -1e30f;
 constexpr float SOFTMAX_LAG = 8.f;  // see softmax_tile_prefix; smaller weights are below a bf16 step of the largest
 
@@ -181,15 +186,16 @@ __device__ __forceinline__ void attn_wait() {
   else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
-// NTW query tiles x KS key streams of wavefronts.  RING: a stream's blocks come through a ring of
-// D blocks in LDS; all operands start at multiples of 16 bytes.  Otherwise every wavefront loads
+// NTW query tiles x KS key streams of wavefronts.  AF_RING: a stream's blocks come through a ring of
+// D blocks in LDS; AF_ONCE: at most D of them, all at once; all operands start at multiples of 16
+// bytes.  AF_REGISTERS: every wavefront loads
 // its blocks into registers by itself, the next K while this block's softmax and P*V run and the
 // next V behind them, and never meets the others before the merge; operands may start anywhere.
 // SELF: one sequence and no prologue launch: every workgroup checks the sequence and works the
 // ancestor bits out for itself (pointer doubling on the lanes of each wavefront), which saves a
 // launch of 5 to 6 us.  The parents are asked for first and the bits worked out only by streams
 // that come to the tree (see own_bits).
-template <int DH, int NTW, int KS, int D, bool RING, bool SELF>
+template <int DH, int NTW, int KS, int D, AttnForm FORM, bool SELF>
 __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArgs a) {
   constexpr int KSTEPS = DH / 16, MTV = DH / 32, SLOTS = 2 * D;
   constexpr int OW = MTV * 16 * 64;     // floats of one wavefront's O tile
@@ -376,7 +382,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
     if (qg == 0 && head == 0 && tid == 0) a.status[0] = !ok;
   };
 
-  if constexpr (RING) {
+  if constexpr (FORM != AF_REGISTERS) {
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem;
     const uint32_t ring = __builtin_amdgcn_readfirstlane(lds0 + ks * SLOTS * SLOT);
     const u32x4* ring_r = reinterpret_cast<const u32x4*>(smem + (size_t)ks * SLOTS * SLOT + lane * 16);
@@ -417,19 +423,33 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
         fetch(a.anc + 2 * (size_t)r0, (uint32_t)qc * 16, ANC_AT + nt * 1024);
       }
     }
+    if constexpr (FORM == AF_RING) {
 #pragma unroll
-    for (int i = 0; i < D; ++i)
-      if (i < nblk) {
-        request(kp, 2 * i);
-        request(vp, 2 * i + 1);
-      }
+      for (int i = 0; i < D; ++i)
+        if (i < nblk) {
+          request(kp, 2 * i);
+          request(vp, 2 * i + 1);
+        }
+    } else {  // all of the range (the plan keeps it to D blocks per stream), K first
+#pragma unroll
+      for (int i = 0; i < D; ++i)
+        if (i < nblk) request(kp, 2 * i);
+#pragma unroll
+      for (int i = 0; i < D; ++i)
+        if (i < nblk) request(vp, 2 * i + 1);
+    }
 
     auto read = [&](u32x4 (&r)[KSTEPS], int sl) {
 #pragma unroll
       for (int k = 0; k < KSTEPS; ++k) r[k] = ring_r[(sl * HALF + k) * 64];
     };
-    // queries, bits and K of the first block: behind it its V and the blocks already requested
-    if (nblk >= D) attn_wait<(2 * D - 1) * HP, true>();
+    // queries, bits and K of the first block: behind it its V and the blocks already requested (at
+    // once: every K has landed, the V are on the way)
+    if constexpr (FORM == AF_ONCE) {
+      if (nblk >= 2) attn_wait<2 * HP, true>();
+      else if (nblk == 1) attn_wait<HP, true>();
+      else attn_wait<0, true>();
+    } else if (nblk >= D) attn_wait<(2 * D - 1) * HP, true>();
     else if (D > 2 && nblk == 2) attn_wait<3 * HP, true>();
     else if (nblk == 1) attn_wait<HP, true>();
     else attn_wait<0, true>();
@@ -447,6 +467,29 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       const u32x4 bits = reinterpret_cast<const u32x4*>(smem + ANC_AT + nt * 1024)[lane];
       anc0 = qi < n ? (uint64_t)bits[1] << 32 | bits[0] : 0;
       anc1 = qi < n ? (uint64_t)bits[3] << 32 | bits[2] : 0;
+    }
+    if constexpr (FORM == AF_ONCE) {
+      // only one more meeting, for V, behind the first block's scores and softmax
+      static_assert(D == 2, "waits above");
+      const int key0 = (b0 + ks) * 32;
+      float alpha;
+      u32x4 pk[2];
+      const bool some = live && nblk > 0;
+      if (some) {
+        read(kreg, 0);
+        softmax(scores(), key0, alpha, pk);
+      }
+      attn_wait<0, true>();
+      if (some) {
+        read(vreg, 1);
+        add_values(key0, alpha, pk);
+      }
+      if (live && nblk > 1) {
+        read(kreg, 2);
+        read(vreg, 3);
+        softmax(scores(), key0 + KS * 32, alpha, pk);
+        add_values(key0 + KS * 32, alpha, pk);
+      }
     }
     // Block i of this stream: its K is in kreg; its V and the next blocks are on the way (slots
     // 2(i%D)+1, ..).  AHEAD: blocks behind it, D when there are at least as many; then block i+D
@@ -474,7 +517,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       if constexpr (AHEAD > 0) read(kreg, next);
       add_values(key0, alpha, pk);
     };
-    if (nblk > 0) {
+    if (FORM == AF_RING && nblk > 0) {
       read(kreg, 0);
       int i = 0;
       for (; i + D < nblk; ++i) block(i, std::integral_constant<int, D>{});
@@ -484,7 +527,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       if (nblk - 1 - i >= 1) block(i++, std::integral_constant<int, 1>{});
       block(i, std::integral_constant<int, 0>{});
     }
-    if (MEET && nblk < rounds) {  // a stream with a block less than the others meets them as often
+    if (FORM == AF_RING && MEET && nblk < rounds) {  // a stream with a block less than the others meets them as often
       attn_wait<0, MEET>();
       attn_wait<0, MEET>();
     }
@@ -762,6 +805,12 @@ AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int m
   if (b > nb) b = nb;
   p.bpwg = b;
   p.nsplit_max = (nb + b - 1) / b;
+  // Two tiles whose workgroup has at most two blocks per stream: all of it at once into LDS, where
+  // both tiles read it and nobody waits for a block behind another.  us of a call, registers -> at
+  // once: 64 rows on 777 slots 17.0 -> 16.7, 1024 17.2 -> 16.0, 1500 19.6 -> 18.5; in a step of two
+  // layers 96 rows on 500 312.9 -> 310.6, grouped-query 69 on 1024 438.8 -> 437.4.  One tile has
+  // nothing to share (16 rows on 512: 12.1 -> 12.8).
+  p.once = dh == 128 && p.ntw == 2 && !p.ring && b <= 8;
   return p;
 }
 
@@ -810,33 +859,36 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
   {
     ProfScope ps_(KC_ATTN, st);
     // loads without registers need operands on multiples of 16 bytes
-    const bool ring = p.ring && (((uintptr_t)q | (uintptr_t)k_layer | (uintptr_t)v_layer | (uintptr_t)anc) & 15) == 0;
-#define TRJ_ATTN_A(DH, Q, KS, D, RING, SELF)                                                      \
+    const bool aligned = (((uintptr_t)q | (uintptr_t)k_layer | (uintptr_t)v_layer | (uintptr_t)anc) & 15) == 0;
+    const bool ring = p.ring && aligned, once = p.once && aligned;
+#define TRJ_ATTN_A(DH, Q, KS, D, FORM, SELF)                                                      \
   do {                                                                                          \
     constexpr size_t rings = (size_t)(KS * 2 * D + Q) * DH * 64 + Q * 1024;                     \
     constexpr size_t handed = (size_t)Q * DH * (KS - 1) * 128;                                  \
-    constexpr size_t lds = RING && rings > handed ? rings : handed;                                     \
-    auto kern = tree_attn_bf16_kernel<DH, Q, KS, D, RING, SELF>;                                  \
+    constexpr size_t lds = FORM != AF_REGISTERS && rings > handed ? rings : handed;                                     \
+    auto kern = tree_attn_bf16_kernel<DH, Q, KS, D, FORM, SELF>;                                  \
     static DeviceOnce once; /* per instantiation */                                             \
     allow_lds(once, kern, lds);                                                                 \
     kern<<<grid, KS * Q * 64, lds, st>>>(a);                                                    \
   } while (0)
-#define TRJ_ATTN(DH, Q, KS, D, RING)                                                            \
+#define TRJ_ATTN(DH, Q, KS, D, FORM)                                                            \
   do {                                                                                          \
-    if (parent) TRJ_ATTN_A(DH, Q, KS, D, RING, true);                                           \
-    else TRJ_ATTN_A(DH, Q, KS, D, RING, false);                                                 \
+    if (parent) TRJ_ATTN_A(DH, Q, KS, D, FORM, true);                                           \
+    else TRJ_ATTN_A(DH, Q, KS, D, FORM, false);                                                 \
   } while (0)
     if (dh == 128) {
-      if (ring && ntw == 1) TRJ_ATTN(128, 1, 4, 2, true);
-      else if (ring && ntw == 2) TRJ_ATTN(128, 2, 4, 2, true);
-      else if (ring) TRJ_ATTN(128, 4, 2, 3, true);
-      else if (ntw == 1) TRJ_ATTN(128, 1, 4, 2, false);
-      else if (ntw == 2) TRJ_ATTN(128, 2, 4, 2, false);
-      else TRJ_ATTN(128, 4, 2, 3, false);  // planned for the ring, operands off the grid
+      if (once && ntw == 1) TRJ_ATTN(128, 1, 4, 2, AF_ONCE);
+      else if (once) TRJ_ATTN(128, 2, 4, 2, AF_ONCE);
+      else if (ring && ntw == 1) TRJ_ATTN(128, 1, 4, 2, AF_RING);
+      else if (ring && ntw == 2) TRJ_ATTN(128, 2, 4, 2, AF_RING);
+      else if (ring) TRJ_ATTN(128, 4, 2, 3, AF_RING);
+      else if (ntw == 1) TRJ_ATTN(128, 1, 4, 2, AF_REGISTERS);
+      else if (ntw == 2) TRJ_ATTN(128, 2, 4, 2, AF_REGISTERS);
+      else TRJ_ATTN(128, 4, 2, 3, AF_REGISTERS);  // planned for the ring, operands off the grid
     } else {
-      if (ring) TRJ_ATTN(64, 1, 4, 2, true);
-      else if (ntw == 1) TRJ_ATTN(64, 1, 4, 2, false);
-      else TRJ_ATTN(64, 2, 4, 2, false);
+      if (ring) TRJ_ATTN(64, 1, 4, 2, AF_RING);
+      else if (ntw == 1) TRJ_ATTN(64, 1, 4, 2, AF_REGISTERS);
+      else TRJ_ATTN(64, 2, 4, 2, AF_REGISTERS);
     }
 #undef TRJ_ATTN
 #undef TRJ_ATTN_A

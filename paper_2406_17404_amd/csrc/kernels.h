@@ -200,6 +200,7 @@ struct AttnPlan {
   int ntw, qg_max;       // query tiles of 32 rows per workgroup, groups of them per sequence at most
   int bpwg, nsplit_max;  // 32-slot blocks per workgroup, key splits per sequence at most
   bool ring;             // K/V through rings in LDS, else registers
+  bool once;             // no ring: all of a workgroup's K/V to LDS at once
   float lag;             // how far the softmax reference may fall behind the running maximum (log2)
 };
 // shared_kv: several workgroups besides a sequence's query groups read the same K/V
