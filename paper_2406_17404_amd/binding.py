@@ -319,6 +319,11 @@ def tr_verify_step_template(desc: ModelDesc, weights: Weights, k_pool, v_pool, k
 
 # ------------------------------------------------------------------ decoding loop
 def _host_i32(values):
+    if getattr(values, "ndim", 0) == 1 and len(values) and str(values.dtype) in ("int32", "int64") \
+            and values.dtype.isnative:
+        # a numpy array as one copy (1000 tokens one by one: some 100 us of a prompt's call)
+        raw = values.astype("int32", copy=False).tobytes()
+        return (C.c_int32 * len(values)).from_buffer_copy(raw), len(values)
     values = [int(v) for v in values]
     return (C.c_int32 * max(1, len(values)))(*values), len(values)
 

@@ -57,6 +57,11 @@ struct LoopConst {  // host -> device once per tree shape
   int32_t kv_off;
   int32_t pad;
 };
+struct Upload {  // what goes up in front of everything, in one copy
+  LoopIn in;
+  LoopConst tree;
+  PrefillBlock prompt;
+};
 
 static int round_up(int x, int m) { return (x + m - 1) / m * m; }
 // slot bound handed to the step for a sequence of `slots` slots: coarse, so that the
@@ -67,8 +72,7 @@ static int slot_bound(int slots, int s_pool) {
 }
 
 static size_t loop_fixed_bytes() {
-  return align_up(sizeof(LoopIn), 256) + align_up(sizeof(LoopOut), 256) +
-         align_up(sizeof(LoopConst), 256) + align_up(sizeof(PrefillBlock), 256);
+  return align_up(sizeof(LoopOut), 256) + align_up(sizeof(Upload), 256);
 }
 
 }  // namespace trj
@@ -127,14 +131,13 @@ int32_t tr_jacobi_generate(const trj_model_desc* desc, const trj_weights* weight
 
   hipStream_t st = (hipStream_t)stream;
   char* base = static_cast<char*>(workspace);
-  LoopIn* d_in = reinterpret_cast<LoopIn*>(base);
-  base += align_up(sizeof(LoopIn), 256);
   LoopOut* d_out = reinterpret_cast<LoopOut*>(base);
   base += align_up(sizeof(LoopOut), 256);
-  LoopConst* d_tree = reinterpret_cast<LoopConst*>(base);
-  base += align_up(sizeof(LoopConst), 256);
-  PrefillBlock* d_pf = reinterpret_cast<PrefillBlock*>(base);
-  base += align_up(sizeof(PrefillBlock), 256);
+  Upload* d_up = reinterpret_cast<Upload*>(base);
+  base += align_up(sizeof(Upload), 256);
+  LoopIn* d_in = &d_up->in;
+  LoopConst* d_tree = &d_up->tree;
+  PrefillBlock* d_pf = &d_up->prompt;
   // the template of the decoding rounds: the tree is the same in every round (appendix
   // "Templates for Token Tree"), so its bookkeeping and the rotary table are made once
   const int max_pos = prompt_len + max_new + N;
@@ -144,64 +147,81 @@ int32_t tr_jacobi_generate(const trj_model_desc* desc, const trj_weights* weight
   void* step_ws = base;
   const size_t step_ws_bytes = ws_bytes - loop_fixed_bytes() - tmpl_bytes;
 
-  LoopIn h_in{};
-  LoopOut h_out{};
-  LoopConst h_c{};
   *h_n_tokens = 0;
   *h_n_steps = 0;
+
+  // ---- host blocks.  Nothing the prompt passes and the first round need from the host depends on
+  // the device: all of it goes up in one copy in front of them, and the host meets the device only
+  // for the first round's predictions.  Copies and synchronizations between prompt pass, template
+  // and first round left the device idle for some 30 us.
+  const int n_ctx0 = prompt_len - 1, full = PREFILL_CHUNKS * TRJ_N_MAX;
+  std::vector<PrefillBlock> later(n_ctx0 > full ? (n_ctx0 - 1) / full : 0);  // prompt passes behind the first
+  std::vector<Upload> up_store(1);
+  Upload& up = up_store[0];
+  LoopIn& h_in = up.in;
+  LoopOut h_out{};
+  std::vector<int32_t> ctx(h_prompt, h_prompt + prompt_len);
+  ctx.reserve(prompt_len + max_new + N);
+  Template tmpl;
+  tmpl.build(cfg->h_parent, N);
+  // copies read the blocks above until they have been carried out: no way out of here before that
+  struct Finish {
+    hipStream_t st;
+    ~Finish() { (void)hipStreamSynchronize(st); }
+  } finish{st};
+  auto prompt_block = [&](PrefillBlock& b, int L, int T) {
+    const int Bc = (T + TRJ_N_MAX - 1) / TRJ_N_MAX;
+    for (int c = 0; c < Bc; ++c) {
+      const int r0 = c * TRJ_N_MAX, n = T - r0 < TRJ_N_MAX ? T - r0 : TRJ_N_MAX;
+      b.node_off[c] = r0;
+      b.kv_off[c] = 0;
+      b.prefix_len[c] = L + r0;
+      for (int i = 0; i < n; ++i) {
+        b.tok[r0 + i] = h_prompt[L + r0 + i];
+        b.parent[r0 + i] = i - 1;
+      }
+    }
+    b.node_off[Bc] = T;
+  };
+  for (int i = 0; i < N; ++i) up.tree.parent[i] = cfg->h_parent[i];
+  up.tree.node_off[0] = 0;
+  up.tree.node_off[1] = N;
+  fill_tree(cfg->h_parent, tmpl, R, ctx.data(), (int)ctx.size(), cfg->max_ngram, cfg->seed, 0, nullptr, 0, h_in.tok);
+  h_in.prefix_len = n_ctx0;
+  if (n_ctx0 > 0) prompt_block(up.prompt, 0, n_ctx0 < full ? n_ctx0 : full);
+  TRJ_HIP(hipMemcpyAsync(d_up, &up, sizeof(up), hipMemcpyHostToDevice, st));
 
   // ---- prompt pass: the K/V of prompt[0 .. P-2] through chain-shaped trees (an ordinary
   // causal forward), up to PREFILL_CHUNKS x TRJ_N_MAX tokens per packed step; the last
   // prompt token becomes the root
   int L = 0;
-  const int n_ctx0 = prompt_len - 1;
-  std::vector<PrefillBlock> h_pf_store(1);
-  PrefillBlock& h_pf = h_pf_store[0];
   while (L < n_ctx0) {
-    const int left = n_ctx0 - L, full = PREFILL_CHUNKS * TRJ_N_MAX;
-    const int T = left < full ? left : full;
+    const int T = n_ctx0 - L < full ? n_ctx0 - L : full;
     const int Bc = (T + TRJ_N_MAX - 1) / TRJ_N_MAX;
-    for (int c = 0; c < Bc; ++c) {
-      const int r0 = c * TRJ_N_MAX, n = T - r0 < TRJ_N_MAX ? T - r0 : TRJ_N_MAX;
-      h_pf.node_off[c] = r0;
-      h_pf.kv_off[c] = 0;
-      h_pf.prefix_len[c] = L + r0;
-      for (int i = 0; i < n; ++i) {
-        h_pf.tok[r0 + i] = h_prompt[L + r0 + i];
-        h_pf.parent[r0 + i] = i - 1;
-      }
+    if (L > 0) {
+      PrefillBlock& b = later[L / full - 1];
+      prompt_block(b, L, T);
+      TRJ_HIP(hipMemcpyAsync(d_pf, &b, sizeof(b), hipMemcpyHostToDevice, st));
     }
-    h_pf.node_off[Bc] = T;
-    TRJ_HIP(hipMemcpyAsync(d_pf, &h_pf, sizeof(h_pf), hipMemcpyHostToDevice, st));
     TRJ_TRY(step_impl(desc, weights, k_pool, v_pool, kv_layer_stride, s_pool, d_pf->tok, d_pf->parent,
                       d_pf->node_off, d_pf->kv_off, d_pf->prefix_len, Bc, T,
                       slot_bound(L + T, s_pool), step_ws, step_ws_bytes, nullptr, nullptr, nullptr,
                       nullptr, nullptr, nullptr, nullptr, d_pf->status, false, st));
-    // the host block is reused by the next pass
-    TRJ_HIP(hipStreamSynchronize(st));
     L += T;
   }
 
   // ---- decoding rounds
-  Template tmpl;
-  tmpl.build(cfg->h_parent, N);
-  for (int i = 0; i < N; ++i) h_c.parent[i] = cfg->h_parent[i];
-  h_c.node_off[0] = 0;
-  h_c.node_off[1] = N;
-  TRJ_HIP(hipMemcpyAsync(d_tree, &h_c, sizeof(h_c), hipMemcpyHostToDevice, st));
   TRJ_TRY(launch_template_prepare(d_tree->parent, d_tree->node_off, 1, N, desc->head_dim, max_pos,
                                   desc->rope_theta, tv, st));
-  TRJ_HIP(hipStreamSynchronize(st));
-
-  std::vector<int32_t> ctx(h_prompt, h_prompt + prompt_len);
-  ctx.reserve(prompt_len + max_new + N);
   int n_out = 0, step = 0;
-  bool have_pred = false, done = false;
+  bool done = false;
   while (!done) {
-    fill_tree(cfg->h_parent, tmpl, R, ctx.data(), (int)ctx.size(), cfg->max_ngram, cfg->seed, step,
-              have_pred ? h_out.argmax : nullptr, h_out.best, h_in.tok);
-    h_in.prefix_len = L;
-    TRJ_HIP(hipMemcpyAsync(d_in, &h_in, sizeof(h_in), hipMemcpyHostToDevice, st));
+    if (step > 0) {
+      fill_tree(cfg->h_parent, tmpl, R, ctx.data(), (int)ctx.size(), cfg->max_ngram, cfg->seed, step, h_out.argmax,
+                h_out.best, h_in.tok);
+      h_in.prefix_len = L;
+      TRJ_HIP(hipMemcpyAsync(d_in, &h_in, sizeof(h_in), hipMemcpyHostToDevice, st));
+    }
     TRJ_TRY(step_impl(desc, weights, k_pool, v_pool, kv_layer_stride, s_pool, d_in->tok,
                       d_tree->parent, d_tree->node_off, &d_tree->kv_off, &d_in->prefix_len, 1, N,
                       slot_bound(L + N, s_pool), step_ws, step_ws_bytes, nullptr, d_out->argmax,
@@ -210,7 +230,6 @@ int32_t tr_jacobi_generate(const trj_model_desc* desc, const trj_weights* weight
     TRJ_HIP(hipMemcpyAsync(&h_out, d_out, sizeof(h_out), hipMemcpyDeviceToHost, st));
     TRJ_HIP(hipStreamSynchronize(st));
     if (h_out.status != 0 || h_out.accept_len < 0 || h_out.accept_len >= N) return TRJ_ERR_BAD_SHAPE;
-    have_pred = true;
     if (h_accept_hist) h_accept_hist[step] = h_out.accept_len;
     ++step;
     const int a = h_out.accept_len;
