@@ -2,11 +2,13 @@
 // workload and as a tight-tolerance check of the data layouts.  Launches of a tiny model are
 // latency: a step of two layers was 25 launches and 218 us, of which the serial loops of one
 // thread per output (a k range of 1024, a row's scores and values) were half.  Now every
-// output is summed by 32 threads, and norm, rotary rotation with the K/V write, and SiLU(g) * u
-// are part of the projection next to them: 14 launches, 78.5 us, and the result is closer to the
+// output is summed by 32 threads whose loads are in flight together, and norm, rotary rotation
+// with the K/V write, and SiLU(g) * u are part of the projection next to them: 14 launches, 65 us, and the result is closer to the
 // 64-bit one (3.4e-7 against 8.1e-7).
 // They read the same tiled weight / KV layouts as the bf16 kernels.  The rotary table at the
 // top serves both modes.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "tree_vis.h"
@@ -70,32 +72,43 @@ __device__ inline void load8(const float* p, float (&v)[8]) {
     for (int e = 0; e < 8; ++e) v[e] = p[e];
   }
 }
-template <int TT, bool VEC>
+// UN granules of a thread are asked for together (past the last: the last one again, not added);
+// they are added in the same order whatever UN is.
+template <int TT, int UN, bool NORM, bool VEC>
 __device__ inline void gemm_f32_sums(const GemmF32Args& a, int rt, int t0, int part, int rl, float (&acc)[TT],
                                      float (&ss)[TT]) {
   const int ng = a.n_in >> 3;
   const float* wt = a.w + (size_t)rt * (a.n_in >> 4) * 512 + rl * 8;
-  for (int gi = part; gi < ng; gi += F32_PARTS) {
-    float wv[8], gv[8];
-    load8<true>(wt + (size_t)gi * 256, wv);  // granule = (k-step, half): 32 rows of 8 values
-    if (a.g) load8<VEC>(a.g + gi * 8, gv);
+  for (int g0 = part; g0 < ng; g0 += F32_PARTS * UN) {
+    float wv[UN][8], gv[UN][8], xv[UN][TT][8];
 #pragma unroll
-    for (int i = 0; i < TT; ++i) {
-      float xv[8];
-      load8<VEC>(a.x + (size_t)min(t0 + i, a.T - 1) * a.n_in + gi * 8, xv);
-      if (a.g) {
+    for (int u = 0; u < UN; ++u) {
+      const int gi = min(g0 + u * F32_PARTS, ng - 1);
+      load8<true>(wt + (size_t)gi * 256, wv[u]);  // granule = (k-step, half): 32 rows of 8 values
+      if (NORM) load8<VEC>(a.g + gi * 8, gv[u]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          ss[i] = fmaf(xv[e], xv[e], ss[i]);
-          xv[e] *= gv[e];
+      for (int i = 0; i < TT; ++i) load8<VEC>(a.x + (size_t)min(t0 + i, a.T - 1) * a.n_in + gi * 8, xv[u][i]);
+    }
+    if (UN > 1) __builtin_amdgcn_sched_barrier(0);  // all loads first
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      if (UN > 1 && g0 + u * F32_PARTS >= ng) break;
+#pragma unroll
+      for (int i = 0; i < TT; ++i) {
+        if (NORM) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            ss[i] = fmaf(xv[u][i][e], xv[u][i][e], ss[i]);
+            xv[u][i][e] *= gv[u][e];
+          }
         }
-      }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[i] = fmaf(wv[e], xv[e], acc[i]);
+        for (int e = 0; e < 8; ++e) acc[i] = fmaf(wv[u][e], xv[u][i][e], acc[i]);
+      }
     }
   }
 }
-template <int TT, class Epi>
+template <int TT, int UN, bool NORM, class Epi>
 __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(GemmF32Args a, Epi epi) {
   __shared__ float red[F32_PARTS][TT][32], sq[F32_PARTS][TT];
   const int rl = threadIdx.x & 31, part = threadIdx.x >> 5;
@@ -105,8 +118,8 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(GemmF32Args a, Ep
   for (int i = 0; i < TT; ++i) acc[i] = ss[i] = 0.f;
   // 16-byte loads of the input where the caller's pointers allow them (uniform)
   const bool vec = ((reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.g)) & 15) == 0;
-  if (vec) gemm_f32_sums<TT, true>(a, rt, t0, part, rl, acc, ss);
-  else gemm_f32_sums<TT, false>(a, rt, t0, part, rl, acc, ss);
+  if (vec) gemm_f32_sums<TT, UN, NORM, true>(a, rt, t0, part, rl, acc, ss);
+  else gemm_f32_sums<TT, UN, NORM, false>(a, rt, t0, part, rl, acc, ss);
 #pragma unroll
   for (int i = 0; i < TT; ++i) {
     red[part][i][rl] = acc[i];
@@ -121,7 +134,7 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(GemmF32Args a, Ep
     v += red[p][i][rl];
     s += sq[p][i];
   }
-  if (a.g) v *= 1.0f / sqrtf(s / a.n_in + a.eps);
+  if (NORM) v *= 1.0f / sqrtf(s / a.n_in + a.eps);
   epi(v, rt, rl, t);
 }
 
@@ -170,12 +183,24 @@ struct EpiF32QKV {
   }
 };
 // tokens per workgroup: four while that keeps the launch within the chip, eight beyond (every
-// group of tokens reads the weights again)
+// group of tokens reads the weights again); where a thread has more than one granule (n_in > 256)
+// and there are few rows, fewer tokens and several granules at a time, whose latencies would
+// otherwise follow one another (15 rows, 256 x 1024: 7.7 -> 5.4 us)
 template <class Epi>
 static int gemm_f32(const GemmF32Args& a, int n_out, const Epi& e, hipStream_t st) {
   if (a.T < 1 || a.n_in < 16 || n_out < 32 || (a.n_in & 15) || (n_out & 31)) return TRJ_ERR_BAD_SHAPE;
-  if (a.T <= 16) gemm_f32_kernel<4><<<dim3(n_out / 32, (a.T + 3) / 4), F32_THREADS, 0, st>>>(a, e);
-  else gemm_f32_kernel<8><<<dim3(n_out / 32, (a.T + 7) / 8), F32_THREADS, 0, st>>>(a, e);
+  const dim3 by4(n_out / 32, (a.T + 3) / 4), by8(n_out / 32, (a.T + 7) / 8);
+  if (a.g) {
+    if (a.T <= 16) gemm_f32_kernel<4, 1, true><<<by4, F32_THREADS, 0, st>>>(a, e);
+    else gemm_f32_kernel<8, 1, true><<<by8, F32_THREADS, 0, st>>>(a, e);
+  } else if constexpr (std::is_same_v<Epi, EpiF32Store>) {  // the others follow a norm
+    if (a.n_in > 8 * F32_PARTS && a.T <= 32)
+      gemm_f32_kernel<2, 4, false><<<dim3(n_out / 32, (a.T + 1) / 2), F32_THREADS, 0, st>>>(a, e);
+    else if (a.T <= 16) gemm_f32_kernel<4, 1, false><<<by4, F32_THREADS, 0, st>>>(a, e);
+    else gemm_f32_kernel<8, 1, false><<<by8, F32_THREADS, 0, st>>>(a, e);
+  } else {
+    return TRJ_ERR_NULLPTR;
+  }
   return check_launch();
 }
 int launch_gemm_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_out, int add_to,
@@ -199,6 +224,9 @@ int launch_gemm_qkv_f32(const float* x, const float* g, float eps, const float* 
 // scores (its row in pieces of 8 values) and, for the values, a column and every FA_PARTS-th
 // group of 4 keys, which are contiguous in a V plane; the parts are added in order through LDS.
 constexpr int FA_THREADS = 512;
+// Groups of a thread's values in flight together, the first of them from the start: 160 keys with
+// heads of 64.  One after the other behind the softmax the kernel took 11.4 us at 143 keys, now 6.2.
+constexpr int FA_EARLY = 5;
 __global__ __launch_bounds__(FA_THREADS) void tree_attn_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k_layer,
     const float* __restrict__ v_layer, const uint64_t* __restrict__ anc,
@@ -224,6 +252,18 @@ __global__ __launch_bounds__(FA_THREADS) void tree_attn_f32_kernel(
   const float* vp = v_layer + (size_t)(head / group) * s_pool * dh;
   const float* qr = q + ((size_t)t * n_heads + head) * dh;
   for (int c = tid; c < dh; c += FA_THREADS) qs[c] = qr[c];
+  // values: columns [c0, c0 + cols) by `parts` threads each.  A thread's first groups are asked for
+  // here, with the keys, instead of behind the softmax one after the other
+  const int cols = dh < FA_THREADS ? dh : FA_THREADS, parts = FA_THREADS / cols;
+  const int col = tid % cols, part = tid / cols, last4 = (nk - 1) & ~3;
+  float early[FA_EARLY][4];
+  auto load_group = [&](int k4, int c, float (&v)[4]) {  // kv_off is a multiple of 32: groups of 4 stay together
+    const float* vg = vp + v_off(base + min(k4, last4), c, dh);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = vg[e];
+  };
+#pragma unroll
+  for (int j = 0; j < FA_EARLY; ++j) load_group(4 * (part + j * parts), col, early[j]);
   __syncthreads();
   const uint64_t a0 = anc[2 * (size_t)t], a1 = anc[2 * (size_t)t + 1];
   float mx = -INFINITY;
@@ -262,22 +302,32 @@ __global__ __launch_bounds__(FA_THREADS) void tree_attn_f32_kernel(
   }
   sum = block_reduce(sum, [](float a, float b) { return a + b; });
   const float inv = 1.0f / sum;
-  // values: columns [c0, c0 + cols) by `parts` threads each
-  const int cols = dh < FA_THREADS ? dh : FA_THREADS, parts = FA_THREADS / cols;
   float* red = sc + ((nk + 3) & ~3);  // parts x cols
-  const int col = tid % cols, part = tid / cols;
   for (int c0 = 0; c0 < dh; c0 += cols) {
     const int c = c0 + col;
     float acc = 0.f;
-    if (part < parts && c < dh)
-      for (int k4 = 4 * part; k4 < nk; k4 += 4 * parts) {  // kv_off is a multiple of 32: groups of 4 stay together
-        const float* vg = vp + v_off(base + k4, c, dh);
+    auto add_group = [&](int k4, const float (&v)[4]) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float p = k4 + e < nk ? sc[k4 + e] : 0.f;
-          if (p != 0.f) acc = fmaf(p, vg[e], acc);  // slots nobody sees may hold anything
-        }
+      for (int e = 0; e < 4; ++e) {
+        const float p = k4 + e < nk ? sc[min(k4 + e, nk - 1)] : 0.f;
+        acc = p != 0.f ? fmaf(p, v[e], acc) : acc;  // slots nobody sees may hold anything
       }
+    };
+    if (part < parts && c < dh) {
+      int k4 = 4 * part;
+      if (c0 == 0) {
+#pragma unroll
+        for (int j = 0; j < FA_EARLY; ++j) add_group(4 * (part + j * parts), early[j]);
+        k4 += 4 * FA_EARLY * parts;
+      }
+      for (; k4 < nk; k4 += 4 * FA_EARLY * parts) {
+        float v[FA_EARLY][4];
+#pragma unroll
+        for (int j = 0; j < FA_EARLY; ++j) load_group(k4 + 4 * j * parts, c, v[j]);
+#pragma unroll
+        for (int j = 0; j < FA_EARLY; ++j) add_group(k4 + 4 * j * parts, v[j]);
+      }
+    }
     if (part < parts) red[part * cols + col] = acc;
     __syncthreads();
     if (part == 0 && c < dh) {
