@@ -67,6 +67,7 @@ struct TreeWs {
   uint64_t* anc;
   float* attn;     // bf16 attention partials
   int32_t* items;  // bf16 attention work items and their count
+  int attn_pack;           // log2 of the heads in a column
   int attn_rows, attn_qg, attn_bpwg, attn_ns;  // the attention launch plan
 };
 struct StepWs {
@@ -81,7 +82,7 @@ struct StepWs {
   float *qf, *of, *actf;
 };
 
-static void carve_tree(Carver& c, int dtype, int B, int T, int H, bool shared_kv, int dh, int max_seq_slots,
+static void carve_tree(Carver& c, int dtype, int B, int T, int H, bool shared_kv, int pack, int dh, int max_seq_slots,
                        TreeWs* w) {
   w->depth = c.take<int32_t>(T);
   w->row_slot = c.take<int32_t>(T);
@@ -91,23 +92,30 @@ static void carve_tree(Carver& c, int dtype, int B, int T, int H, bool shared_kv
   w->anc = c.take<uint64_t>(2 * (size_t)T);
   w->attn = nullptr;
   w->items = nullptr;
+  w->attn_pack = pack;
   w->attn_rows = w->attn_qg = w->attn_bpwg = w->attn_ns = 0;
   if (dtype == TRJ_BF16) {
-    const AttnPlan p = attn_bf16_plan(B, T, H, dh, shared_kv, max_seq_slots);
-    w->attn = c.take<float>(attn_bf16_ws_floats(B, T, H, dh, max_seq_slots));
-    w->items = c.take<int32_t>(attn_bf16_item_words(B, T, H, dh, max_seq_slots));
-    w->attn_rows = 32 * p.ntw;
+    const AttnPlan p = attn_bf16_plan(B, T, H, dh, shared_kv, max_seq_slots, pack);
+    w->attn = c.take<float>(attn_bf16_ws_floats(B, T, H, dh, max_seq_slots, pack));
+    w->items = c.take<int32_t>(attn_bf16_item_words(B, T, H, dh, max_seq_slots, pack));
+    w->attn_rows = 32 * p.ntw >> pack;
     w->attn_qg = p.qg_max;
     w->attn_bpwg = p.bpwg;
     w->attn_ns = p.nsplit_max;
   }
 }
 
-static bool model_shares_kv(const trj_model_desc& m) { return m.n_kv_heads && m.n_kv_heads != m.n_heads; }
+static int model_pack(const trj_model_desc& m, int B, int T, int max_seq_slots) {
+  return m.n_kv_heads ? attn_bf16_pack(B, T, m.n_heads, m.n_kv_heads, max_seq_slots) : 0;
+}
+// several columns per K/V head
+static bool model_shares_kv(const trj_model_desc& m, int B, int T, int max_seq_slots) {
+  return m.n_kv_heads && m.n_kv_heads != m.n_heads >> model_pack(m, B, T, max_seq_slots);
+}
 static void carve_step(Carver& c, const trj_model_desc& m, int B, int T, int max_seq_slots,
                        bool head_scratch, bool shared_kv, StepWs* w) {
   const int d = m.d_model, hd = m.n_heads * m.head_dim, F = m.d_ffn;
-  carve_tree(c, m.dtype, B, T, m.n_heads, shared_kv, m.head_dim, max_seq_slots, &w->t);
+  carve_tree(c, m.dtype, B, T, m.n_heads, shared_kv, model_pack(m, B, T, max_seq_slots), m.head_dim, max_seq_slots, &w->t);
   w->cs = c.take<float2>((size_t)T * (m.head_dim / 2));
   w->x = c.take<float>((size_t)T * d);
   // the head's own scratch: the fp32 mode's logits (if the caller keeps none), the bf16 mode's
@@ -276,7 +284,7 @@ int32_t trj_workspace_bytes(const trj_model_desc* desc, int32_t t_max, int32_t b
   TuneScope tune_scope;
   Carver c(nullptr);
   StepWs w;
-  carve_step(c, *desc, b_max, t_max, l_max, true, model_shares_kv(*desc), &w);
+  carve_step(c, *desc, b_max, t_max, l_max, true, model_shares_kv(*desc, b_max, t_max, l_max), &w);
   *h_bytes = align_up(c.off, 256);
   return TRJ_OK;
 }
@@ -434,18 +442,22 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
     return TRJ_ERR_BAD_SHAPE;
   if (!(scale > 0.f)) return TRJ_ERR_BAD_SHAPE;
   TuneScope tune_scope;
-  if (static_ws) {  // sizes first: nothing is touched when the call does not fit the array
-    Carver need(nullptr);
-    TreeWs wn;
-    carve_tree(need, dtype, B, T, n_heads, n_heads != n_kv_heads, head_dim, max_seq_slots, &wn);
-    if (need.off > (size_t)TRJ_STATIC_SCRATCH_BYTES) return TRJ_ERR_WORKSPACE_TOO_SMALL;
-    TRJ_TRY(static_scratch(&workspace));
-    ws_bytes = TRJ_STATIC_SCRATCH_BYTES;
-  }
-  Carver c(workspace);
+  if (static_ws) ws_bytes = TRJ_STATIC_SCRATCH_BYTES;
+  // sizes first: nothing is touched when the call does not fit; packed heads, or each by itself if
+  // only that fits
+  int pack = dtype == TRJ_BF16 ? attn_bf16_pack(B, T, n_heads, n_kv_heads, max_seq_slots) : 0;
+  auto carve = [&](Carver c, TreeWs* w) {
+    carve_tree(c, dtype, B, T, n_heads, n_heads >> pack != n_kv_heads, pack, head_dim, max_seq_slots, w);
+    return c.off;
+  };
   TreeWs w;
-  carve_tree(c, dtype, B, T, n_heads, n_heads != n_kv_heads, head_dim, max_seq_slots, &w);
-  if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
+  if (carve(Carver(nullptr), &w) > ws_bytes) {
+    if (pack == 0) return TRJ_ERR_WORKSPACE_TOO_SMALL;
+    pack = 0;
+    if (carve(Carver(nullptr), &w) > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
+  }
+  if (static_ws) TRJ_TRY(static_scratch(&workspace));
+  carve(Carver(workspace), &w);
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = dtype == TRJ_BF16, self = bf16 && B == 1;  // one sequence: the kernel checks it itself
   if (!self && B <= PREP_MAX_SEQS) {
@@ -466,7 +478,7 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
   if (bf16) {
     return launch_tree_attn_bf16((const uint16_t*)q, (const uint16_t*)k_layer,
                                  (const uint16_t*)v_layer, w.anc, node_off, kv_off, prefix_len,
-                                 w.status, w.items, B, T, n_heads, n_kv_heads, n_heads != n_kv_heads, head_dim, s_pool, max_seq_slots, scale,
+                                 w.status, w.items, B, T, n_heads, n_kv_heads, n_heads >> pack != n_kv_heads, pack, head_dim, s_pool, max_seq_slots, scale,
                                  w.attn, 0, 0, (uint16_t*)out, self ? parent : nullptr, w.status, st);
   }
   return launch_tree_attn_f32((const float*)q, (const float*)k_layer, (const float*)v_layer, w.anc,
@@ -482,10 +494,15 @@ int32_t tree_attention_workspace_bytes(int32_t B, int32_t T, int32_t n_heads, in
     return TRJ_ERR_BAD_SHAPE;
   if ((long)T > (long)B * TRJ_N_MAX) return TRJ_ERR_TREE_TOO_LARGE;
   TuneScope tune_scope;
-  Carver c(nullptr);
-  TreeWs w;
-  carve_tree(c, dtype, B, T, n_heads, false, head_dim, max_seq_slots, &w);  // the same with shared K/V
-  *h_bytes = align_up(c.off, 256);
+  size_t most = 0;  // whatever the number of K/V heads
+  for (int pack = 0; pack <= 3 && n_heads % (1 << pack) == 0; ++pack) {
+    Carver c(nullptr);
+    TreeWs w;
+    carve_tree(c, dtype, B, T, n_heads, false, pack, head_dim, max_seq_slots, &w);
+    most = c.off > most ? c.off : most;
+    if (dtype != TRJ_BF16) break;
+  }
+  *h_bytes = align_up(most, 256);
   return TRJ_OK;
 }
 
@@ -586,7 +603,7 @@ int32_t trj_dev_attn_plan(int32_t B, int32_t T, int32_t n_heads, int32_t head_di
       max_seq_slots < 1)
     return TRJ_ERR_BAD_SHAPE;
   TuneScope tune_scope;
-  const AttnPlan p = attn_bf16_plan(B, T, n_heads, head_dim, shared_kv != 0, max_seq_slots);
+  const AttnPlan p = attn_bf16_plan(B, T, n_heads, head_dim, shared_kv != 0, max_seq_slots, 0);
   const int32_t v[6] = {p.ntw, p.qg_max, p.bpwg, p.nsplit_max, p.ring, p.lag > 0.f};
   memcpy(h_plan, v, sizeof(v));
   return TRJ_OK;
@@ -638,7 +655,7 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
   StepWs w;
   const bool bf16 = m.dtype == TRJ_BF16;
   // heads of a group read the same K/V, and so do the chunks of a prompt that a pass packs
-  const bool shared_kv = model_shares_kv(m) || (!with_head && B > 1);
+  const bool shared_kv = model_shares_kv(m, B, T, max_seq_slots) || (!with_head && B > 1);
   carve_step(c, m, B, T, max_seq_slots, with_head && (bf16 || !logits), shared_kv, &w);
   if (c.off > ws_bytes && bf16 && logits) {  // no room for the candidates: argmax of the written logits
     c = Carver(workspace);
@@ -712,7 +729,7 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
                               cs_row, w.t.row_slot, kv_only ? nullptr : w.q, kl, vl, st)); }
       if (kv_only) return TRJ_OK;
       TRJ_TRY(launch_tree_attn_bf16(w.q, kl, vl, w.t.anc, node_off, kv_off, prefix_len, status_dev,
-                                    w.t.items, B, T, H, Hkv, shared_kv, dh, s_pool, max_seq_slots, scale, w.t.attn, 1, tp,
+                                    w.t.items, B, T, H, Hkv, shared_kv, w.t.attn_pack, dh, s_pool, max_seq_slots, scale, w.t.attn, 1, tp,
                                     w.op, nullptr, nullptr, st));
       { ProfScope ps_(KC_GEMM_O, st); TRJ_TRY(add_projection(w.op, (const uint16_t*)lw.wo, T, tp, hd, d, sk_o, w.partial, w.x, st)); }
       { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_o > 1 ? sk_o : 0, w.x, lw.g_ffn, T, d, tp, w.hp, w.ssq, st)); }
@@ -752,7 +769,7 @@ size_t step_workspace_bytes(const trj_model_desc& m, int B, int T, int max_seq_s
   TuneScope tune_scope;
   Carver c(nullptr);
   StepWs w;
-  carve_step(c, m, B, T, max_seq_slots, true, model_shares_kv(m), &w);
+  carve_step(c, m, B, T, max_seq_slots, true, model_shares_kv(m, B, T, max_seq_slots), &w);
   return c.off + 256;
 }
 int check_model(const trj_model_desc* m) { return check_desc(m); }

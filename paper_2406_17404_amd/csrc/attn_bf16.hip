@@ -57,7 +57,10 @@ struct AttnArgs {
   const int32_t* kv_off;
   const int32_t* prefix_len;
   const int32_t* status_dev;
-  int n_heads, group, s_pool, bpwg, nsplit_max, qg_max;  // group = query heads per K/V head
+  int n_heads, s_pool, bpwg, nsplit_max, qg_max;
+  // Query heads that share a K/V head are worked on together, 1 << pack of them: query p of a
+  // sequence is (node p >> pack, head p & ..), `columns` packed heads in all, `group` per K/V head
+  int pack, columns, group;
   int n_kv_groups;  // items x K/V heads: sets of workgroups that share K/V blocks
   // work items (sequence, key split, query group) that exist, longest sequence first, and their number
   // (written by the prep kernels): workgroups past the list's end leave at once, and they
@@ -69,12 +72,12 @@ struct AttnArgs {
   const int32_t* n_items;
   float scale_log2e;
   float lag;  // of the softmax reference behind the running maximum, log2
-  // un-normalised partials, one per (sequence, query tile, head, split), stored as the
+  // un-normalised partials, one per (query tile, column, split), stored as the
   // image of the wavefront's accumulator registers: element (mt*16 + v)*64 + lane, so that
   // every store and every load of the merge kernel is a contiguous 256-byte row
-  float* po;        // [B*tiles_per_seq][H][nsplit_max][DH/32 * 16 * 64]
-  float* pm;        // [B*tiles_per_seq][H][nsplit_max][32] running max (log2 domain)
-  float* pl;        // [B*tiles_per_seq][H][nsplit_max][32] sum of weights
+  float* po;        // [part_tiles][columns][nsplit_max][DH/32 * 16 * 64]
+  float* pm;        // [part_tiles][columns][nsplit_max][32] running max (log2 domain)
+  float* pl;        // [part_tiles][columns][nsplit_max][32] sum of weights
   int tiles_per_seq;
   uint16_t* out;
   int tiled, tp;
@@ -170,6 +173,18 @@ __device__ inline void rescale_o(f32x16 (&o)[MTV], float alpha) {
     for (int v = 0; v < 16; ++v) o[mt][v] *= alpha;
 }
 
+// Place of a sequence's first query tile among the partials' (of part_tiles).  Single heads: every
+// sequence has room for the most tiles one could have.  Packed, that would be many times the tiles
+// there are (sequences of 20 rows: 16 for 3): behind the rows in front of it, and one more per
+// sequence for their last tiles that are not full.  The first sequence's place does not depend on
+// its rows, so that the merge of a single one need not wait for them.
+__device__ inline int part_first(const AttnArgs& a, int s, int r0) {
+  return a.pack == 0 ? s * a.tiles_per_seq : s == 0 ? 0 : ((r0 << a.pack) >> 5) + s;
+}
+static size_t part_tiles(int B, int T, int pack, int tiles_per_seq) {
+  return pack == 0 ? (size_t)B * tiles_per_seq : ((size_t)T << pack >> 5) + B;
+}
+
 template <int DH>
 __device__ inline void attn_store_row(const AttnArgs& a, int t, int head, int c, u32x2 v) {
   uint16_t* dst = a.tiled ? a.out + a_off(t, head * DH + c, a.tp)
@@ -218,15 +233,17 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   // the number of K/V heads is a multiple of 8.
   const int slot = blockIdx.x >> 3, kvg = (slot / a.group) * 8 + (blockIdx.x & 7);
   if (kvg >= a.n_kv_groups) return;  // padding to a multiple of 8 (uniform)
-  const int n_kv = a.n_heads / a.group;
-  const int head = (kvg % n_kv) * a.group + slot % a.group;
+  const int n_kv = a.columns / a.group;
+  const int column = (kvg % n_kv) * a.group + slot % a.group;
   const int item = kvg / n_kv;
   int s, qg, r0, n, L, blk_base, sp;
   bool several;  // another query group or sequence reads the same blocks
-  auto zero_rows = [&](int t0, int t1) {  // rows without a valid sequence read as zeros (this head's part)
+  const int head0 = column << a.pack;  // the column's first head
+  auto zero_rows = [&](int t0, int t1) {  // rows without a valid sequence read as zeros (this column's part)
     const u32x2 z = {0, 0};
-    for (int i = tid; i < (t1 - t0) * (DH / 4); i += KS * NTW * 64)
-      attn_store_row<DH>(a, t0 + i / (DH / 4), head, i % (DH / 4) * 4, z);
+    const int quads = (DH / 4) << a.pack;  // of a row; columns of neighbouring heads follow each other
+    for (int i = tid; i < (t1 - t0) * quads; i += KS * NTW * 64)
+      attn_store_row<DH>(a, t0 + i / quads, head0, i % quads * 4, z);
   };
   if constexpr (SELF) {
     s = 0;
@@ -242,11 +259,11 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
     if (qg == 0 && sp == 0) {  // rows that the sequence does not own, for all its workgroups of this head
       zero_rows(0, ok ? r0 : a.T);
       if (ok) zero_rows(r1, a.T);
-      if (!ok && head == 0 && tid == 0) a.status[0] = 1;
+      if (!ok && column == 0 && tid == 0) a.status[0] = 1;
     }
     if (!ok) return;  // uniform over the launch
     blk_base = ko >> 5;
-    several = n > 32 * NTW;
+    several = n << a.pack > 32 * NTW;
   } else {
     const int32_t* rec = a.items + (size_t)item * 8;  // inside the list's memory for every id
     s = rec[0], qg = rec[1], r0 = rec[2], n = rec[3], L = rec[4], blk_base = rec[5], sp = rec[6];
@@ -256,7 +273,8 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   const int total = L + n;
   const int nb = (total + 31) >> 5;
   const int nsplit = (nb + a.bpwg - 1) / a.bpwg;
-  if (sp >= nsplit || qg * 32 * NTW >= n) return;  // uniform as well
+  const int nq = n << a.pack;  // queries of the column
+  if (sp >= nsplit || qg * 32 * NTW >= nq) return;  // uniform as well
   const int b0 = sp * a.bpwg, b1 = min(nb, b0 + a.bpwg);
   const int n32 = lane & 31, hh = lane >> 5;
   // no other workgroup reads these blocks (one query group, no sequence with the same slots, one
@@ -264,13 +282,14 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   // L2 it costs a second trip to HBM
   const bool stream = a.group == 1 && !several;
 
-  const size_t plane = (size_t)(head / a.group) * a.s_pool * DH;  // the group's K/V head
+  const size_t plane = (size_t)(column / a.group) * a.s_pool * DH;  // the K/V head
   // this stream's blocks: b0 + ks, b0 + ks + KS, ..
   const int nblk = b0 + ks < b1 ? (b1 - b0 - ks + KS - 1) / KS : 0;
-  // rows past the tree's end read the last row instead (never stored, always finite) and see no
-  // tree node; a wavefront without any row computes nothing
-  const int qi = (qg * NTW + nt) * 32 + n32, qc = min(qi, n - 1);
-  const bool live = (qg * NTW + nt) * 32 < n;
+  // queries past the last read the last one instead (never stored, always finite) and see no
+  // tree node; a wavefront without any query computes nothing
+  const int qi = (qg * NTW + nt) * 32 + n32, qc = min(qi, nq - 1);
+  const int node = qc >> a.pack, head = head0 + (qc & ((1 << a.pack) - 1));
+  const bool live = (qg * NTW + nt) * 32 < nq;
 
   f32x16 o[MTV];
 #pragma unroll
@@ -356,8 +375,8 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
     uint32_t r[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      const int word = value(b[w], qc);
-      r[w] = qi < n ? (uint32_t)word : 0u;
+      const int word = value(b[w], node);
+      r[w] = qi < nq ? (uint32_t)word : 0u;
     }
     anc0 = (uint64_t)r[1] << 32 | r[0];
     anc1 = (uint64_t)r[3] << 32 | r[2];
@@ -378,8 +397,9 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   };
   auto self_status = [&](bool ok) {  // the verdict on the tree, and zeros for its rows if it is malformed
     if (sp != 0) return;
-    if (!ok) zero_rows(r0 + qg * 32 * NTW, min(r0 + n, r0 + (qg + 1) * 32 * NTW));
-    if (qg == 0 && head == 0 && tid == 0) a.status[0] = !ok;
+    const int rows = 32 * NTW >> a.pack;
+    if (!ok) zero_rows(r0 + qg * rows, min(r0 + n, r0 + (qg + 1) * rows));
+    if (qg == 0 && column == 0 && tid == 0) a.status[0] = !ok;
   };
 
   if constexpr (FORM != AF_REGISTERS) {
@@ -408,11 +428,11 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       auto fetch = [&](const void* base, uint32_t voff, int at) {
         load_to_lds<false>(base, voff, __builtin_amdgcn_readfirstlane(lds0 + at));
       };
-      const uint16_t* qh = a.q + ((size_t)r0 * a.n_heads + head) * DH;
+      const uint16_t* qh = a.q + ((size_t)r0 * a.n_heads + head0) * DH;
 #pragma unroll
       for (int j = 0; j < QP; ++j) {
         const int k = ks * QP + j;
-        fetch(qh, (uint32_t)(qc * a.n_heads * DH + hh * 8 + 16 * k) * 2, QAT + nt * SLOT + k * 1024);
+        fetch(qh, (uint32_t)((node * a.n_heads + head - head0) * DH + hh * 8 + 16 * k) * 2, QAT + nt * SLOT + k * 1024);
       }
       if constexpr (SELF) {
         if (wv == 0) {
@@ -420,7 +440,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
           load_words_to_lds(a.parent + r0, min(lane + 64, n - 1) * 4, __builtin_amdgcn_readfirstlane(lds0 + ANC_AT + 256));
         }
       } else if (ks == 0) {
-        fetch(a.anc + 2 * (size_t)r0, (uint32_t)qc * 16, ANC_AT + nt * 1024);
+        fetch(a.anc + 2 * (size_t)r0, (uint32_t)node * 16, ANC_AT + nt * 1024);
       }
     }
     if constexpr (FORM == AF_RING) {
@@ -465,8 +485,8 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       if (!ok) return;
     } else {
       const u32x4 bits = reinterpret_cast<const u32x4*>(smem + ANC_AT + nt * 1024)[lane];
-      anc0 = qi < n ? (uint64_t)bits[1] << 32 | bits[0] : 0;
-      anc1 = qi < n ? (uint64_t)bits[3] << 32 | bits[2] : 0;
+      anc0 = qi < nq ? (uint64_t)bits[1] << 32 | bits[0] : 0;
+      anc1 = qi < nq ? (uint64_t)bits[3] << 32 | bits[2] : 0;
     }
     if constexpr (FORM == AF_ONCE) {
       // only one more meeting, for V, behind the first block's scores and softmax
@@ -543,7 +563,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       }
       p += (size_t)KS * KSTEPS * 64;
     };
-    const uint16_t* qp = a.q + ((size_t)(r0 + qc) * a.n_heads + head) * DH + hh * 8;
+    const uint16_t* qp = a.q + ((size_t)(r0 + node) * a.n_heads + head) * DH + hh * 8;
     int par[2];
     if constexpr (SELF) {  // first: they are needed first
 #pragma unroll
@@ -552,8 +572,8 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
 #pragma unroll
     for (int k = 0; k < KSTEPS; ++k) qreg[k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * k));
     if constexpr (!SELF) {
-      anc0 = a.anc[2 * (size_t)(r0 + qc)];
-      anc1 = a.anc[2 * (size_t)(r0 + qc) + 1];
+      anc0 = a.anc[2 * (size_t)(r0 + node)];
+      anc1 = a.anc[2 * (size_t)(r0 + node) + 1];
     }
     const int mine = live ? nblk : 0;
     if (mine > 0) {
@@ -564,7 +584,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       const bool ok = own_bits(par);
       self_status(ok);
       if (!ok) return;
-    } else if (qi >= n) {
+    } else if (qi >= nq) {
       anc0 = anc1 = 0;
     }
     // the last block has a copy of the code to itself: behind a condition the compiler would wait
@@ -620,8 +640,8 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
     }
   }
   __syncthreads();
-  const size_t pidx =
-      (((size_t)s * a.tiles_per_seq + qg * NTW + nt) * a.n_heads + head) * a.nsplit_max + sp;
+  if (!live) return;  // no query, no partial; the barriers are behind
+  const size_t pidx = ((size_t)(part_first(a, s, r0) + qg * NTW + nt) * a.columns + column) * a.nsplit_max + sp;
   if (nsplit != 1 && ks == 0 && hh == 0) {
     a.pm[pidx * 32 + n32] = mg;
     a.pl[pidx * 32 + n32] = lg;
@@ -637,12 +657,12 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       for (int v = 0; v < 16; ++v) o[mt][v] += src[(k * 16 + v) * 64];
     if (nsplit == 1) {
       // the workgroup saw every key: write the normalised rows
-      if (qi < n) {
+      if (qi < nq) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           u32x2 v = {pack2bf(o[mt][4 * g] * inv, o[mt][4 * g + 1] * inv),
                      pack2bf(o[mt][4 * g + 2] * inv, o[mt][4 * g + 3] * inv)};
-          attn_store_row<DH>(a, r0 + qi, head, 32 * mt + 8 * g + 4 * hh, v);
+          attn_store_row<DH>(a, r0 + node, head, 32 * mt + 8 * g + 4 * hh, v);
         }
       }
     } else {
@@ -664,16 +684,20 @@ template <int DH, int CB>
 __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
   constexpr int MTV = DH / 32, OW = MTV * 16 * 64;
   const int tile = blockIdx.x % a.tiles_per_seq, s = blockIdx.x / a.tiles_per_seq;
-  const int head = blockIdx.y;
+  const int column = blockIdx.y;
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int mt = grp >> 1, v0 = (grp & 1) * 8;
   if (mt >= MTV) return;
   const int n32 = lane & 31, hh = lane >> 5;
-  const size_t base = (((size_t)s * a.tiles_per_seq + tile) * a.n_heads + head) * a.nsplit_max;
   // The first splits' partials are asked for together with what says how many there are: waiting
   // for one after the other was a third of this launch (4.2 -> 3.1 us for three splits of 16 rows).
   // Splits that do not exist are left out of maximum and sum, whatever their memory holds.
   const int status = a.status_dev[s], r0 = a.node_off[s], r1 = a.node_off[s + 1], L = a.prefix_len[s];
+  // packed: the tile may have no place, and r0 of an invalid sequence be anything
+  if (a.pack > 0 && s > 0 && (status != 0 || tile * 32 >= (r1 - r0) << a.pack)) return;
+  const int there = a.pack > 0 && s == 0 ? min(tile, (a.T << a.pack) >> 5) : tile;
+  const int place = part_first(a, s, r0) + there;
+  const size_t base = ((size_t)place * a.columns + column) * a.nsplit_max;
   float ms[CB], ls[CB], x[CB][8];
   auto load = [&](int k0, int last) {
 #pragma unroll
@@ -687,8 +711,8 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
     }
   };
   load(0, a.nsplit_max - 1);
-  const int n = r1 - r0;
-  if (status != 0 || tile * 32 >= n) return;  // rows of malformed sequences stay zero
+  const int n = r1 - r0, nq = n << a.pack;
+  if (status != 0 || tile * 32 >= nq) return;  // rows of malformed sequences stay zero
   const int nb = (L + n + 31) >> 5;
   const int nsplit = (nb + a.bpwg - 1) / a.bpwg;
   if (nsplit == 1) return;  // written by the attention kernel itself
@@ -721,22 +745,42 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
     mrun = mb;
   }
   const int qi = tile * 32 + n32;
-  if (qi >= n) return;
+  if (qi >= nq) return;
+  const int node = qi >> a.pack, head = (column << a.pack) + (qi & ((1 << a.pack) - 1));
   const float inv = 1.0f / lrun;
 #pragma unroll
   for (int g = 0; g < 2; ++g) {
     u32x2 v = {pack2bf(acc[4 * g] * inv, acc[4 * g + 1] * inv),
                pack2bf(acc[4 * g + 2] * inv, acc[4 * g + 3] * inv)};
-    attn_store_row<DH>(a, r0 + qi, head, 32 * mt + 8 * ((v0 >> 2) + g) + 4 * hh, v);
+    attn_store_row<DH>(a, r0 + node, head, 32 * mt + 8 * ((v0 >> 2) + g) + 4 * hh, v);
   }
 }
 
 // Launch shape: form of the walk, query tiles per workgroup, query groups, blocks per workgroup,
 // splits.  Figures: us of the attention kernel with its merge in a step of 12 layers, where K/V
 // come from HBM, 32 heads of 128; R register form, 2r / 4r ring with two / four tiles.
-AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int max_seq_slots) {
+// Packed heads fill tiles of 32 queries that a tree by itself leaves partly empty (69 rows, four
+// heads: 9 tiles instead of 12), and K/V are read by fewer workgroups: the smallest pack with the
+// fewest tiles for trees of the average size.  Up to 16 blocks, where a call is the latency of one
+// workgroup, the more and smaller ones of single heads win (30 rows on 300 slots: 10.5 against 13.1
+// us).  us of a call, single heads -> packed, 32 heads on 8 K/V heads: 69 rows on 3001 slots 22.8
+// -> 20.9, on 1024 17.7 -> 16.2, 33 on 1024 15.3 -> 14.2, 5 on 16384 31.5 -> 24.3, 100 on 16384 64.6
+// -> 61.0, sixteen sequences of 20 up to 1000 32.2 -> 26.8.
+int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int max_seq_slots) {
+  if (max_seq_slots <= 16 * 32) return 0;
+  const int share = n_heads / n_kv_heads, n = (T + B - 1) / B;
+  int best = 0, fewest = share * ((n + 31) / 32);
+  for (int pack = 1; pack <= 3 && share % (1 << pack) == 0; ++pack) {
+    const int tiles = (share >> pack) * (((n << pack) + 31) / 32);
+    if (tiles < fewest) { best = pack; fewest = tiles; }
+  }
+  return best;
+}
+AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv, int max_seq_slots, int pack) {
   AttnPlan p;
-  const int nmax = T < TRJ_N_MAX ? T : TRJ_N_MAX;
+  // queries and columns take the place of rows and heads
+  const int T = rows_T << pack, n_heads = all_heads >> pack;
+  const int nmax = (rows_T < TRJ_N_MAX ? rows_T : TRJ_N_MAX) << pack;
   int nb = (max_seq_slots + 31) / 32;
   if (nb < 1) nb = 1;
   // The ring pays where so many blocks stream from HBM that it matters how much is in flight
@@ -782,7 +826,7 @@ AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int m
   const int items_est = B > (T + rows - 1) / rows ? B : (T + rows - 1) / rows;
   const long cols = (long)items_est * n_heads;
   int b;
-  if (p.ntw == 4) {  // whole rounds of workgroups at most: a split is four tiles' partials
+  if (p.ntw == 4 || pack > 0) {  // whole rounds of workgroups at most
     const long split = cols < target ? target / cols : 1;
     b = (int)((nb + split - 1) / split);
   } else {
@@ -815,19 +859,19 @@ AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int m
 }
 
 // scratch for either answer to "do query heads share K/V": the workspace queries do not know
-size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots) {
+size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots, int pack) {
   size_t most = 64;  // no partials needed when every sequence fits one workgroup
   for (bool shared : {false, true}) {
-    const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, shared, max_seq_slots);
-    const size_t n = p.nsplit_max > 1 ? (size_t)B * p.qg_max * p.ntw * n_heads * p.nsplit_max * (dh / 32 * 1024 + 64) : 0;
+    const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, shared, max_seq_slots, pack);
+    const size_t n = p.nsplit_max > 1 ? part_tiles(B, T, pack, p.qg_max * p.ntw) * (n_heads >> pack) * p.nsplit_max * (dh / 32 * 1024 + 64) : 0;
     most = n > most ? n : most;
   }
   return most;
 }
-size_t attn_bf16_item_words(int B, int T, int n_heads, int dh, int max_seq_slots) {
+size_t attn_bf16_item_words(int B, int T, int n_heads, int dh, int max_seq_slots, int pack) {
   size_t most = 0;
   for (bool shared : {false, true}) {
-    const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, shared, max_seq_slots);
+    const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, shared, max_seq_slots, pack);
     const size_t n = (size_t)B * p.qg_max * p.nsplit_max * 8 + 8;
     most = n > most ? n : most;
   }
@@ -838,23 +882,23 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
                           const uint64_t* anc, const int32_t* node_off,
                           const int32_t* kv_off, const int32_t* prefix_len,
                           const int32_t* status_dev, const int32_t* items, int B, int T,
-                          int n_heads, int n_kv_heads, bool shared_kv, int dh, int s_pool, int max_seq_slots,
+                          int n_heads, int n_kv_heads, bool shared_kv, int pack, int dh, int s_pool, int max_seq_slots,
                           float scale, float* ws, int tiled, int tp, uint16_t* out, const int32_t* parent,
                           int32_t* status, hipStream_t st) {
   if (dh != 64 && dh != 128) return TRJ_ERR_BAD_SHAPE;
-  const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, shared_kv, max_seq_slots);
+  const AttnPlan p = attn_bf16_plan(B, T, n_heads, dh, shared_kv, max_seq_slots, pack);
+  const int columns = n_heads >> pack, group = columns / n_kv_heads;
   const int ntw = p.ntw, qg_max = p.qg_max, bpwg = p.bpwg, nsplit_max = p.nsplit_max;
   const int tiles_per_seq = qg_max * ntw;
-  size_t parts = nsplit_max > 1 ? (size_t)B * tiles_per_seq * n_heads * nsplit_max : 0;
+  size_t parts = nsplit_max > 1 ? part_tiles(B, T, pack, tiles_per_seq) * columns * nsplit_max : 0;
   float* po = ws;
   float* pm = ws + parts * (dh / 32 * 1024);
   float* pl = pm + parts * 32;
-  AttnArgs a{q, k_layer, v_layer, anc, node_off, kv_off, prefix_len, status_dev, n_heads, n_heads / n_kv_heads,
-             s_pool, bpwg, nsplit_max, qg_max, B * qg_max * nsplit_max * n_kv_heads, items,
+  AttnArgs a{q, k_layer, v_layer, anc, node_off, kv_off, prefix_len, status_dev, n_heads, s_pool, bpwg, nsplit_max, qg_max,
+             pack, columns, group, B * qg_max * nsplit_max * n_kv_heads, items,
              items + (size_t)B * qg_max * nsplit_max * 8, scale * 1.4426950408889634f, p.lag, po, pm, pl, tiles_per_seq, out, tiled, tp,
              parent, status, T, max_seq_slots};
   if (parent && (B != 1 || tiled)) return TRJ_ERR_BAD_SHAPE;
-  const int group = n_heads / n_kv_heads;
   dim3 grid((B * qg_max * n_kv_heads * nsplit_max + 7) / 8 * 8 * group);
   {
     ProfScope ps_(KC_ATTN, st);
@@ -896,7 +940,7 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
   int rc = check_launch();
   if (rc || nsplit_max == 1) return rc;
   ProfScope ps_(KC_ATTN_COMBINE, st);
-  dim3 cgrid(B * tiles_per_seq, n_heads);
+  dim3 cgrid(B * tiles_per_seq, columns);
   if (dh == 128 && nsplit_max <= 4) attn_combine_kernel<128, 4><<<cgrid, 512, 0, st>>>(a);
   else if (dh == 128) attn_combine_kernel<128, 8><<<cgrid, 512, 0, st>>>(a);
   else if (nsplit_max <= 4) attn_combine_kernel<64, 4><<<cgrid, 512, 0, st>>>(a);

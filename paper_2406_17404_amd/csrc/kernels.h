@@ -197,23 +197,25 @@ int launch_tile_activation(const uint16_t* x, int T, int n, int tp, uint16_t* xp
 
 // attn_bf16.hip
 struct AttnPlan {
-  int ntw, qg_max;       // query tiles of 32 rows per workgroup, groups of them per sequence at most
+  int ntw, qg_max;       // query tiles of 32 per workgroup, groups of them per sequence at most
   int bpwg, nsplit_max;  // 32-slot blocks per workgroup, key splits per sequence at most
   bool ring;             // K/V through rings in LDS, else registers
   bool once;             // no ring: all of a workgroup's K/V to LDS at once
   float lag;             // how far the softmax reference may fall behind the running maximum (log2)
 };
+// log2 of the query heads of a K/V head that are worked on together as one column
+int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int max_seq_slots);
 // shared_kv: several workgroups besides a sequence's query groups read the same K/V
-AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int max_seq_slots);
-size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots);
-size_t attn_bf16_item_words(int B, int T, int n_heads, int dh, int max_seq_slots);
+AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int max_seq_slots, int pack);
+size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots, int pack);
+size_t attn_bf16_item_words(int B, int T, int n_heads, int dh, int max_seq_slots, int pack);
 // parent (one sequence, plain `out`): no prologue launch came before, the kernel checks the
 // sequence itself, writes its status and the rows it does not own; anc and items are not read
 int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint16_t* v_layer,
                           const uint64_t* anc, const int32_t* node_off,
                           const int32_t* kv_off, const int32_t* prefix_len,
                           const int32_t* status_dev, const int32_t* items, int B, int T,
-                          int n_heads, int n_kv_heads, bool shared_kv, int dh, int s_pool, int max_seq_slots,
+                          int n_heads, int n_kv_heads, bool shared_kv, int pack, int dh, int s_pool, int max_seq_slots,
                           float scale, float* ws, int tiled, int tp, uint16_t* out, const int32_t* parent,
                           int32_t* status, hipStream_t st);
 
