@@ -70,9 +70,18 @@ struct ManyShape {
 };
 constexpr ManyShape MANY[] = {{GS_MANY_2, 2, 4, 1, 28.f}, {GS_MANY_4x4, 4, 4, 2, 37.f},
                               {GS_MANY_4x8, 4, 8, 2, 55.f}, {GS_MANY_8x8, 8, 8, 4, 95.f}};
+static long many_wgs(const ManyShape& c, int ttiles, int ntiles) {
+  return (long)((ntiles + c.rows - 1) / c.rows) * ((ttiles + c.tokens - 1) / c.tokens);
+}
+// Where two groups of wavefronts take turns (gemm_pair.h): the 4 x 4 tile, if a compute unit has no
+// second workgroup to work in the gaps (more workgroups: 22016 x 4096 at 1024 rows 227 against 210 us)
+// and all phases are whole.
+static bool pair_runs(const ManyShape& c, int ttiles, int ntiles, int ksteps, int split) {
+  return c.s == GS_MANY_4x4 && ksteps % PAIR_PHASE == 0 && split == 1 && many_wgs(c, ttiles, ntiles) <= 256;
+}
 static float many_cost(const ManyShape& c, int ttiles, int ntiles, int ksteps, int split) {
-  const long wgs = (long)((ntiles + c.rows - 1) / c.rows) * ((ttiles + c.tokens - 1) / c.tokens) * split;
-  return (float)((wgs + 255) / 256) * c.us * ksteps / (256.f * split);
+  const float us = pair_runs(c, ttiles, ntiles, ksteps, split) ? 34.f : c.us;
+  return (float)((many_wgs(c, ttiles, ntiles) * split + 255) / 256) * us * ksteps / (256.f * split);
 }
 static const ManyShape& plan_many(int ttiles, int ntiles, int ksteps, int split) {
   const ManyShape* best = nullptr;
@@ -96,12 +105,14 @@ static GemmPlan plan_split(int tp, int n_in, int n_out, int split_k) {
     return (nph + pps - 1) / pps;
   };
   g.many = many_rows(tp);
+  g.pair = false;
   if (g.many) {
     const ManyShape& c = plan_many(ttiles, ntiles, ksteps, split_k);
     g.shape = c.s;
     g.mt = c.tokens;
     g.rows = c.rows;
-    g.kw = c.s == GS_MANY_2 ? 4 : 1;
+    g.pair = pair_runs(c, ttiles, ntiles, ksteps, split_k);
+    g.kw = c.s == GS_MANY_2 ? 4 : g.pair ? 2 : 1;
     g.wt = c.wt;
   } else {
     g.mt = ttiles < 4 ? ttiles : 4;

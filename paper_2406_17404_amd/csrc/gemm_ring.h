@@ -343,6 +343,10 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
   }
 }
 
+}  // namespace trj
+#include "gemm_pair.h"
+namespace trj {
+
 // ---- launch plan (gemm_bf16.hip)
 enum GemmShape {  // {row groups, token groups, k-parts} of wavefronts x {row, token} tiles per wavefront
   GS_4x1, GS_2x4, GS_2x2, GS_4x2, GS_1x4, GS_3x2,  // RT row tiles x KW k-parts, all token tiles of the pass
@@ -355,6 +359,7 @@ struct GemmPlan {
   int rows, kw, wt;     // row tiles per workgroup, k-parts per workgroup, row tiles per wavefront
   int split_k;
   bool many;
+  bool pair;            // gemm_pair_kernel
 };
 GemmPlan plan_gemm(int tp, int n_in, int n_out, int split_k);
 // k-steps per phase; with it the number of phases and the k-splits a request really gets
@@ -420,7 +425,8 @@ static int launch_gemm(const uint16_t* xp, const uint16_t* w, int tp, int n_in, 
       launch_ring_t<2, 1, 4, 1, 4, gemm_phase(GS_MANY_2), 3, false>(xp, w, tp, n_in, n_out, g.split_k, epi, st);
       break;
     case GS_MANY_4x4:
-      launch_ring_t<2, 2, 1, 2, 2, gemm_phase(GS_MANY_4x4), 4, false>(xp, w, tp, n_in, n_out, g.split_k, epi, st);
+      if (g.pair) launch_pair(xp, w, tp, n_in, n_out, epi, st);
+      else launch_ring_t<2, 2, 1, 2, 2, gemm_phase(GS_MANY_4x4), 4, false>(xp, w, tp, n_in, n_out, g.split_k, epi, st);
       break;
     case GS_MANY_4x8:
       launch_ring_t<2, 2, 1, 2, 4, gemm_phase(GS_MANY_4x8), 3, false>(xp, w, tp, n_in, n_out, g.split_k, epi, st);
