@@ -837,8 +837,10 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
   const int min_b = tune().attn_min_bpw > 0 ? tune().attn_min_bpw * (p.ntw == 4 ? 2 : 4)
                                             : (p.ntw == 4 || (p.ntw == 2 && nmax <= 64) ? 4 : 8);
   if (b < min_b) b = min_b;
-  // one and four tiles have half the key streams that workgroups of eight wavefronts could have
-  p.lag = p.ntw == 2 ? 0.f : SOFTMAX_LAG;
+  // one and four tiles have half the key streams that workgroups of eight wavefronts could have, and
+  // packed heads fewer splits than single ones (20 rows on 8192 slots 2.11e-3 without
+  // lag, 2.03e-3 with; single heads 2.03e-3)
+  p.lag = p.ntw == 2 && pack == 0 ? 0.f : SOFTMAX_LAG;
   // up to 16 blocks (four per stream) the walk is shorter than the merge launch that a split
   // needs: 16 rows on 300 slots 11.9 against 13.6 us a call, 64 rows on 128 12.9 against 15.1,
   // on 512 (18 blocks) 17.2 against 15.9
@@ -904,7 +906,11 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
     ProfScope ps_(KC_ATTN, st);
     // loads without registers need operands on multiples of 16 bytes
     const bool aligned = (((uintptr_t)q | (uintptr_t)k_layer | (uintptr_t)v_layer | (uintptr_t)anc) & 15) == 0;
-    const bool ring = p.ring && aligned, once = p.once && aligned;
+    // several query groups of a sequence that the kernel checks itself find each other's blocks in the
+    // caches while the ancestor bits are worked out, which at once has to wait for (100 rows on 600
+    // slots 17.0 against 19.8 us, 128 on 760 18.4, 18.2; behind a prologue, 96 rows on 500 in the
+    // step, at once is 1 us a layer ahead)
+    const bool ring = p.ring && aligned, once = p.once && aligned && (qg_max == 1 || !parent);
 #define TRJ_ATTN_A(DH, Q, KS, D, FORM, SELF)                                                      \
   do {                                                                                          \
     constexpr size_t rings = (size_t)(KS * 2 * D + Q) * DH * 64 + Q * 1024;                     \
