@@ -161,8 +161,9 @@ int32_t tree_attention(const void* q, const void* k_layer, const void* v_layer,
                        int32_t max_seq_slots, int32_t dtype, float scale, void* workspace,
                        size_t ws_bytes, void* out, void* stream);
 
-/* Bytes of device scratch tree_attention alone needs at these sizes (at most what
- * trj_workspace_bytes reports for a model with these heads). */
+/* Bytes of device scratch that let tree_attention choose its launch at these sizes, whatever
+ * the number of K/V heads.  What trj_workspace_bytes reports for a model with these heads is
+ * enough too: where only that fits, query heads that share K/V are worked on one by one. */
 int32_t tree_attention_workspace_bytes(int32_t B, int32_t T, int32_t n_heads, int32_t head_dim,
                                        int32_t max_seq_slots, int32_t dtype, size_t* h_bytes);
 
@@ -170,9 +171,9 @@ int32_t tree_attention_workspace_bytes(int32_t B, int32_t T, int32_t n_heads, in
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same kernels and results, with the scratch in a fixed array of
  * TRJ_STATIC_SCRATCH_BYTES inside the library (every GPU the library runs on holds one
- * copy until the process ends).  A call for which tree_attention_workspace_bytes reports
- * more than that returns TRJ_ERR_WORKSPACE_TOO_SMALL and does nothing (the need is the
- * partial sums of sequences whose keys are split over several workgroups: 8 to 17 MiB for
+ * copy until the process ends).  A call that needs more than that even
+ * with its query heads one by one returns TRJ_ERR_WORKSPACE_TOO_SMALL and does nothing (the need is
+ * the partial sums of sequences whose keys are split over several workgroups: 8 to 21 MiB for
  * one to four sequences with 32 heads of 128 at any length, little for larger batches;
  * more only when a development knob asks for more splits).  No
  * hipMalloc, hipFree or other allocating call is made.  All calls on one GPU share that

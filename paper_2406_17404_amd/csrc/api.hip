@@ -106,16 +106,16 @@ static void carve_tree(Carver& c, int dtype, int B, int T, int H, bool shared_kv
 }
 
 static int model_pack(const trj_model_desc& m, int B, int T, int max_seq_slots) {
-  return m.n_kv_heads ? attn_bf16_pack(B, T, m.n_heads, m.n_kv_heads, max_seq_slots) : 0;
+  return m.dtype == TRJ_BF16 && m.n_kv_heads ? attn_bf16_pack(B, T, m.n_heads, m.n_kv_heads, max_seq_slots) : 0;
 }
 // several columns per K/V head
-static bool model_shares_kv(const trj_model_desc& m, int B, int T, int max_seq_slots) {
-  return m.n_kv_heads && m.n_kv_heads != m.n_heads >> model_pack(m, B, T, max_seq_slots);
+static bool model_shares_kv(const trj_model_desc& m, int pack) {
+  return m.n_kv_heads && m.n_kv_heads != m.n_heads >> pack;
 }
 static void carve_step(Carver& c, const trj_model_desc& m, int B, int T, int max_seq_slots,
-                       bool head_scratch, bool shared_kv, StepWs* w) {
+                       bool head_scratch, bool shared_kv, int pack, StepWs* w) {
   const int d = m.d_model, hd = m.n_heads * m.head_dim, F = m.d_ffn;
-  carve_tree(c, m.dtype, B, T, m.n_heads, shared_kv, model_pack(m, B, T, max_seq_slots), m.head_dim, max_seq_slots, &w->t);
+  carve_tree(c, m.dtype, B, T, m.n_heads, shared_kv, pack, m.head_dim, max_seq_slots, &w->t);
   w->cs = c.take<float2>((size_t)T * (m.head_dim / 2));
   w->x = c.take<float>((size_t)T * d);
   // the head's own scratch: the fp32 mode's logits (if the caller keeps none), the bf16 mode's
@@ -137,6 +137,20 @@ static void carve_step(Carver& c, const trj_model_desc& m, int B, int T, int max
     w->of = c.take<float>((size_t)T * hd);
     w->actf = c.take<float>((size_t)T * F);
   }
+}
+// Of a step with these sizes, however its heads are packed: a smaller step in the same workspace may
+// pack other numbers of them (32 heads on 8 K/V heads beyond 512 slots: 32 rows none, 24 rows four).
+static size_t step_bytes(const trj_model_desc& m, int B, int T, int max_seq_slots) {
+  const int share = m.n_kv_heads ? m.n_heads / m.n_kv_heads : 1;
+  size_t most = 0;
+  for (int pack = 0; pack <= 3 && share % (1 << pack) == 0; ++pack) {
+    Carver c(nullptr);
+    StepWs w;
+    carve_step(c, m, B, T, max_seq_slots, true, model_shares_kv(m, pack), pack, &w);
+    most = c.off > most ? c.off : most;
+    if (m.dtype != TRJ_BF16) break;
+  }
+  return most;
 }
 
 static int check_desc(const trj_model_desc* m) {
@@ -282,10 +296,7 @@ int32_t trj_workspace_bytes(const trj_model_desc* desc, int32_t t_max, int32_t b
   TRJ_TRY(check_desc(desc));
   if (t_max < 1 || b_max < 1 || l_max < 1) return TRJ_ERR_BAD_SHAPE;
   TuneScope tune_scope;
-  Carver c(nullptr);
-  StepWs w;
-  carve_step(c, *desc, b_max, t_max, l_max, true, model_shares_kv(*desc, b_max, t_max, l_max), &w);
-  *h_bytes = align_up(c.off, 256);
+  *h_bytes = align_up(step_bytes(*desc, b_max, t_max, l_max), 256);
   return TRJ_OK;
 }
 
@@ -655,13 +666,24 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
   StepWs w;
   const bool bf16 = m.dtype == TRJ_BF16;
   // heads of a group read the same K/V, and so do the chunks of a prompt that a pass packs
-  const bool shared_kv = model_shares_kv(m, B, T, max_seq_slots) || (!with_head && B > 1);
-  carve_step(c, m, B, T, max_seq_slots, with_head && (bf16 || !logits), shared_kv, &w);
-  if (c.off > ws_bytes && bf16 && logits) {  // no room for the candidates: argmax of the written logits
+  // (packed heads, or each by itself if only that fits)
+  int pack = model_pack(m, B, T, max_seq_slots);
+  bool shared_kv = false;
+  auto carve = [&](Carver& c) {
+    shared_kv = model_shares_kv(m, pack) || (!with_head && B > 1);
     c = Carver(workspace);
-    carve_step(c, m, B, T, max_seq_slots, false, shared_kv, &w);
+    carve_step(c, m, B, T, max_seq_slots, with_head && (bf16 || !logits), shared_kv, pack, &w);
+    if (c.off > ws_bytes && bf16 && logits) {  // no room for the candidates: argmax of the written logits
+      c = Carver(workspace);
+      carve_step(c, m, B, T, max_seq_slots, false, shared_kv, pack, &w);
+    }
+    return c.off <= ws_bytes;
+  };
+  if (!carve(c)) {
+    if (pack == 0) return TRJ_ERR_WORKSPACE_TOO_SMALL;
+    pack = 0;
+    if (!carve(c)) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   }
-  if (c.off > ws_bytes) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   float* lg = logits ? logits : w.logits;
   const float scale = 1.0f / sqrtf((float)dh);
 
@@ -767,10 +789,7 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
 // workspace bytes of one step_impl call (pure arithmetic)
 size_t step_workspace_bytes(const trj_model_desc& m, int B, int T, int max_seq_slots) {
   TuneScope tune_scope;
-  Carver c(nullptr);
-  StepWs w;
-  carve_step(c, m, B, T, max_seq_slots, true, model_shares_kv(m, B, T, max_seq_slots), &w);
-  return c.off + 256;
+  return step_bytes(m, B, T, max_seq_slots) + 256;
 }
 int check_model(const trj_model_desc* m) { return check_desc(m); }
 

@@ -3,6 +3,7 @@ and lack powers of two, trees that fill the shared tiles exactly, by one query m
 forms of the walk with and without key splits, batches with ragged and malformed trees, and the
 workspace sizes around which heads are packed or not."""
 import math
+from dataclasses import replace
 
 import numpy as np
 import pytest
@@ -15,6 +16,7 @@ from paper_2406_17404_amd import binding as b
 from paper_2406_17404_amd import inputs as I
 from test_gpu_attention import TOL, case, run_attention
 from test_gpu_attention_ring import knobs  # noqa: F401
+from test_gpu_step import prefix_normal, run_and_check
 
 pytestmark = pytest.mark.gpu
 
@@ -99,3 +101,15 @@ def test_less_workspace_still_accepted_where_single_heads_fit():
         for s, c in enumerate(cases):
             assert rel_err(got[s * n:(s + 1) * n], O.tree_attention(*c)) <= TOL["bf16"], size
     assert accepted[0] and not accepted[-1]
+
+
+@pytest.mark.parametrize("n,L", [(16, 1000), (20, 700)])
+def test_step_in_a_workspace_that_holds_single_heads_only(monkeypatch, n, L):
+    """Sized for a larger tree, whose heads are not packed, a workspace holds this one's single heads."""
+    shape = I.ModelShape(2, 256, 16, 128, 512, 512, "bf16", n_kv_heads=4)
+    size, packed = (b.trj_workspace_bytes(b.make_desc(s), n, 1, L + n)
+                    for s in (replace(shape, n_kv_heads=0), shape))
+    assert size < packed
+    monkeypatch.setattr(b, "trj_workspace_bytes", lambda *sizes: size)
+    run_and_check(shape, I.gen_weights(shape, 88), [I.tree_random(n, np.random.default_rng(n))],
+                  [I.gen_tokens(shape.vocab, n, 88, "tree", 0)], [L], [prefix_normal(shape, 88, 0, L)], 1e-2)
