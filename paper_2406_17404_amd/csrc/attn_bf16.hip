@@ -38,6 +38,7 @@
 // invalidates a whole L2, which measured 3-4x the cost of the separate launch.)
 #include <type_traits>
 
+#include "attn_parts.h"
 #include "common.h"
 #include "kernels.h"
 #include "tree_vis.h"
@@ -69,7 +70,7 @@ struct AttnArgs {
   // length, first K/V block of the sequence, key split; a workgroup needs nothing else
   // from memory to find its work, and reads record and count together.
   const int32_t* items;
-  const int32_t* n_items;
+  const int32_t* n_items;  // and, behind it, whether packed heads are walked without splits (attn_parts.h)
   float scale_log2e;
   float lag;  // of the softmax reference behind the running maximum, log2
   // un-normalised partials, one per (query tile, column, split), stored as the
@@ -173,18 +174,6 @@ __device__ inline void rescale_o(f32x16 (&o)[MTV], float alpha) {
     for (int v = 0; v < 16; ++v) o[mt][v] *= alpha;
 }
 
-// Place of a sequence's first query tile among the partials' (of part_tiles).  Single heads: every
-// sequence has room for the most tiles one could have.  Packed, that would be many times the tiles
-// there are (sequences of 20 rows: 16 for 3): behind the rows in front of it, and one more per
-// sequence for their last tiles that are not full.  The first sequence's place does not depend on
-// its rows, so that the merge of a single one need not wait for them.
-__device__ inline int part_first(const AttnArgs& a, int s, int r0) {
-  return a.pack == 0 ? s * a.tiles_per_seq : s == 0 ? 0 : ((r0 << a.pack) >> 5) + s;
-}
-static size_t part_tiles(int B, int T, int pack, int tiles_per_seq) {
-  return pack == 0 ? (size_t)B * tiles_per_seq : ((size_t)T << pack >> 5) + B;
-}
-
 template <int DH>
 __device__ inline void attn_store_row(const AttnArgs& a, int t, int head, int c, u32x2 v) {
   uint16_t* dst = a.tiled ? a.out + a_off(t, head * DH + c, a.tp)
@@ -237,6 +226,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   const int column = (kvg % n_kv) * a.group + slot % a.group;
   const int item = kvg / n_kv;
   int s, qg, r0, n, L, blk_base, sp;
+  bool whole = false;  // no splits, whatever the plan
   bool several;  // another query group or sequence reads the same blocks
   const int head0 = column << a.pack;  // the column's first head
   auto zero_rows = [&](int t0, int t1) {  // rows without a valid sequence read as zeros (this column's part)
@@ -268,14 +258,16 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
     const int32_t* rec = a.items + (size_t)item * 8;  // inside the list's memory for every id
     s = rec[0], qg = rec[1], r0 = rec[2], n = rec[3], L = rec[4], blk_base = rec[5], sp = rec[6];
     several = rec[7] != 0;
+    whole = a.pack > 0 && a.n_items[1] != 0;
     if (item >= a.n_items[0]) return;  // uniform over the workgroup, before any barrier
   }
   const int total = L + n;
   const int nb = (total + 31) >> 5;
-  const int nsplit = (nb + a.bpwg - 1) / a.bpwg;
+  const int bpwg = whole ? nb : a.bpwg;
+  const int nsplit = (nb + bpwg - 1) / bpwg;
   const int nq = n << a.pack;  // queries of the column
   if (sp >= nsplit || qg * 32 * NTW >= nq) return;  // uniform as well
-  const int b0 = sp * a.bpwg, b1 = min(nb, b0 + a.bpwg);
+  const int b0 = sp * bpwg, b1 = min(nb, b0 + bpwg);
   const int n32 = lane & 31, hh = lane >> 5;
   // no other workgroup reads these blocks (one query group, no sequence with the same slots, one
   // query head per K/V head): the loads carry the streaming hint; with a second reader through
@@ -450,7 +442,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
           request(kp, 2 * i);
           request(vp, 2 * i + 1);
         }
-    } else {  // all of the range (the plan keeps it to D blocks per stream), K first
+    } else {  // all of the range (the plan keeps it to D blocks per stream), or D of them, K first
 #pragma unroll
       for (int i = 0; i < D; ++i)
         if (i < nblk) request(kp, 2 * i);
@@ -489,26 +481,39 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       anc1 = qi < nq ? (uint64_t)bits[3] << 32 | bits[2] : 0;
     }
     if constexpr (FORM == AF_ONCE) {
-      // only one more meeting, for V, behind the first block's scores and softmax
+      // only one more meeting, for V, behind the first block's scores and softmax; a sequence walked
+      // whole has further turns of D blocks per stream
       static_assert(D == 2, "waits above");
-      const int key0 = (b0 + ks) * 32;
-      float alpha;
-      u32x4 pk[2];
-      const bool some = live && nblk > 0;
-      if (some) {
-        read(kreg, 0);
-        softmax(scores(), key0, alpha, pk);
-      }
-      attn_wait<0, true>();
-      if (some) {
-        read(vreg, 1);
-        add_values(key0, alpha, pk);
-      }
-      if (live && nblk > 1) {
-        read(kreg, 2);
-        read(vreg, 3);
-        softmax(scores(), key0 + KS * 32, alpha, pk);
-        add_values(key0 + KS * 32, alpha, pk);
+      for (int i = 0;;) {
+        const int key0 = (b0 + ks + i * KS) * 32;
+        float alpha;
+        u32x4 pk[2];
+        const bool some = live && i < nblk;
+        if (some) {
+          read(kreg, 0);
+          softmax(scores(), key0, alpha, pk);
+        }
+        attn_wait<0, true>();
+        if (some) {
+          read(vreg, 1);
+          add_values(key0, alpha, pk);
+        }
+        if (live && i + 1 < nblk) {
+          read(kreg, 2);
+          read(vreg, 3);
+          softmax(scores(), key0 + KS * 32, alpha, pk);
+          add_values(key0 + KS * 32, alpha, pk);
+        }
+        i += D;
+        if (i >= rounds) break;  // uniform
+        attn_wait<0, true>();    // everybody has read the last turn's
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+          if (i + j < nblk) {
+            request(kp, 2 * j);
+            request(vp, 2 * j + 1);
+          }
+        attn_wait<0, true>();
       }
     }
     // Block i of this stream: its K is in kreg; its V and the next blocks are on the way (slots
@@ -641,7 +646,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
   }
   __syncthreads();
   if (!live) return;  // no query, no partial; the barriers are behind
-  const size_t pidx = ((size_t)(part_first(a, s, r0) + qg * NTW + nt) * a.columns + column) * a.nsplit_max + sp;
+  const size_t pidx = ((size_t)(part_first(a.pack, a.tiles_per_seq, s, r0) + qg * NTW + nt) * a.columns + column) * a.nsplit_max + sp;
   if (nsplit != 1 && ks == 0 && hh == 0) {
     a.pm[pidx * 32 + n32] = mg;
     a.pl[pidx * 32 + n32] = lg;
@@ -693,10 +698,11 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
   // for one after the other was a third of this launch (4.2 -> 3.1 us for three splits of 16 rows).
   // Splits that do not exist are left out of maximum and sum, whatever their memory holds.
   const int status = a.status_dev[s], r0 = a.node_off[s], r1 = a.node_off[s + 1], L = a.prefix_len[s];
+  const bool whole = a.pack > 0 && !a.parent && a.n_items[1] != 0;  // (a.parent: there is no list)
   // packed: the tile may have no place, and r0 of an invalid sequence be anything
   if (a.pack > 0 && s > 0 && (status != 0 || tile * 32 >= (r1 - r0) << a.pack)) return;
   const int there = a.pack > 0 && s == 0 ? min(tile, (a.T << a.pack) >> 5) : tile;
-  const int place = part_first(a, s, r0) + there;
+  const int place = part_first(a.pack, a.tiles_per_seq, s, r0) + there;
   const size_t base = ((size_t)place * a.columns + column) * a.nsplit_max;
   float ms[CB], ls[CB], x[CB][8];
   auto load = [&](int k0, int last) {
@@ -712,7 +718,7 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
   };
   load(0, a.nsplit_max - 1);
   const int n = r1 - r0, nq = n << a.pack;
-  if (status != 0 || tile * 32 >= nq) return;  // rows of malformed sequences stay zero
+  if (status != 0 || tile * 32 >= nq || whole) return;  // rows of malformed sequences stay zero
   const int nb = (L + n + 31) >> 5;
   const int nsplit = (nb + a.bpwg - 1) / a.bpwg;
   if (nsplit == 1) return;  // written by the attention kernel itself

@@ -2,6 +2,7 @@
 // rows), greedy argmax, longest accepted path, KV compaction, and the layout
 // converters.  All results here are exact (no floating point decides anything except
 // the comparisons inside argmax).
+#include "attn_parts.h"
 #include "common.h"
 #include "embed_row.h"
 #include "kernels.h"
@@ -191,7 +192,13 @@ __device__ inline void attn_items_body(
     carry += scan[1023];
     __syncthreads();
   }
-  if (tid == 0) items[(size_t)B * qg_max * nsplit_max * 8] = carry;
+  bool descends = false;
+  for (int s = tid; s < B; s += 1024) descends |= range_descends(node_off, s);
+  const int any = __syncthreads_or(descends);
+  if (tid == 0) {
+    items[(size_t)B * qg_max * nsplit_max * 8] = carry;
+    items[(size_t)B * qg_max * nsplit_max * 8 + 1] = any;
+  }
 }
 
 __global__ __launch_bounds__(1024) void attn_items_kernel(
@@ -358,6 +365,7 @@ __device__ inline void few_items_body(const int32_t* node_off, const int32_t* pr
   }
   __syncthreads();
   const int total = end[PREP_MAX_SEQS - 1];
+  const int any = __syncthreads_or(tid < B && range_descends(node_off, tid));
   for (int r = tid; r < total; r += blockDim.x) {
     int p = 0;
     while (end[p] <= r) ++p;
@@ -373,7 +381,10 @@ __device__ inline void few_items_body(const int32_t* node_off, const int32_t* pr
     rec[6] = j / ng;
     rec[7] = shared[s];
   }
-  if (tid == 0) items[(size_t)B * qg_max * nsplit_max * 8] = total;
+  if (tid == 0) {
+    items[(size_t)B * qg_max * nsplit_max * 8] = total;
+    items[(size_t)B * qg_max * nsplit_max * 8 + 1] = any;
+  }
 }
 
 __device__ inline void prep_all_sequences(const StepPrep& a) {
