@@ -24,3 +24,15 @@ def test_the_copy_is_the_callees_own():
     buf, _ = b._host_i32(a)
     a[0] = 99
     assert buf[0] == 0
+
+
+def test_other_one_dimensional_arrays_go_number_by_number():
+    """What only looks like a numpy array (pandas' Series and Index have its ndim and dtype) is taken
+    as before, and a masked array with a masked number in it is refused as before."""
+    pd = pytest.importorskip("pandas")
+    for values in (pd.Series([3, 1, 2]), pd.Series([3, 1, 2], index=[7, 8, 9]), pd.Index([4, 5]),
+                   pd.Series(np.array([1, 2], np.int32)), np.ma.MaskedArray([1, 2, 3])):
+        buf, n = b._host_i32(values)
+        assert n == len(values) and list(buf) == [int(v) for v in values]
+    with pytest.raises(Exception):
+        b._host_i32(np.ma.MaskedArray([1, 2, 3], mask=[0, 1, 0]))
