@@ -47,7 +47,8 @@ int32_t trj_dev_attn_plan(int32_t B, int32_t T, int32_t n_heads, int32_t head_di
  * is split up to), "max_split_k", "gemm_cfg" (0: choose the workgroup shape per
  * projection, 1..6 force one), "gemm_big_t" (padded token rows from which the packed-batch
  * projection kernel is used, 0: never), "gemm_big_wt" (row tiles per wavefront of that
- * kernel: 2, 4, or 0 to choose per projection), "attn_target_wgs" (attention workgroups aimed at
+ * kernel: 2, 4, or 0 to choose per projection), "gemm_pair_min_k" (k range from which that kernel's
+ * 4 x 4 tile may have two groups of wavefronts take turns), "attn_target_wgs" (attention workgroups aimed at
  * per launch), "attn_min_bpw" (32-slot blocks per key stream, at least; 0 = chosen from the tree
  * size), "attn_xchg_min_blocks" (32-slot blocks of 32 heads from which the wavefronts of a
  * key stream share its K/V through rings in LDS for one query tile, twice as many for two and

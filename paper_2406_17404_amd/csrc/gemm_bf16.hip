@@ -74,10 +74,13 @@ static long many_wgs(const ManyShape& c, int ttiles, int ntiles) {
   return (long)((ntiles + c.rows - 1) / c.rows) * ((ttiles + c.tokens - 1) / c.tokens);
 }
 // Where two groups of wavefronts take turns (gemm_pair.h): the 4 x 4 tile, if a compute unit has no
-// second workgroup to work in the gaps (more workgroups: 22016 x 4096 at 1024 rows 227 against 210 us)
-// and all phases are whole.
+// second workgroup to work in the gaps (more workgroups: 22016 x 4096 at 1024 rows 227 against 210 us),
+// all phases are whole and the k range is long enough for the ring of five buffers to fill and drain:
+// bare products with cold weights, without turns -> with, us: 4096 x 1024 at 1024 rows 18.9 -> 19.8,
+// 8192 x 2048 at 512 28.5 -> 30.2, 11008 x 2048 at 160 26.6 -> 28.9; 4096 x 4096 at 1024 51.0 -> 49.7,
+// 4096 x 11008 116.7 -> 114.0.
 static bool pair_runs(const ManyShape& c, int ttiles, int ntiles, int ksteps, int split) {
-  return c.s == GS_MANY_4x4 && ksteps % PAIR_PHASE == 0 && split == 1 && many_wgs(c, ttiles, ntiles) <= 256;
+  return c.s == GS_MANY_4x4 && ksteps % PAIR_PHASE == 0 && ksteps * 16 >= tune().gemm_pair_min_k && split == 1 && many_wgs(c, ttiles, ntiles) <= 256;
 }
 static float many_cost(const ManyShape& c, int ttiles, int ntiles, int ksteps, int split) {
   const float us = pair_runs(c, ttiles, ntiles, ksteps, split) ? 34.f : c.us;

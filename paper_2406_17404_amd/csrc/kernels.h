@@ -10,6 +10,7 @@ struct Tunables {
   int max_split_k = 8;
   int gemm_cfg = 0;            // 0: choose the workgroup shape per GEMM; 1..6 force one
   int gemm_big_t = 256;        // padded token rows from which wavefronts own two row tiles (0: never)
+  int gemm_pair_min_k = 4096;  // k range from which two groups of wavefronts may take turns (gemm_pair.h)
   int attn_target_wgs = 256;   // attention workgroups per launch aimed at (one per CU)
   int gemm_big_wt = 0;         // row tiles per wavefront of the many-rows kernel (2, 4; 0 = choose)
   int attn_xchg_min_blocks = 48;  // blocks of 32 heads from which K/V go through rings, one query tile (1: always)

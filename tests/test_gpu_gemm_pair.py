@@ -13,6 +13,14 @@ from test_gpu_linear import run_linear
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def short_k_ranges_too():
+    """By itself the plan takes turns from a k range of 4096 on (test_gemm_pair_plan_cpu.py)."""
+    b.trj_set_tunable("gemm_pair_min_k", 64)
+    yield
+    b.trj_set_tunable("gemm_pair_min_k", 4096)
+
+
 def takes_turns(T, n_in, n_out):
     plan = b.trj_dev_gemm_plan(T, n_in, n_out, True)
     return plan["many_rows"] == 1 and plan["row_tiles"] == 4 and plan["k_parts"] == 2
