@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "f32_rule.h"
 #include "kernels.h"
 #include "tree_vis.h"
 
@@ -55,7 +56,7 @@ int launch_embed(const float* embed, const int32_t* tok, int T, int d, int vocab
 // 32 parts are added in order through LDS.  With a gain `g` the input is RMSNorm(x): the
 // products use x * g and the sum is divided by the token's norm, whose sum of squares comes
 // from the same reads.
-constexpr int F32_PARTS = 32, F32_THREADS = 32 * F32_PARTS;
+constexpr int F32_THREADS = 32 * F32_PARTS;
 struct GemmF32Args {
   const float *x, *w, *g;
   int T, n_in;
@@ -182,10 +183,7 @@ struct EpiF32QKV {
     else k_layer[(size_t)head * s_pool * dh + k_off(slot, c, dh)] = r;
   }
 };
-// tokens per workgroup: four while that keeps the launch within the chip, eight beyond (every
-// group of tokens reads the weights again); where a thread has more than one granule (n_in > 256)
-// and there are few rows, fewer tokens and several granules at a time, whose latencies would
-// otherwise follow one another (15 rows, 256 x 1024: 7.7 -> 5.4 us)
+// tokens per workgroup: gemm_f32_tokens; behind a norm four or eight
 template <class Epi>
 static int gemm_f32(const GemmF32Args& a, int n_out, const Epi& e, hipStream_t st) {
   if (a.T < 1 || a.n_in < 16 || n_out < 32 || (a.n_in & 15) || (n_out & 31)) return TRJ_ERR_BAD_SHAPE;
@@ -194,9 +192,10 @@ static int gemm_f32(const GemmF32Args& a, int n_out, const Epi& e, hipStream_t s
     if (a.T <= 16) gemm_f32_kernel<4, 1, true><<<by4, F32_THREADS, 0, st>>>(a, e);
     else gemm_f32_kernel<8, 1, true><<<by8, F32_THREADS, 0, st>>>(a, e);
   } else if constexpr (std::is_same_v<Epi, EpiF32Store>) {  // the others follow a norm
-    if (a.n_in > 8 * F32_PARTS && a.T <= 32)
+    const int tokens = gemm_f32_tokens(a.T, a.n_in, n_out);
+    if (tokens == 2)
       gemm_f32_kernel<2, 4, false><<<dim3(n_out / 32, (a.T + 1) / 2), F32_THREADS, 0, st>>>(a, e);
-    else if (a.T <= 16) gemm_f32_kernel<4, 1, false><<<by4, F32_THREADS, 0, st>>>(a, e);
+    else if (tokens == 4) gemm_f32_kernel<4, 1, false><<<by4, F32_THREADS, 0, st>>>(a, e);
     else gemm_f32_kernel<8, 1, false><<<by8, F32_THREADS, 0, st>>>(a, e);
   } else {
     return TRJ_ERR_NULLPTR;
