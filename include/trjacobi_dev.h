@@ -35,13 +35,22 @@ int32_t trj_linear(const void* x, const void* w_packed, int32_t T, int32_t n_in,
  * grid k-splits, 1 if the many-rows kernel (packed batches) is used. */
 int32_t trj_dev_gemm_plan(int32_t T, int32_t n_in, int32_t n_out, int32_t fused, int32_t* h_plan);
 
-/* The launch plan of a bf16 attention over B sequences with T rows in all.  shared_kv != 0:
- * several query heads per K/V head.  h_plan[6] (HOST): query tiles per workgroup, query groups
+/* The launch plan of a bf16 attention over B sequences with T rows in all whose query heads are
+ * worked on one by one.  shared_kv != 0: several query heads per K/V head.  h_plan[6] (HOST): query tiles per workgroup, query groups
  * per sequence, 32-slot blocks per workgroup, key splits, 1 if K/V go through rings in LDS
  * (operands on multiples of 16 bytes), 1 if every block's largest key sets the softmax
  * reference. */
 int32_t trj_dev_attn_plan(int32_t B, int32_t T, int32_t n_heads, int32_t head_dim, int32_t shared_kv,
                           int32_t max_seq_slots, int32_t* h_plan);
+
+/* The launch that tree_attention, or with in_step != 0 a verify step, really makes for these sizes
+ * where the workspace has room for it and all operands start at multiples of 16 bytes.  h_plan[7]
+ * (HOST): log2 of the query heads of a K/V head that are worked on together, query tiles per
+ * workgroup, query groups per sequence at most, 32-slot blocks per workgroup, key splits, form (0
+ * K/V to registers, 1 through rings in LDS, 2 all of a workgroup's K/V to LDS at once), 1 if every
+ * block's largest key sets the softmax reference. */
+int32_t trj_dev_attn_launch(int32_t B, int32_t T, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
+                            int32_t max_seq_slots, int32_t in_step, int32_t* h_plan);
 
 /* Launch-shape knobs for experiments: "gemm_target_wgs" (workgroups a split-k projection
  * is split up to), "max_split_k", "gemm_cfg" (0: choose the workgroup shape per

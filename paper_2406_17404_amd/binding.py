@@ -74,6 +74,7 @@ _SIGS = {
     "trj_dev_device_info": (_i32, [_ip]),
     "trj_dev_gemm_plan": (_i32, [_i32, _i32, _i32, _i32, _ip]),
     "trj_dev_attn_plan": (_i32, [_i32, _i32, _i32, _i32, _i32, _i32, _ip]),
+    "trj_dev_attn_launch": (_i32, [_i32] * 7 + [_ip]),
     "trj_workspace_bytes": (_i32, [C.POINTER(ModelDesc), _i32, _i32, _i32, C.POINTER(_sz)]),
     "trj_pack_weight": (_i32, [_vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp]),
     "trj_kv_pack": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp]),
@@ -210,6 +211,17 @@ def trj_dev_attn_plan(B: int, T: int, n_heads: int, head_dim: int, shared_kv: bo
     out = (C.c_int32 * 6)()
     _check("trj_dev_attn_plan", lib().trj_dev_attn_plan(B, T, n_heads, head_dim, int(shared_kv), max_seq_slots, out))
     return dict(zip(("tiles", "groups", "blocks", "splits", "ring", "lag"), (int(v) for v in out)))
+
+
+def trj_dev_attn_launch(B: int, T: int, n_heads: int, n_kv_heads: int, head_dim: int, max_seq_slots: int,
+                        in_step: bool = False) -> dict:
+    out = (C.c_int32 * 7)()
+    _check("trj_dev_attn_launch", lib().trj_dev_attn_launch(B, T, n_heads, n_kv_heads, head_dim, max_seq_slots,
+                                                            int(in_step), out))
+    names = ("pack", "tiles", "groups", "blocks", "splits", "form", "lag")
+    plan = dict(zip(names, (int(v) for v in out)))
+    plan["form"] = ("registers", "ring", "once")[plan["form"]]
+    return plan
 
 
 def trj_workspace_bytes(desc: ModelDesc, t_max: int, b_max: int, l_max: int) -> int:

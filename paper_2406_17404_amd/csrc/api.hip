@@ -621,6 +621,21 @@ int32_t trj_dev_attn_plan(int32_t B, int32_t T, int32_t n_heads, int32_t head_di
   return TRJ_OK;
 }
 
+int32_t trj_dev_attn_launch(int32_t B, int32_t T, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
+                            int32_t max_seq_slots, int32_t in_step, int32_t* h_plan) {
+  if (!h_plan) return TRJ_ERR_NULLPTR;
+  if (n_kv_heads == 0) n_kv_heads = n_heads;
+  if (B < 1 || T < B || (long)T > (long)B * TRJ_N_MAX || n_heads < 1 || n_kv_heads < 1 || n_heads % n_kv_heads != 0 ||
+      (head_dim != 64 && head_dim != 128) || max_seq_slots < 1)
+    return TRJ_ERR_BAD_SHAPE;
+  TuneScope tune_scope;
+  const int pack = attn_bf16_pack(B, T, n_heads, n_kv_heads, max_seq_slots);
+  const AttnPlan p = attn_bf16_plan(B, T, n_heads, head_dim, n_heads >> pack != n_kv_heads, max_seq_slots, pack);
+  const int32_t v[7] = {pack, p.ntw, p.qg_max, p.bpwg, p.nsplit_max, attn_bf16_form(p, B == 1 && !in_step, true), p.lag > 0.f};
+  memcpy(h_plan, v, sizeof(v));
+  return TRJ_OK;
+}
+
 }  // extern "C"
 
 namespace trj {

@@ -45,7 +45,6 @@
 
 namespace trj {
 
-enum AttnForm { AF_REGISTERS, AF_RING, AF_ONCE };  // see the top
 constexpr float NEG_BIG = -1e30f;
 constexpr float SOFTMAX_LAG = 8.f;  // see softmax_tile_prefix; smaller weights are below a bf16 step of the largest
 
@@ -866,6 +865,16 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
   return p;
 }
 
+// Loads without registers need operands on multiples of 16 bytes.  Several query groups of a sequence
+// that the kernel checks itself find each other's blocks in the caches while the ancestor bits are
+// worked out, which at once has to wait for (100 rows on 600 slots 17.0 against 19.8 us, 128 on 760
+// 18.4, 18.2; behind a prologue, 96 rows on 500 in the step, at once is 1 us a layer ahead).
+AttnForm attn_bf16_form(const AttnPlan& p, bool self, bool aligned) {
+  if (!aligned) return AF_REGISTERS;
+  if (p.ring) return AF_RING;
+  return p.once && (p.qg_max == 1 || !self) ? AF_ONCE : AF_REGISTERS;
+}
+
 // scratch for either answer to "do query heads share K/V": the workspace queries do not know
 size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots, int pack) {
   size_t most = 64;  // no partials needed when every sequence fits one workgroup
@@ -910,13 +919,9 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
   dim3 grid((B * qg_max * n_kv_heads * nsplit_max + 7) / 8 * 8 * group);
   {
     ProfScope ps_(KC_ATTN, st);
-    // loads without registers need operands on multiples of 16 bytes
     const bool aligned = (((uintptr_t)q | (uintptr_t)k_layer | (uintptr_t)v_layer | (uintptr_t)anc) & 15) == 0;
-    // several query groups of a sequence that the kernel checks itself find each other's blocks in the
-    // caches while the ancestor bits are worked out, which at once has to wait for (100 rows on 600
-    // slots 17.0 against 19.8 us, 128 on 760 18.4, 18.2; behind a prologue, 96 rows on 500 in the
-    // step, at once is 1 us a layer ahead)
-    const bool ring = p.ring && aligned, once = p.once && aligned && (qg_max == 1 || !parent);
+    const AttnForm form = attn_bf16_form(p, parent != nullptr, aligned);
+    const bool ring = form == AF_RING, once = form == AF_ONCE;
 #define TRJ_ATTN_A(DH, Q, KS, D, FORM, SELF)                                                      \
   do {                                                                                          \
     constexpr size_t rings = (size_t)(KS * 2 * D + Q) * DH * 64 + Q * 1024;                     \

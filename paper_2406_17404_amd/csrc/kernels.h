@@ -197,6 +197,7 @@ int launch_sum_splits(const float* partial, int n_split, size_t n, float* y, hip
 int launch_tile_activation(const uint16_t* x, int T, int n, int tp, uint16_t* xp, hipStream_t st);
 
 // attn_bf16.hip
+enum AttnForm { AF_REGISTERS, AF_RING, AF_ONCE };  // how K/V come to a wavefront
 struct AttnPlan {
   int ntw, qg_max;       // query tiles of 32 per workgroup, groups of them per sequence at most
   int bpwg, nsplit_max;  // 32-slot blocks per workgroup, key splits per sequence at most
@@ -206,6 +207,9 @@ struct AttnPlan {
 };
 // log2 of the query heads of a K/V head that are worked on together as one column
 int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int max_seq_slots);
+// the form in which a plan runs.  self: one sequence that the kernel checks itself; aligned: all
+// operands start at multiples of 16 bytes
+AttnForm attn_bf16_form(const AttnPlan& p, bool self, bool aligned);
 // shared_kv: several workgroups besides a sequence's query groups read the same K/V
 AttnPlan attn_bf16_plan(int B, int T, int n_heads, int dh, bool shared_kv, int max_seq_slots, int pack);
 size_t attn_bf16_ws_floats(int B, int T, int n_heads, int dh, int max_seq_slots, int pack);

@@ -1,0 +1,47 @@
+"""The attention launch that really runs, on the host: with grouped-query heads too it covers every
+query and slot of its ranges and fits the workspace the queries report, and with single heads it is
+the plan of trj_dev_attn_plan."""
+import itertools
+
+import pytest
+
+from paper_2406_17404_amd import binding as b
+
+
+def test_every_launch_covers_its_rows_and_slots_and_fits_the_workspace():
+    packed = 0
+    for B, n, slots, (H, Hkv), dh in itertools.product(
+            (1, 2, 3, 5, 8, 16, 40, 70), (1, 5, 9, 16, 20, 32, 33, 64, 69, 100, 128), (200, 520, 700, 1100, 3100, 12100, 33000),
+            ((32, 32), (32, 16), (32, 8), (32, 4), (24, 8), (28, 4), (8, 1)), (64, 128)):
+        for in_step in (False, True):
+            p = b.trj_dev_attn_launch(B, B * n, H, Hkv, dh, slots, in_step)
+            share, heads = H // Hkv, 1 << p["pack"]
+            nb = -(-slots // 32)
+            assert share % heads == 0 and (slots > 512 or heads == 1)
+            assert p["tiles"] * 32 * p["groups"] >= min(B * n, 128) * heads
+            assert 1 <= p["blocks"] <= nb and p["blocks"] * p["splits"] >= nb > p["blocks"] * (p["splits"] - 1)
+            assert p["form"] != "ring" or share == heads          # K/V that several workgroups read come from L2
+            assert p["form"] == "ring" or p["tiles"] < 4
+            assert p["form"] != "once" or (p["tiles"] == 2 and dh == 128)
+            assert p["lag"] == 1 or (p["tiles"] == 2 and heads == 1)
+            queries = B * n * heads
+            parts = (queries // 32 + B if heads > 1 else B * p["groups"] * p["tiles"]) if p["splits"] > 1 else 0
+            floats = parts * (H // heads) * p["splits"] * (dh // 32 * 1024 + 64)
+            items = 8 * B * p["groups"] * p["splits"] + 8
+            assert 4 * (floats + items) <= b.tree_attention_workspace_bytes(B, B * n, H, dh, slots, b.BF16)
+            packed += heads > 1
+    assert packed > 1000
+
+
+def test_single_heads_are_the_other_query_plan():
+    for B, n, slots in itertools.product((1, 2, 8, 16), (1, 33, 64, 100), (100, 600, 2000, 9000)):
+        p, q = b.trj_dev_attn_launch(B, B * n, 32, 32, 128, slots, True), b.trj_dev_attn_plan(B, B * n, 32, 128, False, slots)
+        assert p["pack"] == 0 and all(p[k] == q[k] for k in ("tiles", "groups", "blocks", "splits", "lag"))
+        assert (p["form"] == "ring") == bool(q["ring"])
+
+
+def test_bad_arguments():
+    for args in ((0, 1, 1, 1, 64, 1), (1, 129, 1, 1, 64, 1), (2, 1, 1, 1, 64, 1), (1, 1, 0, 1, 64, 1), (1, 1, 4, 3, 64, 1),
+                 (1, 1, 4, -1, 64, 1), (1, 1, 1, 1, 96, 1), (1, 1, 1, 1, 64, 0)):
+        with pytest.raises(b.TrjError):
+            b.trj_dev_attn_launch(*args)
