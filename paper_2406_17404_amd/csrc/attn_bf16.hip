@@ -938,8 +938,7 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
     else TRJ_ATTN_A(DH, Q, KS, D, FORM, false);                                                 \
   } while (0)
     if (dh == 128) {
-      if (once && ntw == 1) TRJ_ATTN(128, 1, 4, 2, AF_ONCE);
-      else if (once) TRJ_ATTN(128, 2, 4, 2, AF_ONCE);
+      if (once) TRJ_ATTN(128, 2, 4, 2, AF_ONCE);
       else if (ring && ntw == 1) TRJ_ATTN(128, 1, 4, 2, AF_RING);
       else if (ring && ntw == 2) TRJ_ATTN(128, 2, 4, 2, AF_RING);
       else if (ring) TRJ_ATTN(128, 4, 2, 3, AF_RING);
