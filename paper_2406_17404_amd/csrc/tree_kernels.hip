@@ -138,8 +138,10 @@ __device__ inline void attn_items_body(
   const int tid = threadIdx.x;
   __shared__ int32_t first[1024];
   int carry = 0;
+  bool descends = false;
   for (int base = 0; base < B; base += 1024) {
     const int s = base + tid;
+    descends |= s < B && range_descends(node_off, s);
     int n = 0, len = -1;
     if (s < B && status[s] == 0) {
       n = node_off[s + 1] - node_off[s];
@@ -192,8 +194,6 @@ __device__ inline void attn_items_body(
     carry += scan[1023];
     __syncthreads();
   }
-  bool descends = false;
-  for (int s = tid; s < B; s += 1024) descends |= range_descends(node_off, s);
   const int any = __syncthreads_or(descends);
   if (tid == 0) {
     items[(size_t)B * qg_max * nsplit_max * 8] = carry;
@@ -332,12 +332,16 @@ __device__ inline void few_items_body(const int32_t* node_off, const int32_t* pr
   __shared__ int32_t order[PREP_MAX_SEQS], groups[PREP_MAX_SEQS], end[PREP_MAX_SEQS];
   const int tid = threadIdx.x;
   int n = 0, l = -1, slot0 = 0;
+  static_assert(PREP_MAX_SEQS == WAVE, "the vote");
+  uint64_t descends = 0;  // sequences whose range does (asked for here: at the end it took 0.6 us of a call)
   if (tid < PREP_MAX_SEQS) {
+    const int s = min(tid, B - 1), r0 = node_off[s], r1 = node_off[s + 1];
     if (tid < B && bad[tid] == 0) {
-      n = node_off[tid + 1] - node_off[tid];
+      n = r1 - r0;
       l = prefix_len[tid] + n;
       slot0 = kv_off[tid];
     }
+    descends = __ballot(r1 < r0);
     len[tid] = l;
     first[tid] = slot0;
     order[tid] = tid;  // places past the last sequence: nothing
@@ -365,7 +369,6 @@ __device__ inline void few_items_body(const int32_t* node_off, const int32_t* pr
   }
   __syncthreads();
   const int total = end[PREP_MAX_SEQS - 1];
-  const int any = __syncthreads_or(tid < B && range_descends(node_off, tid));
   for (int r = tid; r < total; r += blockDim.x) {
     int p = 0;
     while (end[p] <= r) ++p;
@@ -383,7 +386,7 @@ __device__ inline void few_items_body(const int32_t* node_off, const int32_t* pr
   }
   if (tid == 0) {
     items[(size_t)B * qg_max * nsplit_max * 8] = total;
-    items[(size_t)B * qg_max * nsplit_max * 8 + 1] = any;
+    items[(size_t)B * qg_max * nsplit_max * 8 + 1] = descends != 0;
   }
 }
 
