@@ -857,11 +857,18 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
   p.bpwg = b;
   p.nsplit_max = (nb + b - 1) / b;
   // Two tiles whose workgroup has at most two blocks per stream: all of it at once into LDS, where
-  // both tiles read it and nobody waits for a block behind another.  us of a call, registers -> at
-  // once: 64 rows on 777 slots 17.0 -> 16.7, 1024 17.2 -> 16.0, 1500 19.6 -> 18.5; in a step of two
-  // layers 96 rows on 500 312.9 -> 310.6, grouped-query 69 on 1024 438.8 -> 437.4.  One tile has
-  // nothing to share (16 rows on 512: 12.1 -> 12.8).
-  p.once = dh == 128 && p.ntw == 2 && !p.ring && b <= 8;
+  // both tiles read it and nobody waits for a block behind another, if the streams have equally many:
+  // one each, or two.  Where some have two and some one, the meetings make them wait for each other,
+  // in the last split too.  us of a call of 32 heads, registers -> at once, by blocks of a workgroup:
+  // 3 (33 rows on 60 slots) 9.1 -> 9.0, 4 (64 on 60) 10.5 -> 9.4, 5 (33 on 100) 9.3 -> 11.2, 6 (64 on
+  // 100, behind a prologue) 15.3 -> 16.1, 8 (128 on 100, the same) 18.2 -> 17.4.  Of splits: 4 (56 on
+  // 850) 23.0 -> 22.5, 5 (64 on 1000) 18.7 -> 18.5, 6 (33 on 1250) 17.9 -> 21.1, 8 (33 on 2000) 19.1 ->
+  // 21.0; with more rows registers cost more, as every tile's wavefronts load the blocks for
+  // themselves: 8, 8, 8 and 1 (96 on 700) 22.8 -> 21.9, but 8, 8, 8 and 6 (on 850) 22.0 -> 23.1.  One
+  // tile has nothing to share (16 rows on 512: 12.1 -> 12.8).
+  const int last = nb - (p.nsplit_max - 1) * b;  // several sequences' are device data
+  const bool even = b == 5 ? p.nsplit_max > 1 : b == 8 && (p.nsplit_max == 1 || T > 64 * B);
+  p.once = dh == 128 && p.ntw == 2 && !p.ring && (b <= 4 || (even && (B > 1 || last <= 4 || last == 8)));
   return p;
 }
 

@@ -40,6 +40,22 @@ def test_single_heads_are_the_other_query_plan():
         assert (p["form"] == "ring") == bool(q["ring"])
 
 
+# us of a call of 32 heads through registers -> at once
+@pytest.mark.parametrize("n,slots,in_step,form", [
+    (33, 93, False, "once"), (64, 124, False, "once"),                 # 3 and 4 blocks: 9.1 -> 9.0, 10.5 -> 9.4
+    (33, 133, False, "registers"), (64, 164, True, "registers"),       # 5 and 6 blocks: 9.3 -> 11.2, 15.3 -> 16.1
+    (64, 256, False, "once"), (128, 228, True, "once"),                # 8 blocks of one workgroup, two per stream: 18.2 -> 17.4
+    (64, 764, False, "once"), (56, 906, True, "once"),                 # splits of 4: 23.0 -> 22.5
+    (64, 1064, True, "once"),                                          # of 5: 23.5 -> 23.3
+    (33, 1283, False, "registers"), (33, 1533, False, "registers"),    # of 6: 17.9 -> 21.1, 17.5 -> 20.1
+    (33, 2033, False, "registers"), (48, 2048, False, "registers"),    # of 8 with one query group: 19.1 -> 21.0
+    (96, 796, True, "once"), (96, 616, True, "once"),                  # with two; the last of 1 and 4 blocks: 22.8 -> 21.9
+    (96, 946, True, "registers"), (80, 680, True, "registers"),        # the last of 6: 22.0 -> 23.1
+    (100, 700, False, "registers"), (128, 888, False, "registers")])   # which wait for ancestor bits: 18.1 -> 20.5
+def test_form_at_once(n, slots, in_step, form):
+    assert b.trj_dev_attn_launch(1, n, 32, 32, 128, slots, in_step)["form"] == form
+
+
 def test_bad_arguments():
     for args in ((0, 1, 1, 1, 64, 1), (1, 129, 1, 1, 64, 1), (2, 1, 1, 1, 64, 1), (1, 1, 0, 1, 64, 1), (1, 1, 4, 3, 64, 1),
                  (1, 1, 4, -1, 64, 1), (1, 1, 1, 1, 96, 1), (1, 1, 1, 1, 64, 0)):
