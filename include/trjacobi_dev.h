@@ -58,7 +58,8 @@ int32_t trj_dev_attn_launch(int32_t B, int32_t T, int32_t n_heads, int32_t n_kv_
  * projection kernel is used, 0: never), "gemm_big_wt" (row tiles per wavefront of that
  * kernel: 2, 4, or 0 to choose per projection), "gemm_pair_min_k" (k range from which that kernel's
  * 4 x 4 tile may have two groups of wavefronts take turns), "attn_target_wgs" (attention workgroups aimed at
- * per launch), "attn_min_bpw" (32-slot blocks per key stream, at least; 0 = chosen from the tree
+ * per launch), "attn_pack" (0: choose; 1 to 4: 1, 2, 4 or 8 query heads of a K/V head are worked
+ * on together where its group is a multiple of that, else one by one), "attn_min_bpw" (32-slot blocks per key stream, at least; 0 = chosen from the tree
  * size), "attn_xchg_min_blocks" (32-slot blocks of 32 heads from which the wavefronts of a
  * key stream share its K/V through rings in LDS for one query tile, twice as many for two and
  * 8/3 as many for more; heads of 128 that share no K/V; 1: always).  Results do not depend on them beyond fp32 summation order and, in the

@@ -105,8 +105,9 @@ static void carve_tree(Carver& c, int dtype, int B, int T, int H, bool shared_kv
   }
 }
 
-static int model_pack(const trj_model_desc& m, int B, int T, int max_seq_slots) {
-  return m.dtype == TRJ_BF16 && m.n_kv_heads ? attn_bf16_pack(B, T, m.n_heads, m.n_kv_heads, max_seq_slots) : 0;
+static int model_pack(const trj_model_desc& m, int B, int T, int max_seq_slots, bool common_kv) {
+  return m.dtype == TRJ_BF16 && m.n_kv_heads
+             ? attn_bf16_pack(B, T, m.n_heads, m.n_kv_heads, m.head_dim, max_seq_slots, common_kv) : 0;
 }
 // several columns per K/V head
 static bool model_shares_kv(const trj_model_desc& m, int pack) {
@@ -208,6 +209,7 @@ int32_t trj_set_tunable(const char* name, int32_t value) {
   else if (!strcmp(name, "gemm_big_wt") && (value == 0 || value == 2 || value == 4)) g_tune.gemm_big_wt = value;
   else if (!strcmp(name, "gemm_pair_min_k") && positive) g_tune.gemm_pair_min_k = value;
   else if (!strcmp(name, "attn_target_wgs") && positive) g_tune.attn_target_wgs = value;
+  else if (!strcmp(name, "attn_pack") && value >= 0 && value <= 4) g_tune.attn_pack = value;
   else if (!strcmp(name, "attn_min_bpw") && (positive || value == 0)) g_tune.attn_min_bpw = value;
   else if (!strcmp(name, "attn_xchg_min_blocks") && positive) g_tune.attn_xchg_min_blocks = value;
   else return TRJ_ERR_BAD_SHAPE;
@@ -457,7 +459,7 @@ static int tree_attention_impl(const void* q, const void* k_layer, const void* v
   if (static_ws) ws_bytes = TRJ_STATIC_SCRATCH_BYTES;
   // sizes first: nothing is touched when the call does not fit; packed heads, or each by itself if
   // only that fits
-  int pack = dtype == TRJ_BF16 ? attn_bf16_pack(B, T, n_heads, n_kv_heads, max_seq_slots) : 0;
+  int pack = dtype == TRJ_BF16 ? attn_bf16_pack(B, T, n_heads, n_kv_heads, head_dim, max_seq_slots, false) : 0;
   auto carve = [&](Carver c, TreeWs* w) {
     carve_tree(c, dtype, B, T, n_heads, n_heads >> pack != n_kv_heads, pack, head_dim, max_seq_slots, w);
     return c.off;
@@ -629,7 +631,7 @@ int32_t trj_dev_attn_launch(int32_t B, int32_t T, int32_t n_heads, int32_t n_kv_
       (head_dim != 64 && head_dim != 128) || max_seq_slots < 1)
     return TRJ_ERR_BAD_SHAPE;
   TuneScope tune_scope;
-  const int pack = attn_bf16_pack(B, T, n_heads, n_kv_heads, max_seq_slots);
+  const int pack = attn_bf16_pack(B, T, n_heads, n_kv_heads, head_dim, max_seq_slots, false);
   const AttnPlan p = attn_bf16_plan(B, T, n_heads, head_dim, n_heads >> pack != n_kv_heads, max_seq_slots, pack);
   const int32_t v[7] = {pack, p.ntw, p.qg_max, p.bpwg, p.nsplit_max, attn_bf16_form(p, B == 1 && !in_step, true), p.lag > 0.f};
   memcpy(h_plan, v, sizeof(v));
@@ -683,7 +685,7 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
   const bool bf16 = m.dtype == TRJ_BF16;
   // heads of a group read the same K/V, and so do the chunks of a prompt that a pass packs
   // (packed heads, or each by itself if only that fits)
-  int pack = model_pack(m, B, T, max_seq_slots);
+  int pack = model_pack(m, B, T, max_seq_slots, !with_head && B > 1);
   bool shared_kv = false;
   auto carve = [&](Carver& c) {
     shared_kv = model_shares_kv(m, pack) || (!with_head && B > 1);

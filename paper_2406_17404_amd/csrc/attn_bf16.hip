@@ -770,23 +770,6 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
 // Launch shape: form of the walk, query tiles per workgroup, query groups, blocks per workgroup,
 // splits.  Figures: us of the attention kernel with its merge in a step of 12 layers, where K/V
 // come from HBM, 32 heads of 128; R register form, 2r / 4r ring with two / four tiles.
-// Packed heads fill tiles of 32 queries that a tree by itself leaves partly empty (69 rows, four
-// heads: 9 tiles instead of 12), and K/V are read by fewer workgroups: the smallest pack with the
-// fewest tiles for trees of the average size.  Up to 16 blocks, where a call is the latency of one
-// workgroup, the more and smaller ones of single heads win (30 rows on 300 slots: 10.5 against 13.1
-// us).  us of a call, single heads -> packed, 32 heads on 8 K/V heads: 69 rows on 3001 slots 22.8
-// -> 20.9, on 1024 17.7 -> 16.2, 33 on 1024 15.3 -> 14.2, 5 on 16384 31.5 -> 24.3, 100 on 16384 64.6
-// -> 61.0, sixteen sequences of 20 up to 1000 32.2 -> 26.8.
-int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int max_seq_slots) {
-  if (max_seq_slots <= 16 * 32) return 0;
-  const int share = n_heads / n_kv_heads, n = (T + B - 1) / B;
-  int best = 0, fewest = share * ((n + 31) / 32);
-  for (int pack = 1; pack <= 3 && share % (1 << pack) == 0; ++pack) {
-    const int tiles = (share >> pack) * (((n << pack) + 31) / 32);
-    if (tiles < fewest) { best = pack; fewest = tiles; }
-  }
-  return best;
-}
 AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv, int max_seq_slots, int pack) {
   AttnPlan p;
   // queries and columns take the place of rows and heads
@@ -876,6 +859,66 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
   const bool even = b == 5 ? p.nsplit_max > 1 : b == 8 && (p.nsplit_max == 1 || T > 64 * B);
   p.once = dh == 128 && p.ntw == 2 && !p.ring && (b <= 4 || (even && (B > 1 || last <= 4 || last == 8)));
   return p;
+}
+
+// Heads of 128 beyond 16 blocks whose group of 2, 4 or 8 fills tiles of 32 queries that a tree by
+// itself leaves partly empty (69 rows, four heads: 9 tiles instead of 12): the packing with the fewest
+// tiles for trees of the average size, of those that pay.  Up to 16 blocks a call is the latency of
+// one workgroup (30 rows on 300 slots: 10.5 against 13.1 us packed); heads of 64 gain nothing below
+// 32000 slots and lose there (16 heads on 2, one row: 18.7 against 27.3).  What pays, us of a call of
+// 32 heads on 8 K/V heads, single -> packed, K/V from HBM, from 1467 sizes with all packings each:
+//  - trees of up to 32 rows whose packed queries are one tile too, while workgroups stay as they
+//    are (5 rows on 12000 slots 27.2 -> 19.7; sixteen sequences of 16 up to 520 28.2 -> 20.1).  Not
+//    where only the packed ones need splits and their merge launch (eight of 16 up to 520: 17.6 ->
+//    27.4) or an idle second tile (two of 9 up to 700: 14.3 -> 16.4), unless the launch needs fewer
+//    rounds of workgroups (32 of 1 up to 520: 36.0 -> 26.3) or the walk is long (eight of 5 up to 3000:
+//    36.4 -> 27.5);
+//  - one tile packed into two is twice the work per block (20 rows on 1000: 13.2 -> 15.3): only for
+//    half of the rounds (sixteen of 20 up to 520: 29.0 -> 22.0) or splits of 24 blocks and more (20
+//    on 12000: 27.2 -> 23.5);
+//  - more rows: one sequence (69 on 4000: 24.9 -> 21.8), but not 33 to 64 rows of eight heads per K/V
+//    head, which L2 feeds, on less than 128 blocks (33 on 1000: 15.5 -> 16.2); several where the
+//    rounds get fewer (four of 69 up to 1000: 38.7 -> 23.7; eight of 33 up to 520, as many: 19.1 -> 19.8).
+int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int dh, int max_seq_slots, bool common_kv) {
+  const int share = n_heads / n_kv_heads;
+  if (const int forced = tune().attn_pack) return forced <= 4 && share % (1 << (forced - 1)) == 0 ? forced - 1 : 0;
+  if (max_seq_slots <= 16 * 32 || dh != 128) return 0;
+  const int n = (T + B - 1) / B, nb = (max_seq_slots + 31) / 32;
+  const bool walks_far = nb >= 64;
+  constexpr int CUS = 256;
+  struct Launch {
+    AttnPlan p;
+    int tiles;  // of a group of heads
+    long wgs;   // with trees of equal size and length
+  };
+  auto launch = [&](int pack) {
+    Launch l;
+    l.p = attn_bf16_plan(B, T, n_heads, dh, common_kv || n_heads >> pack != n_kv_heads, max_seq_slots, pack);
+    const int nq = n << pack, rows = 32 * l.p.ntw;
+    l.tiles = (share >> pack) * ((nq + 31) / 32);
+    l.wgs = (long)B * ((nq + rows - 1) / rows) * (n_heads >> pack) * l.p.nsplit_max;
+    return l;
+  };
+  const Launch single = launch(0);
+  int best = 0, fewest = single.tiles;
+  for (int pack = 1; pack <= 3 && share % (1 << pack) == 0; ++pack) {
+    const Launch l = launch(pack);
+    if (l.tiles >= fewest) continue;
+    const bool unsplit = l.p.nsplit_max == 1;
+    const bool fewer_rounds = unsplit && single.wgs > CUS && 5 * l.wgs <= 4 * single.wgs;
+    bool pays;
+    if (n <= 32 && n << pack <= 32)
+      pays = (l.p.ntw == single.p.ntw && (unsplit || single.p.nsplit_max > 1)) || fewer_rounds || (walks_far && l.p.bpwg >= 24);
+    else if (n <= 32)
+      pays = (single.p.nsplit_max > 1 && l.p.bpwg >= 24) ||
+             (fewer_rounds && 2 * l.wgs <= single.wgs && (!walks_far || single.wgs >= 4 * CUS));
+    else if (B == 1)
+      pays = share <= 4 || n > 64 || nb >= 128;
+    else
+      pays = unsplit ? fewer_rounds || (walks_far && l.wgs <= single.wgs) : l.wgs <= CUS && single.wgs > CUS;
+    if (pays) { best = pack; fewest = l.tiles; }
+  }
+  return best;
 }
 
 // Loads without registers need operands on multiples of 16 bytes.  Several query groups of a sequence

@@ -14,6 +14,7 @@ struct Tunables {
   int attn_target_wgs = 256;   // attention workgroups per launch aimed at (one per CU)
   int gemm_big_wt = 0;         // row tiles per wavefront of the many-rows kernel (2, 4; 0 = choose)
   int attn_xchg_min_blocks = 48;  // blocks of 32 heads from which K/V go through rings, one query tile (1: always)
+  int attn_pack = 0;           // 0: choose; 1, 2, 3, 4: work on 1, 2, 4, 8 query heads of a K/V head together
   int attn_min_bpw = 0;        // 32-slot blocks per key stream, at least (0: chosen from the tree size)
 };
 // trj_set_tunable writes the process-wide set; every entry point copies it once on entry
@@ -205,8 +206,9 @@ struct AttnPlan {
   bool once;             // no ring: all of a workgroup's K/V to LDS at once
   float lag;             // how far the softmax reference may fall behind the running maximum (log2)
 };
-// log2 of the query heads of a K/V head that are worked on together as one column
-int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int max_seq_slots);
+// log2 of the query heads of a K/V head that are worked on together as one column.  common_kv: the
+// sequences read the same K/V
+int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int dh, int max_seq_slots, bool common_kv);
 // the form in which a plan runs.  self: one sequence that the kernel checks itself; aligned: all
 // operands start at multiples of 16 bytes
 AttnForm attn_bf16_form(const AttnPlan& p, bool self, bool aligned);

@@ -56,6 +56,26 @@ def test_form_at_once(n, slots, in_step, form):
     assert b.trj_dev_attn_launch(1, n, 32, 32, 128, slots, in_step)["form"] == form
 
 
+# 32 heads of 128; us of a call with 1, 2, 4, .. heads worked on together
+@pytest.mark.parametrize("B,n,L,Hkv,heads", [
+    (1, 5, 12000, 8, 4), (1, 16, 32000, 8, 2), (1, 20, 12000, 8, 4),    # 26.9 20.7 19.6; 48.7 35.2 36.3; 27.2 25.8 23.5
+    (1, 20, 700, 8, 1), (1, 20, 1000, 8, 1), (1, 20, 1000, 4, 1),       # 12.6 14.3 14.8; 13.1 15.2 15.2
+    (1, 69, 3001, 8, 4), (1, 33, 1000, 8, 4), (1, 33, 1000, 4, 1), (1, 33, 32000, 4, 8),
+    (8, 16, 520, 8, 1), (8, 16, 1000, 8, 1), (8, 20, 520, 8, 1),        # 17.6 27.4 27.2; 21.5 27.4 29.2; 17.8 28.4 31.6
+    (8, 1, 700, 8, 1), (8, 5, 3000, 8, 4), (8, 20, 3000, 8, 1),         # 38.7 42.7 45.6
+    (16, 1, 700, 8, 2), (16, 16, 520, 8, 2), (16, 20, 520, 8, 4), (16, 20, 3000, 8, 1), (32, 1, 520, 8, 4),
+    (2, 9, 700, 8, 1), (2, 33, 3000, 8, 1), (2, 69, 1000, 8, 4),        # 14.0 15.9 16.7; 24.9 30.8 28.1
+    (4, 33, 520, 8, 1), (4, 69, 1000, 8, 4), (8, 33, 520, 8, 1), (8, 33, 3000, 8, 4), (16, 100, 1000, 8, 1),
+    (1, 64, 3000, 8, 1), (1, 5, 500, 8, 1)])                            # no tile saved; up to 16 blocks
+def test_heads_worked_on_together(B, n, L, Hkv, heads):
+    assert b.trj_dev_attn_launch(B, B * n, 32, Hkv, 128, L + n)["pack"] == heads.bit_length() - 1
+
+
+def test_heads_of_64_one_by_one():
+    for n, L in itertools.product((1, 5, 20, 33, 100), (600, 3000, 12000, 32000)):
+        assert b.trj_dev_attn_launch(1, n, 16, 2, 64, L + n)["pack"] == 0
+
+
 def test_bad_arguments():
     for args in ((0, 1, 1, 1, 64, 1), (1, 129, 1, 1, 64, 1), (2, 1, 1, 1, 64, 1), (1, 1, 0, 1, 64, 1), (1, 1, 4, 3, 64, 1),
                  (1, 1, 4, -1, 64, 1), (1, 1, 1, 1, 96, 1), (1, 1, 1, 1, 64, 0)):

@@ -18,6 +18,14 @@ from test_gpu_attention_ring import knobs  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture
+def packing():
+    def put(heads):
+        b.trj_set_tunable("attn_pack", heads.bit_length())
+    yield put
+    b.trj_set_tunable("attn_pack", 0)
+
+
 def run_out_of_order(H, Hkv, dh, sizes, lens, turn):
     """Sequences 0..turn-1 own the last rows, one with an impossible range follows, then the others
     own the first rows.  Returns (rows of a valid sequence, oracle's) for all of them."""
@@ -56,15 +64,26 @@ def run_out_of_order(H, Hkv, dh, sizes, lens, turn):
 @pytest.mark.parametrize("H,Hkv,dh", [(8, 2, 128), (16, 1, 128), (8, 1, 64), (4, 4, 128)])
 @pytest.mark.parametrize("sizes,lens,turn", [([28, 50], [1500, 1300], 1), ([20, 5, 64, 33], [900, 1600, 700, 3000], 2),
                                              ([9, 7, 3, 12, 6, 10], [1100] * 6, 3)])
-def test_valid_sequences_keep_their_answers(knobs, H, Hkv, dh, sizes, lens, turn):
+def test_valid_sequences_keep_their_answers(knobs, packing, H, Hkv, dh, sizes, lens, turn):
+    forms = set()
     # the plan's own, many short splits (two tiles: all of one at once), rings
     for wgs, bpw, least in ((256, 0, 48), (4096, 1, 1 << 20), (4096, 1, 1)):
         knobs(attn_target_wgs=wgs, attn_min_bpw=bpw, attn_xchg_min_blocks=least)
-        for got, want in run_out_of_order(H, Hkv, dh, sizes, lens, turn):
-            assert np.isfinite(got).all() and rel_err(got, want) <= TOL["bf16"], (wgs, least)
+        for heads in (1, 2, 4, 8):
+            if (H // Hkv) % heads:
+                continue
+            packing(heads)
+            plan = b.trj_dev_attn_launch(len(sizes) + 1, sum(sizes), H, Hkv, dh, max(map(sum, zip(sizes, lens))))
+            assert 1 << plan["pack"] == heads
+            forms.add((heads > 1, plan["form"], plan["splits"] > 1))
+            for got, want in run_out_of_order(H, Hkv, dh, sizes, lens, turn):
+                assert np.isfinite(got).all() and rel_err(got, want) <= TOL["bf16"], (wgs, least, heads)
+    if (H, dh) == (8, 128):   # a batch that the plan splits, in every form
+        assert {(True, form, True) for form in ("registers", "ring", "once")} <= forms
 
 
-def test_more_sequences_than_the_common_prologue_takes(knobs):
+def test_more_sequences_than_the_common_prologue_takes(knobs, packing):
+    packing(4)
     rng = np.random.default_rng(4)
     sizes, lens = [int(n) for n in rng.integers(1, 20, 70)], [int(l) for l in rng.integers(500, 900, 70)]
     knobs(attn_target_wgs=4096, attn_min_bpw=1, attn_xchg_min_blocks=1 << 20)
