@@ -569,18 +569,12 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
     };
     const uint16_t* qp = a.q + ((size_t)(r0 + node) * a.n_heads + head) * DH + hh * 8;
     int par[2];
-    auto load_parents = [&]() {
+    if constexpr (SELF) {  // first: they are needed first
 #pragma unroll
       for (int h = 0; h < 2; ++h) par[h] = a.parent[r0 + min(lane + 64 * h, n - 1)];
-    };
-    // The parents first, as they are needed first; but behind the queries where two tiles of heads of
-    // 64 walk far: in front of them 69 rows took 29.4 us on 16000 slots and 46.9 on 32000, behind
-    // them 26.9 and 40.0 (64 on 1000 13.6 both ways)
-    constexpr bool PARENTS_FIRST = DH == 128 || NTW == 1;
-    if constexpr (SELF && PARENTS_FIRST) load_parents();
+    }
 #pragma unroll
     for (int k = 0; k < KSTEPS; ++k) qreg[k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * k));
-    if constexpr (SELF && !PARENTS_FIRST) load_parents();
     if constexpr (!SELF) {
       anc0 = a.anc[2 * (size_t)(r0 + node)];
       anc1 = a.anc[2 * (size_t)(r0 + node) + 1];
@@ -610,7 +604,13 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       add_values(key0, alpha, pk);
       if constexpr (MORE) load(vreg, vb);  // in flight during the next S^T and softmax
     };
-    for (int i = 0; i + 1 < mine; ++i) block(i, std::true_type{});
+    if (mine > 1) {
+      // Once, for all loads.  The wait for the parents leaves the first V on the way; coming from
+      // there the loop would wait for V wherever it waits for K, in every turn (heads of 64, 32 on 8
+      // K/V heads, 16 rows on 32000 slots 39.6 against 30.2 us; of 128, 31 rows 49.6, 47.2).
+      if constexpr (SELF) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+      for (int i = 0; i + 1 < mine; ++i) block(i, std::true_type{});
+    }
     if (mine > 0) block(mine - 1, std::false_type{});
   }
 
