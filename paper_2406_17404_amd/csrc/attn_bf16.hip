@@ -861,28 +861,31 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
   return p;
 }
 
-// Heads of 128 beyond 16 blocks whose group of 2, 4 or 8 fills tiles of 32 queries that a tree by
-// itself leaves partly empty (69 rows, four heads: 9 tiles instead of 12): the packing with the fewest
-// tiles for trees of the average size, of those that pay.  Up to 16 blocks a call is the latency of
-// one workgroup (30 rows on 300 slots: 10.5 against 13.1 us packed); heads of 64 gain nothing below
-// 32000 slots and lose there (16 heads on 2, one row: 18.7 against 27.3).  What pays, us of a call of
-// 32 heads on 8 K/V heads, single -> packed, K/V from HBM, from 1467 sizes with all packings each:
+// Beyond 16 blocks, where a group of 2, 4 or 8 heads fills tiles of 32 queries that a tree by itself
+// leaves partly empty (69 rows, four heads: 9 tiles instead of 12): the packing with the fewest tiles for
+// trees of the average size, of those that pay.  Up to 16 blocks a call is the latency of one workgroup
+// (30 rows on 300 slots: 10.5 against 13.1 us packed).  What pays, us of a call of 32 heads of 128 on
+// 8 K/V heads, single -> packed, K/V from HBM, from 2004 sizes with all packings each:
 //  - trees of up to 32 rows whose packed queries are one tile too, while workgroups stay as they
-//    are (5 rows on 12000 slots 27.2 -> 19.7; sixteen sequences of 16 up to 520 28.2 -> 20.1).  Not
+//    are (5 rows on 12000 slots 25.7 -> 19.6; sixteen sequences of 16 up to 520 28.2 -> 20.1).  Not
 //    where only the packed ones need splits and their merge launch (eight of 16 up to 520: 17.6 ->
 //    27.4) or an idle second tile (two of 9 up to 700: 14.3 -> 16.4), unless the launch needs fewer
 //    rounds of workgroups (32 of 1 up to 520: 36.0 -> 26.3) or the walk is long (eight of 5 up to 3000:
 //    36.4 -> 27.5);
 //  - one tile packed into two is twice the work per block (20 rows on 1000: 13.2 -> 15.3): only for
-//    half of the rounds (sixteen of 20 up to 520: 29.0 -> 22.0) or splits of 24 blocks and more (20
-//    on 12000: 27.2 -> 23.5);
-//  - more rows: one sequence (69 on 4000: 24.9 -> 21.8), but not 33 to 64 rows of eight heads per K/V
+//    half of the rounds (sixteen of 20 up to 520: 29.0 -> 22.0; not sixteen up to 3000, two rounds of far
+//    walks: 52.4 -> 57.1; 26 of 17 on four K/V heads 80.0 -> 56.3) or splits of 24 blocks and more (20
+//    on 12000: 25.8 -> 23.3);
+//  - more rows: one sequence (69 on 4000: 24.5 -> 21.5), but not 33 to 64 rows of eight heads per K/V
 //    head, which L2 feeds, on less than 128 blocks (33 on 1000: 15.5 -> 16.2); several where the
 //    rounds get fewer (four of 69 up to 1000: 38.7 -> 23.7; eight of 33 up to 520, as many: 19.1 -> 19.8).
+// Heads of 64 have half the bytes per block, so there is less to save: one-tile packings only on long
+// walks (two sequences of 1 up to 520 11.2 -> 12.2; 5 rows on 12000 17.3 -> 14.1) and nothing below 32 heads in all (16 on 4
+// K/V heads, 5 rows on 12000: 14.4 -> 16.7) but for fewer rounds (32 of 5 up to 1000 42.6 -> 23.9).
 int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int dh, int max_seq_slots, bool common_kv) {
   const int share = n_heads / n_kv_heads;
   if (const int forced = tune().attn_pack) return forced <= 4 && share % (1 << (forced - 1)) == 0 ? forced - 1 : 0;
-  if (max_seq_slots <= 16 * 32 || dh != 128) return 0;
+  if (max_seq_slots <= 16 * 32) return 0;
   const int n = (T + B - 1) / B, nb = (max_seq_slots + 31) / 32;
   const bool walks_far = nb >= 64;
   constexpr int CUS = 256;
@@ -900,22 +903,26 @@ int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int dh, int max_se
     return l;
   };
   const Launch single = launch(0);
+  const bool half = dh == 64, few = half && n_heads * B < 32;
+  const long round = half && single.p.ntw == 1 ? 2 * CUS : CUS;  // two small workgroups share a compute unit
   int best = 0, fewest = single.tiles;
   for (int pack = 1; pack <= 3 && share % (1 << pack) == 0; ++pack) {
     const Launch l = launch(pack);
     if (l.tiles >= fewest) continue;
     const bool unsplit = l.p.nsplit_max == 1;
-    const bool fewer_rounds = unsplit && single.wgs > CUS && 5 * l.wgs <= 4 * single.wgs;
+    const bool fewer_rounds = unsplit && single.wgs > round && 5 * l.wgs <= 4 * single.wgs;
     bool pays;
     if (n <= 32 && n << pack <= 32)
-      pays = (l.p.ntw == single.p.ntw && (unsplit || single.p.nsplit_max > 1)) || fewer_rounds || (walks_far && l.p.bpwg >= 24);
+      pays = fewer_rounds || (walks_far && l.p.bpwg >= 24 && !few) ||
+             (l.p.ntw == single.p.ntw && (unsplit || single.p.nsplit_max > 1) && (!half || (walks_far && !few)));
     else if (n <= 32)
-      pays = (single.p.nsplit_max > 1 && l.p.bpwg >= 24) ||
-             (fewer_rounds && 2 * l.wgs <= single.wgs && (!walks_far || single.wgs >= 4 * CUS));
+      pays = (single.p.nsplit_max > 1 && l.p.bpwg >= 24 && !few) ||
+             (fewer_rounds && 2 * l.wgs <= single.wgs && (!walks_far || single.wgs > 3 * CUS));
     else if (B == 1)
-      pays = share <= 4 || n > 64 || nb >= 128;
+      pays = half ? share <= 4 && !few : share <= 4 || n > 64 || nb >= 128;
     else
-      pays = unsplit ? fewer_rounds || (walks_far && l.wgs <= single.wgs) : l.wgs <= CUS && single.wgs > CUS;
+      pays = unsplit ? fewer_rounds || (walks_far && l.wgs <= single.wgs)
+                     : l.wgs <= CUS && single.wgs > CUS && !(half && walks_far);
     if (pays) { best = pack; fewest = l.tiles; }
   }
   return best;
