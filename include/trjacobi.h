@@ -162,8 +162,10 @@ int32_t tree_attention(const void* q, const void* k_layer, const void* v_layer,
                        size_t ws_bytes, void* out, void* stream);
 
 /* Bytes of device scratch that let tree_attention choose its launch at these sizes, whatever
- * the number of K/V heads.  What trj_workspace_bytes reports for a model with these heads is
- * enough too: where only that fits, query heads that share K/V are worked on one by one. */
+ * the number of K/V heads: where some number of them would have query heads worked on together,
+ * room for the partial sums of that too.  A call is accepted with less as long as its query
+ * heads fit one by one, which is then how they are worked on; what trj_workspace_bytes reports
+ * for a model with these heads is always enough for that. */
 int32_t tree_attention_workspace_bytes(int32_t B, int32_t T, int32_t n_heads, int32_t head_dim,
                                        int32_t max_seq_slots, int32_t dtype, size_t* h_bytes);
 
@@ -173,9 +175,10 @@ int32_t tree_attention_workspace_bytes(int32_t B, int32_t T, int32_t n_heads, in
  * TRJ_STATIC_SCRATCH_BYTES inside the library (every GPU the library runs on holds one
  * copy until the process ends).  A call that needs more than that even
  * with its query heads one by one returns TRJ_ERR_WORKSPACE_TOO_SMALL and does nothing (the need is
- * the partial sums of sequences whose keys are split over several workgroups: 8 to 21 MiB for
- * one to four sequences with 32 heads of 128 at any length, little for larger batches;
- * more only when a development knob asks for more splits).  No
+ * the partial sums of sequences whose keys are split over several workgroups: with 32 heads of
+ * 128, at any length and tree size, up to 17 MiB for one and two sequences, 19 for three and four, 21,
+ * 25 and 29 for five, six and seven; from eight on below 0.5, and up to 17 where heads that share
+ * K/V are worked on together; more only when a development knob asks for more splits).  No
  * hipMalloc, hipFree or other allocating call is made.  All calls on one GPU share that
  * GPU's array: calls that overlap in time on one GPU (two streams, two threads) race;
  * calls on one stream are ordered and safe.  Nothing in the array needs clearing between

@@ -508,13 +508,17 @@ int32_t tree_attention_workspace_bytes(int32_t B, int32_t T, int32_t n_heads, in
     return TRJ_ERR_BAD_SHAPE;
   if ((long)T > (long)B * TRJ_N_MAX) return TRJ_ERR_TREE_TOO_LARGE;
   TuneScope tune_scope;
-  size_t most = 0;  // whatever the number of K/V heads
-  for (int pack = 0; pack <= 3 && n_heads % (1 << pack) == 0; ++pack) {
+  size_t most = 0;  // whatever the number of K/V heads: single heads, and packed ones where a number packs them
+  unsigned packs = 1;
+  if (dtype == TRJ_BF16)
+    for (int n_kv = 1; n_kv < n_heads; ++n_kv)
+      if (n_heads % n_kv == 0) packs |= 1u << attn_bf16_pack(B, T, n_heads, n_kv, head_dim, max_seq_slots, false);
+  for (int pack = 0; pack <= 3; ++pack) {
+    if (!(packs >> pack & 1)) continue;
     Carver c(nullptr);
     TreeWs w;
     carve_tree(c, dtype, B, T, n_heads, false, pack, head_dim, max_seq_slots, &w);
     most = c.off > most ? c.off : most;
-    if (dtype != TRJ_BF16) break;
   }
   *h_bytes = align_up(most, 256);
   return TRJ_OK;
