@@ -257,7 +257,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
     const int32_t* rec = a.items + (size_t)item * 8;  // inside the list's memory for every id
     s = rec[0], qg = rec[1], r0 = rec[2], n = rec[3], L = rec[4], blk_base = rec[5], sp = rec[6];
     several = rec[7] != 0;
-    whole = a.pack > 0 && a.n_items[1] != 0;
+    if constexpr (FORM != AF_ONCE) whole = a.pack > 0 && a.n_items[1] != 0;  // (at once: never)
     if (item >= a.n_items[0]) return;  // uniform over the workgroup, before any barrier
   }
   const int total = L + n;
@@ -441,7 +441,7 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
           request(kp, 2 * i);
           request(vp, 2 * i + 1);
         }
-    } else {  // all of the range (the plan keeps it to D blocks per stream), or D of them, K first
+    } else {  // all of the range (the plan keeps it to D blocks per stream), K first
 #pragma unroll
       for (int i = 0; i < D; ++i)
         if (i < nblk) request(kp, 2 * i);
@@ -480,39 +480,26 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
       anc1 = qi < nq ? (uint64_t)bits[3] << 32 | bits[2] : 0;
     }
     if constexpr (FORM == AF_ONCE) {
-      // only one more meeting, for V, behind the first block's scores and softmax; a sequence walked
-      // whole has further turns of D blocks per stream
+      // only one more meeting, for V, behind the first block's scores and softmax
       static_assert(D == 2, "waits above");
-      for (int i = 0;;) {
-        const int key0 = (b0 + ks + i * KS) * 32;
-        float alpha;
-        u32x4 pk[2];
-        const bool some = live && i < nblk;
-        if (some) {
-          read(kreg, 0);
-          softmax(scores(), key0, alpha, pk);
-        }
-        attn_wait<0, true>();
-        if (some) {
-          read(vreg, 1);
-          add_values(key0, alpha, pk);
-        }
-        if (live && i + 1 < nblk) {
-          read(kreg, 2);
-          read(vreg, 3);
-          softmax(scores(), key0 + KS * 32, alpha, pk);
-          add_values(key0 + KS * 32, alpha, pk);
-        }
-        i += D;
-        if (i >= rounds) break;  // uniform
-        attn_wait<0, true>();    // everybody has read the last turn's
-#pragma unroll
-        for (int j = 0; j < D; ++j)
-          if (i + j < nblk) {
-            request(kp, 2 * j);
-            request(vp, 2 * j + 1);
-          }
-        attn_wait<0, true>();
+      const int key0 = (b0 + ks) * 32;
+      float alpha;
+      u32x4 pk[2];
+      const bool some = live && nblk > 0;
+      if (some) {
+        read(kreg, 0);
+        softmax(scores(), key0, alpha, pk);
+      }
+      attn_wait<0, true>();
+      if (some) {
+        read(vreg, 1);
+        add_values(key0, alpha, pk);
+      }
+      if (live && nblk > 1) {
+        read(kreg, 2);
+        read(vreg, 3);
+        softmax(scores(), key0 + KS * 32, alpha, pk);
+        add_values(key0 + KS * 32, alpha, pk);
       }
     }
     // Block i of this stream: its K is in kreg; its V and the next blocks are on the way (slots
@@ -858,6 +845,9 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
   const int last = nb - (p.nsplit_max - 1) * b;  // several sequences' are device data
   const bool even = b == 5 ? p.nsplit_max > 1 : b == 8 && (p.nsplit_max == 1 || T > 64 * B);
   p.once = dh == 128 && p.ntw == 2 && !p.ring && (b <= 4 || (even && (B > 1 || last <= 4 || last == 8)));
+  // not for packed heads of several sequences, which may have to be walked whole (attn_parts.h); there
+  // the form gained 1.3 % with more than 64 queries and lost 2.5 % with up to 32
+  p.once = p.once && (pack == 0 || B == 1);
   return p;
 }
 

@@ -81,7 +81,8 @@ def test_batch(knobs, packing, sizes, lens):
             forms.add((heads, plan["form"]))
             for g, c in zip(got, cases):
                 assert rel_err(g, O.tree_attention(*c)) <= TOL["bf16"], (wgs, least, heads)
-    assert {(4, "ring"), (4, "registers"), (2, "registers")} <= forms and ((4, "once") in forms or len(sizes) == 7)
+    assert {(4, "ring"), (4, "registers"), (2, "registers")} <= forms
+    assert not {(4, "once"), (2, "once")} & forms   # which does not take a sequence that must be walked whole
 
 
 def call(batch, q, k, v, H, Hkv, dh, ws, out, parent=None):
