@@ -838,13 +838,16 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
   // in the last split too.  us of a call of 32 heads, registers -> at once, by blocks of a workgroup:
   // 3 (33 rows on 60 slots) 9.1 -> 9.0, 4 (64 on 60) 10.5 -> 9.4, 5 (33 on 100) 9.3 -> 11.2, 6 (64 on
   // 100, behind a prologue) 15.3 -> 16.1, 8 (128 on 100, the same) 18.2 -> 17.4.  Of splits: 4 (56 on
-  // 850) 23.0 -> 22.5, 5 (64 on 1000) 18.7 -> 18.5, 6 (33 on 1250) 17.9 -> 21.1, 8 (33 on 2000) 19.1 ->
-  // 21.0; with more rows registers cost more, as every tile's wavefronts load the blocks for
-  // themselves: 8, 8, 8 and 1 (96 on 700) 22.8 -> 21.9, but 8, 8, 8 and 6 (on 850) 22.0 -> 23.1.  One
-  // tile has nothing to share (16 rows on 512: 12.1 -> 12.8).
+  // 850) 23.0 -> 22.5, 6 (33 on 1250) 17.9 -> 21.1, 8 (33 on 2000) 19.1 -> 21.0; with more rows registers
+  // cost more, as every tile's wavefronts load the blocks for themselves: 8, 8, 8 and 1 (96 on 700)
+  // 22.8 -> 21.9, but 8, 8, 8 and 6 (on 850) 22.0 -> 23.1.  5 (64 rows) where the last has 2 to 4 and
+  // units stay free for those that wait (224 workgroups, 1024 slots 18.3 -> 18.0; 256, 1072 to 1184 18.0
+  // to 18.5 -> 18.3 to 20.6) or heads share K/V (1024: 17.7 -> 16.6).  One tile has nothing to share (16
+  // rows on 512: 12.1 -> 12.8).
   const int last = nb - (p.nsplit_max - 1) * b;  // several sequences' are device data
-  const bool even = b == 5 ? p.nsplit_max > 1 : b == 8 && (p.nsplit_max == 1 || T > 64 * B);
-  p.once = dh == 128 && p.ntw == 2 && !p.ring && (b <= 4 || (even && (B > 1 || last <= 4 || last == 8)));
+  const bool fours = b <= 4 || (b == 8 && (p.nsplit_max == 1 || T > 64 * B) && (B > 1 || last <= 4 || last == 8));
+  const bool fives = b == 5 && p.nsplit_max > 1 && last >= 2 && last <= 4 && (shared_kv || 8 * cols * p.nsplit_max <= 7 * target);
+  p.once = dh == 128 && p.ntw == 2 && !p.ring && (fours || fives);
   // not for packed heads of several sequences, which may have to be walked whole (attn_parts.h); there
   // the form gained 1.3 % with more than 64 queries and lost 2.5 % with up to 32
   p.once = p.once && (pack == 0 || B == 1);

@@ -46,7 +46,8 @@ def test_single_heads_are_the_other_query_plan():
     (33, 133, False, "registers"), (64, 164, True, "registers"),       # 5 and 6 blocks: 9.3 -> 11.2, 15.3 -> 16.1
     (64, 256, False, "once"), (128, 228, True, "once"),                # 8 blocks of one workgroup, two per stream: 18.2 -> 17.4
     (64, 764, False, "once"), (56, 906, True, "once"),                 # splits of 4: 23.0 -> 22.5
-    (64, 1064, True, "once"),                                          # of 5: 23.5 -> 23.3
+    (64, 1088, True, "once"), (64, 1152, True, "registers"),           # of 5, 7 of them and 8: 18.3 -> 18.0, 18.5 -> 20.6
+    (64, 1248, False, "registers"), (64, 1280, True, "registers"),     # the last of 4 in 8, the last of 5
     (33, 1283, False, "registers"), (33, 1533, False, "registers"),    # of 6: 17.9 -> 21.1, 17.5 -> 20.1
     (33, 2033, False, "registers"), (48, 2048, False, "registers"),    # of 8 with one query group: 19.1 -> 21.0
     (96, 796, True, "once"), (96, 616, True, "once"),                  # with two; the last of 1 and 4 blocks: 22.8 -> 21.9
