@@ -146,6 +146,9 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs 
   // In the step, us: 22016 x 4096 at 128 rows 49.0 -> 44.6, 12288 x 4096 at 128 35.3 -> 34.3, at 64
   // 25.7 -> 25.2, 128256 x 4096 at 96 180 -> 166, 32000 x 4096 at 64 47.5 -> 45.1, 4096 x 4096 at
   // 32 9.1 -> 7.8.  Left out: 4096 x 11008 at 128 rows 26.9 -> 27.3, 6144 x 4096 at 96 23.4 -> 23.9.
+  // Launches that do not rotate are not back where they were without the rotation in the kernel (the
+  // down projection in the step at 64 rows 19.3 -> 19.7, at 128 26.1 -> 27.0; why is not known, the wrap in
+  // the loop is not the reason).
   const bool tail = ksteps % PH != 0;
   const bool spread = NT && WR > 1 && !tail && a.tp * a.n_in <= 1 << 19;
   const int rot = spread ? (int)(((blockIdx.x >> 3) * 40503u + (blockIdx.x & 7) * 8192u & 0xffffu) * n >> 16) : 0;
