@@ -18,8 +18,11 @@ SOURCES = ["api.hip", "tree_kernels.hip", "f32_kernels.hip", "gemm_bf16.hip", "g
 # without the flag, none with it).  The host pass of the same command does not know the
 # feature and prints "not a recognized feature for this target": harmless, and left
 # visible.
+# Kernarg preload: a kernel's first plain arguments (up to 14 registers of them) are in scalar registers
+# when its wavefronts start.
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 def _compile(src: str) -> str:

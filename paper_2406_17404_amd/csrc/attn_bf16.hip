@@ -198,8 +198,28 @@ __device__ __forceinline__ void attn_wait() {
 // ancestor bits out for itself (pointer doubling on the lanes of each wavefront), which saves a
 // launch of 5 to 6 us.  The parents are asked for first and the bits worked out only by streams
 // that come to the tree (see own_bits).
+// The arguments in front of the struct come in scalar registers when a wavefront starts (build.py's kernarg
+// preload): what the chain of first loads begins with.  SELF: node_off, kv_off, prefix_len, parent; else
+// items, n_items.  us of a call, 3001 x 69 on 8 K/V heads 20.0 -> 19.3, 8192 x 64 35.4
+// -> 35.0.
 template <int DH, int NTW, int KS, int D, AttnForm FORM, bool SELF>
-__global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArgs a) {
+__global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(
+    const int32_t* first0, const int32_t* first1, const int32_t* first2, const int32_t* first3, int group,
+    int n_kv_groups, int columns, int qg_max, AttnArgs rest) {
+  AttnArgs a = rest;
+  if constexpr (SELF) {
+    a.node_off = first0;
+    a.kv_off = first1;
+    a.prefix_len = first2;
+    a.parent = first3;
+  } else {
+    a.items = first0;
+    a.n_items = first1;
+  }
+  a.group = group;
+  a.n_kv_groups = n_kv_groups;
+  a.columns = columns;
+  a.qg_max = qg_max;
   constexpr int KSTEPS = DH / 16, MTV = DH / 32, SLOTS = 2 * D;
   constexpr int OW = MTV * 16 * 64;     // floats of one wavefront's O tile
   constexpr int HALF = KSTEPS;          // 1-KiB pieces of a block's K, and of its V
@@ -678,7 +698,18 @@ __global__ __launch_bounds__(KS* NTW * 64, 2) void tree_attn_bf16_kernel(AttnArg
 // that lane `lane` of the attention wavefront held, i.e. query lane%32, 8 columns.  The loads
 // of a batch of splits are all issued together (clamped, never predicated).
 template <int DH, int CB>
-__global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
+__global__ __launch_bounds__(512) void attn_combine_kernel(const int32_t* status_dev, const int32_t* node_off,
+                                                           const int32_t* prefix_len, int tiles_per_seq, int pack,
+                                                           int columns, int nsplit_max, float* po, AttnArgs rest) {
+  AttnArgs a = rest;
+  a.status_dev = status_dev;
+  a.node_off = node_off;
+  a.prefix_len = prefix_len;
+  a.tiles_per_seq = tiles_per_seq;
+  a.pack = pack;
+  a.columns = columns;
+  a.nsplit_max = nsplit_max;
+  a.po = po;
   constexpr int MTV = DH / 32, OW = MTV * 16 * 64;
   const int tile = blockIdx.x % a.tiles_per_seq, s = blockIdx.x / a.tiles_per_seq;
   const int column = blockIdx.y;
@@ -986,7 +1017,8 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
     auto kern = tree_attn_bf16_kernel<DH, Q, KS, D, FORM, SELF>;                                  \
     static DeviceOnce once; /* per instantiation */                                             \
     allow_lds(once, kern, lds);                                                                 \
-    kern<<<grid, KS * Q * 64, lds, st>>>(a);                                                    \
+    if (SELF) kern<<<grid, KS * Q * 64, lds, st>>>(node_off, kv_off, prefix_len, parent, a.group, a.n_kv_groups, columns, qg_max, a); \
+    else kern<<<grid, KS * Q * 64, lds, st>>>(a.items, a.n_items, nullptr, nullptr, a.group, a.n_kv_groups, columns, qg_max, a); \
   } while (0)
 #define TRJ_ATTN(DH, Q, KS, D, FORM)                                                            \
   do {                                                                                          \
@@ -1013,10 +1045,10 @@ int launch_tree_attn_bf16(const uint16_t* q, const uint16_t* k_layer, const uint
   if (rc || nsplit_max == 1) return rc;
   ProfScope ps_(KC_ATTN_COMBINE, st);
   dim3 cgrid(B * tiles_per_seq, columns);
-  if (dh == 128 && nsplit_max <= 4) attn_combine_kernel<128, 4><<<cgrid, 512, 0, st>>>(a);
-  else if (dh == 128) attn_combine_kernel<128, 8><<<cgrid, 512, 0, st>>>(a);
-  else if (nsplit_max <= 4) attn_combine_kernel<64, 4><<<cgrid, 512, 0, st>>>(a);
-  else attn_combine_kernel<64, 8><<<cgrid, 512, 0, st>>>(a);
+  if (dh == 128 && nsplit_max <= 4) attn_combine_kernel<128, 4><<<cgrid, 512, 0, st>>>(status_dev, node_off, prefix_len, tiles_per_seq, pack, columns, nsplit_max, po, a);
+  else if (dh == 128) attn_combine_kernel<128, 8><<<cgrid, 512, 0, st>>>(status_dev, node_off, prefix_len, tiles_per_seq, pack, columns, nsplit_max, po, a);
+  else if (nsplit_max <= 4) attn_combine_kernel<64, 4><<<cgrid, 512, 0, st>>>(status_dev, node_off, prefix_len, tiles_per_seq, pack, columns, nsplit_max, po, a);
+  else attn_combine_kernel<64, 8><<<cgrid, 512, 0, st>>>(status_dev, node_off, prefix_len, tiles_per_seq, pack, columns, nsplit_max, po, a);
   return check_launch();
 }
 

@@ -28,7 +28,9 @@ namespace trj {
 //   pieces of phase t+1 are there and those of t+3 may not be.
 // Phases behind the last are requested from the last one again, into buffers nobody reads any more.
 template <int PH, int NB, class Epi>
-__global__ __launch_bounds__(512, 2) void gemm_pair_kernel(GemmArgs a, Epi epi) {
+__global__ __launch_bounds__(512, 2) void gemm_pair_kernel(const uint16_t* xp, const uint16_t* w, int n_in, int n_out, int tp,
+    int phases_per_split, Epi epi) {
+  const GemmArgs a{xp, w, n_in, n_out, tp, phases_per_split};
   constexpr int RT = 2, CT = 2, WT = 2, MT = 2, WR = RT * WT, XC = CT * MT;
   constexpr int XP = PH * XC, P = XP + PH * WR, PL = P / 4, BUF = P * 1024;  // PL: of one wavefront
   static_assert(NB == 5 && XP % 4 == 0 && P % 4 == 0 && NB * BUF <= 160 * 1024 && 16 * 4096 <= NB * BUF, "shape");
@@ -166,12 +168,12 @@ template <class Epi>
 static void launch_pair(const uint16_t* xp, const uint16_t* w, int tp, int n_in, int n_out, const Epi& epi,
                         hipStream_t st) {
   const int rgs = (n_out / 32 + 3) / 4, tblocks = (tp / 32 + 3) / 4;
-  GemmArgs a{xp, w, n_in, n_out, tp, (n_in >> 4) / PAIR_PHASE};
   auto kern = gemm_pair_kernel<PAIR_PHASE, PAIR_BUFFERS, Epi>;
   constexpr size_t lds = (size_t)PAIR_BUFFERS * PAIR_PHASE * 8 * 1024;
   static DeviceOnce once;  // per instantiation
   allow_lds(once, kern, lds);
-  kern<<<tblocks == 1 ? rgs : (rgs + 7) / 8 * 8 * tblocks, 512, lds, st>>>(a, epi);
+  kern<<<tblocks == 1 ? rgs : (rgs + 7) / 8 * 8 * tblocks, 512, lds, st>>>(xp, w, n_in, n_out, tp,
+                                                                             (n_in >> 4) / PAIR_PHASE, epi);
 }
 
 }  // namespace trj

@@ -101,8 +101,16 @@ __device__ __forceinline__ void wait_and_meet() {
 // beyond, 4 leave room for a second workgroup on the compute unit: 128 rows 64 against 88).
 // 22016 x 4096 with weights one element off: 64 rows 45 us (33 aligned), 1024 rows 264 (181);
 // copied to LDS at once and waited for, in one shape for all rows: 64 and 750.
+//
+// What the first loads need are plain arguments in front: those come in scalar registers when a
+// wavefront starts (build.py's kernarg preload; members of a struct do not) and save it a read of
+// memory that nothing has in a cache yet.  Steps of two layers, 21 launches, us: 777 x 5 242.2 -> 239.4,
+// 1024 x 64 283.8 -> 281.1, 4096 x 128 390.8 -> 387.5.
 template <int RT, int CT, int KW, int WT, int MT, int PH, int NB, bool NT, bool ALIGNED, class Epi>
-__global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(GemmArgs a, Epi epi) {
+__global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(const uint16_t* xp, const uint16_t* w, int n_in,
+                                                                       int n_out, int tp, int phases_per_split,
+                                                                       Epi epi) {
+  const GemmArgs a{xp, w, n_in, n_out, tp, phases_per_split};
   constexpr int NW = RT * CT * KW, WR = RT * WT, XC = CT * MT, WS = PH / KW;
   constexpr int XP = PH * XC, P = XP + PH * WR, PL = (P + NW - 1) / NW, REM = P % NW;
   constexpr int BUF = P * 1024;
@@ -376,7 +384,6 @@ static void launch_ring_t(const uint16_t* xp, const uint16_t* w, int tp, int n_i
   constexpr int WR = RT * WT, XC = CT * MT;
   const int nph = ((n_in >> 4) + PH - 1) / PH, pps = (nph + split_k - 1) / split_k;
   const int rgs = (n_out / 32 + WR - 1) / WR, tblocks = (tp / 32 + XC - 1) / XC;
-  GemmArgs a{xp, w, n_in, n_out, tp, pps};
   // (the unaligned form stands in for a shape with more phases: its last splits may be empty)
   dim3 grid(tblocks == 1 ? rgs : (rgs + 7) / 8 * 8 * tblocks, ALIGNED ? (nph + pps - 1) / pps : split_k);
   constexpr size_t lds_x = (size_t)NB * PH * (XC + WR) * 1024, lds_r = (size_t)(KW - 1) * CT * WR * MT * 4096;
@@ -385,7 +392,7 @@ static void launch_ring_t(const uint16_t* xp, const uint16_t* w, int tp, int n_i
   auto kern = gemm_ring_kernel<RT, CT, KW, WT, MT, PH, NB, NT, ALIGNED, Epi>;
   static DeviceOnce once;  // per instantiation
   allow_lds(once, kern, 160 * 1024);
-  kern<<<grid, RT * CT * KW * 64, lds, st>>>(a, epi);
+  kern<<<grid, RT * CT * KW * 64, lds, st>>>(xp, w, n_in, n_out, tp, pps, epi);
 }
 template <int M, class Epi>
 static void launch_ring_few(const GemmPlan& g, const uint16_t* xp, const uint16_t* w, int tp, int n_in, int n_out,
