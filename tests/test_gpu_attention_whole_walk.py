@@ -1,0 +1,34 @@
+"""One query tile whose sequence is walked by one workgroup per head: up to 24 blocks of slots, 25 are split;
+a last block of one key, one row and a full tile, one sequence and two, K/V heads shared and not, heads of
+64 and 128."""
+import numpy as np
+import pytest
+
+from gpu_util import rel_err
+from oracle import tr_oracle as O
+from paper_2406_17404_amd import binding as b
+from test_gpu_attention import TOL, case, run_attention
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dh,H", [(128, 4), (64, 2)])
+@pytest.mark.parametrize("n", [1, 8, 32])
+@pytest.mark.parametrize("slots", [512, 513, 544, 767, 768, 769])
+def test_walk(slots, n, dh, H):
+    L, nb = slots - n, -(-slots // 32)
+    cases = [case(slots + s, H, dh, L - 40 * s, n, "bf16") for s in (0, 1)]
+    want = [O.tree_attention(*c) for c in cases]
+    for B in (1, 2):
+        plan = b.trj_dev_attn_launch(B, B * n, H, H, dh, slots)
+        if dh == 128 and B * n <= 32:   # heads of 64 come through rings, which have their own rule; more rows may be one tree
+            assert (plan["tiles"], plan["form"], plan["splits"] == 1) == (1, "registers", nb <= 24)
+        for got, w in zip(run_attention("bf16", H, dh, cases[:B]), want):
+            assert np.isfinite(got).all() and rel_err(got, w) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("B,n,Hkv,heads", [(1, 5, 8, 1), (3, 5, 8, 2), (4, 5, 8, 1), (8, 1, 8, 1), (12, 1, 8, 2)])
+def test_heads_worked_on_together(B, n, Hkv, heads):
+    """Up to 24 blocks: not one sequence's, several's while compute units stay free or rounds get fewer."""
+    plan = b.trj_dev_attn_launch(B, B * n, 32, Hkv, 128, 640)
+    assert 1 << plan["pack"] == heads and plan["splits"] == 1
