@@ -859,7 +859,7 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
   // 11.0 whole, 600 12.1, 11.2, 8 on 700 12.7, 11.5, two sequences of 16 on 660 17.2, 15.4, 16 rows of 16
   // heads on 512 11.2, 10.5; from 25 blocks on it turns, 5 on 777 11.2, 11.7).  Eight key streams instead
   // of four take longer in one workgroup (16 rows on 480 slots 10.4 -> 11.7)
-  if (tune().attn_min_bpw == 0 && nb <= (p.ntw == 1 && !p.ring ? 24 : 16) && b < nb) {
+  if (tune().attn_min_bpw == 0 && nb <= (p.ntw == 1 && pack == 0 && !p.ring ? 24 : 16) && b < nb) {
     b = nb;
     p.lag = SOFTMAX_LAG;
   }
@@ -898,9 +898,9 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
 //    where only the packed ones need splits and their merge launch (eight of 16 up to 520: 17.6 ->
 //    27.4) or an idle second tile (two of 9 up to 700: 14.3 -> 16.4), unless the launch needs fewer
 //    rounds of workgroups (32 of 1 up to 520: 36.0 -> 26.3) or the walk is long (eight of 5 up to 3000:
-//    36.4 -> 27.5).  Up to 24 blocks neither is split: one sequence's single heads are ahead (5 rows on
-//    520 9.8 packed, 9.5), several's are level while they leave compute units free, and six of 8 up to
-//    600 go 20.5 -> 17.9;
+//    36.4 -> 27.5).  Up to 24 blocks, where single heads of
+//    one tile are not split, only for fewer rounds (5 rows on 520: 9.8 packed, 9.5 single; four sequences
+//    of 5 up to 600 18.2 packed in splits, 14.6);
 //  - one tile packed into two is twice the work per block (20 rows on 1000: 13.2 -> 15.3): only for
 //    half of the rounds (sixteen of 20 up to 520: 29.0 -> 22.0; not sixteen up to 3000, two rounds of far
 //    walks: 52.4 -> 57.1; 26 of 17 on four K/V heads 80.0 -> 56.3) or splits of 24 blocks and more (20
@@ -941,8 +941,8 @@ int attn_bf16_pack(int B, int T, int n_heads, int n_kv_heads, int dh, int max_se
     const bool unsplit = l.p.nsplit_max == 1;
     const bool fewer_rounds = unsplit && single.wgs > round && 5 * l.wgs <= 4 * single.wgs;
     bool pays;
-    if (n <= 32 && n << pack <= 32 && nb <= 24)
-      pays = fewer_rounds || (B > 1 && B * n_heads < CUS && l.p.ntw == single.p.ntw && !half);
+    if (n <= 32 && n << pack <= 32 && nb <= 24 && single.p.ntw == 1)
+      pays = fewer_rounds;
     else if (n <= 32 && n << pack <= 32)
       pays = fewer_rounds || (walks_far && l.p.bpwg >= 24 && !few) ||
              (l.p.ntw == single.p.ntw && (unsplit || single.p.nsplit_max > 1) && (!half || (walks_far && !few)));

@@ -27,8 +27,9 @@ def test_walk(slots, n, dh, H):
             assert np.isfinite(got).all() and rel_err(got, w) <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("B,n,Hkv,heads", [(1, 5, 8, 1), (3, 5, 8, 2), (4, 5, 8, 1), (8, 1, 8, 1), (12, 1, 8, 2)])
-def test_heads_worked_on_together(B, n, Hkv, heads):
-    """Up to 24 blocks: not one sequence's, several's while compute units stay free or rounds get fewer."""
-    plan = b.trj_dev_attn_launch(B, B * n, 32, Hkv, 128, 640)
-    assert 1 << plan["pack"] == heads and plan["splits"] == 1
+@pytest.mark.parametrize("B,n,heads,splits", [(1, 5, 1, 1), (3, 5, 1, 1), (6, 5, 1, 1), (8, 1, 1, 1), (12, 1, 2, 1),
+                                              (2, 16, 1, 1), (2, 17, 1, 4)])   # 34 rows may be one tree: two tiles
+def test_heads_worked_on_together(B, n, heads, splits):
+    """Up to 24 blocks single heads are walked whole; packed only for fewer rounds of workgroups."""
+    plan = b.trj_dev_attn_launch(B, B * n, 32, 8, 128, 640)
+    assert (1 << plan["pack"], plan["splits"]) == (heads, splits)
