@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtrjacobi.so")
 SOURCES = ["api.hip", "tree_kernels.hip", "f32_kernels.hip", "gemm_bf16.hip", "gemm_qkv.hip",
-           "gemm_gate_up.hip", "gemm_lm.hip", "gemm_residual.hip", "attn_bf16.hip",
+           "gemm_gate_up.hip", "gemm_lm.hip", "gemm_residual.hip", "gemm_slim.hip", "attn_bf16.hip",
            "decode_loop.hip", "loop_host.cpp"]
 # -packed-fp32-ops is a DEVICE code generation feature: with it hipcc emits no v_pk_*_f32
 # from float code (checked on the device assembly of a float2 kernel: one v_pk_fma_f32

@@ -759,7 +759,21 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
   if (m.dtype == TRJ_BF16) {
     const int sk_o = gemm_bf16_split_k(d, tp, hd), sk_d = gemm_bf16_split_k(d, tp, F);
     // the norm's division is done by the projection that consumes hp (RowScale)
-    const RowScale rs{w.ssq, reduce_norm_parts(d), tp, 1.0f / (float)d, m.rms_eps};
+    RowScale rs{w.ssq, reduce_norm_parts(d), tp, 1.0f / (float)d, m.rms_eps, 0};
+    const RowScale coarse = rs, fine{w.partial, d / 16, tp, rs.inv_d, rs.eps, T};
+    // a projection into the residual stream and what its consumer reads of it
+    auto add = [&](int cls, const uint16_t* xp, const void* wt, int n_in, int split, const float* g, const void* w_next) -> int {
+      // (a consumer off the 16-byte grid takes a kernel that reads few parts)
+      if (gemm_slim_runs(T, n_in, d, xp, wt) && (((uintptr_t)w_next | (uintptr_t)w.hp | (uintptr_t)w.partial) & 15) == 0) {
+        ProfScope ps_(cls, st);
+        rs = fine;
+        return launch_gemm_slim(xp, (const uint16_t*)wt, T, n_in, d, w.x, g, w.hp, w.partial, st);
+      }
+      rs = coarse;
+      { ProfScope ps_(cls, st); TRJ_TRY(add_projection(xp, (const uint16_t*)wt, T, tp, n_in, d, split, w.partial, w.x, st)); }
+      ProfScope ps_(KC_REDUCE_NORM, st);
+      return launch_reduce_norm(w.partial, split > 1 ? split : 0, w.x, g, T, d, tp, w.hp, w.ssq, st);
+    };
     if (!one_prep) { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_embed_norm((const uint16_t*)weights->embed, tok, T, d, V, w.x,
                               weights->h_layers[0].g_attn, tp, w.hp, w.ssq, st)); }
     for (int l = 0; l < m.n_layers; ++l) {
@@ -775,12 +789,11 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
       TRJ_TRY(launch_tree_attn_bf16(w.q, kl, vl, w.t.anc, node_off, kv_off, prefix_len, status_dev,
                                     w.t.items, B, T, H, Hkv, shared_kv, w.t.attn_pack, dh, s_pool, max_seq_slots, scale, w.t.attn, 1, tp,
                                     w.op, nullptr, nullptr, st));
-      { ProfScope ps_(KC_GEMM_O, st); TRJ_TRY(add_projection(w.op, (const uint16_t*)lw.wo, T, tp, hd, d, sk_o, w.partial, w.x, st)); }
-      { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_o > 1 ? sk_o : 0, w.x, lw.g_ffn, T, d, tp, w.hp, w.ssq, st)); }
+      TRJ_TRY(add(KC_GEMM_O, w.op, lw.wo, hd, sk_o, lw.g_ffn, lw.w_gate_up));
       { ProfScope ps_(KC_GEMM_GATE_UP, st); TRJ_TRY(launch_gemm_gate_up(w.hp, (const uint16_t*)lw.w_gate_up, tp, d, F, rs, w.act, st)); }
-      { ProfScope ps_(KC_GEMM_DOWN, st); TRJ_TRY(add_projection(w.act, (const uint16_t*)lw.w_down, T, tp, F, d, sk_d, w.partial, w.x, st)); }
-      const float* g_next = l + 1 < m.n_layers ? weights->h_layers[l + 1].g_attn : weights->g_final;
-      { ProfScope ps_(KC_REDUCE_NORM, st); TRJ_TRY(launch_reduce_norm(w.partial, sk_d > 1 ? sk_d : 0, w.x, g_next, T, d, tp, w.hp, w.ssq, st)); }
+      const bool last = l + 1 == m.n_layers;
+      TRJ_TRY(add(KC_GEMM_DOWN, w.act, lw.w_down, F, sk_d, last ? weights->g_final : weights->h_layers[l + 1].g_attn,
+                  last ? weights->w_lm : weights->h_layers[l + 1].wqkv));
     }
     ProfScope ps_(KC_GEMM_LM, st);
     TRJ_TRY(launch_gemm_lm(w.hp, (const uint16_t*)weights->w_lm, T, tp, d, V, rs, logits, w.cand, argmax_out, st));

@@ -48,7 +48,7 @@ __device__ inline void row_scale_load(const RowScale& rs, int ttile0, int ttiles
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int p = 0; p < RS_MAX_PARTS; ++p) ssq[m][p] = 0.f;
-  if (!rs.ssq) return;  // uniform
+  if (!rs.ssq || rs.fine) return;  // uniform
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     const int t = min(ttile0 + m, ttiles - 1) * 32 + (lane & 31);
@@ -58,7 +58,7 @@ __device__ inline void row_scale_load(const RowScale& rs, int ttile0, int ttiles
   }
 }
 __device__ inline float row_scale_factor(const RowScale& rs, const float (&ssq)[RS_MAX_PARTS]) {
-  if (!rs.ssq) return 1.0f;
+  if (!rs.ssq || rs.fine) return 1.0f;
   float s = 0.f;
 #pragma unroll
   for (int p = 0; p < RS_MAX_PARTS; ++p) s += p < rs.parts ? ssq[p] : 0.f;  // fixed order
@@ -290,11 +290,25 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(const uin
   constexpr std::integral_constant<int, 2> k2{};
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
-  if (ALIGNED || n > 0) {
+  if (ALIGNED || n > 0)
     for (int p = 0; p < NB && p < n; ++p) {
       request();
       store_held();
     }
+  // sums in many parts: each wavefront takes some of the (up to eight) rows and hands their factors on
+  // through LDS
+  constexpr bool FINE = Epi::kScaled && NT && MT == 1;
+  constexpr int FR = (8 + NW - 1) / NW;
+  f32x4 fine[FINE ? FR : 1];
+  if constexpr (FINE) {
+    if (epi.rs.fine) {  // uniform
+#pragma unroll
+      for (int j = 0; j < FR; ++j)
+        if (j * NW + wv < epi.rs.fine)
+          fine[j] = *reinterpret_cast<const f32x4*>(epi.rs.ssq + (size_t)(j * NW + wv) * epi.rs.parts + min(lane * 4, epi.rs.parts - 4));
+    }
+  }
+  if (ALIGNED || n > 0) {
     if (n >= NB) wait_younger(std::integral_constant<int, NB - 1>{});
     else if (NB > 3 && n == 3) wait_younger(k2);
     else if (NB > 2 && n == 2) wait_younger(k1);
@@ -316,6 +330,22 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(const uin
   if constexpr (Epi::kScaled) {
 #pragma unroll
     for (int m = 0; m < MT; ++m) rsf[m] = row_scale_factor(epi.rs, ssq[m]);
+  }
+  if constexpr (FINE) {
+    if (epi.rs.fine) {  // uniform
+      float* factor = reinterpret_cast<float*>(smem);  // the ring is done with once all are here
+      wait_and_meet<0>();
+#pragma unroll
+      for (int j = 0; j < FR; ++j) {
+        if (j * NW + wv >= epi.rs.fine) break;
+        float s = lane * 4 < epi.rs.parts ? (fine[j][0] + fine[j][1]) + (fine[j][2] + fine[j][3]) : 0.f;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (lane == 0) factor[j * NW + wv] = 1.0f / sqrtf(s * epi.rs.inv_d + epi.rs.eps);
+      }
+      __syncthreads();
+      rsf[0] = factor[min(lane & 31, epi.rs.fine - 1)];
+    }
   }
 
   // The k-parts of a tile are added through LDS, tile i by k-part i % KW (own part first, then

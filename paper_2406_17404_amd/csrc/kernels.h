@@ -164,7 +164,14 @@ struct RowScale {
   const float* ssq;  // [parts][tp]; nullptr: activations are used as they are
   int parts, tp;
   float inv_d, eps;
+  int fine;          // this many rows, sums as [row][parts], up to 256 parts (gemm_slim.hip); 0: as above
 };
+// A projection into the residual stream and the next norm's input in one launch, for few rows:
+// x += xp w^T, hp = bf16(x * g) tiled (rows T .. 7 of 32 as zeros, the others are left alone), n_out / 16
+// sums of squares per row, [row][part] (at 16-byte boundaries: RowScale::fine).
+bool gemm_slim_runs(int T, int n_in, int n_out, const void* xp, const void* w);
+int launch_gemm_slim(const uint16_t* xp, const uint16_t* w, int T, int n_in, int n_out, float* x, const float* g,
+                     uint16_t* hp, float* ssq, hipStream_t st);
 int reduce_norm_parts(int d);    // column parts of a row
 int reduce_norm_threads(int d);  // threads per part, 8 columns each, in whole wavefronts
 int gemm_bf16_split_k(int n_out, int tp, int n_in);
