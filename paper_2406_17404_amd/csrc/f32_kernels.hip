@@ -110,7 +110,9 @@ __device__ inline void gemm_f32_sums(const GemmF32Args& a, int rt, int t0, int p
   }
 }
 template <int TT, int UN, bool NORM, class Epi>
-__global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(GemmF32Args a, Epi epi) {
+__global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(const float* x, const float* w, const float* g, int T, int n_in,
+                                                            float eps, Epi epi) {
+  const GemmF32Args a{x, w, g, T, n_in, eps};  // plain arguments: in scalar registers from the start (build.py)
   __shared__ float red[F32_PARTS][TT][32], sq[F32_PARTS][TT];
   const int rl = threadIdx.x & 31, part = threadIdx.x >> 5;
   const int rt = blockIdx.x, t0 = blockIdx.y * TT;
@@ -189,14 +191,14 @@ static int gemm_f32(const GemmF32Args& a, int n_out, const Epi& e, hipStream_t s
   if (a.T < 1 || a.n_in < 16 || n_out < 32 || (a.n_in & 15) || (n_out & 31)) return TRJ_ERR_BAD_SHAPE;
   const dim3 by4(n_out / 32, (a.T + 3) / 4), by8(n_out / 32, (a.T + 7) / 8);
   if (a.g) {
-    if (a.T <= 16) gemm_f32_kernel<4, 1, true><<<by4, F32_THREADS, 0, st>>>(a, e);
-    else gemm_f32_kernel<8, 1, true><<<by8, F32_THREADS, 0, st>>>(a, e);
+    if (a.T <= 16) gemm_f32_kernel<4, 1, true><<<by4, F32_THREADS, 0, st>>>(a.x, a.w, a.g, a.T, a.n_in, a.eps, e);
+    else gemm_f32_kernel<8, 1, true><<<by8, F32_THREADS, 0, st>>>(a.x, a.w, a.g, a.T, a.n_in, a.eps, e);
   } else if constexpr (std::is_same_v<Epi, EpiF32Store>) {  // the others follow a norm
     const int tokens = gemm_f32_tokens(a.T, a.n_in, n_out);
     if (tokens == 2)
-      gemm_f32_kernel<2, 4, false><<<dim3(n_out / 32, (a.T + 1) / 2), F32_THREADS, 0, st>>>(a, e);
-    else if (tokens == 4) gemm_f32_kernel<4, 1, false><<<by4, F32_THREADS, 0, st>>>(a, e);
-    else gemm_f32_kernel<8, 1, false><<<by8, F32_THREADS, 0, st>>>(a, e);
+      gemm_f32_kernel<2, 4, false><<<dim3(n_out / 32, (a.T + 1) / 2), F32_THREADS, 0, st>>>(a.x, a.w, a.g, a.T, a.n_in, a.eps, e);
+    else if (tokens == 4) gemm_f32_kernel<4, 1, false><<<by4, F32_THREADS, 0, st>>>(a.x, a.w, a.g, a.T, a.n_in, a.eps, e);
+    else gemm_f32_kernel<8, 1, false><<<by8, F32_THREADS, 0, st>>>(a.x, a.w, a.g, a.T, a.n_in, a.eps, e);
   } else {
     return TRJ_ERR_NULLPTR;
   }
@@ -227,11 +229,10 @@ constexpr int FA_THREADS = 512;
 // heads of 64.  One after the other behind the softmax the kernel took 11.4 us at 143 keys, now 6.2.
 constexpr int FA_EARLY = 5;
 __global__ __launch_bounds__(FA_THREADS) void tree_attn_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ k_layer,
-    const float* __restrict__ v_layer, const uint64_t* __restrict__ anc,
     const int32_t* __restrict__ row_seq, const int32_t* __restrict__ node_off,
     const int32_t* __restrict__ kv_off, const int32_t* __restrict__ prefix_len,
-    const int32_t* __restrict__ status_dev, int n_heads, int group, int dh, int s_pool,
+    const int32_t* __restrict__ status_dev, const float* __restrict__ q, const float* __restrict__ k_layer,
+    const float* __restrict__ v_layer, const uint64_t* __restrict__ anc, int n_heads, int group, int dh, int s_pool,
     int max_slots, float scale, float* __restrict__ out) {
   extern __shared__ float lds[];
   float* qs = lds;            // dh
@@ -350,8 +351,8 @@ int launch_tree_attn_f32(const float* q, const float* k_layer, const float* v_la
   static DeviceOnce once;
   allow_lds(once, tree_attn_f32_kernel, 96 * 1024);  // a little more than 64 KiB at the limit
   dim3 grid(T, n_heads);
-  tree_attn_f32_kernel<<<grid, FA_THREADS, lds, st>>>(q, k_layer, v_layer, anc, row_seq, node_off,
-                                              kv_off, prefix_len, status_dev, n_heads,
+  tree_attn_f32_kernel<<<grid, FA_THREADS, lds, st>>>(row_seq, node_off, kv_off, prefix_len, status_dev, q,
+                                              k_layer, v_layer, anc, n_heads,
                                               n_heads / n_kv_heads, dh, s_pool, max_slots, scale,
                                               out);
   return check_launch();
