@@ -74,7 +74,7 @@ struct StepWs {
   TreeWs t;
   float2* cs;
   float *x, *logits;
-  void* cand;  // bf16 mode: argmax candidates of the LM head's epilogue, if there is room
+  ArgmaxCand* cand;  // argmax candidates of the LM head's epilogue, if there is room (fp32: and few of them)
   // bf16 mode
   uint16_t *hp, *q, *op, *act;
   float *partial, *ssq;
@@ -122,8 +122,7 @@ static void carve_step(Carver& c, const trj_model_desc& m, int B, int T, int max
   // the head's own scratch: the fp32 mode's logits (if the caller keeps none), the bf16 mode's
   // argmax candidates from the LM head's epilogue
   w->logits = head_scratch && m.dtype != TRJ_BF16 ? c.take<float>((size_t)T * m.vocab) : nullptr;
-  w->cand = head_scratch && m.dtype == TRJ_BF16
-                ? c.take<char>(gemm_lm_argmax_scratch_bytes(T, m.vocab)) : nullptr;
+  w->cand = head_scratch && m.dtype == TRJ_BF16 ? c.take<ArgmaxCand>((size_t)T * (m.vocab / 32)) : nullptr;
   if (m.dtype == TRJ_BF16) {
     const int tp = padded_rows(T);
     w->hp = c.take<uint16_t>((size_t)tp * d);
@@ -148,6 +147,7 @@ static size_t step_bytes(const trj_model_desc& m, int B, int T, int max_seq_slot
     Carver c(nullptr);
     StepWs w;
     carve_step(c, m, B, T, max_seq_slots, true, model_shares_kv(m, pack), pack, &w);
+    if (m.dtype != TRJ_BF16 && accept_picks(B, T, m.vocab)) c.take<ArgmaxCand>((size_t)T * (m.vocab / 32));
     most = c.off > most ? c.off : most;
     if (m.dtype != TRJ_BF16) break;
   }
@@ -706,6 +706,11 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
     pack = 0;
     if (!carve(c)) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   }
+  const bool picks = with_head && accept_picks(B, T, V);
+  if (!bf16 && picks) {  // where there is room for them
+    w.cand = c.take<ArgmaxCand>((size_t)T * (V / 32));
+    if (c.off > ws_bytes) w.cand = nullptr;
+  }
   float* lg = logits ? logits : w.logits;
   const float scale = 1.0f / sqrtf((float)dh);
 
@@ -796,7 +801,8 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
                   last ? weights->w_lm : weights->h_layers[l + 1].wqkv));
     }
     ProfScope ps_(KC_GEMM_LM, st);
-    TRJ_TRY(launch_gemm_lm(w.hp, (const uint16_t*)weights->w_lm, T, tp, d, V, rs, logits, w.cand, argmax_out, st));
+    TRJ_TRY(launch_gemm_lm(w.hp, (const uint16_t*)weights->w_lm, T, tp, d, V, rs, logits, w.cand,
+                           picks ? nullptr : argmax_out, st));
   } else {
     if (!one_prep) TRJ_TRY(launch_embed((const float*)weights->embed, tok, T, d, V, w.x, st));
     for (int l = 0; l < m.n_layers; ++l) {
@@ -812,11 +818,12 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
       TRJ_TRY(launch_gemm_gate_up_f32(w.x, lw.g_ffn, m.rms_eps, (const float*)lw.w_gate_up, T, d, F, w.actf, st));
       TRJ_TRY(launch_gemm_f32(w.actf, nullptr, 0.f, (const float*)lw.w_down, T, F, d, 1, w.x, st));
     }
-    TRJ_TRY(launch_gemm_f32(w.x, weights->g_final, m.rms_eps, (const float*)weights->w_lm, T, d, V, 0, lg, st));
+    if (w.cand) TRJ_TRY(launch_gemm_lm_f32(w.x, weights->g_final, m.rms_eps, (const float*)weights->w_lm, T, d, V, lg, w.cand, st));
+    else TRJ_TRY(launch_gemm_f32(w.x, weights->g_final, m.rms_eps, (const float*)weights->w_lm, T, d, V, 0, lg, st));
   }
   if (!w.cand) { ProfScope ps_(KC_ARGMAX, st); TRJ_TRY(launch_argmax(lg, T, V, argmax_out, st)); }
   ProfScope ps_(KC_ACCEPT, st);
-  return launch_accept_compact(k_pool, v_pool, kv_layer_stride, argmax_out, tok, parent, node_off, kv_off, prefix_len,
+  return launch_accept_compact(k_pool, v_pool, kv_layer_stride, picks ? w.cand : nullptr, V / 32, argmax_out, tok, parent, node_off, kv_off, prefix_len,
                                status_dev, B, T, m.n_layers, Hkv, dh, s_pool, m.dtype, accept_len, best_node, path,
                                bonus_tok, new_len, st);
 }

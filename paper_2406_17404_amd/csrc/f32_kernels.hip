@@ -149,6 +149,24 @@ struct EpiF32Store {
     *o = add_to ? *o + v : v;
   }
 };
+// logits, and of every row the largest of this tile with its index (ArgmaxCand)
+struct EpiF32Lm {
+  float* y;
+  ArgmaxCand* cand;
+  int n_out;
+  __device__ void operator()(float v, int rt, int rl, int t) const {
+    y[(size_t)t * n_out + rt * 32 + rl] = v;
+    float bv = -INFINITY;
+    int bi = INT32_MAX;
+    if (v == v) { bv = v; bi = rt * 32 + rl; }  // NaN never wins
+    for (int o = 16; o > 0; o >>= 1) {          // within the row's 32 lanes
+      const float ov = __shfl_xor(bv, o);
+      const int oi = __shfl_xor(bi, o);
+      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    }
+    if (rl == 0) cand[(size_t)t * (n_out >> 5) + rt] = ArgmaxCand{bv, bi};
+  }
+};
 // tile rows 0..15 are gate rows 16 rt .., rows 16..31 the matching up rows
 struct EpiF32GateUp {
   float* act;
@@ -207,6 +225,10 @@ static int gemm_f32(const GemmF32Args& a, int n_out, const Epi& e, hipStream_t s
 int launch_gemm_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_out, int add_to,
                     float* y, hipStream_t st) {
   return gemm_f32({x, w, g, T, n_in, eps}, n_out, EpiF32Store{y, n_out, add_to}, st);
+}
+int launch_gemm_lm_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_out, float* y,
+                       ArgmaxCand* cand, hipStream_t st) {
+  return gemm_f32({x, w, g, T, n_in, eps}, n_out, EpiF32Lm{y, cand, n_out}, st);
 }
 int launch_gemm_gate_up_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int F,
                             float* act, hipStream_t st) {

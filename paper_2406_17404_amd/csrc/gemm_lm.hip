@@ -13,10 +13,6 @@ namespace trj {
 // index wins ties, NaN never wins (a candidate that saw nothing keeps index INT32_MAX).
 // Reading the logits back for the argmax took 6.4 us at 5 rows x 32000 and 17 us at 69 x
 // 128256, the candidates' kernel 4.6.
-struct ArgmaxCand {
-  float v;
-  int32_t i;
-};
 struct EpiLm {
   static constexpr bool kScaled = true;
   RowScale rs;
@@ -76,12 +72,11 @@ __global__ __launch_bounds__(256) void argmax_cand_kernel(const ArgmaxCand* __re
     out[blockIdx.x] = bi == INT32_MAX ? 0 : bi;
   }
 }
-size_t gemm_lm_argmax_scratch_bytes(int T, int n_out) { return (size_t)T * (n_out / 32) * sizeof(ArgmaxCand); }
 int launch_gemm_lm(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out, const RowScale& rs,
                    float* logits, void* cand, int32_t* argmax_out, hipStream_t st) {
   EpiLm e{rs, static_cast<ArgmaxCand*>(cand), logits, T, n_out / 32};
   int rc = launch_gemm(xp, w, tp, n_in, n_out, 1, e, st);
-  if (rc != TRJ_OK || !cand) return rc;
+  if (rc != TRJ_OK || !cand || !argmax_out) return rc;
   argmax_cand_kernel<<<T, 256, 0, st>>>(static_cast<const ArgmaxCand*>(cand), n_out / 32, argmax_out);
   return check_launch();
 }

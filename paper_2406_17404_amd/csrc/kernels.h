@@ -114,12 +114,24 @@ int launch_template_step_prep(const TemplateView& v, const int32_t* node_off, co
                               int32_t* row_pos, int32_t* row_seq, int rows_per_item, int qg_max,
                               int blocks_per_item, int nsplit_max, int32_t* items, void* zero,
                               size_t zero_bytes, const EmbedRow& e, hipStream_t st);
+// The largest of a tile of 32 logits and its index (INT32_MAX: no value that is a number), [row][n_out / 32].
+struct ArgmaxCand {
+  float v;
+  int32_t i;
+};
 int launch_argmax(const float* logits, int T, int V, int32_t* out, hipStream_t st);
 int launch_accept(const int32_t* argmax, const int32_t* tok, const int32_t* parent, const int32_t* node_off, int B,
                   int T, int32_t* accept_len, int32_t* best_node, int32_t* path, int32_t* bonus_tok,
                   int32_t* status_dev, hipStream_t st);
-// both of a step; status_dev: as the prologue wrote it, 1 is added for a malformed parent[]
-int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const int32_t* argmax, const int32_t* tok,
+// One sequence with so few candidates (16 KiB) that the acceptance launch picks among them by itself, in every
+// workgroup: a launch of 4 us less for one round of loads more.  us of a step, tiny fp32 model (15 rows, 64
+// candidates each) 62.0 -> 60.7, 7B shape of two layers with one row (1000 candidates) 229.0 -> 228.2, two 229.5 ->
+// 228.7; a row more is three rounds of loads.
+inline bool accept_picks(int B, int T, int vocab) { return B == 1 && (long)T * (vocab >> 5) <= 2048; }
+// both of a step; status_dev: as the prologue wrote it, 1 is added for a malformed parent[]; cand (may be
+// null): argmax is not there yet and is written from these (accept_picks)
+int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const ArgmaxCand* cand, int n_cand,
+                          int32_t* argmax, const int32_t* tok,
                           const int32_t* parent, const int32_t* node_off, const int32_t* kv_off,
                           const int32_t* prefix_len, int32_t* status_dev, int B, int T, int n_layers,
                           int n_heads, int dh, int s_pool, int dtype, int32_t* accept_len, int32_t* best_node,
@@ -141,6 +153,9 @@ int launch_embed(const float* embed, const int32_t* tok, int T, int d, int vocab
 // g: RMSNorm's gain, applied to x with its division (null: x as it is); add_to: y += instead of y =
 int launch_gemm_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_out, int add_to,
                     float* y, hipStream_t st);
+// logits y and candidates of their argmax, behind a norm
+int launch_gemm_lm_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_out, float* y,
+                       ArgmaxCand* cand, hipStream_t st);
 int launch_gemm_gate_up_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int F,
                             float* act, hipStream_t st);
 int launch_gemm_qkv_f32(const float* x, const float* g, float eps, const float* w, int T, int n_in, int n_heads,
@@ -182,9 +197,8 @@ int launch_gemm_store_f32(const uint16_t* xp, const uint16_t* w, int T, int tp, 
 // x += the whole product (no k-split)
 int launch_gemm_residual(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out, float* x,
                          hipStream_t st);
-size_t gemm_lm_argmax_scratch_bytes(int T, int n_out);
 // fp32 logits (null: none) and the greedy argmax of every row, from candidates of the epilogue
-// (cand null: the logits alone)
+// (cand null: the logits alone; argmax_out null: the candidates stay)
 int launch_gemm_lm(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out, const RowScale& rs,
                    float* logits, void* cand, int32_t* argmax_out, hipStream_t st);
 int launch_gemm_gate_up(const uint16_t* xp, const uint16_t* w, int tp, int n_in, int d_ffn,

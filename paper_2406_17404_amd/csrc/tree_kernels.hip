@@ -623,26 +623,38 @@ struct Accepted {
   int depth, best, bonus;  // depth of the best node, -1 for a malformed sequence; uniform
   int path[2];             // nodes lane and lane + 64 of the path, root first; -1 behind its end
 };
-__device__ inline Accepted accept_sequence(const int32_t* __restrict__ argmax, const int32_t* __restrict__ tok,
-                                           const int32_t* __restrict__ parent, const int32_t* __restrict__ node_off,
-                                           int T, bool known_bad, int s) {
+// what a sequence's nodes bring with them, nodes lane and lane + 64: asked for ahead of the predictions
+// where these have still to be worked out
+struct AcceptNodes {
+  int r0, n, par[2], tk[2];
+  bool bad;  // this lane's verdict
+};
+__device__ inline AcceptNodes accept_nodes(const int32_t* __restrict__ tok, const int32_t* __restrict__ parent,
+                                           const int32_t* __restrict__ node_off, int T, int s) {
   const int lane = threadIdx.x & 63;
   const int r0 = node_off[s], r1 = node_off[s + 1];
   const bool range_ok = r0 >= 0 && r1 <= T && r1 > r0 && (r1 - r0) <= TRJ_N_MAX;
-  const int n = range_ok ? r1 - r0 : 0;
-  Accepted r{-1, -1, -1, {-1, -1}};
-  int par[2], tk[2], am[2];
-  bool bad = !range_ok || known_bad;
+  AcceptNodes a{r0, range_ok ? r1 - r0 : 0, {-1, -1}, {0, 0}, !range_ok};
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int i = lane + 64 * h;
-    par[h] = -1;
-    tk[h] = am[h] = 0;
-    if (i >= n) continue;
-    par[h] = parent[r0 + i];
-    tk[h] = tok[r0 + i];
-    am[h] = argmax[r0 + i];
-    bad = bad || (i == 0 ? par[h] != -1 : (par[h] < 0 || par[h] >= i));
+    if (i >= a.n) continue;
+    a.par[h] = parent[r0 + i];
+    a.tk[h] = tok[r0 + i];
+  }
+  return a;
+}
+__device__ inline Accepted accept_sequence(const AcceptNodes& a, const int32_t* argmax, bool known_bad) {
+  const int lane = threadIdx.x & 63, n = a.n;
+  const int (&par)[2] = a.par, (&tk)[2] = a.tk;
+  Accepted r{-1, -1, -1, {-1, -1}};
+  int am[2];
+  bool bad = a.bad || known_bad;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int i = lane + 64 * h;
+    am[h] = i < n ? argmax[a.r0 + i] : 0;
+    if (i < n) bad = bad || (i == 0 ? par[h] != -1 : (par[h] < 0 || par[h] >= i));
   }
   if (__ballot(bad)) return r;
   // one word per node: nearest ancestor not yet accounted for (255: none), distance to it,
@@ -698,7 +710,7 @@ __global__ __launch_bounds__(WAVE) void accept_kernel(
     int32_t* __restrict__ accept_len, int32_t* __restrict__ best_node, int32_t* __restrict__ path,
     int32_t* __restrict__ bonus_tok, int32_t* __restrict__ status_dev) {
   const int s = blockIdx.x;
-  const Accepted r = accept_sequence(argmax, tok, parent, node_off, T, false, s);
+  const Accepted r = accept_sequence(accept_nodes(tok, parent, node_off, T, s), argmax, false);
   accept_store(r, s, accept_len, best_node, path, bonus_tok);
   if (threadIdx.x == 0) status_dev[s] = r.depth < 0;
 }
@@ -765,25 +777,59 @@ int launch_kv_compact(void* k_pool, void* v_pool, size_t layer_stride, const int
   return check_launch();
 }
 
+// picked[t] = the winner among row t's candidates, for T rows, by TRJ_N_MAX threads: as many per row as there
+// are, each with eight candidates on the way at a time.  Lowest index wins ties, NaN never wins.
+__device__ inline void pick_argmax(const ArgmaxCand* __restrict__ cand, int n_cand, int T, int32_t* picked) {
+  int per = TRJ_N_MAX;  // threads of a row, a power of two, of one wavefront
+  while (per > WAVE || per * T > TRJ_N_MAX) per >>= 1;
+  const int t = threadIdx.x / per, j0 = threadIdx.x % per;
+  float bv = -INFINITY;
+  int bi = INT32_MAX;
+  if (t < T) {
+    const ArgmaxCand* row = cand + (size_t)t * n_cand;
+    for (int j = j0; j < n_cand; j += 8 * per) {
+      ArgmaxCand c[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) c[u] = row[min(j + u * per, n_cand - 1)];  // the last again: changes nothing
+#pragma unroll
+      for (int u = 0; u < 8; ++u) amax_merge(bv, bi, c[u].v, c[u].i);
+    }
+  }
+  for (int o = per >> 1; o > 0; o >>= 1) amax_merge(bv, bi, __shfl_xor(bv, o), __shfl_xor(bi, o));
+  if (t < T && j0 == 0) picked[t] = bi == INT32_MAX ? 0 : bi;
+}
+
 // Acceptance and compaction of a step in one launch: every plane's workgroup works the path
 // out for itself (three 512-byte reads and a few rounds on registers) instead of waiting for a launch
 // that does only this; plane 0 writes it out.  Tail of a step 9.4 -> 5.0 us.
 template <typename E>
 __global__ __launch_bounds__(TRJ_N_MAX) void accept_compact_kernel(
-    E* __restrict__ k_pool, E* __restrict__ v_pool, size_t layer_stride, const int32_t* __restrict__ argmax,
-    const int32_t* __restrict__ tok, const int32_t* __restrict__ parent, const int32_t* __restrict__ node_off,
-    const int32_t* __restrict__ kv_off, const int32_t* __restrict__ prefix_len, int32_t* status_dev,
-    int T, int n_heads, int dh, int s_pool, int32_t* __restrict__ accept_len, int32_t* __restrict__ best_node,
+    E* __restrict__ k_pool, E* __restrict__ v_pool, size_t layer_stride, const ArgmaxCand* __restrict__ cand, int n_cand,
+    int32_t* argmax, const int32_t* __restrict__ tok, const int32_t* __restrict__ parent,
+    const int32_t* __restrict__ node_off, const int32_t* __restrict__ kv_off, const int32_t* __restrict__ prefix_len,
+    int32_t* status_dev, int T, int n_heads, int dh, int s_pool, int32_t* __restrict__ accept_len, int32_t* __restrict__ best_node,
     int32_t* __restrict__ path, int32_t* __restrict__ bonus_tok, int32_t* __restrict__ new_len) {
   __shared__ int32_t pth[TRJ_N_MAX];
   __shared__ int32_t depth;
+  __shared__ int32_t picked[TRJ_N_MAX];
   const int s = blockIdx.x, plane = blockIdx.y;
   const int L = prefix_len[s], ko = kv_off[s];
+  AcceptNodes nodes{};
+  bool known_bad = false;
   if (threadIdx.x < WAVE) {
     // the prologue's verdict on tree and slots stands; what only parent[] shows (a prepared template
     // is not compared with it) is added.  Every plane reads the word while plane 0 may write it and
     // comes to the same end with either value.
-    const Accepted r = accept_sequence(argmax, tok, parent, node_off, T, status_dev[s] != 0, s);
+    nodes = accept_nodes(tok, parent, node_off, T, s);
+    known_bad = status_dev[s] != 0;
+  }
+  if (cand) {  // uniform; one sequence
+    pick_argmax(cand, n_cand, T, picked);
+    __syncthreads();
+    if (plane == 0 && (int)threadIdx.x < T) argmax[threadIdx.x] = picked[threadIdx.x];
+  }
+  if (threadIdx.x < WAVE) {
+    const Accepted r = cand ? accept_sequence(nodes, picked, known_bad) : accept_sequence(nodes, argmax, known_bad);
     if (plane == 0) {
       accept_store(r, s, accept_len, best_node, path, bonus_tok);
       if (threadIdx.x == 0) {
@@ -802,7 +848,8 @@ __global__ __launch_bounds__(TRJ_N_MAX) void accept_compact_kernel(
   compact_plane(k_pool + off, v_pool + off, pth, d, ko + L, dh, s_pool);
 }
 
-int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const int32_t* argmax, const int32_t* tok,
+int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const ArgmaxCand* cand, int n_cand,
+                          int32_t* argmax, const int32_t* tok,
                           const int32_t* parent, const int32_t* node_off, const int32_t* kv_off,
                           const int32_t* prefix_len, int32_t* status_dev, int B, int T, int n_layers,
                           int n_heads, int dh, int s_pool, int dtype, int32_t* accept_len, int32_t* best_node,
@@ -810,11 +857,11 @@ int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const
   dim3 grid(B, n_layers * n_heads);
   if (dtype == TRJ_BF16)
     accept_compact_kernel<uint16_t><<<grid, TRJ_N_MAX, 0, st>>>(
-        (uint16_t*)k_pool, (uint16_t*)v_pool, layer_stride, argmax, tok, parent, node_off, kv_off, prefix_len,
+        (uint16_t*)k_pool, (uint16_t*)v_pool, layer_stride, cand, n_cand, argmax, tok, parent, node_off, kv_off, prefix_len,
         status_dev, T, n_heads, dh, s_pool, accept_len, best_node, path, bonus_tok, new_len);
   else
     accept_compact_kernel<uint32_t><<<grid, TRJ_N_MAX, 0, st>>>(
-        (uint32_t*)k_pool, (uint32_t*)v_pool, layer_stride, argmax, tok, parent, node_off, kv_off, prefix_len,
+        (uint32_t*)k_pool, (uint32_t*)v_pool, layer_stride, cand, n_cand, argmax, tok, parent, node_off, kv_off, prefix_len,
         status_dev, T, n_heads, dh, s_pool, accept_len, best_node, path, bonus_tok, new_len);
   return check_launch();
 }
