@@ -774,6 +774,11 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
         rs = fine;
         return launch_gemm_slim(xp, (const uint16_t*)wt, T, n_in, d, w.x, g, w.hp, w.partial, st);
       }
+      if (split == 1 && gemm_residual_norm_runs(tp, n_in, d, xp, wt)) {
+        ProfScope ps_(cls, st);
+        rs = RowScale{w.partial, d / 128, tp, coarse.inv_d, coarse.eps, 0};
+        return launch_gemm_residual_norm(xp, (const uint16_t*)wt, T, tp, n_in, d, w.x, g, w.hp, w.partial, st);
+      }
       rs = coarse;
       { ProfScope ps_(cls, st); TRJ_TRY(add_projection(xp, (const uint16_t*)wt, T, tp, n_in, d, split, w.partial, w.x, st)); }
       ProfScope ps_(KC_REDUCE_NORM, st);

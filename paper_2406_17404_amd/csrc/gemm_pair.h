@@ -136,7 +136,16 @@ __global__ __launch_bounds__(512, 2) void gemm_pair_kernel(const uint16_t* xp, c
   if constexpr (Epi::kScaled) {
 #pragma unroll
     for (int m = 0; m < MT; ++m) rsf[m] = row_scale_factor(epi.rs, ssq[m]);
+    if (epi.rs.ssq && epi.rs.parts > RS_MAX_PARTS) {  // uniform
+      float* factor = reinterpret_cast<float*>(smem) + 16 * 1024;  // behind what the sums below use
+      row_factors<XC * 32>(epi.rs, tt0 * 32, factor);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) rsf[m] = factor[(ct * MT + m) * 32 + (lane & 31)];
+    }
   }
+  // an epilogue that returns a sum per token row (gemm_residual.hip)
+  constexpr bool SUMS = !std::is_void_v<decltype(epi(acc[0][0], 0, 0, 0, 0))>;
+  float* sums = reinterpret_cast<float*>(smem) + 16 * 1024;  // behind what the next sums use
   // tile i of both k-parts is added by group i % 2
   float* red = reinterpret_cast<float*>(smem) + (size_t)(wv & 3) * WT * MT * 1024 + lane;
 #pragma unroll
@@ -158,7 +167,20 @@ __global__ __launch_bounds__(512, 2) void gemm_pair_kernel(const uint16_t* xp, c
       const int tt = tt0 + ct * MT + m;
       if (tile >= ntiles || tt >= ttiles || grp != (r * MT + m) % 2) continue;  // uniform
       if constexpr (Epi::kScaled) epi(scaled(acc[r][m], rsf[m]), tile, tt, lane, 0);
-      else epi(acc[r][m], tile, tt, lane, 0);
+      else if constexpr (SUMS) {
+        const float ss = epi(acc[r][m], tile, tt, lane, 0);
+        if (lane < 32) sums[(rt * WT + r) * XC * 32 + (ct * MT + m) * 32 + lane] = ss;
+      } else epi(acc[r][m], tile, tt, lane, 0);
+    }
+  }
+  if constexpr (SUMS) {  // of the workgroup's features, in order
+    __syncthreads();
+    const int t = tt0 * 32 + tid;
+    if (tid < XC * 32 && t < a.tp) {
+      float s = 0.f;
+#pragma unroll
+      for (int r = 0; r < WR; ++r) s += sums[r * XC * 32 + tid];
+      epi.ssq[(size_t)rg * a.tp + t] = s;
     }
   }
 }

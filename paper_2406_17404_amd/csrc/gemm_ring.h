@@ -48,7 +48,7 @@ __device__ inline void row_scale_load(const RowScale& rs, int ttile0, int ttiles
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int p = 0; p < RS_MAX_PARTS; ++p) ssq[m][p] = 0.f;
-  if (!rs.ssq || rs.fine) return;  // uniform
+  if (!rs.ssq || rs.fine || rs.parts > RS_MAX_PARTS) return;  // uniform
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     const int t = min(ttile0 + m, ttiles - 1) * 32 + (lane & 31);
@@ -58,11 +58,31 @@ __device__ inline void row_scale_load(const RowScale& rs, int ttile0, int ttiles
   }
 }
 __device__ inline float row_scale_factor(const RowScale& rs, const float (&ssq)[RS_MAX_PARTS]) {
-  if (!rs.ssq || rs.fine) return 1.0f;
+  if (!rs.ssq || rs.fine || rs.parts > RS_MAX_PARTS) return 1.0f;
   float s = 0.f;
 #pragma unroll
   for (int p = 0; p < RS_MAX_PARTS; ++p) s += p < rs.parts ? ssq[p] : 0.f;  // fixed order
   return 1.0f / sqrtf(s * rs.inv_d + rs.eps);
+}
+// Many rows with sums in more parts (gemm_residual.hip): a thread per token row of the workgroup adds its
+// parts in order and hands the factor on through `factor` (LDS that nothing uses any more, once all
+// wavefronts are here).  Behind the main loop; 32 parts of 256 rows are 32 KiB per workgroup.
+template <int ROWS>
+__device__ inline void row_factors(const RowScale& rs, int row0, float* factor) {
+  __syncthreads();
+  if ((int)threadIdx.x < ROWS) {
+    const float* p = rs.ssq + min(row0 + (int)threadIdx.x, rs.tp - 1);
+    float s = 0.f;
+    for (int k0 = 0; k0 < rs.parts; k0 += 16) {
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = p[(size_t)min(k0 + k, rs.parts - 1) * rs.tp];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) s += k0 + k < rs.parts ? v[k] : 0.f;
+    }
+    factor[threadIdx.x] = 1.0f / sqrtf(s * rs.inv_d + rs.eps);
+  }
+  __syncthreads();
 }
 // a scaled copy for the epilogue (the accumulators themselves stay where they are)
 __device__ inline f32x16 scaled(const f32x16& acc, float f) {
@@ -345,6 +365,15 @@ __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(const uin
       }
       __syncthreads();
       rsf[0] = factor[min(lane & 31, epi.rs.fine - 1)];
+    }
+  }
+
+  if constexpr (Epi::kScaled && !NT) {
+    if (epi.rs.ssq && epi.rs.parts > RS_MAX_PARTS) {  // uniform
+      float* factor = reinterpret_cast<float*>(smem);
+      row_factors<XC * 32>(epi.rs, tt0 * 32, factor);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) rsf[m] = factor[(ct * MT + m) * 32 + (lane & 31)];
     }
   }
 

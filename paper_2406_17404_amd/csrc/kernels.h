@@ -176,7 +176,7 @@ int launch_tree_attn_f32(const float* q, const float* k_layer, const float* v_la
 // The producer then needs no row-wide reduction and spreads over the whole chip.
 constexpr int RS_MAX_PARTS = 4;
 struct RowScale {
-  const float* ssq;  // [parts][tp]; nullptr: activations are used as they are
+  const float* ssq;  // [parts][tp], more than RS_MAX_PARTS only for many rows; nullptr: activations are used as they are
   int parts, tp;
   float inv_d, eps;
   int fine;          // this many rows, sums as [row][parts], up to 256 parts (gemm_slim.hip); 0: as above
@@ -197,6 +197,10 @@ int launch_gemm_store_f32(const uint16_t* xp, const uint16_t* w, int T, int tp, 
 // x += the whole product (no k-split)
 int launch_gemm_residual(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out, float* x,
                          hipStream_t st);
+// the same for many rows with the next norm's input (RowScale: [n_out / 128][tp] sums of squares)
+bool gemm_residual_norm_runs(int tp, int n_in, int n_out, const void* xp, const void* w);
+int launch_gemm_residual_norm(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out, float* x,
+                              const float* g, uint16_t* hp, float* ssq, hipStream_t st);
 // fp32 logits (null: none) and the greedy argmax of every row, from candidates of the epilogue
 // (cand null: the logits alone; argmax_out null: the candidates stay)
 int launch_gemm_lm(const uint16_t* xp, const uint16_t* w, int T, int tp, int n_in, int n_out, const RowScale& rs,
