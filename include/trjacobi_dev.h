@@ -30,7 +30,8 @@ int32_t trj_linear(const void* x, const void* w_packed, int32_t T, int32_t n_in,
 /* The launch plan a bf16 projection of the verify step gets at T token rows (section
  * "TR-Jacobi Decoding": the projections of the decoder forward over the tree's rows).
  * fused != 0: the QKV and gate/up projections (no k-split across workgroups); else the
- * plan of a projection that writes split-k partial sums.  h_plan[6] (HOST): token-row
+ * plan of a projection that writes split-k partial sums (up to eight rows a step's output and
+ * down projections run in a kernel without such a plan where their shapes allow it).  h_plan[6] (HOST): token-row
  * tiles per pass, row tiles per workgroup, k-parts per workgroup, row tiles per wavefront,
  * grid k-splits, 1 if the many-rows kernel (packed batches) is used. */
 int32_t trj_dev_gemm_plan(int32_t T, int32_t n_in, int32_t n_out, int32_t fused, int32_t* h_plan);
