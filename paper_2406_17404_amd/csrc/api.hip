@@ -74,7 +74,7 @@ struct StepWs {
   TreeWs t;
   float2* cs;
   float *x, *logits;
-  ArgmaxCand* cand;  // argmax candidates of the LM head's epilogue, if there is room (fp32: and few of them)
+  ArgmaxCand* cand;  // argmax candidates of the LM head's epilogue, if there is room (fp32: in the layers' buffers)
   // bf16 mode
   uint16_t *hp, *q, *op, *act;
   float *partial, *ssq;
@@ -147,7 +147,6 @@ static size_t step_bytes(const trj_model_desc& m, int B, int T, int max_seq_slot
     Carver c(nullptr);
     StepWs w;
     carve_step(c, m, B, T, max_seq_slots, true, model_shares_kv(m, pack), pack, &w);
-    if (m.dtype != TRJ_BF16 && accept_picks(B, T, m.vocab)) c.take<ArgmaxCand>((size_t)T * (m.vocab / 32));
     most = c.off > most ? c.off : most;
     if (m.dtype != TRJ_BF16) break;
   }
@@ -707,10 +706,11 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
     if (!carve(c)) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   }
   const bool picks = with_head && accept_picks(B, T, V);
-  if (!bf16 && picks) {  // where there is room for them
-    w.cand = c.take<ArgmaxCand>((size_t)T * (V / 32));
-    if (c.off > ws_bytes) w.cand = nullptr;
-  }
+  // fp32: the head's candidates go where the layers' q, attention output and activations were, one
+  // behind the other at the workspace's end: no scratch of their own, so that a step takes the sizes it took
+  // without them
+  if (!bf16 && picks && (size_t)T * (V / 32) * sizeof(ArgmaxCand) <= c.off - ((char*)w.qf - (char*)workspace))
+    w.cand = reinterpret_cast<ArgmaxCand*>(w.qf);
   float* lg = logits ? logits : w.logits;
   const float scale = 1.0f / sqrtf((float)dh);
 

@@ -3,10 +3,13 @@ few candidates, up to the limit and beyond it, one candidate per row and one row
 by ties within a tile and across tiles, rows with NaN logits; and a sequence whose tree is malformed."""
 import numpy as np
 import pytest
+import torch
 
-from gpu_util import Batch, device_weights, fill_pool, nan_pool, run_step
+from gpu_util import DEV, Batch, device_weights, fill_pool, nan_pool, run_step
 from oracle import tr_oracle as O
+from paper_2406_17404_amd import binding as b
 from paper_2406_17404_amd import inputs as I
+from test_gpu_loop import make_model
 
 pytestmark = pytest.mark.gpu
 
@@ -55,3 +58,18 @@ def test_malformed_tree(dtype):
     res = run_step(shape, desc, dw, batch, kp, vp)
     assert res["status"][0] == 1 and res["accept_len"][0] == -1 and res["new_len"][0] == 9
     assert np.array_equal(res["argmax"], O.greedy_argmax(res["logits"]))
+
+
+@pytest.mark.parametrize("prompt_len,size", [(1, 260608), (32, 518656)])
+def test_generation_in_a_workspace_of_the_size_without_candidates(prompt_len, size):
+    """Sizes that were enough before the fp32 head wrote candidates: the same tokens as with room to spare."""
+    w = make_model(I.TINY, 4)
+    desc, dw = device_weights(I.TINY, w)
+    prompt = I.gen_tokens(I.TINY.vocab, prompt_len, 4, "prompt")
+    stride = 4 * 512 * 64
+    out = []
+    for room in (0, 1 << 20):
+        kp, vp = (torch.zeros(2, stride, device=DEV) for _ in "kv")
+        ws = torch.full((size + room,), 255, dtype=torch.uint8, device=DEV)
+        out.append(b.tr_jacobi_generate(desc, dw.struct, kp, vp, stride, 512, prompt, I.tree_c0(), 5, 3, 32, -1, 4, ws))
+    assert out[0] == out[1] and len(out[0][0]) == 32
