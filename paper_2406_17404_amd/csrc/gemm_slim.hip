@@ -92,14 +92,25 @@ __global__ __launch_bounds__(SLIM_WAVES * 64, 2) void gemm_slim_kernel(const uin
 }
 
 // At least half of the compute units with a workgroup, and no more parts per row than the wavefronts
-// of the consuming projection read with one load (4 x 64).
+// of the consuming projection read with one load (4 x 64).  A k range of at most so many rounds of 2048
+// columns (SLIM_STEPS pairs of k-steps for each wavefront, as long for a part of one): a workgroup's time grows with
+// the rounds alone, that of a projection split over all compute units with the product, so the narrower the
+// output the sooner the split one is ahead in spite of its sum.  us of one projection, this less split with
+// its sum, 1 to 8 rows alike:
+//   outputs  2048  4 rounds -0.5 (8192 columns) +0.6 (6176)    5 rounds +2.2 (10240) +2.9 (8224)
+//            2560  5        -0.7 (10240)        -0.1 (8224)    6        -0.5 (12288) +0.9 (10272)
+//            3072  6        -1.4 (12288)        -0.1 (10272)   7         0.0 (14336) +1.3 (12800)
+//            3328  8        -1.9 (16384)        -1.2 (14368)   9        +1.1 (17408)
+//            4096  8        -0.7 (16384)        +0.2 (14368)   9        +1.4 (18432) +3.2 (16416)
+constexpr int SLIM_STEPS = 8;
+static int slim_rounds(int n_out) { return n_out < 2560 ? 4 : n_out < 2816 ? 5 : n_out < 3328 ? 6 : 8; }
 bool gemm_slim_runs(int T, int n_in, int n_out, const void* xp, const void* w) {
   return T <= SLIM_ROWS && n_in % 32 == 0 && n_out % 64 == 0 && n_out >= 2048 && n_out <= 4096 &&
-         (((uintptr_t)xp | (uintptr_t)w) & 15) == 0;
+         n_in <= slim_rounds(n_out) * SLIM_STEPS * SLIM_WAVES * 32 && (((uintptr_t)xp | (uintptr_t)w) & 15) == 0;
 }
 int launch_gemm_slim(const uint16_t* xp, const uint16_t* w, int T, int n_in, int n_out, float* x, const float* g,
                      uint16_t* hp, float* ssq, hipStream_t st) {
-  gemm_slim_kernel<8><<<n_out / 16, SLIM_WAVES * 64, 0, st>>>(xp, w, n_in / 32, T, n_out, x, g, hp, ssq);
+  gemm_slim_kernel<SLIM_STEPS><<<n_out / 16, SLIM_WAVES * 64, 0, st>>>(xp, w, n_in / 32, T, n_out, x, g, hp, ssq);
   return check_launch();
 }
 

@@ -4,8 +4,9 @@ with a rest, one row, all eight and nine, several sequences, every shape of the 
 many partial sums of squares, and matrices off the 16-byte grid, which keep the launches of more rows."""
 import numpy as np
 import pytest
+import torch
 
-from gpu_util import device_weights
+from gpu_util import DEV, Batch, device_weights, kv_heads
 from paper_2406_17404_amd import binding as b
 from paper_2406_17404_amd import inputs as I
 from test_gpu_odd_pointers import off_the_grid
@@ -56,3 +57,39 @@ def test_matrices_off_the_grid(monkeypatch):
         return desc, dw
     monkeypatch.setattr(S, "device_weights", moved)
     check(I.ModelShape(2, 2048, 4, 64, 96, 512, "bf16"), [5], 8)
+
+
+def sum_launches(shape, n):
+    """Launches of the split-k sum in a step of one sequence with n rows, random weights made on the device."""
+    desc = b.make_desc(shape)
+    dw = b.DeviceWeights(desc)
+    d, hd, kvd, f = shape.d_model, shape.n_heads * shape.head_dim, kv_heads(shape) * shape.head_dim, shape.d_ffn
+
+    def matrix(rows, cols):
+        return (torch.randn(rows, cols, device=DEV) * 0.02).to(torch.bfloat16)
+    for _ in range(shape.n_layers):
+        dw.add_layer(torch.ones(d, device=DEV), matrix(hd + 2 * kvd, d), matrix(d, hd), torch.ones(d, device=DEV),
+                     matrix(2 * f, d), matrix(d, f))
+    dw.set_globals(matrix(shape.vocab, d), torch.ones(d, device=DEV), matrix(shape.vocab, d))
+    dw.finish()
+    batch = Batch([I.tree_chain(n)], [0], [np.arange(n, dtype=np.int32)])
+    stride = kv_heads(shape) * batch.s_pool * shape.head_dim
+    kp, vp = (torch.zeros(shape.n_layers, stride, dtype=torch.bfloat16, device=DEV) for _ in "kv")
+    ws = torch.empty(b.trj_workspace_bytes(desc, n, 1, batch.max_seq_slots), dtype=torch.uint8, device=DEV)
+    out = [torch.zeros(n, dtype=torch.int32, device=DEV) for _ in range(6)]
+    path = torch.zeros(1, b.N_MAX, dtype=torch.int32, device=DEV)
+    b.trj_profile_begin(5, 8 * shape.n_layers)
+    b.tr_verify_step(desc, dw.struct, kp, vp, stride, batch.s_pool, batch.tok, batch.parent, batch.node_off, batch.kv_off,
+                     batch.prefix, 1, n, batch.max_seq_slots, ws, None, out[0], out[1], out[2], path, out[3], out[4], out[5])
+    torch.cuda.synchronize()
+    return len(b.trj_profile_end(8 * shape.n_layers))
+
+
+# one layer: the sums behind the output projection (k range heads x 128) and the down projection (k range ffn)
+@pytest.mark.parametrize("d,heads,ffn,sums", [
+    (2048, 2, 8192, 0), (2048, 2, 8224, 1), (2496, 2, 8224, 1), (2048, 65, 64, 1), (2048, 64, 64, 0), (2560, 2, 10240, 0),
+    (2560, 2, 10272, 1), (2816, 2, 12288, 0), (2816, 2, 12320, 1), (3264, 2, 12320, 1), (3328, 2, 16384, 0),
+    (4096, 2, 16384, 0), (4096, 2, 16416, 1), (4096, 32, 11008, 0), (1984, 2, 64, 2), (4160, 2, 64, 2)])
+def test_long_k_ranges_keep_their_splits(d, heads, ffn, sums):
+    shape = I.ModelShape(1, d, heads, 128, ffn, 512, "bf16")
+    assert [sum_launches(shape, n) for n in (1, 8, 9)] == [sums, sums, 2]
