@@ -705,7 +705,7 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
     pack = 0;
     if (!carve(c)) return TRJ_ERR_WORKSPACE_TOO_SMALL;
   }
-  const bool picks = with_head && accept_picks(B, T, V);
+  const bool picks = with_head && accept_picks(B, T, V, !bf16);
   // fp32: the head's candidates go where the layers' q, attention output and activations were, one
   // behind the other at the workspace's end: no scratch of their own, so that a step takes the sizes it took
   // without them

@@ -124,10 +124,26 @@ int launch_accept(const int32_t* argmax, const int32_t* tok, const int32_t* pare
                   int T, int32_t* accept_len, int32_t* best_node, int32_t* path, int32_t* bonus_tok,
                   int32_t* status_dev, hipStream_t st);
 // One sequence with so few candidates (16 KiB) that the acceptance launch picks among them by itself, in every
-// workgroup: a launch of 4 us less for one round of loads more.  us of a step, tiny fp32 model (15 rows, 64
-// candidates each) 62.0 -> 60.7, 7B shape of two layers with one row (1000 candidates) 229.0 -> 228.2, two 229.5 ->
-// 228.7; a row more is three rounds of loads.
-inline bool accept_picks(int B, int T, int vocab) { return B == 1 && (long)T * (vocab >> 5) <= 2048; }
+// workgroup: a launch less for one or two rounds of loads, PICK_LOADS of each thread, one behind the other.
+// From the LM head's launch to the end of acceptance, bf16, less than with a launch for the pick, us, in models
+// of 8, 256 and 1024 layers x K/V heads (a workgroup each): one round (1 row of 512 candidates, 8 of 128) 1.0 to 1.6,
+// two (1 of 1000, 4 of 512, 16 of 128, 31 of 64) 0.3 to 1.2 (128 rows of 16 1.7, 1.4, -0.4), three (1 of 1536, 3 of
+// 682) -0.3 to 0.2, four (1 of 2048, 5 of 406, 17 of 120) -0.2 to -0.9 (65 of 31 0.7,
+// 0.3, -0.3).  Steps of the tiny fp32 model (15 rows, 64
+// candidates each, one round) 62.0 -> 60.7.  fp32 has no other candidates, and an argmax that reads logits
+// takes longer the longer a row is: with up to four rows, whose candidates are 512 and more each, the pick
+// stays 1 to 3 us ahead in three and four rounds (1 of 2048 3.0, 3 of 682 1.0; 5 of 406 -0.2, 17 of 120 -0.2).
+constexpr int PICK_LOADS = 8;
+// threads that pick among one row's candidates, a power of two, of one wavefront
+__host__ __device__ inline int pick_threads(int T) {
+  int per = WAVE;
+  while (per * T > TRJ_N_MAX) per >>= 1;
+  return per;
+}
+inline bool accept_picks(int B, int T, int vocab, bool fp32) {
+  if (B != 1 || T > TRJ_N_MAX || (long)T * (vocab >> 5) > 2048) return false;
+  return (vocab >> 5) <= 2 * PICK_LOADS * pick_threads(T) || (fp32 && T <= 4);
+}
 // both of a step; status_dev: as the prologue wrote it, 1 is added for a malformed parent[]; cand (may be
 // null): argmax is not there yet and is written from these (accept_picks)
 int launch_accept_compact(void* k_pool, void* v_pool, size_t layer_stride, const ArgmaxCand* cand, int n_cand,

@@ -777,22 +777,21 @@ int launch_kv_compact(void* k_pool, void* v_pool, size_t layer_stride, const int
   return check_launch();
 }
 
-// picked[t] = the winner among row t's candidates, for T rows, by TRJ_N_MAX threads: as many per row as there
-// are, each with eight candidates on the way at a time.  Lowest index wins ties, NaN never wins.
+// picked[t] = the winner among row t's candidates, for T rows, by TRJ_N_MAX threads: equally many per row, up
+// to a wavefront, each with PICK_LOADS candidates on the way at a time.  Lowest index wins ties, NaN never wins.
 __device__ inline void pick_argmax(const ArgmaxCand* __restrict__ cand, int n_cand, int T, int32_t* picked) {
-  int per = TRJ_N_MAX;  // threads of a row, a power of two, of one wavefront
-  while (per > WAVE || per * T > TRJ_N_MAX) per >>= 1;
+  const int per = pick_threads(T);
   const int t = threadIdx.x / per, j0 = threadIdx.x % per;
   float bv = -INFINITY;
   int bi = INT32_MAX;
   if (t < T) {
     const ArgmaxCand* row = cand + (size_t)t * n_cand;
-    for (int j = j0; j < n_cand; j += 8 * per) {
-      ArgmaxCand c[8];
+    for (int j = j0; j < n_cand; j += PICK_LOADS * per) {
+      ArgmaxCand c[PICK_LOADS];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) c[u] = row[min(j + u * per, n_cand - 1)];  // the last again: changes nothing
+      for (int u = 0; u < PICK_LOADS; ++u) c[u] = row[min(j + u * per, n_cand - 1)];  // the last again: changes nothing
 #pragma unroll
-      for (int u = 0; u < 8; ++u) amax_merge(bv, bi, c[u].v, c[u].i);
+      for (int u = 0; u < PICK_LOADS; ++u) amax_merge(bv, bi, c[u].v, c[u].i);
     }
   }
   for (int o = per >> 1; o > 0; o >>= 1) amax_merge(bv, bi, __shfl_xor(bv, o), __shfl_xor(bi, o));

@@ -73,3 +73,32 @@ def test_generation_in_a_workspace_of_the_size_without_candidates(prompt_len, si
         ws = torch.full((size + room,), 255, dtype=torch.uint8, device=DEV)
         out.append(b.tr_jacobi_generate(desc, dw.struct, kp, vp, stride, 512, prompt, I.tree_c0(), 5, 3, 32, -1, 4, ws))
     assert out[0] == out[1] and len(out[0][0]) == 32
+
+
+def argmax_launches(shape, n):
+    """Launches of the argmax over logits in an fp32 step of one sequence with n rows, whose result is checked."""
+    w = I.gen_weights(shape, n)
+    desc, dw = device_weights(shape, w)
+    batch = Batch([I.tree_random(n, np.random.default_rng(n))], [9], [I.gen_tokens(shape.vocab, n, 3, "tree")])
+    kp, vp = (nan_pool(1, shape.n_heads, batch.s_pool, 64, "f32") for _ in range(2))
+    fill_pool(kp, vp, 0, batch, 0, *I.gen_prefix_kv(shape, 3, 0, 0, 9))
+    b.trj_profile_begin(9, 4)
+    res = run_step(shape, desc, dw, batch, kp, vp)
+    launches = len(b.trj_profile_end(4))
+    assert np.array_equal(res["argmax"], O.greedy_argmax(res["logits"]))
+    return launches
+
+
+# rounds of 8 loads per thread: rows, vocabulary and whether a launch of its own takes the argmax
+@pytest.mark.parametrize("n,vocab,own", [
+    (5, 8192, 0), (5, 8224, 1), (5, 12992, 1), (8, 8192, 0), (16, 4096, 0), (17, 2048, 0), (17, 2080, 1), (17, 3840, 1),
+    (33, 1024, 0), (33, 1056, 1), (65, 512, 0), (65, 544, 1), (128, 512, 0),          # two rounds at most
+    (1, 65536, 0), (1, 65568, 1), (2, 32768, 0), (3, 21824, 0), (4, 16384, 0)])       # long rows: up to the limit
+def test_rounds_of_loads(n, vocab, own):
+    assert argmax_launches(I.ModelShape(1, 64, 1, 64, 4096, vocab, "f32"), n) == own
+
+
+@pytest.mark.parametrize("vocab,own", [(4096, 0), (4128, 1), (65536, 1)])
+def test_vocabulary_wider_than_the_layers_buffers(vocab, own):
+    """Candidates lie where q, attention output and activations were: 4 x (64 + 64 + 128) bytes a row."""
+    assert argmax_launches(I.ModelShape(1, 64, 1, 64, 128, vocab, "f32"), 1) == own
