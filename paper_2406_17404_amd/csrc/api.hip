@@ -708,9 +708,13 @@ int step_impl(const trj_model_desc* desc, const trj_weights* weights, void* k_po
   const bool picks = with_head && accept_picks(B, T, V, !bf16);
   // fp32: the head's candidates go where the layers' q, attention output and activations were, one
   // behind the other at the workspace's end: no scratch of their own, so that a step takes the sizes it took
-  // without them
-  if (!bf16 && picks && (size_t)T * (V / 32) * sizeof(ArgmaxCand) <= c.off - ((char*)w.qf - (char*)workspace))
-    w.cand = reinterpret_cast<ArgmaxCand*>(w.qf);
+  // without them.  At the end of these, where the activations are the longest idle: a step with one row and
+  // a vocabulary of 32000 80.5 us (in q's place 80.8, in memory of their own 80.2), of 2048 in each place 56.4
+  const size_t cand_bytes = (size_t)T * (V / 32) * sizeof(ArgmaxCand);
+  if (!bf16 && picks && cand_bytes <= c.off) {
+    char* at = c.base + ((c.off - cand_bytes) & ~(size_t)255);
+    if (at >= reinterpret_cast<char*>(w.qf)) w.cand = reinterpret_cast<ArgmaxCand*>(at);
+  }
   float* lg = logits ? logits : w.logits;
   const float scale = 1.0f / sqrtf((float)dh);
 
