@@ -1,7 +1,10 @@
 """Steps of up to eight rows, whose output and down projections add to the residual stream and write the
 next norm's input in one launch: k ranges shorter than a pair of k-steps per wavefront up to several rounds
 with a rest, one row, all eight and nine, several sequences, every shape of the projections that read the
-many partial sums of squares, and matrices off the 16-byte grid, which keep the launches of more rows."""
+many partial sums of squares, and matrices off the 16-byte grid and k ranges too long for the output's
+width, which keep the launches of more rows.  Launches of the split-k sum, which the steps do without,
+are counted; and as 1e-2 does not see one of 128 or more equal parts missing from a sum of squares, rows
+whose sum is one part are among the cases."""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +19,8 @@ pytestmark = pytest.mark.gpu
 TOL = 1e-2   # bf16 storage, as for all steps
 
 
-def check(shape, sizes, seed, weights=None):
+def check(shape, sizes, seed, weights=None, sums=0):
+    """sums: launches of the split-k sum per layer; none up to eight rows."""
     w = weights or I.gen_weights(shape, seed)
     for l in w["layers"]:   # gains of their own, exact in 16 bits
         l["g_ffn"] = (0.5 + 0.25 * (np.arange(shape.d_model) % 5)).astype(np.float32)
@@ -24,7 +28,12 @@ def check(shape, sizes, seed, weights=None):
     trees = [I.tree_random(n, rng) for n in sizes]
     toks = [I.gen_tokens(shape.vocab, n, seed, "tree", s) for s, n in enumerate(sizes)]
     Ls = [40 + 9 * s for s in range(len(sizes))]
-    S.run_and_check(shape, w, trees, toks, Ls, [S.prefix_normal(shape, seed, s, L) for s, L in enumerate(Ls)], TOL)
+    b.trj_profile_begin(5, 8)
+    try:
+        S.run_and_check(shape, w, trees, toks, Ls, [S.prefix_normal(shape, seed, s, L) for s, L in enumerate(Ls)], TOL)
+    finally:
+        launches = len(b.trj_profile_end(8))
+    assert launches == (sums if sum(sizes) <= 8 else 2) * shape.n_layers
     return w
 
 
@@ -35,6 +44,20 @@ def test_rows_and_k_ranges(d, heads, ffn):
     w = None
     for sizes in ([1], [5], [8], [9], [3, 1, 4]):
         w = check(shape, sizes, 77 + ffn, w)
+
+
+# 16-column parts: first and last, both sides of what a lane reads (four parts) and of half a wavefront's
+@pytest.mark.parametrize("d,part", [(2048, 0), (2048, 3), (2048, 4), (2048, 127), (2112, 128), (2112, 131), (4096, 0),
+                                    (4096, 7), (4096, 124), (4096, 128), (4096, 255)])
+def test_every_part_of_a_sum_of_squares_counts(d, part):
+    """Rows whose residual stream is large in one part alone, and in no two rows of neighbouring ids as large:
+    without the part, or with another row's, the factor is far off."""
+    shape = I.ModelShape(2, d, 2, 64, 128, 512, "bf16")
+    w = I.gen_weights(shape, part)
+    cols = slice(16 * part, 16 * part + 16)
+    size = 4 * (1 + np.arange(shape.vocab) % 5)[:, None]
+    w["embed"][:, cols] = I.bf16_round((np.sign(w["embed"][:, cols]) * size).astype(np.float32))
+    check(shape, [8], part, w)
 
 
 @pytest.mark.parametrize("cfg", [1, 2, 3, 4, 5, 6])
@@ -56,7 +79,7 @@ def test_matrices_off_the_grid(monkeypatch):
         off_the_grid(dw)
         return desc, dw
     monkeypatch.setattr(S, "device_weights", moved)
-    check(I.ModelShape(2, 2048, 4, 64, 96, 512, "bf16"), [5], 8)
+    check(I.ModelShape(2, 2048, 4, 64, 96, 512, "bf16"), [5], 8, sums=2)
 
 
 def sum_launches(shape, n):
