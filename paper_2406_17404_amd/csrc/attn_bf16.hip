@@ -857,7 +857,8 @@ AttnPlan attn_bf16_plan(int B, int rows_T, int all_heads, int dh, bool shared_kv
   // needs: 16 rows on 300 slots 11.9 against 13.6 us a call, 64 rows on 128 12.9 against 15.1,
   // on 512 (18 blocks) 17.2 against 15.9; with one query tile up to 24 (16 rows on 512 slots 11.9 split,
   // 11.0 whole, 600 12.1, 11.2, 8 on 700 12.7, 11.5, two sequences of 16 on 660 17.2, 15.4, 16 rows of 16
-  // heads on 512 11.2, 10.5; from 25 blocks on it turns, 5 on 777 11.2, 11.7).  Eight key streams instead
+  // heads on 512 11.2, 10.5; heads of 64 that share K/V, 12 rows on 724 12.1, 9.4, four sequences of 7 on 655
+  // 15.6, 12.8, 60 sizes 0.76 to 1.01 of the time; from 25 blocks on it turns, 5 on 777 11.2, 11.7).  Eight key streams instead
   // of four take longer in one workgroup (16 rows on 480 slots 10.4 -> 11.7)
   if (tune().attn_min_bpw == 0 && nb <= (p.ntw == 1 && pack == 0 && !p.ring ? 24 : 16) && b < nb) {
     b = nb;

@@ -163,9 +163,11 @@ int gemm_bf16_split_k(int n_out, int tp, int n_in) {
   int sk = 1;
   if (many_rows(tp)) {
     // us at 1024 x 4096 behind the product: an unsplit one is added to the residual stream in its
-    // epilogue and the next kernel only reads it (8), split ones are images to write, read again
+    // epilogue and a launch only reads it (8), split ones are images to write, read again
     // and add (30 for two, 50 for four).  With the output projection unsplit at 1024 rows:
-    // 41.0 + 19.8 us for the sum -> 47.5 + 10.1
+    // 41.0 + 19.8 us for the sum -> 47.5 + 10.1.  An unsplit projection that takes turns, with whole
+    // row groups, has no such launch (gemm_residual.hip; its readers pay 1 to 2 us) and is charged the 8 all the
+    // same: 4096 x 11008 keeps two splits at 640 and 768 rows, 4096 x 14336 four or two from 640 to 1024
     float best = 0.f;
     for (int s : {1, 2, 4}) {
       const float cost = many_cost(plan_many(ttiles, ntiles, ksteps, s), ttiles, ntiles, ksteps, s) +

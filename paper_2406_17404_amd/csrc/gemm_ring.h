@@ -124,7 +124,7 @@ __device__ __forceinline__ void wait_and_meet() {
 //
 // What the first loads need are plain arguments in front: those come in scalar registers when a
 // wavefront starts (build.py's kernarg preload; members of a struct do not) and save it a read of
-// memory that nothing has in a cache yet.  Steps of two layers, 21 launches, us: 777 x 5 242.2 -> 239.4,
+// memory that nothing has in a cache yet.  Steps of two layers, 20 launches, us: 777 x 5 242.2 -> 239.4,
 // 1024 x 64 283.8 -> 281.1, 4096 x 128 390.8 -> 387.5.
 template <int RT, int CT, int KW, int WT, int MT, int PH, int NB, bool NT, bool ALIGNED, class Epi>
 __global__ __launch_bounds__(RT* CT* KW * 64, 2) void gemm_ring_kernel(const uint16_t* xp, const uint16_t* w, int n_in,

@@ -128,11 +128,11 @@ int launch_accept(const int32_t* argmax, const int32_t* tok, const int32_t* pare
 // From the LM head's launch to the end of acceptance, bf16, less than with a launch for the pick, us, in models
 // of 8, 256 and 1024 layers x K/V heads (a workgroup each): one round (1 row of 512 candidates, 8 of 128) 1.0 to 1.6,
 // two (1 of 1000, 4 of 512, 16 of 128, 31 of 64) 0.3 to 1.2 (128 rows of 16 1.7, 1.4, -0.4), three (1 of 1536, 3 of
-// 682) -0.3 to 0.2, four (1 of 2048, 5 of 406, 17 of 120) -0.2 to -0.9 (65 of 31 0.7,
-// 0.3, -0.3).  Steps of the tiny fp32 model (15 rows, 64
-// candidates each, one round) 62.0 -> 60.7.  fp32 has no other candidates, and an argmax that reads logits
-// takes longer the longer a row is: with up to four rows, whose candidates are 512 and more each, the pick
-// stays 1 to 3 us ahead in three and four rounds (1 of 2048 3.0, 3 of 682 1.0; 5 of 406 -0.2, 17 of 120 -0.2).
+// 682) -0.3 to 0.2, four (1 of 2048, 5 of 406, 17 of 120) -0.2 to -0.9 (65 of 31 0.7, 0.3, -0.3).  Steps of the
+// tiny fp32 model (15 rows, 64 candidates each, one round) 62.0 -> 60.7.  fp32 has no other candidates, and an
+// argmax that reads logits takes longer the longer a row is: up to four rows, whose candidates in three and
+// four rounds are more than 512 each, the pick stays 1 to 3 us ahead (1 of 2048 3.0, 3 of 682 1.0; 5 of 406 -0.2,
+// 17 of 120 -0.2).
 constexpr int PICK_LOADS = 8;
 // threads that pick among one row's candidates, a power of two, of one wavefront
 __host__ __device__ inline int pick_threads(int T) {
