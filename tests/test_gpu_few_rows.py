@@ -116,3 +116,9 @@ def sum_launches(shape, n):
 def test_long_k_ranges_keep_their_splits(d, heads, ffn, sums):
     shape = I.ModelShape(1, d, heads, 128, ffn, 512, "bf16")
     assert [sum_launches(shape, n) for n in (1, 8, 9)] == [sums, sums, 2]
+
+
+@pytest.mark.parametrize("shape", [I.ModelShape(2, 2048, 2, 64, 8224, 512, "bf16"),     # down projections split
+                                   I.ModelShape(2, 2048, 65, 128, 64, 512, "bf16")])    # output projections split
+def test_one_projection_of_a_layer_split(shape):
+    check(shape, [3, 2], 3, sums=1)
